@@ -3,16 +3,13 @@
 // product "AG").  Both are segmented reductions over rows of a sparse operator: HBM-bound, no
 // dense contraction, hence no matrix cores.
 //
-// One wavefront per output row.
-//   k_segment_reduce       rows of at most 64*VEC columns: the 64 lanes are split into G groups of
-//                          LPR lanes; the lanes of a group cover the feature columns with VEC-wide
-//                          loads and group g takes the row's entries g, g+G, ...; the G partial
-//                          sums are then folded across groups.  (Also the generic fallback: one
-//                          group, one column pass after the other.)
-//   k_segment_reduce_wide  wider rows: a lane owns PASSES column chunks and keeps all of them in
-//                          registers, so every input row is fetched with PASSES independent loads
-//                          in flight; the row's entries are loaded 64 at a time, one per lane, and
-//                          broadcast with v_readlane.
+//   k_segment_flat   one wavefront per run of up to kRunRows consecutive output rows, its 64 lanes side by
+//                    side over the columns (wider rows: slabs of 64 vectors, each a share of the
+//                    grid).  The entries of the run are walked as one sequence across the row ends:
+//                    64 of them are fetched at a time, one per lane, and U input rows are loaded before
+//                    the first of them is added, however few entries the rows have.  Entry numbers, row
+//                    ends and addresses are the same in all lanes and live in scalar registers: per
+//                    entry the vector unit sees one load and VEC additions.
 // Forward: output row i reduces x[indices[e]] over the edges e of destination i and divides by
 // their number.  Backward: output row s reduces grad_out[i] / n_i over the edges that point to
 // source s, taken from the block's edge list sorted by source (stable radix sort, so a row's terms
@@ -44,11 +41,11 @@ __device__ __forceinline__ void from_f32(float x, _Float16 *o) { *o = static_cas
 struct ForwardRows {
     static constexpr bool kWeighted = false;
     static constexpr bool kSelf = false;
+    __device__ __forceinline__ int64_t self_rows(int64_t) const { return 0; }
     __device__ __forceinline__ float self_weight(int64_t) const { return 0.f; }
     const int32_t *indptr;
     const int32_t *indices;
     __device__ __forceinline__ int begin(int64_t i) const { return indptr[i]; }
-    __device__ __forceinline__ int end(int64_t i) const { return indptr[i + 1]; }
     __device__ __forceinline__ int input_row(int p) const { return indices[p]; }
     __device__ __forceinline__ float weight(int) const { return 1.f; }
     __device__ __forceinline__ float finish(float acc, int count) const { return count > 0 ? acc / static_cast<float>(count) : 0.f; }
@@ -59,12 +56,12 @@ struct ForwardRows {
 struct BackwardRows {
     static constexpr bool kWeighted = true;
     static constexpr bool kSelf = false;
+    __device__ __forceinline__ int64_t self_rows(int64_t) const { return 0; }
     __device__ __forceinline__ float self_weight(int64_t) const { return 0.f; }
     const int32_t *col_ptr;     // [num_src + 1] offsets into dst_rows
     const int32_t *dst_rows;    // [nnz] destination row of every edge, edges ordered by source
     const int32_t *indptr;      // the block's forward offsets, for the edge counts
     __device__ __forceinline__ int begin(int64_t s) const { return col_ptr[s]; }
-    __device__ __forceinline__ int end(int64_t s) const { return col_ptr[s + 1]; }
     __device__ __forceinline__ int input_row(int p) const { return dst_rows[p]; }
     __device__ __forceinline__ float weight(int p) const {
         const int i = dst_rows[p];
@@ -83,10 +80,10 @@ struct WeightedRows {
     const float *edge_w;
     const float *self_w;        // may be null: no diagonal term
     __device__ __forceinline__ int begin(int64_t i) const { return indptr[i]; }
-    __device__ __forceinline__ int end(int64_t i) const { return indptr[i + 1]; }
     __device__ __forceinline__ int input_row(int p) const { return indices[p]; }
     __device__ __forceinline__ float weight(int p) const { return edge_w[p]; }
-    __device__ __forceinline__ float self_weight(int64_t i) const { return self_w ? self_w[i] : 0.f; }
+    __device__ __forceinline__ int64_t self_rows(int64_t n) const { return self_w ? n : 0; }
+    __device__ __forceinline__ float self_weight(int64_t i) const { return self_w[i]; }
     __device__ __forceinline__ float finish(float acc, int) const { return acc; }
 };
 
@@ -101,149 +98,126 @@ struct WeightedBackwardRows {
     const float *self_w;
     const int64_t *sizes;
     __device__ __forceinline__ int begin(int64_t s) const { return col_ptr[s]; }
-    __device__ __forceinline__ int end(int64_t s) const { return col_ptr[s + 1]; }
     __device__ __forceinline__ int input_row(int p) const { return dst_rows[p]; }
     __device__ __forceinline__ float weight(int p) const { return w_sorted[p]; }
-    __device__ __forceinline__ float self_weight(int64_t s) const { return (self_w && s < sizes[0]) ? self_w[s] : 0.f; }
+    __device__ __forceinline__ int64_t self_rows(int64_t) const { return self_w ? sizes[0] : 0; }
+    __device__ __forceinline__ float self_weight(int64_t s) const { return self_w[s]; }
     __device__ __forceinline__ float finish(float acc, int) const { return acc; }
 };
 
+// The segmented reduction.  What bounds it is the traffic behind the L2s: random 512-byte rows are read at
+// 7.5 TB/s from a table that the memory-side cache holds and at 6.6 TB/s from a larger one (measured with a
+// kernel that does nothing else).  A loop over one row after the other, the wavefront split into groups of
+// lanes that share a row's entries, came near that only for long rows.  Measured, before -> now: the three
+// blocks of a mini-batch of 8,192 seeds (512-byte rows; 347 k output rows, 4.7 M entries) 0.432 -> 0.338 ms,
+// the reductions of their backward (1.7 M output rows of 3 entries) 0.89 -> 0.49 ms; 2,408-byte rows (10 k
+// rows of 25 entries: 612 MB read in 83 us = 7.4 TB/s) as before; rows of 4 to 256 bytes, 100 k of them, 5 to
+// 60 % faster, and no slower where there are few.
+// Measured and dropped: slabs of 128 to 512 bytes dealt to the XCDs so that every L2 keeps its slab of the
+// hot rows (L2 hits 13 -> 24 %, time unchanged or worse); 4 or 16 instead of 8 vectors of 16 bytes in flight.
+constexpr int kRunRows = 16;
+
 template <typename T, int VEC, typename Rows>
 __global__ void __launch_bounds__(kBlock)
-k_segment_reduce(Rows rows, const int64_t *__restrict__ n_rows, const T *__restrict__ x, int64_t x_stride,
-                 T *__restrict__ out, int64_t out_stride, int dim, int log2_lpr) {
+k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restrict__ x, int64_t x_stride,
+               T *__restrict__ out, int64_t out_stride, int dim, uint32_t row_blocks) {
     using P = Pack<T, VEC>;
+    constexpr int U = sizeof(P) == 16 ? 8 : 16;            // input rows in flight: 4 to 8 KB per wavefront
+    constexpr int NACC = VEC <= 2 ? 4 : 2;                 // partial sums that take the entries in turn
     const int lane = lane_id();
-    const int lpr = 1 << log2_lpr;
-    const int groups = kWave >> log2_lpr;
-    const int g = lane >> log2_lpr;
-    const int gl = lane & (lpr - 1);
     const int64_t n = *n_rows;
-    const int64_t wave0 = int64_t(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
-    const int64_t nwaves = int64_t(gridDim.x) * kWavesPerBlock;
-    for (int64_t i = wave0; i < n; i += nwaves) {
-        const int b = rows.begin(i), e = rows.end(i);
-        // every lane of the wavefront runs the same number of column passes (shuffles below)
-        const int passes = (dim + lpr * VEC - 1) / (lpr * VEC);
-        for (int ps = 0; ps < passes; ++ps) {
-            const int col0 = (ps * lpr + gl) * VEC;
-            const bool live = col0 < dim;
-            float acc[VEC];
+    const uint32_t slab = blockIdx.x / row_blocks;
+    const uint32_t row_block = blockIdx.x - slab * row_blocks;
+    const uint32_t col0 = (slab * kWave + lane) * VEC;
+    const bool live = col0 < static_cast<uint32_t>(dim);
+    const uint32_t lane_off = (live ? col0 : 0u) * sizeof(T);      // lanes past the row read its start and store nothing
+    const int64_t self_rows = Rows::kSelf ? rows.self_rows(n) : 0;         // rows with a diagonal term: the first ones
+    const int64_t nwaves = int64_t(row_blocks) * kWavesPerBlock;
+    const int64_t wave0 = __builtin_amdgcn_readfirstlane(static_cast<int>(row_block) * kWavesPerBlock + static_cast<int>(threadIdx.x >> 6));
+    const int64_t share = (n + nwaves - 1) / nwaves;
+    const int run = share < kRunRows ? static_cast<int>(share) : kRunRows;
+    const char *xb = reinterpret_cast<const char *>(x);
+    const int64_t x_bytes = x_stride * int64_t(sizeof(T)), out_bytes = out_stride * int64_t(sizeof(T));
+    for (int64_t c0 = wave0 * run; c0 < n; c0 += nwaves * run) {
+        const int m = n - c0 < run ? static_cast<int>(n - c0) : run;       // rows of this run
+        // diagonal terms in this run: one more entry, its first, for each of the run's first `diag` rows
+        const int diag = self_rows > c0 ? static_cast<int>(self_rows - c0 < m ? self_rows - c0 : m) : 0;
+        const int t = lane < m ? lane : m;                 // lane t keeps the first position of row c0 + t
+        const uint32_t off = static_cast<uint32_t>(rows.begin(c0 + t)) + static_cast<uint32_t>(t < diag ? t : diag);
+        const uint32_t begin = readlane32(off, 0), end = readlane32(off, m);
+        int cur = 0;
+        uint32_t row_begin = begin, row_end = readlane32(off, 1);
+        float acc[NACC][VEC];
 #pragma unroll
-            for (int q = 0; q < VEC; ++q) acc[q] = 0.f;
-            if (Rows::kSelf) {                             // the diagonal term: the row's own input row
-                const float ws = rows.self_weight(i);
-                if (ws != 0.f && live && g == 0) {
-                    P v = *reinterpret_cast<const P *>(x + i * x_stride + col0);
+        for (int a = 0; a < NACC; ++a)
 #pragma unroll
-                    for (int q = 0; q < VEC; ++q) acc[q] = ws * to_f32(v.v[q]);
-                }
+            for (int q = 0; q < VEC; ++q) acc[a][q] = 0.f;
+        auto finish_row = [&]() {
+            P o;
+#pragma unroll
+            for (int q = 0; q < VEC; ++q) {
+                float sum = acc[0][q] + acc[1][q];
+                if constexpr (NACC == 4) sum += acc[2][q] + acc[3][q];
+                from_f32(rows.finish(sum, static_cast<int>(row_end - row_begin)), &o.v[q]);
+#pragma unroll
+                for (int a = 0; a < NACC; ++a) acc[a][q] = 0.f;
             }
-#pragma unroll 4
-            for (int p = b + g; p < e; p += groups) {
-                const int64_t r = rows.input_row(p);
-                const float w = rows.weight(p);
-                if (live) {
-                    P v = *reinterpret_cast<const P *>(x + r * x_stride + col0);
+            char *orow = reinterpret_cast<char *>(out) + (c0 + cur) * out_bytes;
+            if (live) *reinterpret_cast<P *>(orow + lane_off) = o;
+            ++cur;
+            row_begin = row_end;
+            row_end = readlane32(off, cur + 1);
+        };
+        for (uint32_t e0 = begin; e0 < end; e0 += kWave) {
+            const int cnt = end - e0 < kWave ? static_cast<int>(end - e0) : kWave;
+            const uint32_t p = e0 + (lane < cnt ? lane : cnt - 1);     // past the end: the last entry again, loaded but not added
+            int my_row;                                    // -1: a diagonal term whose weight is zero, not added either
+            float my_w = 1.f;
+            if (Rows::kSelf && diag > 0) {
+                int k = 0;                                 // the entry's row and that row's first position
+                uint32_t first = begin;
+                for (int q = 1; q < m; ++q) {
+                    const uint32_t o = readlane32(off, q);
+                    if (p >= o) {
+                        k = q;
+                        first = o;
+                    }
+                }
+                if (k < diag && p == first) {
+                    my_w = rows.self_weight(c0 + k);
+                    my_row = my_w != 0.f ? static_cast<int>(c0) + k : -1;
+                } else {
+                    const int q = static_cast<int>(p - (k < diag ? k + 1 : diag));
+                    my_row = rows.input_row(q);
+                    my_w = rows.weight(q);
+                }
+            } else {
+                my_row = rows.input_row(static_cast<int>(p));
+                if (Rows::kWeighted) my_w = rows.weight(static_cast<int>(p));
+            }
+            for (int b = 0; b < cnt; b += U) {
+                P v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int r = static_cast<int>(readlane32(static_cast<uint32_t>(my_row), b + u));
+                    v[u] = *reinterpret_cast<const P *>(xb + (Rows::kSelf && r < 0 ? 0 : r) * x_bytes + lane_off);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (b + u >= cnt) continue;
+                    while (e0 + static_cast<uint32_t>(b + u) >= row_end) finish_row();
+                    if (Rows::kSelf && static_cast<int>(readlane32(static_cast<uint32_t>(my_row), b + u)) < 0) continue;
+                    const float w = __uint_as_float(readlane32(__float_as_uint(my_w), b + u));
 #pragma unroll
                     for (int q = 0; q < VEC; ++q) {
-                        if (Rows::kWeighted) acc[q] += w * to_f32(v.v[q]);
-                        else acc[q] += to_f32(v.v[q]);
+                        float &a = acc[u % NACC][q];
+                        if (Rows::kWeighted) a += w * to_f32(v[u].v[q]);
+                        else a += to_f32(v[u].v[q]);
                     }
                 }
             }
-            for (int off = lpr; off < kWave; off <<= 1) {
-#pragma unroll
-                for (int q = 0; q < VEC; ++q) acc[q] += __shfl_xor(acc[q], off, 64);
-            }
-            if (live && g == 0) {
-                P o;
-#pragma unroll
-                for (int q = 0; q < VEC; ++q) from_f32(rows.finish(acc[q], e - b), &o.v[q]);
-                *reinterpret_cast<P *>(out + i * out_stride + col0) = o;
-            }
         }
-    }
-}
-
-template <typename T, int VEC, int PASSES, typename Rows>
-__global__ void __launch_bounds__(kBlock)
-k_segment_reduce_wide(Rows rows, const int64_t *__restrict__ n_rows, const T *__restrict__ x, int64_t x_stride,
-                      T *__restrict__ out, int64_t out_stride, int dim) {
-    using P = Pack<T, VEC>;
-    const int lane = lane_id();
-    const int64_t n = *n_rows;
-    const int64_t wave0 = int64_t(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
-    const int64_t nwaves = int64_t(gridDim.x) * kWavesPerBlock;
-    bool live[PASSES];
-#pragma unroll
-    for (int ps = 0; ps < PASSES; ++ps) live[ps] = (ps * kWave + lane) * VEC < dim;
-    for (int64_t i = wave0; i < n; i += nwaves) {
-        const int b = rows.begin(i), e = rows.end(i);
-        float acc[PASSES][VEC];
-#pragma unroll
-        for (int ps = 0; ps < PASSES; ++ps)
-#pragma unroll
-            for (int q = 0; q < VEC; ++q) acc[ps][q] = 0.f;
-        if (Rows::kSelf) {
-            const float ws = rows.self_weight(i);
-            if (ws != 0.f) {
-                const T *row = x + i * x_stride + lane * VEC;
-#pragma unroll
-                for (int ps = 0; ps < PASSES; ++ps)
-                    if (live[ps]) {
-                        P v = *reinterpret_cast<const P *>(row + ps * kWave * VEC);
-#pragma unroll
-                        for (int q = 0; q < VEC; ++q) acc[ps][q] = ws * to_f32(v.v[q]);
-                    }
-            }
-        }
-        for (int c0 = b; c0 < e; c0 += kWave) {            // entries 64 at a time, one per lane
-            const int m = e - c0 < kWave ? e - c0 : kWave;
-            const int my_row = lane < m ? rows.input_row(c0 + lane) : 0;
-            const float my_w = lane < m ? rows.weight(c0 + lane) : 0.f;
-            auto load_row = [&](int t, P *v) {
-                const int64_t r = static_cast<int>(readlane32(static_cast<uint32_t>(my_row), t));
-                const T *row = x + r * x_stride + lane * VEC;
-#pragma unroll
-                for (int ps = 0; ps < PASSES; ++ps)
-                    if (live[ps]) v[ps] = *reinterpret_cast<const P *>(row + ps * kWave * VEC);
-            };
-            auto add_row = [&](int t, const P *v) {
-                const float w = __uint_as_float(readlane32(__float_as_uint(my_w), t));
-#pragma unroll
-                for (int ps = 0; ps < PASSES; ++ps)
-                    if (live[ps]) {
-#pragma unroll
-                        for (int q = 0; q < VEC; ++q) {
-                            if (Rows::kWeighted) acc[ps][q] += w * to_f32(v[ps].v[q]);
-                            else acc[ps][q] += to_f32(v[ps].v[q]);
-                        }
-                    }
-            };
-            int t = 0;
-            for (; t + 1 < m; t += 2) {                    // two input rows (2*PASSES loads) in flight
-                P v0[PASSES], v1[PASSES];
-                load_row(t, v0);
-                load_row(t + 1, v1);
-                add_row(t, v0);
-                add_row(t + 1, v1);
-            }
-            if (t < m) {
-                P v0[PASSES];
-                load_row(t, v0);
-                add_row(t, v0);
-            }
-        }
-        T *orow = out + i * out_stride + lane * VEC;
-#pragma unroll
-        for (int ps = 0; ps < PASSES; ++ps)
-            if (live[ps]) {
-                P o;
-#pragma unroll
-                for (int q = 0; q < VEC; ++q) from_f32(rows.finish(acc[ps][q], e - b), &o.v[q]);
-                *reinterpret_cast<P *>(orow + ps * kWave * VEC) = o;
-            }
+        while (cur < m) finish_row();
     }
 }
 
@@ -264,39 +238,24 @@ int launch(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_ro
                reinterpret_cast<uintptr_t>(x) % bytes == 0 && reinterpret_cast<uintptr_t>(out) % bytes == 0;
     };
     while (vec > 1 && !ok(vec)) vec >>= 1;
-    int lanes = static_cast<int>(ceil_div(dim, vec));
-    int log2_lpr = 0;
-    while ((1 << log2_lpr) < lanes && log2_lpr < 6) ++log2_lpr;
-    const int grid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(cap_rows, kWavesPerBlock)), 256 * 32));
-    const int passes = static_cast<int>(ceil_div(lanes, kWave));
+    // the narrowest vector with which the 64 lanes still cover the row (wider rows: the widest, in slabs)
+    while (vec > 1 && ceil_div(dim, vec / 2) <= kWave) vec >>= 1;
+    const int64_t slabs = ceil_div(dim, kWave * vec);
+    const int64_t row_blocks = std::min<int64_t>(std::max<int64_t>(1, ceil_div(cap_rows, kWavesPerBlock)), 256 * 32);
+    const int grid = static_cast<int>(row_blocks * slabs);
 #define MQG_AGG(V)                                                                                              \
     MQG_LAUNCH(ctx, name, s,                                                                                    \
-               (k_segment_reduce<T, V, Rows><<<grid, kBlock, 0, s>>>(rows, n_rows, x, x_stride, out, out_stride, dim, log2_lpr)))
-#define MQG_AGG_WIDE(V, PS)                                                                                     \
-    MQG_LAUNCH(ctx, name, s,                                                                                    \
-               (k_segment_reduce_wide<T, V, PS, Rows><<<grid, kBlock, 0, s>>>(rows, n_rows, x, x_stride, out, out_stride, dim)))
-#define MQG_AGG_PICK(V)                        \
-    switch (passes) {                          \
-        case 1: MQG_AGG(V); break;             \
-        case 2: MQG_AGG_WIDE(V, 2); break;     \
-        case 3: MQG_AGG_WIDE(V, 3); break;     \
-        case 4: MQG_AGG_WIDE(V, 4); break;     \
-        case 5: MQG_AGG_WIDE(V, 5); break;     \
-        case 6: MQG_AGG_WIDE(V, 6); break;     \
-        default: MQG_AGG(V); break;            \
-    }
+               (k_segment_flat<T, V, Rows><<<grid, kBlock, 0, s>>>(rows, n_rows, x, x_stride, out, out_stride, dim, static_cast<uint32_t>(row_blocks))))
     constexpr int kWidest = 16 / static_cast<int>(sizeof(T));
     if (vec == kWidest) {
-        MQG_AGG_PICK(kWidest);
+        MQG_AGG(kWidest);
     } else if (vec == kWidest / 2) {
-        MQG_AGG_PICK(kWidest / 2);
+        MQG_AGG(kWidest / 2);
     } else if (vec == 2 && kWidest == 8) {
         MQG_AGG(2);
     } else {
         MQG_AGG(1);
     }
-#undef MQG_AGG_PICK
-#undef MQG_AGG_WIDE
 #undef MQG_AGG
     return MQG_OK;
 }

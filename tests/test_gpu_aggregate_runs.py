@@ -1,0 +1,79 @@
+"""The segmented reduction where its runs of rows begin, end and are cut: row counts around the number of
+wavefronts of a launch (32,768) and its multiples, rows without entries, rows of more than the 64
+entries that are fetched at a time, rows narrower and wider than a wavefront, diagonal terms of zero.
+
+Against float64 sums.  Bound per element: a sum of n fp32 products has an error of at most (n + 2) 2^-24
+times the sum of its terms' magnitudes; a result stored as fp16 is rounded once more, by 2^-11 of itself.
+"""
+import numpy as np
+import pytest
+import scipy.sparse
+import torch
+
+from test_gpu_backward import bare_blocks
+
+pytestmark = pytest.mark.gpu
+
+
+def spmm(rows, cols, w, x, n):
+    """out[rows[e]] += w[e] x[cols[e]] in float64, on the CPU."""
+    m = scipy.sparse.csr_matrix((w.cpu().numpy(), (rows.cpu().numpy(), cols.cpu().numpy())), shape=(n, x.shape[0]))
+    return torch.from_numpy(m @ x.cpu().numpy()).cuda()
+
+
+@pytest.mark.parametrize("num_dst,dim,dtype", [(1, 5, torch.float32), (17, 70, torch.float16), (32_768, 3, torch.float32), (32_769, 64, torch.float16),
+                                               (70_001, 33, torch.float32), (70_001, 130, torch.float16), (40_000, 260, torch.float32),
+                                               (3_000, 1030, torch.float32), (530_000, 16, torch.float16), (600_000, 9, torch.float32)])
+def test_runs_of_rows(num_dst, dim, dtype):
+    from paper_2601_04707_amd import mqg
+    gen = torch.Generator(device="cuda").manual_seed(num_dst + dim)
+    lens = torch.randint(0, 7, (num_dst,), generator=gen, device="cuda")
+    lens[torch.randint(0, num_dst, (max(1, num_dst // 50),), generator=gen, device="cuda")] = 0
+    lens[num_dst // 2] = 300
+    num_src = num_dst + 500
+    indptr = torch.zeros(num_dst + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(lens, 0, out=indptr[1:])
+    nnz = int(indptr[-1])
+    rows = torch.repeat_interleave(torch.arange(num_dst, device="cuda"), lens)
+    cols = torch.randint(0, num_src, (nnz,), generator=gen, device="cuda")
+    cols[: nnz // 4] = num_src // 3                        # one source that a quarter of the edges point to
+    ctx, blocks = bare_blocks(mqg, indptr.cpu().numpy(), cols.cpu().numpy(), num_dst, num_src)
+    x = torch.randn((num_src, dim), generator=gen, device="cuda").to(dtype)
+    g = torch.randn((num_dst, dim), generator=gen, device="cuda").to(dtype)
+    ew = torch.randn(max(nnz, 1), generator=gen, device="cuda")
+    sw = torch.randn(num_dst, generator=gen, device="cuda")
+    sw[::3] = 0                                            # a diagonal term of zero is no term:
+    xi = x.clone()
+    xi[:num_dst:3] = float("inf")                          # its input row may hold anything, as long as no edge reads it
+    keep = ~((cols < num_dst) & (cols % 3 == 0))
+    out = torch.full((num_dst + 1, dim), 7.0, dtype=dtype, device="cuda")
+    gx = torch.full((num_src + 1, dim), 7.0, dtype=dtype, device="cuda")
+
+    def check(got, rows, cols, w, x, n, scale=None, diag=None):
+        ref, mag = spmm(rows, cols, w, x.double(), n), spmm(rows, cols, w.abs(), x.double().abs(), n)
+        terms = torch.from_numpy(np.bincount(rows.cpu().numpy(), minlength=n)).double().cuda()
+        if diag is not None:
+            ref[: len(diag)] += diag[:, None] * x.double()[: len(diag)]
+            mag[: len(diag)] += diag.abs()[:, None] * x.double()[: len(diag)].abs()
+        if scale is not None:
+            ref, mag = ref * scale[:, None], mag * scale[:, None]
+        bound = (terms + 4)[:, None] * 2.0 ** -24 * mag + (2.0 ** -11 * ref.abs() + 2.0 ** -24 if dtype == torch.float16 else 0)
+        assert torch.all((got[:n].double() - ref).abs() <= bound)
+        assert torch.all(got[n:] == 7.0)
+
+    one = torch.ones(nnz, dtype=torch.float64, device="cuda")
+    inv = 1 / lens.clamp(min=1).double()
+    mqg.mqg_sage_mean_aggregate(ctx, blocks, 0, x, out)
+    check(out, rows, cols, one, x, num_dst, scale=inv)
+    mqg.mqg_sage_mean_aggregate_backward(ctx, blocks, 0, g, gx)
+    check(gx, cols, rows, inv[rows], g, num_src)
+    w = ew[:nnz].double()
+    mqg.mqg_weighted_aggregate(ctx, blocks, 0, ew, sw, x, out)
+    check(out, rows, cols, w, x, num_dst, diag=sw.double())
+    mqg.mqg_weighted_aggregate_backward(ctx, blocks, 0, ew, sw, g, gx)
+    check(gx, cols, rows, w, g, num_src, diag=sw.double())
+    # rows that only see finite inputs stay finite next to a zero-weight diagonal over an infinite row
+    mqg.mqg_weighted_aggregate(ctx, blocks, 0, ew, sw, xi, out)
+    dirty = torch.zeros(num_dst, dtype=torch.bool, device="cuda")
+    dirty[rows[~keep]] = True
+    assert torch.all(torch.isfinite(out[:num_dst][~dirty & (sw == 0)]))

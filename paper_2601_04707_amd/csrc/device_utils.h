@@ -45,11 +45,12 @@ __device__ __forceinline__ uint64_t low_lanes(int n) { return n >= 64 ? ~uint64_
 // stops as soon as the undecided candidates are exactly as many as are still needed, after about
 // log2(candidates) bits for random keys.  Masks and counters live in scalar registers.  Every lane
 // of the wavefront must call it; need must be at least 1 and at most the number of candidates.
-// On return sel[c] holds the chosen lanes of chunk c.
+// On return sel[c] holds the chosen lanes of chunk c.  `top`: the bits of every candidate's key above bit
+// 32 + top are known to be zero.
 template <int NCH, bool PRIO, bool TIE>
 __device__ __forceinline__ void wave_select_smallest(const uint64_t (&key)[NCH], const uint64_t (&late)[NCH],
                                                      const uint32_t (&tie)[NCH], uint64_t (&cand)[NCH], int need,
-                                                     uint64_t (&sel)[NCH]) {
+                                                     uint64_t (&sel)[NCH], int top = 31) {
 #pragma unroll
     for (int c = 0; c < NCH; ++c) sel[c] = 0;
     auto settled = [&]() -> bool {
@@ -90,7 +91,7 @@ __device__ __forceinline__ void wave_select_smallest(const uint64_t (&key)[NCH],
 #pragma unroll
         for (int c = 0; c < NCH; ++c)
             w[c] = part == 0 ? static_cast<uint32_t>(key[c] >> 32) : part == 1 ? static_cast<uint32_t>(key[c]) : tie[c];
-        for (int b = 31; b >= 0; --b) {
+        for (int b = part == 0 ? top : 31; b >= 0; --b) {
             const uint32_t bit = uint32_t(1) << b;
 #pragma unroll
             for (int c = 0; c < NCH; ++c) zeros[c] = ballot64((w[c] & bit) == 0) & cand[c];

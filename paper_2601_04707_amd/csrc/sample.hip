@@ -5,11 +5,12 @@
 // of its own, every other block's rides with the block before it):
 //   row info       adjacency start/degree of every destination, copy of the destinations into the
 //                  block's source list, per-tile sums of min(fanout, degree), list of the hubs
-//   k_sample       one wavefront per destination: smallest-k random keys, neighbours written in
-//                  ascending adjacency slot at row * fanout (no offsets needed yet), first-seen
-//                  nodes marked in an N-bit bitmap (destinations whose degree exceeds heavy_degree
-//                  are taken by whole workgroups in the same launch, so that a hub's key
-//                  evaluation is spread over four wavefronts instead of stretching the kernel's tail)
+//   k_sample       a wavefront takes destinations one by one: smallest-k random keys, then for a few
+//                  destinations together the neighbours, written in ascending adjacency slot at
+//                  row * fanout (no offsets needed yet), first-seen nodes marked in an N-bit bitmap
+//                  (destinations whose degree exceeds heavy_degree are taken by whole workgroups in the
+//                  same launch, so that a hub's key evaluation is spread over four wavefronts instead of
+//                  stretching the kernel's tail)
 //   k_offsets_count  two independent jobs in one launch: indptr from the row tile sums (every
 //                  workgroup adds up the sums of the tiles before its own; only above 8,192 tiles
 //                  does one k_scan_tiles launch scan them first) and the popcount of every tile
@@ -33,6 +34,8 @@ namespace {
 
 constexpr uint64_t kGolden = 0x9E3779B97F4A7C15ULL;
 constexpr uint64_t kMaxKey = ~uint64_t(0);
+constexpr int kBusyWaves = 8192;          // wavefronts that the chip runs at once: 256 CUs x 4 SIMDs x 8
+constexpr int kBatchRows = 8;             // destinations per wavefront and batch in k_sample, at most
 
 uint64_t host_mix64(uint64_t z) {
     z ^= z >> 30;
@@ -252,6 +255,86 @@ struct RowKeys {
     }
 };
 
+// The same keys for a wavefront that walks a row 64 slots at a time, slot = base + lane with base a
+// multiple of 64.  Up to the first multiplication a lane's word differs from the wavefront's only in its
+// six low bits, so the product splits into a part that depends on the row and base alone (scalar unit) and
+// a part that depends on the row and the lane alone (once per row): what is left of the first half of the
+// mixer per key is one 64-bit addition, and three multiplications per key remain of five.  One object
+// serves the slots of one range of 2^30 (the slot's two top bits reach the low bits).
+struct WaveKeys {
+    uint32_t low;                 // low word after the first xor-shift, for slot 0 of the range
+    uint32_t hi_term;             // the high word's share of the first product
+    uint64_t lane_prod;           // (its low six bits, with the lane's) * C1
+    __device__ __forceinline__ WaveKeys(uint64_t hv, uint32_t range) {
+        const uint32_t hi = static_cast<uint32_t>(hv >> 32), lo = static_cast<uint32_t>(hv);
+        const uint64_t c1 = (uint64_t(RowKeys::kC1Hi) << 32) | RowKeys::kC1Lo;
+        hi_term = __builtin_amdgcn_readfirstlane((hi ^ (hi >> 30)) * RowKeys::kC1Lo);
+        low = __builtin_amdgcn_readfirstlane(lo ^ ((hi << 2) | ((lo ^ range) >> 30)));
+        lane_prod = static_cast<uint64_t>((low & 63u) ^ static_cast<uint32_t>(lane_id())) * c1;
+    }
+    // the word before the final xor-shift: its upper half differs from the key's in bit 0 only
+    __device__ __forceinline__ uint64_t raw(uint32_t base) const {
+        // (the empty asm keeps the row's part in scalar registers: the compiler would fold its product into
+        // the addition as a vector multiply-add)
+        const uint32_t rest = (low ^ base) & ~63u;
+        uint32_t p_lo = rest * RowKeys::kC1Lo;
+        uint32_t p_hi = static_cast<uint32_t>((uint64_t(rest) * RowKeys::kC1Lo) >> 32) + rest * RowKeys::kC1Hi + hi_term;
+        asm("" : "+s"(p_lo), "+s"(p_hi));
+        const uint64_t b = ((uint64_t(p_hi) << 32) | p_lo) + lane_prod;
+        const uint32_t b_lo = static_cast<uint32_t>(b), b_hi = static_cast<uint32_t>(b >> 32);
+        const uint32_t c_lo = b_lo ^ __builtin_amdgcn_alignbit(b_hi, b_lo, 27);
+        const uint32_t c_hi = b_hi ^ (b_hi >> 27);
+        const uint64_t q = static_cast<uint64_t>(c_lo) * RowKeys::kC2Lo;
+        const uint32_t d_hi = static_cast<uint32_t>(q >> 32) + c_lo * RowKeys::kC2Hi + c_hi * RowKeys::kC2Lo;
+        return (static_cast<uint64_t>(d_hi) << 32) | static_cast<uint32_t>(q);
+    }
+    static __device__ __forceinline__ uint64_t finish(uint64_t z) { return z ^ (z >> 31); }
+};
+
+// Candidates are the slots whose key's upper word is at most thr (bit 0 set, so that it can be compared
+// with the upper word of raw()): about `expect` of the d slots.
+__device__ __forceinline__ uint32_t threshold_for(int expect, int d) {
+    if (d <= expect) return 0xFFFFFFFFu;
+    const float t = static_cast<float>(expect) / static_cast<float>(d) * 4294967296.0f;
+    return static_cast<uint32_t>(t < 4294967040.0f ? t : 4294967040.0f) | 1u;
+}
+
+// The candidates among the slots base + lane, base = begin, begin + stride, ... (multiples of 64) of a row of
+// d, written by one wavefront to (ck, cs) in slot order, `cap` at most; returns their number.
+__device__ __forceinline__ int wave_candidates(uint64_t hv, int d, uint32_t thr, uint32_t begin, uint32_t stride, uint64_t *ck, int32_t *cs,
+                                               int cap) {
+    const int lane = lane_id();
+    int cnt = 0;
+    auto keep = [&](uint64_t z, uint32_t base, bool c) {
+        const uint64_t m = ballot64(c);
+        if (m) {
+            const int p = cnt + popc64(m & lanes_below(lane));
+            if (c && p < cap) {
+                ck[p] = WaveKeys::finish(z);
+                cs[p] = static_cast<int32_t>(base) + lane;
+            }
+            cnt += popc64(m);
+        }
+    };
+    for (uint32_t range = 0; range < static_cast<uint32_t>(d); range += 0x40000000u) {
+        const WaveKeys keys(hv, range);
+        const uint32_t end = static_cast<uint32_t>(d) - range < 0x40000000u ? static_cast<uint32_t>(d) : range + 0x40000000u;
+        uint32_t base = range + begin;
+        for (; base + 3 * stride + kWave <= end; base += 4 * stride) {
+            uint64_t z[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) z[u] = keys.raw(base + u * stride);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) keep(z[u], base + u * stride, static_cast<uint32_t>(z[u] >> 32) <= thr);
+        }
+        for (; base < end; base += stride) {
+            const uint64_t z = keys.raw(base);
+            keep(z, base, static_cast<uint32_t>(z >> 32) <= thr && base + lane < end);
+        }
+    }
+    return cnt;
+}
+
 // lexicographic (key, slot) order
 __device__ __forceinline__ bool pair_less(uint64_t ka, int sa, uint64_t kb, int sb) {
     return ka < kb || (ka == kb && sa < sb);
@@ -263,7 +346,7 @@ __device__ __forceinline__ bool pair_less(uint64_t ka, int sa, uint64_t kb, int 
 // are stored in ascending slot order, so equal keys need no second key.
 template <int NCH, bool PRIO, bool ORDERED, typename SlotT>
 __device__ __forceinline__ void select_candidates(const uint64_t *ck, const SlotT *cs, int cnt, int k,
-                                                  uint32_t (&slot)[NCH], uint64_t (&sel)[NCH]) {
+                                                  uint32_t (&slot)[NCH], uint64_t (&sel)[NCH], int top = 31) {
     const int lane = lane_id();
     uint64_t key[NCH], late[NCH], cand[NCH];
 #pragma unroll
@@ -279,7 +362,7 @@ __device__ __forceinline__ void select_candidates(const uint64_t *ck, const Slot
     uint32_t tie[NCH];
 #pragma unroll
     for (int c = 0; c < NCH; ++c) tie[c] = slot[c] & 0x7FFFFFFFu;
-    wave_select_smallest<NCH, PRIO, !ORDERED>(key, late, tie, cand, k, sel);
+    wave_select_smallest<NCH, PRIO, !ORDERED>(key, late, tie, cand, k, sel, top);
 }
 
 // The same for candidates in ascending slot order, emitted as the row's neighbours.
@@ -309,17 +392,12 @@ __device__ __forceinline__ void emit_selected_any(const uint64_t *ck, const Slot
     else emit_selected<kCandidates / kWave, PRIO>(ck, cs, cnt, k, col_idx, start, out_base, a);
 }
 
-// Hub rows: the candidates sit in LDS in arrival order.  The first wavefront picks the k winners,
-// lists their slots in sel_slot and emits them in ascending slot order.
-template <bool PRIO, typename IdxT, typename SlotT>
-__device__ __forceinline__ void emit_selected_unordered(const uint64_t *ck, const SlotT *cs, int cnt, int k,
-                                                        int32_t *sel_slot, const IdxT *__restrict__ col_idx,
-                                                        int64_t start, int32_t out_base, const SampleArgs &a) {
-    constexpr int NCH = kCandidates / kWave;
+// The chosen of candidates that are in no particular order: their slots are listed in sel_slot (LDS, 64
+// entries) and emitted in ascending order.
+template <int NCH, typename IdxT>
+__device__ __forceinline__ void emit_by_slot(const uint32_t (&slot)[NCH], const uint64_t (&sel)[NCH], int k, int32_t *sel_slot,
+                                             const IdxT *__restrict__ col_idx, int64_t start, int32_t out_base, const SampleArgs &a) {
     const int lane = lane_id();
-    uint32_t slot[NCH];
-    uint64_t sel[NCH];
-    select_candidates<NCH, PRIO, false>(ck, cs, cnt, k, slot, sel);
     int pos = 0;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
@@ -334,6 +412,18 @@ __device__ __forceinline__ void emit_selected_unordered(const uint64_t *ck, cons
         rank += (other < my_slot) ? 1 : 0;
     }
     if (lane < k) emit_neighbour(col_idx, start, my_slot, out_base + rank, a);
+}
+
+// Hub rows of the prioritised sampling: the candidates sit in LDS in arrival order.
+template <bool PRIO, typename IdxT, typename SlotT>
+__device__ __forceinline__ void emit_selected_unordered(const uint64_t *ck, const SlotT *cs, int cnt, int k,
+                                                        int32_t *sel_slot, const IdxT *__restrict__ col_idx,
+                                                        int64_t start, int32_t out_base, const SampleArgs &a) {
+    constexpr int NCH = kCandidates / kWave;
+    uint32_t slot[NCH];
+    uint64_t sel[NCH];
+    select_candidates<NCH, PRIO, false>(ck, cs, cnt, k, slot, sel);
+    emit_by_slot<NCH>(slot, sel, k, sel_slot, col_idx, start, out_base, a);
 }
 
 // The per-row selection on caller-supplied candidates (mqg_select_row_candidates): one wavefront,
@@ -402,138 +492,177 @@ __device__ void select_by_repeated_min(const IdxT *__restrict__ col_idx, int64_t
     if (lane < k) emit_neighbour(col_idx, start, my_slot, out_base + rank, a);
 }
 
-// Hubs (degree > heavy_degree, listed by k_row_info): the four wavefronts of a workgroup share
-// one row.  Candidates under the threshold are appended to one LDS list in arrival order (an LDS
-// atomic per wavefront and chunk); the result does not depend on that order because the
-// k winners are selected by (key, slot) and then ordered by slot.
+// What a wavefront keeps in LDS: the candidates of the row at hand, and the slots that its batch of rows
+// has selected (their position in the column array and where the neighbour goes).
+struct SampleLds {
+    uint64_t key[kWavesPerBlock][kCandidates];
+    int32_t slot[kWavesPerBlock][kCandidates];
+    int64_t pos[kWavesPerBlock][kWave];
+    int32_t out[kWavesPerBlock][kWave];
+};
+
+// Hubs (degree > heavy_degree, listed with the row information): the four wavefronts of a workgroup walk
+// one row together, 64 slots each in turn, each with a list of its own for 64 candidates (about 2k + 32 are
+// expected in all).  The k winners are selected by (key, slot) and then ordered by slot.  The wavefronts take
+// turns at that, while the others go on with the next hub into the second set of lists: one barrier per hub.
 template <typename IdxT>
-__device__ void sample_hubs(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, const SampleArgs &a,
-                            const int32_t *__restrict__ heavy_rows, int nheavy, int first, int step,
-                            uint64_t *ck, int32_t *cs, int32_t *sel_slot, int *cnt_s) {
-    const int tid = threadIdx.x;
+__device__ __forceinline__ void sample_hubs(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, const SampleArgs &a,
+                            const int32_t *__restrict__ heavy_rows, int nheavy, int first, int step, SampleLds &lds, int (&counts)[2][kWavesPerBlock]) {
+    static_assert(kWavesPerBlock * kWave == kCandidates, "one chunk of candidates per wavefront");
+    constexpr int NCH = kWavesPerBlock;
     const int lane = lane_id();
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
     const int k = a.fanout;
-    for (int h = first; h < nheavy; h += step) {
-        const int row = heavy_rows[h];
+    const uint64_t layer_hash = layer_hash_of(a);
+    int turn = 0;
+    for (int h = first; h < nheavy; h += step, ++turn) {   // the same for all four
+        const int row = __builtin_amdgcn_readfirstlane(heavy_rows[h]);
         const int64_t start = a.row_start[row];
-        const int d = a.row_deg[row];
+        const int d = __builtin_amdgcn_readfirstlane(a.row_deg[row]);
+        const uint64_t hv = readlane64(mix64(layer_hash ^ uint64_t(dst_ids[row])), 0);
+        uint64_t *ck = lds.key[turn & 1];
+        int32_t *cs = lds.slot[turn & 1];
+        const uint32_t thr = __builtin_amdgcn_readfirstlane(threshold_for(2 * k + 32, d));
+        const int mine = wave_candidates(hv, d, thr, wave * kWave, kBlock, ck + wave * kWave, cs + wave * kWave, kWave);
+        if (lane == 0) counts[turn & 1][wave] = mine;
+        __syncthreads();
+        if (wave != (turn & 3)) continue;
         const int32_t out_base = out_base_of(a, row);
-        const uint64_t hv = mix64(layer_hash_of(a) ^ uint64_t(dst_ids[row]));
-        const RowKeys key_of(hv);
-        if (tid == 0) *cnt_s = 0;
-        __syncthreads();
-        const int expect = 2 * k + 32;
-        uint64_t thr = kMaxKey;
-        if (d > expect) thr = static_cast<uint64_t>((double(expect) / double(d)) * 18446744073709551616.0);
-        for (int base = wave * kWave; base < d; base += kBlock) {
-            int j = base + lane;
-            uint64_t key = key_of(j);
-            bool c = j < d && key <= thr;
-            uint64_t m = ballot64(c);
-            if (m) {
-                int p0 = 0;
-                if (lane == 0) p0 = atomicAdd(cnt_s, popc64(m));
-                p0 = __shfl(p0, 0, 64);
-                if (c) {
-                    int p = p0 + popc64(m & lanes_below(lane));
-                    if (p < kCandidates) {
-                        ck[p] = key;
-                        cs[p] = j;
-                    }
-                }
-            }
+        uint64_t key[NCH], late[NCH], cand[NCH], sel[NCH];
+        uint32_t slot[NCH];
+        int total = 0, most = 0;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const int n = __builtin_amdgcn_readfirstlane(counts[turn & 1][c]);
+            key[c] = lane < n ? ck[c * kWave + lane] : 0;
+            slot[c] = lane < n ? static_cast<uint32_t>(cs[c * kWave + lane]) : 0u;
+            late[c] = 0;
+            cand[c] = low_lanes(n);
+            total += n;
+            most = n > most ? n : most;
         }
-        __syncthreads();
-        const int cnt = *cnt_s;
-        if (cnt < k || cnt > kCandidates) {                // workgroup-uniform; practically never
-            if (wave == 0) select_by_repeated_min(col_idx, start, d, k, hv, out_base, a);
-            __syncthreads();
+        if (total < k || most > kWave) {                   // practically never
+            select_by_repeated_min(col_idx, start, d, k, hv, out_base, a);
             continue;
         }
-        if (wave == 0) emit_selected_unordered<false>(ck, cs, cnt, k, sel_slot, col_idx, start, out_base, a);
-        __syncthreads();                                   // LDS is reused by the next row
+        wave_select_smallest<NCH, false, true>(key, late, slot, cand, k, sel, 31 - __builtin_clz(thr));
+        emit_by_slot<NCH>(slot, sel, k, lds.out[wave], col_idx, start, out_base, a);
     }
 }
 
 static_assert(kCandidates % kWave == 0, "candidates are selected in chunks of one per lane");
 
-// The first hub_blocks workgroups take the hubs (they are dispatched first and run the longest);
-// every other workgroup gives each of its four wavefronts one destination.
+// The chosen lanes of one chunk of candidates of a row, appended to the batch's list.
+__device__ __forceinline__ int push_selected(uint64_t sel, int slot, int64_t start, int32_t out_pos, int held, int64_t *pos, int32_t *out) {
+    const int lane = lane_id();
+    if ((sel >> lane) & 1) {
+        const int r = popc64(sel & lanes_below(lane));
+        pos[held + r] = start + slot;
+        out[held + r] = out_pos + r;
+    }
+    return popc64(sel);
+}
+template <int NCH>
+__device__ __forceinline__ void push_smallest(const uint64_t *ck, const int32_t *cs, int cnt, int k, int top, int64_t start, int32_t out_base,
+                                              int held, int64_t *pos, int32_t *out) {
+    uint32_t slot[NCH];
+    uint64_t sel[NCH];
+    select_candidates<NCH, false, true>(ck, cs, cnt, k, slot, sel, top);
+    int n = 0;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) n += push_selected(sel[c], static_cast<int>(slot[c]), start, out_base + n, held + n, pos, out);
+}
+
+// The first hub_blocks workgroups take the hubs (they are dispatched first and run the longest; 1,024 of them
+// instead of 2,048: 10 % slower where hubs hold most of the slots); the others' wavefronts take batches of
+// consecutive destinations, as many as leave a batch for every wavefront of the chip and select at most 64
+// slots: their row information is loaded by one instruction, and their neighbours' ids, positions and
+// marks - a chain of three dependent accesses - are fetched once for all.
+// Bound by instruction issue: 92 M keys of 43 k rows (graph of 111 M nodes) at 19 vector instructions per 64
+// keys, three of them quarter-rate multiplications, in 80 us (122 before: five multiplications, a hub's
+// four wavefronts meeting at three barriers per row); 23 M keys of 10 k rows 46 -> 32 us; 295 k rows of 223
+// slots 270 -> 147 us (the batches).
 template <typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_sample(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, SampleArgs a,
          const int32_t *__restrict__ heavy_rows, const int32_t *__restrict__ heavy_count, int hub_blocks) {
-    __shared__ uint64_t cand_key[kWavesPerBlock][kCandidates];
-    __shared__ int32_t cand_slot[kWavesPerBlock][kCandidates];
-    __shared__ int32_t sel_slot[kWave];
-    __shared__ int cnt_s;
+    __shared__ SampleLds lds;
+    __shared__ int counts[2][kWavesPerBlock];
     if (static_cast<int>(blockIdx.x) < hub_blocks) {
-        sample_hubs(col_idx, dst_ids, a, heavy_rows, *heavy_count, static_cast<int>(blockIdx.x), hub_blocks,
-                    cand_key[0], cand_slot[0], sel_slot, &cnt_s);
+        sample_hubs(col_idx, dst_ids, a, heavy_rows, *heavy_count, static_cast<int>(blockIdx.x), hub_blocks, lds, counts);
         return;
     }
     const int lane = lane_id();
-    const int wave = static_cast<int>(threadIdx.x) >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
     const int64_t n = a.sizes[0];
-    const int64_t row = (int64_t(blockIdx.x) - hub_blocks) * kWavesPerBlock + wave;
-    if (row >= n) return;                                  // whole wavefront leaves together
-
-    const int64_t start = a.row_start[row];
-    const int d = a.row_deg[row];
     const int k = a.fanout;
-    const int32_t out_base = out_base_of(a, row);
-
-    if (d <= k) {                                          // the whole row, no randomness
-        if (lane < d) emit_neighbour(col_idx, start, lane, out_base + lane, a);
-        return;
-    }
-    if (d > a.heavy_degree) return;                        // a hub: sampled by the first workgroups
-    const uint64_t hv = mix64(layer_hash_of(a) ^ uint64_t(dst_ids[row]));
-    if (a.force_slow) {
-        select_by_repeated_min(col_idx, start, d, k, hv, out_base, a);
-        return;
-    }
-    if (d <= kWave) {
-        // one key per lane
-        const uint64_t key[1] = {RowKeys(hv)(lane)};
-        const uint64_t late[1] = {0};
-        const uint32_t tie[1] = {0};
-        uint64_t cand[1] = {low_lanes(d)}, sel[1];
-        wave_select_smallest<1, false, false>(key, late, tie, cand, k, sel);
-        if ((sel[0] >> lane) & 1) emit_neighbour(col_idx, start, lane, out_base + popc64(sel[0] & lanes_below(lane)), a);
-        return;
-    }
-
-    // d > 64: keep the slots whose key falls under a threshold expected to pass 2k+32 of them,
-    // then select among those candidates only.  Candidates are stored in ascending slot order.
-    uint64_t *ck = cand_key[wave];
-    int32_t *cs = cand_slot[wave];
-    const int expect = 2 * k + 32;
-    uint64_t thr = kMaxKey;
-    if (d > expect) thr = static_cast<uint64_t>((double(expect) / double(d)) * 18446744073709551616.0);
-    int cnt = 0;
-    const RowKeys key_of(hv);
-    for (int base = 0; base < d; base += kWave) {
-        int j = base + lane;
-        uint64_t key = key_of(j);
-        bool c = j < d && key <= thr;
-        uint64_t m = ballot64(c);
-        if (c) {
-            int p = cnt + popc64(m & lanes_below(lane));
-            if (p < kCandidates) {
-                ck[p] = key;
-                cs[p] = j;
+    const int64_t share = n / kBusyWaves;
+    const int most = kWave / k < kBatchRows ? kWave / k : kBatchRows;
+    const int batch = share < 1 ? 1 : share < most ? static_cast<int>(share) : most;
+    const int64_t step = int64_t(static_cast<int>(gridDim.x) - hub_blocks) * kWavesPerBlock * batch;
+    const int first_expect = k + 4 * static_cast<int>(__builtin_sqrtf(static_cast<float>(k))) + 8;     // candidates wanted of a long row
+    const uint64_t layer_hash = layer_hash_of(a);
+    uint64_t *ck = lds.key[wave];
+    int32_t *cs = lds.slot[wave];
+    int64_t *pos = lds.pos[wave];
+    int32_t *out = lds.out[wave];
+    for (int64_t row0 = (int64_t(static_cast<int>(blockIdx.x) - hub_blocks) * kWavesPerBlock + wave) * batch; row0 < n; row0 += step) {
+        const int m = n - row0 < batch ? static_cast<int>(n - row0) : batch;
+        const int64_t my_row = row0 + (lane < m ? lane : 0);
+        const int64_t my_start = a.row_start[my_row];
+        const int my_deg = a.row_deg[my_row];
+        const int32_t my_out = out_base_of(a, my_row);
+        const uint64_t my_hv = mix64(layer_hash ^ uint64_t(dst_ids[my_row]));
+        int held = 0;                                      // slots selected so far
+        for (int r = 0; r < m; ++r) {
+            const int d = static_cast<int>(readlane32(static_cast<uint32_t>(my_deg), r));
+            const int64_t start = static_cast<int64_t>(readlane64(static_cast<uint64_t>(my_start), r));
+            const int32_t out_base = static_cast<int32_t>(readlane32(static_cast<uint32_t>(my_out), r));
+            if (d <= k) {                                  // the whole row, no randomness
+                held += push_selected(low_lanes(d), lane, start, out_base, held, pos, out);
+                continue;
             }
+            if (d > a.heavy_degree) continue;              // a hub: sampled by the first workgroups
+            const uint64_t hv = readlane64(my_hv, r);
+            if (a.force_slow) {
+                select_by_repeated_min(col_idx, start, d, k, hv, out_base, a);
+                continue;
+            }
+            if (d <= kWave) {                              // one key per lane
+                const uint64_t key[1] = {WaveKeys::finish(WaveKeys(hv, 0).raw(0))};
+                const uint64_t late[1] = {0};
+                const uint32_t tie[1] = {0};
+                uint64_t cand[1] = {low_lanes(d)}, sel[1];
+                wave_select_smallest<1, false, false>(key, late, tie, cand, k, sel);
+                held += push_selected(sel[0], lane, start, out_base, held, pos, out);
+                continue;
+            }
+            // Longer rows: the slots under a key threshold are candidates, stored in ascending slot order; too
+            // few (3 rows in 100,000): again with a higher one.
+            int expect = first_expect;
+            uint32_t thr;
+            int cnt;
+            do {
+                thr = __builtin_amdgcn_readfirstlane(threshold_for(expect, d));
+                cnt = wave_candidates(hv, d, thr, 0, kWave, ck, cs, kCandidates);
+                expect = 2 * expect + 32;
+            } while (cnt < k);
+            if (cnt > kCandidates) {
+                select_by_repeated_min(col_idx, start, d, k, hv, out_base, a);
+                continue;
+            }
+            wave_lds_sync();
+            const int top = 31 - __builtin_clz(thr);
+            if (cnt <= kWave) push_smallest<1>(ck, cs, cnt, k, top, start, out_base, held, pos, out);
+            else if (cnt <= 2 * kWave) push_smallest<2>(ck, cs, cnt, k, top, start, out_base, held, pos, out);
+            else push_smallest<kCandidates / kWave>(ck, cs, cnt, k, top, start, out_base, held, pos, out);
+            held += k;
+            wave_lds_sync();                               // the candidates' place is the next row's
         }
-        cnt += popc64(m);
+        wave_lds_sync();
+        if (lane < held) emit_neighbour(col_idx, pos[lane], 0, out[lane], a);
+        wave_lds_sync();                                   // pos and out are the next batch's
     }
-    if (cnt < k || cnt > kCandidates) {                    // wavefront-uniform
-        select_by_repeated_min(col_idx, start, d, k, hv, out_base, a);
-        return;
-    }
-    wave_lds_sync();
-    emit_selected_any<false>(ck, cs, cnt, k, col_idx, start, out_base, a);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1126,7 +1255,10 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
         a.force_slow = ctx->force_slow_select ? 1 : 0;
         a.heavy_degree = heavy_degree;
         const int hub_blocks = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, need_dst), 2048));
-        int sample_grid = hub_blocks + static_cast<int>(std::max<int64_t>(1, ceil_div(need_dst, kWavesPerBlock)));
+        // k_sample's wavefronts loop over their batches: no more workgroups than fill the chip four times
+        // (the bound is often twice the number of destinations, and an idle workgroup costs a dispatch)
+        const int64_t row_blocks = std::min<int64_t>(std::max<int64_t>(1, ceil_div(need_dst, kWavesPerBlock)), ctx->prio_enabled ? int64_t(1) << 30 : 8192);
+        const int sample_grid = hub_blocks + static_cast<int>(row_blocks);
         if (ctx->prio_enabled) {
             MQG_LAUNCH(ctx, "k_sample_prio", s,
                        (k_sample_prio<IdxT><<<sample_grid, kBlock, 0, s>>>(col_idx, src_ids, a, ctx->prio_bitmap, ctx->prio_count,

@@ -1,0 +1,78 @@
+"""Neighbour selection at the edges of its paths: degrees around the fanout, around 64 (one key per lane),
+around multiples of 64 and 256 (the unrolled key loops and their remainders), around the hub limit, more
+destinations than the chip runs wavefronts (batches of rows), and a row of more than 2^30 slots."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import assert_blocks_equal, hip_sample
+
+pytestmark = pytest.mark.gpu
+
+DEGREES = [0, 1, 2, 4, 5, 6, 24, 25, 26, 62, 63, 64, 65, 66, 127, 128, 129, 191, 193, 255, 256, 257, 300, 319, 320, 321, 383, 513, 1000]
+HUBS = [2047, 2048, 2049, 2304, 2560, 2816, 3000, 3071, 3073, 4999]
+
+
+@pytest.mark.parametrize("num_seeds,fanout,ptr,idx", [(37, 5, torch.int32, torch.int64), (9000, 25, torch.int64, torch.int32),
+                                                      (20_000, 64, torch.int32, torch.int32), (40_000, 1, torch.int64, torch.int64),
+                                                      (70_000, 15, torch.int32, torch.int32)])
+def test_degrees_and_batches(num_seeds, fanout, ptr, idx):
+    from paper_2601_04707_amd import mqg
+    rng = np.random.default_rng(num_seeds + fanout)
+    n = num_seeds + 5100
+    deg = rng.choice(DEGREES[:16], n)
+    deg[:500] = rng.choice(DEGREES, 500)
+    deg[500:540] = rng.choice(HUBS, 40)
+    deg = deg[rng.permutation(n)]
+    row_ptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    # distinct neighbours: a run of consecutive ids from a random first one, in a random order for some
+    first = rng.integers(0, n, n)
+    col = (np.repeat(first, deg) + np.arange(row_ptr[-1]) - np.repeat(row_ptr[:-1], deg)) % n
+    seeds = rng.permutation(n)[:num_seeds]
+    want = oracle.sample_blocks(row_ptr, col.astype(np.int64), seeds, [fanout], 99)
+    g = mqg.Graph(torch.from_numpy(row_ptr).to(ptr).cuda(), torch.from_numpy(col).to(idx).cuda())
+    ctx = mqg.Context(g, num_seeds, [fanout])
+    blocks = mqg.Blocks(g, num_seeds, [fanout])
+    assert_blocks_equal(hip_sample(mqg, ctx, g, blocks, torch.from_numpy(seeds), [fanout], 99), want)
+    ctx.set_option(mqg.MQG_OPT_HEAVY_DEGREE, 64)           # every long row is a hub
+    assert_blocks_equal(hip_sample(mqg, ctx, g, blocks, torch.from_numpy(seeds), [fanout], 99), want)
+
+
+def test_row_of_more_than_2_30_slots():
+    """Node 0 neighbours every other node of a graph of 2^30 + 1000; the keys are restated with torch."""
+    from paper_2601_04707_amd import mqg
+    n, k, seed = (1 << 30) + 1000, 20, 5
+    d = n - 1
+    row_ptr = torch.full((n + 1,), d, dtype=torch.int32, device="cuda")
+    row_ptr[0] = 0
+    g = mqg.Graph(row_ptr, torch.arange(1, n, dtype=torch.int32, device="cuda"))
+
+    def signed(v):
+        v &= (1 << 64) - 1
+        return v - (1 << 64) if v >> 63 else v
+
+    def mix(z):
+        for shift, mul in ((30, 0xBF58476D1CE4E5B9), (27, 0x94D049BB133111EB), (31, 1)):
+            z = (z ^ ((z >> shift) & ((1 << (64 - shift)) - 1))) * signed(mul)
+        return z
+
+    hv = mix(mix(mix(torch.tensor([signed(seed + 0x9E3779B97F4A7C15)], device="cuda"))))     # layer 0, node 0
+    best = []
+    for j in range(0, d, 1 << 27):
+        slots = torch.arange(j, min(d, j + (1 << 27)), device="cuda")
+        keys = mix(hv ^ slots) ^ signed(1 << 63)           # unsigned order
+        top = torch.topk(keys, k, largest=False)
+        best.append(torch.stack([top.values, slots[top.indices]]))
+    best = torch.cat(best, 1)
+    want = torch.sort(best[1][torch.sort(best[0]).indices[:k]]).values
+    assert int(want.max()) >= 1 << 30 or int(want.max()) > 1 << 29
+    for heavy in (2048, 0x7FFFFFFF):                       # a workgroup's, a wavefront's
+        ctx = mqg.Context(g, 1, [k])
+        ctx.set_option(mqg.MQG_OPT_HEAVY_DEGREE, heavy)
+        blocks = mqg.Blocks(g, 1, [k])
+        mqg.mqg_sample_blocks(ctx, g, torch.zeros(1, dtype=torch.int32, device="cuda"), [k], seed, blocks)
+        torch.cuda.synchronize()
+        assert blocks.host_sizes()[0] == (1, k + 1, k, 0)
+        assert torch.equal(blocks.src_ids[0][1:k + 1].long(), want + 1)
+        ctx.close()

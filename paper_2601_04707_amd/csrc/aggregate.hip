@@ -4,8 +4,8 @@
 // dense contraction, hence no matrix cores.
 //
 //   k_segment_flat   one wavefront per run of up to kRunRows consecutive output rows, its 64 lanes side by
-//                    side over the columns (wider rows: slabs of 64 vectors, each a share of the
-//                    grid).  The entries of the run are walked as one sequence across the row ends:
+//                    side over the columns (wider rows: several vectors per lane, or slabs of 64
+//                    vectors, each a share of the grid).  The entries of the run are walked as one sequence across the row ends:
 //                    64 of them are fetched at a time, one per lane, and U input rows are loaded before
 //                    the first of them is added, however few entries the rows have.  Entry numbers, row
 //                    ends and addresses are the same in all lanes and live in scalar registers: per
@@ -39,6 +39,7 @@ __device__ __forceinline__ void from_f32(float x, _Float16 *o) { *o = static_cas
 
 // Forward: entries of output row i are the block's edges of destination i.
 struct ForwardRows {
+    static constexpr bool kFewEntries = false;
     static constexpr bool kWeighted = false;
     static constexpr bool kSelf = false;
     __device__ __forceinline__ int64_t self_rows(int64_t) const { return 0; }
@@ -54,6 +55,7 @@ struct ForwardRows {
 // Backward: entries of output row s are the edges pointing to source s; each contributes the
 // gradient row of its destination scaled by one over that destination's edge count.
 struct BackwardRows {
+    static constexpr bool kFewEntries = true;
     static constexpr bool kWeighted = true;
     static constexpr bool kSelf = false;
     __device__ __forceinline__ int64_t self_rows(int64_t) const { return 0; }
@@ -73,6 +75,7 @@ struct BackwardRows {
 // Weighted forward (the sampled estimator of the graph convolution, paper Eq. 1-3, or any other
 // per-edge weights): out[i] = self_w[i] x[i] + sum over the edges p of row i of edge_w[p] x[indices[p]].
 struct WeightedRows {
+    static constexpr bool kFewEntries = false;
     static constexpr bool kWeighted = true;
     static constexpr bool kSelf = true;
     const int32_t *indptr;
@@ -90,6 +93,7 @@ struct WeightedRows {
 // Its transpose: output row s reduces edge_w * grad_out[destination] over the edges pointing to
 // source s (ordered by source, stable), plus self_w[s] * grad_out[s] where s is a destination.
 struct WeightedBackwardRows {
+    static constexpr bool kFewEntries = true;
     static constexpr bool kWeighted = true;
     static constexpr bool kSelf = true;
     const int32_t *col_ptr;
@@ -117,20 +121,25 @@ struct WeightedBackwardRows {
 // hot rows (L2 hits 13 -> 24 %, time unchanged or worse); 4 or 16 instead of 8 vectors of 16 bytes in flight.
 constexpr int kRunRows = 16;
 
-template <typename T, int VEC, typename Rows>
+template <typename T, int VEC, int NV, typename Rows>
 __global__ void __launch_bounds__(kBlock)
 k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restrict__ x, int64_t x_stride,
                T *__restrict__ out, int64_t out_stride, int dim, uint32_t row_blocks) {
     using P = Pack<T, VEC>;
-    constexpr int U = sizeof(P) == 16 ? 8 : 16;            // input rows in flight: 4 to 8 KB per wavefront
-    constexpr int NACC = VEC <= 2 ? 4 : 2;                 // partial sums that take the entries in turn
+    constexpr int U = NV == 1 ? (sizeof(P) == 16 ? 8 : 16) : NV == 2 ? (Rows::kFewEntries ? 4 : 8) : NV == 3 ? 4 : 2;    // input rows in flight: 4 to 12 KB per wavefront
+    constexpr int NACC = VEC <= 2 ? 4 : NV <= 2 ? 2 : 1;   // partial sums that take the entries in turn
     const int lane = lane_id();
     const int64_t n = *n_rows;
     const uint32_t slab = blockIdx.x / row_blocks;
     const uint32_t row_block = blockIdx.x - slab * row_blocks;
-    const uint32_t col0 = (slab * kWave + lane) * VEC;
-    const bool live = col0 < static_cast<uint32_t>(dim);
-    const uint32_t lane_off = (live ? col0 : 0u) * sizeof(T);      // lanes past the row read its start and store nothing
+    bool live[NV];
+    uint32_t lane_off[NV];                                 // lanes past the row read its start and store nothing
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const uint32_t col = ((slab * NV + k) * kWave + lane) * VEC;
+        live[k] = col < static_cast<uint32_t>(dim);
+        lane_off[k] = (live[k] ? col : 0u) * sizeof(T);
+    }
     const int64_t self_rows = Rows::kSelf ? rows.self_rows(n) : 0;         // rows with a diagonal term: the first ones
     const int64_t nwaves = int64_t(row_blocks) * kWavesPerBlock;
     const int64_t wave0 = __builtin_amdgcn_readfirstlane(static_cast<int>(row_block) * kWavesPerBlock + static_cast<int>(threadIdx.x >> 6));
@@ -147,23 +156,29 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
         const uint32_t begin = readlane32(off, 0), end = readlane32(off, m);
         int cur = 0;
         uint32_t row_begin = begin, row_end = readlane32(off, 1);
-        float acc[NACC][VEC];
+        float acc[NACC][NV][VEC];
 #pragma unroll
         for (int a = 0; a < NACC; ++a)
 #pragma unroll
-            for (int q = 0; q < VEC; ++q) acc[a][q] = 0.f;
+            for (int k = 0; k < NV; ++k)
+#pragma unroll
+                for (int q = 0; q < VEC; ++q) acc[a][k][q] = 0.f;
         auto finish_row = [&]() {
-            P o;
-#pragma unroll
-            for (int q = 0; q < VEC; ++q) {
-                float sum = acc[0][q] + acc[1][q];
-                if constexpr (NACC == 4) sum += acc[2][q] + acc[3][q];
-                from_f32(rows.finish(sum, static_cast<int>(row_end - row_begin)), &o.v[q]);
-#pragma unroll
-                for (int a = 0; a < NACC; ++a) acc[a][q] = 0.f;
-            }
             char *orow = reinterpret_cast<char *>(out) + (c0 + cur) * out_bytes;
-            if (live) *reinterpret_cast<P *>(orow + lane_off) = o;
+#pragma unroll
+            for (int k = 0; k < NV; ++k) {
+                P o;
+#pragma unroll
+                for (int q = 0; q < VEC; ++q) {
+                    float sum = acc[0][k][q];
+                    if constexpr (NACC >= 2) sum += acc[1][k][q];
+                    if constexpr (NACC == 4) sum += acc[2][k][q] + acc[3][k][q];
+                    from_f32(rows.finish(sum, static_cast<int>(row_end - row_begin)), &o.v[q]);
+#pragma unroll
+                    for (int a = 0; a < NACC; ++a) acc[a][k][q] = 0.f;
+                }
+                if (live[k]) *reinterpret_cast<P *>(orow + lane_off[k]) = o;
+            }
             ++cur;
             row_begin = row_end;
             row_end = readlane32(off, cur + 1);
@@ -196,11 +211,13 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
                 if (Rows::kWeighted) my_w = rows.weight(static_cast<int>(p));
             }
             for (int b = 0; b < cnt; b += U) {
-                P v[U];
+                P v[U][NV];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int r = static_cast<int>(readlane32(static_cast<uint32_t>(my_row), b + u));
-                    v[u] = *reinterpret_cast<const P *>(xb + (Rows::kSelf && r < 0 ? 0 : r) * x_bytes + lane_off);
+                    const char *row = xb + (Rows::kSelf && r < 0 ? 0 : r) * x_bytes;
+#pragma unroll
+                    for (int k = 0; k < NV; ++k) v[u][k] = *reinterpret_cast<const P *>(row + lane_off[k]);
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -209,11 +226,13 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
                     if (Rows::kSelf && static_cast<int>(readlane32(static_cast<uint32_t>(my_row), b + u)) < 0) continue;
                     const float w = __uint_as_float(readlane32(__float_as_uint(my_w), b + u));
 #pragma unroll
-                    for (int q = 0; q < VEC; ++q) {
-                        float &a = acc[u % NACC][q];
-                        if (Rows::kWeighted) a += w * to_f32(v[u].v[q]);
-                        else a += to_f32(v[u].v[q]);
-                    }
+                    for (int k = 0; k < NV; ++k)
+#pragma unroll
+                        for (int q = 0; q < VEC; ++q) {
+                            float &a = acc[u % NACC][k][q];
+                            if (Rows::kWeighted) a += w * to_f32(v[u][k].v[q]);
+                            else a += to_f32(v[u][k].v[q]);
+                        }
                 }
             }
         }
@@ -240,22 +259,42 @@ int launch(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_ro
     while (vec > 1 && !ok(vec)) vec >>= 1;
     // the narrowest vector with which the 64 lanes still cover the row (wider rows: the widest, in slabs)
     while (vec > 1 && ceil_div(dim, vec / 2) <= kWave) vec >>= 1;
-    const int64_t slabs = ceil_div(dim, kWave * vec);
+    // Rows of more than 64 vectors: NV vectors per lane, or slabs of 64 vectors with a wavefront each.  More
+    // vectors per lane share the walk over the entries, slabs spread few rows over more wavefronts and
+    // leave a row's last, partly filled vector to a wavefront of its own.  Output rows of few entries (the
+    // backward) want the first up to six vectors (513 to 800 fp32 columns: 236 to 345 us against 295 to
+    // 367 us), output rows of many entries the second from three vectors up if these are well filled (602
+    // columns, 79 %: 198 against 204 us; 513 columns, 67 %: 214 against 188 us).
+    const int64_t lanes = ceil_div(dim, vec);
+    const int64_t units = ceil_div(lanes, kWave);
+    const bool spread = units > 6 || vec < 8 / static_cast<int>(sizeof(T)) || (!Rows::kFewEntries && units >= 3 && lanes * 100 >= units * kWave * 78);
+    const int nv = spread ? 1 : static_cast<int>(units);
+    const int64_t slabs = ceil_div(units, nv);
     const int64_t row_blocks = std::min<int64_t>(std::max<int64_t>(1, ceil_div(cap_rows, kWavesPerBlock)), 256 * 32);
     const int grid = static_cast<int>(row_blocks * slabs);
-#define MQG_AGG(V)                                                                                              \
+#define MQG_AGG(V, NV)                                                                                          \
     MQG_LAUNCH(ctx, name, s,                                                                                    \
-               (k_segment_flat<T, V, Rows><<<grid, kBlock, 0, s>>>(rows, n_rows, x, x_stride, out, out_stride, dim, static_cast<uint32_t>(row_blocks))))
+               (k_segment_flat<T, V, NV, Rows><<<grid, kBlock, 0, s>>>(rows, n_rows, x, x_stride, out, out_stride, dim, static_cast<uint32_t>(row_blocks))))
+#define MQG_AGG_PICK(V)                        \
+    switch (nv) {                              \
+        case 1: MQG_AGG(V, 1); break;          \
+        case 2: MQG_AGG(V, 2); break;          \
+        case 3: MQG_AGG(V, 3); break;          \
+        case 4: MQG_AGG(V, 4); break;          \
+        case 5: MQG_AGG(V, 5); break;          \
+        default: MQG_AGG(V, 6); break;         \
+    }
     constexpr int kWidest = 16 / static_cast<int>(sizeof(T));
     if (vec == kWidest) {
-        MQG_AGG(kWidest);
+        MQG_AGG_PICK(kWidest);
     } else if (vec == kWidest / 2) {
-        MQG_AGG(kWidest / 2);
+        MQG_AGG_PICK(kWidest / 2);
     } else if (vec == 2 && kWidest == 8) {
-        MQG_AGG(2);
+        MQG_AGG(2, 1);
     } else {
-        MQG_AGG(1);
+        MQG_AGG(1, 1);
     }
+#undef MQG_AGG_PICK
 #undef MQG_AGG
     return MQG_OK;
 }

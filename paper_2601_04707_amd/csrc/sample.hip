@@ -97,31 +97,40 @@ __device__ __forceinline__ void row_info_tile(const RowInfoArgs<PtrT, IdxT> &a, 
         cnt = d < a.fanout ? static_cast<int>(d) : a.fanout;
         heavy = d > a.heavy_degree;
     }
-    {   // list the hubs: one atomic per wavefront that has any
-        uint64_t m = ballot64(heavy);
-        if (m) {
-            int base = 0;
-            if (lane_id() == 0) base = atomicAdd(a.heavy_count, popc64(m));
-            base = __shfl(base, 0, 64);
-            if (heavy) a.heavy_rows[base + popc64(m & lanes_below(lane_id()))] = static_cast<int32_t>(i);
-        }
+    // list the hubs: one atomic per workgroup that has any (one per wavefront queued up at the counter: the
+    // relabel and row information of a block of 295 k destinations 32 -> 21 us, of 43 k 10.2 -> 5.7 us)
+    const uint64_t hubs = ballot64(heavy);
+    const int w = wave_sum(cnt);
+    const int wave = static_cast<int>(threadIdx.x) >> 6;
+    if (lane_id() == 0) {
+        lds[wave] = w;
+        lds[kWavesPerBlock + wave] = popc64(hubs);
     }
-    int w = wave_sum(cnt);
-    if (lane_id() == 0) lds[threadIdx.x >> 6] = w;
     __syncthreads();
     if (threadIdx.x == 0) {
-        int t = 0;
+        int t = 0, h = 0;
 #pragma unroll
-        for (int k = 0; k < kWavesPerBlock; ++k) t += lds[k];
+        for (int k = 0; k < kWavesPerBlock; ++k) {
+            t += lds[k];
+            h += lds[kWavesPerBlock + k];
+        }
         a.tile_sums[tile] = t;
         if (tile == 0 && a.n_seeds >= 0) a.sizes_rw[0] = a.n_seeds;
+        if (h) lds[2 * kWavesPerBlock] = atomicAdd(a.heavy_count, h);
+    }
+    __syncthreads();
+    if (heavy) {
+        int base = lds[2 * kWavesPerBlock];
+        for (int k = 0; k < wave; ++k) base += lds[kWavesPerBlock + k];
+        a.heavy_rows[base + popc64(hubs & lanes_below(lane_id()))] = static_cast<int32_t>(i);
     }
 }
+constexpr int kRowInfoLds = 2 * kWavesPerBlock + 1;
 
 template <typename PtrT, typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_row_info(RowInfoArgs<PtrT, IdxT> a) {
-    __shared__ int lds[kWavesPerBlock];
+    __shared__ int lds[kRowInfoLds];
     row_info_tile(a, static_cast<int>(blockIdx.x), lds);
 }
 
@@ -1155,7 +1164,7 @@ __global__ void __launch_bounds__(kBlock)
 k_relabel_rowinfo(const int32_t *__restrict__ nbr, const int64_t *__restrict__ sizes, const int32_t *__restrict__ indptr,
                   int fanout, const int32_t *__restrict__ local_of, int32_t *__restrict__ indices, int relabel_blocks,
                   RowInfoArgs<PtrT, IdxT> next, uint32_t *__restrict__ clear, int64_t nclear) {
-    __shared__ int lds[kWavesPerBlock];
+    __shared__ int lds[kRowInfoLds];
     const int b = static_cast<int>(blockIdx.x);
     if (b < relabel_blocks) {
         clear_words(clear, nclear, b, relabel_blocks);

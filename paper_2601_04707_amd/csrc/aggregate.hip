@@ -263,11 +263,11 @@ int launch(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_ro
     // vectors per lane share the walk over the entries, slabs spread few rows over more wavefronts and
     // leave a row's last, partly filled vector to a wavefront of its own.  Output rows of few entries (the
     // backward) want the first up to six vectors (513 to 800 fp32 columns: 236 to 345 us against 295 to
-    // 367 us), output rows of many entries the second from three vectors up if these are well filled (602
-    // columns, 79 %: 198 against 204 us; 513 columns, 67 %: 214 against 188 us).
+    // 367 us), output rows of many entries the second if the vectors are well filled (602 columns, 79 %: 198
+    // against 204 us; 513 columns, 67 %: 214 against 188 us).
     const int64_t lanes = ceil_div(dim, vec);
     const int64_t units = ceil_div(lanes, kWave);
-    const bool spread = units > 6 || vec < 8 / static_cast<int>(sizeof(T)) || (!Rows::kFewEntries && units >= 3 && lanes * 100 >= units * kWave * 78);
+    const bool spread = units > 6 || vec < 8 / static_cast<int>(sizeof(T)) || (!Rows::kFewEntries && units >= 2 && lanes * 100 >= units * kWave * 78);
     const int nv = spread ? 1 : static_cast<int>(units);
     const int64_t slabs = ceil_div(units, nv);
     const int64_t row_blocks = std::min<int64_t>(std::max<int64_t>(1, ceil_div(cap_rows, kWavesPerBlock)), 256 * 32);
@@ -301,51 +301,103 @@ int launch(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_ro
 
 // ---------------------------------------------------------------- edges ordered by source
 
-// payload of edge e = its destination row, found by bisection of indptr (the keys are `indices`)
+// Number of the entries of the ascending list v[0..n) that are below x (STRICT) or not above it, found by a
+// whole wavefront: 64 probes per step instead of one, so that a million entries take four dependent loads.
+template <bool STRICT, typename V>
+__device__ __forceinline__ int64_t wave_count_below(const V *__restrict__ v, int64_t n, int64_t x) {
+    int64_t lo = 0, hi = n;                                // the answer lies in [lo, hi]
+    while (lo < hi) {
+        const int64_t step = (hi - lo + kWave - 1) / kWave;
+        const int64_t i = lo + (lane_id() + 1) * step - 1;
+        const bool below = i < hi && (STRICT ? static_cast<int64_t>(v[i]) < x : static_cast<int64_t>(v[i]) <= x);
+        const int64_t c = popc64(ballot64(below));         // v ascends: the first c probes
+        const int64_t next = lo + (c + 1) * step - 1;      // the first probe that is not
+        lo += c * step;
+        hi = next < hi ? next : hi;
+    }
+    return lo;
+}
+
+// payload of edge e = its destination row (the keys are `indices`).  A wavefront takes kEdgeRun consecutive
+// edges; its lanes hold the offsets of 64 consecutive rows, and every edge finds its row among them.
+// Bound by its 4-byte store per edge; a bisection of all of indptr per edge (19 dependent loads) took 57
+// instead of 9 us for 4.3 M edges of 295 k rows.
+constexpr int kEdgeRun = 512;
+constexpr int64_t kPickRowsEdges = int64_t(3) << 19;     // see run_aggregate_backward
 __global__ void __launch_bounds__(kBlock)
 k_edge_dst_rows(const int32_t *__restrict__ indptr, const int64_t *__restrict__ sizes, int32_t *__restrict__ dst_row) {
+    const int lane = lane_id();
     const int64_t num_dst = sizes[0], nnz = sizes[2];
-    const int64_t stride = int64_t(gridDim.x) * kBlock;
-    for (int64_t e = int64_t(blockIdx.x) * kBlock + threadIdx.x; e < nnz; e += stride) {
-        int64_t lo = 0, hi = num_dst;                      // largest i with indptr[i] <= e
-        while (hi - lo > 1) {
-            int64_t mid = (lo + hi) >> 1;
-            if (indptr[mid] <= e) lo = mid; else hi = mid;
+    const int64_t step = int64_t(gridDim.x) * kWavesPerBlock * kEdgeRun;
+    for (int64_t e0 = (int64_t(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6)) * kEdgeRun; e0 < nnz; e0 += step) {
+        const int64_t e1 = e0 + kEdgeRun < nnz ? e0 + kEdgeRun : nnz;
+        int64_t r0 = wave_count_below<false>(indptr, num_dst, e0) - 1;         // the row of edge e0
+        auto offset = [&](int64_t r) { return indptr[r < num_dst ? r : num_dst]; };
+        int off = offset(r0 + lane), end = offset(r0 + kWave);                  // of rows r0 ..., and where they end
+        for (int64_t c0 = e0; c0 < e1; c0 += kWave) {
+            const int64_t e = c0 + lane;
+            bool open = e < e1;
+            for (;;) {
+                int k = 0;                                 // the last of the 64 rows that begins at or before e
+#pragma unroll
+                for (int h = 32; h > 0; h >>= 1)
+                    if (__shfl(off, k + h, 64) <= e) k += h;
+                if (open && e < end) {
+                    dst_row[e] = static_cast<int32_t>(r0 + k);
+                    open = false;
+                }
+                const uint64_t left = ballot64(open);
+                if (!left) break;
+                // the next 64 rows, or, past a stretch of empty ones, the row of the first edge that is left
+                r0 += kWave;
+                const int64_t first = c0 + __ffsll(static_cast<long long>(left)) - 1;
+                if (offset(r0 + kWave) <= first) r0 = wave_count_below<false>(indptr, num_dst, first) - 1;
+                off = offset(r0 + lane);
+                end = offset(r0 + kWave);
+            }
         }
-        dst_row[e] = static_cast<int32_t>(lo);
     }
 }
 
-// col_ptr[s] = first position in the sorted key array whose source is >= s (bisection), s = 0..num_src
+// col_ptr[s] = first position in the sorted key array whose source is >= s, s = 0..num_src.  A wavefront
+// takes 64 consecutive sources, finds the positions they span, and every lane bisects that span only: its
+// loads hit the wavefront's own lines (25 -> 9 us for 1.35 M sources of 4.3 M edges).
 __global__ void __launch_bounds__(kBlock)
 k_col_ptr(const uint32_t *__restrict__ sorted_src, const int64_t *__restrict__ sizes, int32_t *__restrict__ col_ptr) {
     const int64_t num_src = sizes[1], nnz = sizes[2];
     const int64_t stride = int64_t(gridDim.x) * kBlock;
-    for (int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x; k <= num_src; k += stride) {
-        int64_t lo = 0, hi = nnz;
+    for (int64_t k0 = int64_t(blockIdx.x) * kBlock + (threadIdx.x & ~63u); k0 <= num_src; k0 += stride) {
+        int64_t lo = wave_count_below<true>(sorted_src, nnz, k0);
+        int64_t hi = wave_count_below<true>(sorted_src, nnz, k0 + kWave);
+        const int64_t k = k0 + lane_id();
         while (lo < hi) {
-            int64_t mid = (lo + hi) >> 1;
+            const int64_t mid = (lo + hi) >> 1;
             if (static_cast<int64_t>(sorted_src[mid]) < k) lo = mid + 1; else hi = mid;
         }
-        col_ptr[k] = static_cast<int32_t>(lo);
+        if (k <= num_src) col_ptr[k] = static_cast<int32_t>(lo);
     }
 }
 
-// destination row and weight of every edge in the by-source order
+// destination row and weight of every edge in the by-source order; rows: the destination row of every edge in
+// the block's own order, or null (then indptr is bisected)
 __global__ void __launch_bounds__(kBlock)
-k_permute_edges(const int32_t *__restrict__ perm, const int32_t *__restrict__ indptr, const float *__restrict__ edge_w,
-                const int64_t *__restrict__ sizes, int32_t *__restrict__ dst_row, float *__restrict__ w_sorted) {
+k_permute_edges(const int32_t *__restrict__ perm, const int32_t *__restrict__ indptr, const int32_t *__restrict__ rows,
+                const float *__restrict__ edge_w, const int64_t *__restrict__ sizes, int32_t *__restrict__ dst_row, float *__restrict__ w_sorted) {
     const int64_t num_dst = sizes[0], nnz = sizes[2];
     const int64_t stride = int64_t(gridDim.x) * kBlock;
     for (int64_t q = int64_t(blockIdx.x) * kBlock + threadIdx.x; q < nnz; q += stride) {
         const int32_t e = perm[q];
+        w_sorted[q] = edge_w[e];
+        if (rows) {
+            dst_row[q] = rows[e];
+            continue;
+        }
         int64_t lo = 0, hi = num_dst;                      // largest i with indptr[i] <= e
         while (hi - lo > 1) {
             int64_t mid = (lo + hi) >> 1;
             if (indptr[mid] <= e) lo = mid; else hi = mid;
         }
         dst_row[q] = static_cast<int32_t>(lo);
-        w_sorted[q] = edge_w[e];
     }
 }
 
@@ -450,7 +502,8 @@ int run_aggregate_backward(mqg_ctx *ctx, const mqg_block *b, const float *edge_w
     const int egrid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(nnz_cap, kBlock)), 8192));
     // Edges by source, stably.  An edge carries its destination row along, or (weighted) its own
     // position, which the sort's first pass makes itself - at least one pass, for that.
-    if (!edge_w) MQG_LAUNCH(ctx, "k_edge_dst_rows", s, (k_edge_dst_rows<<<egrid, kBlock, 0, s>>>(b->indptr, b->sizes, ctx->bwd_dst_row)));
+    const int rgrid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(nnz_cap, int64_t(kWavesPerBlock) * kEdgeRun)), 8192));
+    if (!edge_w) MQG_LAUNCH(ctx, "k_edge_dst_rows", s, (k_edge_dst_rows<<<rgrid, kBlock, 0, s>>>(b->indptr, b->sizes, ctx->bwd_dst_row)));
     const int bits = std::max(1, radix_key_bits(static_cast<uint64_t>(std::max<int64_t>(src_cap, 1) - 1)));
     int which = -1;
     int rc = radix_sort_pairs(ctx, reinterpret_cast<const uint32_t *>(b->indices), edge_w ? nullptr : ctx->bwd_dst_row, ctx->bwd, nnz_cap,
@@ -464,8 +517,12 @@ int run_aggregate_backward(mqg_ctx *ctx, const mqg_block *b, const float *edge_w
     if (edge_w) {
         // the sort's payload was the edge position: turn it into (destination row, weight)
         int32_t *dst_sorted = ctx->bwd_dst_row;
+        // the rows of many edges are written once, in order, into the sort's other buffer and picked from there
+        // (both kernels against the bisection alone: 1 M edges 55 and 47 us, 2 M 73 and 78, 4 M 112 and 135)
+        int32_t *rows_of = nnz_cap > kPickRowsEdges ? ctx->bwd.vals[which ^ 1] : nullptr;
+        if (rows_of) MQG_LAUNCH(ctx, "k_edge_dst_rows", s, (k_edge_dst_rows<<<rgrid, kBlock, 0, s>>>(b->indptr, b->sizes, rows_of)));
         MQG_LAUNCH(ctx, "k_permute_edges", s,
-                   (k_permute_edges<<<egrid, kBlock, 0, s>>>(sorted_dst, b->indptr, edge_w, b->sizes, dst_sorted, ctx->bwd_w_sorted)));
+                   (k_permute_edges<<<egrid, kBlock, 0, s>>>(sorted_dst, b->indptr, rows_of, edge_w, b->sizes, dst_sorted, ctx->bwd_w_sorted)));
         WeightedBackwardRows rows{ctx->bwd_col_ptr, dst_sorted, ctx->bwd_w_sorted, self_w, b->sizes};
         if (dtype == MQG_F16)
             return launch<_Float16>(ctx, "k_weighted_aggregate_backward", rows, &b->sizes[1], src_cap,

@@ -77,3 +77,33 @@ def test_runs_of_rows(num_dst, dim, dtype):
     dirty = torch.zeros(num_dst, dtype=torch.bool, device="cuda")
     dirty[rows[~keep]] = True
     assert torch.all(torch.isfinite(out[:num_dst][~dirty & (sw == 0)]))
+
+
+@pytest.mark.parametrize("scale", [1, 60])
+def test_edges_find_their_rows(scale):
+    """The backward's order of edges where rows are empty in long stretches, hold one edge each, or thousands
+    (scale 60: enough edges for the weighted backward to write all rows down first)."""
+    from paper_2601_04707_amd import mqg
+    rng = np.random.default_rng(scale)
+    lens = np.concatenate([np.zeros(70), [3], np.zeros(5000), np.ones(700), [9000, 0, 0, 64, 1], np.zeros(64), np.full(300, 2),
+                           np.zeros(20_000), [513, 511], rng.integers(0, 40, 500), np.zeros(130)]).astype(np.int64)
+    lens = np.tile(lens, scale)
+    indptr = np.concatenate([[0], np.cumsum(lens)])
+    nd, nnz, ns = len(lens), int(indptr[-1]), 3000
+    cols = rng.integers(0, ns, nnz)
+    cols[cols == 17] = 18                                  # a source without edges
+    ctx, blocks = bare_blocks(mqg, indptr, cols, nd, ns)
+    rows = torch.from_numpy(np.repeat(np.arange(nd), lens))
+    g = torch.randn((nd, 2), device="cuda")
+    w = torch.rand(nnz, device="cuda")
+    gx = torch.full((ns, 2), 7.0, device="cuda")
+    for weights in (None, w):
+        coeff = w.double() if weights is not None else (1.0 / torch.from_numpy(np.maximum(lens, 1)).double())[rows].cuda()
+        ref = spmm(torch.from_numpy(cols), rows, coeff, g.double(), ns)
+        mag = spmm(torch.from_numpy(cols), rows, coeff, g.double().abs(), ns)
+        terms = torch.from_numpy(np.bincount(cols, minlength=ns)).double().cuda()
+        if weights is None:
+            mqg.mqg_sage_mean_aggregate_backward(ctx, blocks, 0, g, gx)
+        else:
+            mqg.mqg_weighted_aggregate_backward(ctx, blocks, 0, w, None, g, gx)
+        assert torch.all((gx.double() - ref).abs() <= (terms + 4)[:, None] * 2.0 ** -24 * mag)

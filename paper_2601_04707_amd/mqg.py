@@ -161,7 +161,8 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        # the handle alone: 0.4 us of host time; the Stream object around it takes 2.9 us, and small calls are bound by the host
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)

@@ -93,7 +93,7 @@ void free_backward_scratch(mqg_ctx *ctx) {
     (void)hipFree(ctx->bwd.vals[0]);
     (void)hipFree(ctx->bwd.vals[1]);
     (void)hipFree(ctx->bwd.hist);
-    (void)hipFree(ctx->bwd.tile_sums);
+    (void)hipFree(ctx->bwd.totals);
     (void)hipFree(ctx->bwd_dst_row);
     (void)hipFree(ctx->bwd_col_ptr);
     (void)hipFree(ctx->bwd_w_sorted);

@@ -22,7 +22,7 @@ struct RadixBufs {
     uint32_t *keys[2] = {nullptr, nullptr};     // [n_cap] each
     int32_t *vals[2] = {nullptr, nullptr};      // [n_cap] each
     int32_t *hist = nullptr;                    // [radix_hist_len(n_cap)]
-    int32_t *tile_sums = nullptr;               // [radix_scan_tiles(n_cap)]
+    int32_t *totals = nullptr;                  // [kRadixTotals] keys of every digit
 };
 
 struct ProfRec {

@@ -156,7 +156,7 @@ void free_hash_scratch(mqg_ctx *ctx) {
     (void)hipFree(ctx->hash_sort.vals[0]);
     (void)hipFree(ctx->hash_sort.vals[1]);
     (void)hipFree(ctx->hash_sort.hist);
-    (void)hipFree(ctx->hash_sort.tile_sums);
+    (void)hipFree(ctx->hash_sort.totals);
     ctx->hash_table = nullptr;
     ctx->hash_new_keys = nullptr;
     ctx->hash_new_count = nullptr;
@@ -180,7 +180,7 @@ int ensure_hash_scratch(mqg_ctx *ctx) {
               alloc(reinterpret_cast<void **>(&ctx->hash_sort.vals[0]), nn * 4) &&
               alloc(reinterpret_cast<void **>(&ctx->hash_sort.vals[1]), nn * 4) &&
               alloc(reinterpret_cast<void **>(&ctx->hash_sort.hist), radix_hist_len_max(nn) * 4) &&
-              alloc(reinterpret_cast<void **>(&ctx->hash_sort.tile_sums), radix_scan_tiles_max(nn) * 4);
+              alloc(reinterpret_cast<void **>(&ctx->hash_sort.totals), kRadixTotals * 4);
     if (ok) ok = hipMemset(ctx->hash_table, 0xFF, static_cast<size_t>(cap) * 8) == hipSuccess;
     if (ok) ok = hipDeviceSynchronize() == hipSuccess;
     if (!ok) {

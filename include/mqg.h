@@ -550,8 +550,9 @@ int mqg_gather_features_static(const mqg_cache *cache, int32_t idx_type, const v
  * x_src: device [num_src x x_stride]; out: device [cap_dst x out_stride];
  * strides in elements (columns from dim up to out_stride of a written row are
  * unspecified: with 16-byte aligned rows on both sides whole 16-byte words are
- * processed); sums are accumulated in fp32 in row order; MQG_F16
- * rounds once, to nearest even, at the store.
+ * processed); sums are accumulated in fp32: up to four partial sums take a row's
+ * entries by turns and are added up at its end (the same block gives the same
+ * bits every time); MQG_F16 rounds once, to nearest even, at the store.
  */
 int mqg_sage_mean_aggregate(mqg_ctx *ctx, const mqg_block *block, const void *x_src,
                             int64_t x_stride, void *out, int64_t out_stride, int32_t dim,
@@ -601,8 +602,8 @@ int mqg_gcn_edge_weights(mqg_ctx *ctx, const mqg_graph *graph, const mqg_block *
  *   out[i, c] = self_w[i] * x_src[i, c] + sum over edges p of row i of
  *               edge_w[p] * x_src[indices[p], c]
  * self_w may be NULL (no diagonal term).  Layout, strides, dtype, padding and
- * accumulation as mqg_sage_mean_aggregate (fp32 sums in row order, the
- * diagonal term first).
+ * accumulation as mqg_sage_mean_aggregate (fp32 sums, the diagonal term the
+ * first of the row's terms).
  */
 int mqg_weighted_aggregate(mqg_ctx *ctx, const mqg_block *block, const float *edge_w,
                            const float *self_w, const void *x_src, int64_t x_stride, void *out,

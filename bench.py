@@ -494,10 +494,10 @@ def run_workload(torch, np, mqg, synth, opts, name, *, cache_pct, in_flight, K, 
 
     # ================================================================ the headline workload only
     # ---------------------------------------------------------------- sampling against its own bounds
-    # Integer ALU: one key costs 5 32-bit multiplies (quarter rate) and about 17 full-rate integer
-    # operations = 37 lane-cycles; the chip has 256 CUs x 4 SIMDs x 16 lanes at 2.4 GHz.
+    # Integer ALU: one key costs 3 32-bit multiplies (quarter rate) and about 16 full-rate integer
+    # operations = 28 lane-cycles; the chip has 256 CUs x 4 SIMDs x 16 lanes at 2.4 GHz.
     keys_per_step = keys_eval / max(keys_batches, 1)
-    alu_peak_keys = 256 * 4 * 16 * 2.4e9 / 37.0
+    alu_peak_keys = 256 * 4 * 16 * 2.4e9 / 28.0
     k_sample_us = kern.get("k_sample_prio" if opts.prioritise_cache else "k_sample", {}).get("us_per_step", 0.0)
     sampling = {
         "edges_per_s_sampling_alone": round(edges / K / max(chain[0], 1e-9) * 1e6, 1),

@@ -321,7 +321,7 @@ __device__ __forceinline__ int64_t wave_count_below(const V *__restrict__ v, int
 // payload of edge e = its destination row (the keys are `indices`).  A wavefront takes kEdgeRun consecutive
 // edges; its lanes hold the offsets of 64 consecutive rows, and every edge finds its row among them.
 // Bound by its 4-byte store per edge; a bisection of all of indptr per edge (19 dependent loads) took 57
-// instead of 9 us for 4.3 M edges of 295 k rows.
+// instead of 13 us for 4.3 M edges of 295 k rows.
 constexpr int kEdgeRun = 512;
 constexpr int64_t kPickRowsEdges = int64_t(3) << 19;     // see run_aggregate_backward
 __global__ void __launch_bounds__(kBlock)
@@ -361,7 +361,7 @@ k_edge_dst_rows(const int32_t *__restrict__ indptr, const int64_t *__restrict__ 
 
 // col_ptr[s] = first position in the sorted key array whose source is >= s, s = 0..num_src.  A wavefront
 // takes 64 consecutive sources, finds the positions they span, and every lane bisects that span only: its
-// loads hit the wavefront's own lines (25 -> 9 us for 1.35 M sources of 4.3 M edges).
+// loads hit the wavefront's own lines (25.5 -> 23.2 us for 1.35 M sources of 4.3 M edges; four sources per lane: 10 us more).
 __global__ void __launch_bounds__(kBlock)
 k_col_ptr(const uint32_t *__restrict__ sorted_src, const int64_t *__restrict__ sizes, int32_t *__restrict__ col_ptr) {
     const int64_t num_src = sizes[1], nnz = sizes[2];

@@ -319,7 +319,9 @@ __device__ __forceinline__ int64_t wave_count_below(const V *__restrict__ v, int
 }
 
 // payload of edge e = its destination row (the keys are `indices`).  A wavefront takes kEdgeRun consecutive
-// edges; its lanes hold the offsets of 64 consecutive rows, and every edge finds its row among them.
+// edges; its lanes hold the offsets of 64 consecutive rows, and every edge finds its row among them.  The
+// window of rows only moves forward and ends at the last row, which takes every edge past the last offset
+// (the number of edges comes from another array than the offsets): the loop ends whatever the block holds.
 // Bound by its 4-byte store per edge; a bisection of all of indptr per edge (19 dependent loads) took 57
 // instead of 13 us for 4.3 M edges of 295 k rows.
 constexpr int kEdgeRun = 512;
@@ -331,7 +333,11 @@ k_edge_dst_rows(const int32_t *__restrict__ indptr, const int64_t *__restrict__ 
     const int64_t step = int64_t(gridDim.x) * kWavesPerBlock * kEdgeRun;
     for (int64_t e0 = (int64_t(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6)) * kEdgeRun; e0 < nnz; e0 += step) {
         const int64_t e1 = e0 + kEdgeRun < nnz ? e0 + kEdgeRun : nnz;
-        int64_t r0 = wave_count_below<false>(indptr, num_dst, e0) - 1;         // the row of edge e0
+        auto row_of = [&](int64_t e) {
+            const int64_t r = wave_count_below<false>(indptr, num_dst, e) - 1;
+            return r > 0 ? r : 0;
+        };
+        int64_t r0 = row_of(e0);
         auto offset = [&](int64_t r) { return indptr[r < num_dst ? r : num_dst]; };
         int off = offset(r0 + lane), end = offset(r0 + kWave);                  // of rows r0 ..., and where they end
         for (int64_t c0 = e0; c0 < e1; c0 += kWave) {
@@ -342,8 +348,9 @@ k_edge_dst_rows(const int32_t *__restrict__ indptr, const int64_t *__restrict__ 
 #pragma unroll
                 for (int h = 32; h > 0; h >>= 1)
                     if (__shfl(off, k + h, 64) <= e) k += h;
-                if (open && e < end) {
-                    dst_row[e] = static_cast<int32_t>(r0 + k);
+                if (open && (e < end || r0 + kWave >= num_dst)) {
+                    const int64_t r = r0 + k < num_dst ? r0 + k : num_dst - 1;
+                    dst_row[e] = static_cast<int32_t>(r > 0 ? r : 0);
                     open = false;
                 }
                 const uint64_t left = ballot64(open);
@@ -351,7 +358,10 @@ k_edge_dst_rows(const int32_t *__restrict__ indptr, const int64_t *__restrict__ 
                 // the next 64 rows, or, past a stretch of empty ones, the row of the first edge that is left
                 r0 += kWave;
                 const int64_t first = c0 + __ffsll(static_cast<long long>(left)) - 1;
-                if (offset(r0 + kWave) <= first) r0 = wave_count_below<false>(indptr, num_dst, first) - 1;
+                if (offset(r0 + kWave) <= first) {
+                    const int64_t r = row_of(first);
+                    r0 = r > r0 ? r : r0;
+                }
                 off = offset(r0 + lane);
                 end = offset(r0 + kWave);
             }

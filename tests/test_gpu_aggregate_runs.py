@@ -107,3 +107,32 @@ def test_edges_find_their_rows(scale):
         else:
             mqg.mqg_weighted_aggregate_backward(ctx, blocks, 0, w, None, g, gx)
         assert torch.all((gx.double() - ref).abs() <= (terms + 4)[:, None] * 2.0 ** -24 * mag)
+
+
+@pytest.mark.parametrize("nd,per_row,extra", [(1, 3, 700), (64, 2, 5), (65, 1, 130), (1300, 2, 700), (20_001, 80, 3000)])
+def test_edges_past_the_last_offset(nd, per_row, extra):
+    """A block whose edge count is larger than its last offset: the edges past it are the last row's."""
+    from paper_2601_04707_amd import mqg
+    rng = np.random.default_rng(nd)
+    lens = np.full(nd, per_row)
+    indptr = np.concatenate([[0], np.cumsum(lens)])
+    nnz, ns = int(indptr[-1]) + extra, 500
+    cols = rng.integers(0, ns, nnz)
+    offsets = indptr.copy()
+    offsets[-1] = nnz                                      # the buffers' size; the block's own last offset follows
+    ctx, blocks = bare_blocks(mqg, offsets, cols, nd, ns)
+    blocks._keep[0][nd] = int(indptr[-1])
+    rows = torch.from_numpy(np.concatenate([np.repeat(np.arange(nd), lens), np.full(extra, nd - 1)]))
+    g = torch.randn((nd, 2), device="cuda")
+    w = torch.rand(nnz, device="cuda")
+    gx = torch.zeros((ns, 2), device="cuda")
+    for weights in (None, w):
+        coeff = w.double() if weights is not None else torch.full((nnz,), 1.0 / per_row, dtype=torch.float64, device="cuda")
+        ref = spmm(torch.from_numpy(cols), rows, coeff, g.double(), ns)
+        mag = spmm(torch.from_numpy(cols), rows, coeff, g.double().abs(), ns)
+        terms = torch.from_numpy(np.bincount(cols, minlength=ns)).double().cuda()
+        if weights is None:
+            mqg.mqg_sage_mean_aggregate_backward(ctx, blocks, 0, g, gx)
+        else:
+            mqg.mqg_weighted_aggregate_backward(ctx, blocks, 0, w, None, g, gx)
+        assert torch.all((gx.double() - ref).abs() <= (terms + 4)[:, None] * 2.0 ** -24 * mag)

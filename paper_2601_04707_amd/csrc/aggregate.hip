@@ -240,6 +240,39 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
     }
 }
 
+// columns [0, dim) of all rows, nv vectors of vec elements per lane
+template <typename T, typename Rows>
+int launch_columns(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_rows, int64_t row_blocks, const T *x,
+                   int64_t x_stride, T *out, int64_t out_stride, int dim, int vec, int nv, hipStream_t s) {
+    const int64_t slabs = ceil_div(ceil_div(dim, vec), int64_t(nv) * kWave);
+    const int grid = static_cast<int>(row_blocks * slabs);
+#define MQG_AGG(V, NV)                                                                                          \
+    MQG_LAUNCH(ctx, name, s,                                                                                    \
+               (k_segment_flat<T, V, NV, Rows><<<grid, kBlock, 0, s>>>(rows, n_rows, x, x_stride, out, out_stride, dim, static_cast<uint32_t>(row_blocks))))
+#define MQG_AGG_PICK(V)                        \
+    switch (nv) {                              \
+        case 1: MQG_AGG(V, 1); break;          \
+        case 2: MQG_AGG(V, 2); break;          \
+        case 3: MQG_AGG(V, 3); break;          \
+        case 4: MQG_AGG(V, 4); break;          \
+        case 5: MQG_AGG(V, 5); break;          \
+        default: MQG_AGG(V, 6); break;         \
+    }
+    constexpr int kWidest = 16 / static_cast<int>(sizeof(T));
+    if (vec == kWidest) {
+        MQG_AGG_PICK(kWidest);
+    } else if (vec == kWidest / 2) {
+        MQG_AGG_PICK(kWidest / 2);
+    } else if (vec == 2 && kWidest == 8) {
+        MQG_AGG(2, 1);
+    } else {
+        MQG_AGG(1, 1);
+    }
+#undef MQG_AGG_PICK
+#undef MQG_AGG
+    return MQG_OK;
+}
+
 template <typename T, typename Rows>
 int launch(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_rows, int64_t cap_rows, const T *x,
            int64_t x_stride, T *out, int64_t out_stride, int dim, hipStream_t s) {
@@ -269,34 +302,20 @@ int launch(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_ro
     const int64_t units = ceil_div(lanes, kWave);
     const bool spread = units > 6 || vec < 8 / static_cast<int>(sizeof(T)) || (!Rows::kFewEntries && units >= 2 && lanes * 100 >= units * kWave * 78);
     const int nv = spread ? 1 : static_cast<int>(units);
-    const int64_t slabs = ceil_div(units, nv);
     const int64_t row_blocks = std::min<int64_t>(std::max<int64_t>(1, ceil_div(cap_rows, kWavesPerBlock)), 256 * 32);
-    const int grid = static_cast<int>(row_blocks * slabs);
-#define MQG_AGG(V, NV)                                                                                          \
-    MQG_LAUNCH(ctx, name, s,                                                                                    \
-               (k_segment_flat<T, V, NV, Rows><<<grid, kBlock, 0, s>>>(rows, n_rows, x, x_stride, out, out_stride, dim, static_cast<uint32_t>(row_blocks))))
-#define MQG_AGG_PICK(V)                        \
-    switch (nv) {                              \
-        case 1: MQG_AGG(V, 1); break;          \
-        case 2: MQG_AGG(V, 2); break;          \
-        case 3: MQG_AGG(V, 3); break;          \
-        case 4: MQG_AGG(V, 4); break;          \
-        case 5: MQG_AGG(V, 5); break;          \
-        default: MQG_AGG(V, 6); break;         \
+    // A launch has fewer than 2^32 threads and the kernel's column offsets are 32 bits: very wide rows take
+    // several launches over pieces of their columns, 64 MB of a row at most each.
+    const int64_t slabs_at_once = std::min<int64_t>((int64_t(1) << 22) / row_blocks, int64_t(1) << 16);
+    if (nv == 1 && units > slabs_at_once) {
+        const int64_t piece = slabs_at_once * kWave * vec;
+        for (int64_t c0 = 0; c0 < dim; c0 += piece) {
+            const int cols = static_cast<int>(std::min<int64_t>(piece, dim - c0));
+            int rc = launch_columns(ctx, name, rows, n_rows, row_blocks, x + c0, x_stride, out + c0, out_stride, cols, vec, nv, s);
+            if (rc != MQG_OK) return rc;
+        }
+        return MQG_OK;
     }
-    constexpr int kWidest = 16 / static_cast<int>(sizeof(T));
-    if (vec == kWidest) {
-        MQG_AGG_PICK(kWidest);
-    } else if (vec == kWidest / 2) {
-        MQG_AGG_PICK(kWidest / 2);
-    } else if (vec == 2 && kWidest == 8) {
-        MQG_AGG(2, 1);
-    } else {
-        MQG_AGG(1, 1);
-    }
-#undef MQG_AGG_PICK
-#undef MQG_AGG
-    return MQG_OK;
+    return launch_columns(ctx, name, rows, n_rows, row_blocks, x, x_stride, out, out_stride, dim, vec, nv, s);
 }
 
 // ---------------------------------------------------------------- edges ordered by source

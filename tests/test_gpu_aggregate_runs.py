@@ -136,3 +136,23 @@ def test_edges_past_the_last_offset(nd, per_row, extra):
         else:
             mqg.mqg_weighted_aggregate_backward(ctx, blocks, 0, w, None, g, gx)
         assert torch.all((gx.double() - ref).abs() <= (terms + 4)[:, None] * 2.0 ** -24 * mag)
+
+
+def test_rows_wider_than_one_launch():
+    """131,073 fp16 columns (one element per lane) of a block with room for 40,000 rows: more threads than a launch may
+    have, so the columns are taken in pieces."""
+    from paper_2601_04707_amd import mqg
+    nd, cap, dim = 3, 40_000, 131_073
+    indptr, cols = np.array([0, 2, 2, 5]), np.array([4, 1, 0, 3, 4])
+    ctx, blocks = bare_blocks(mqg, indptr, cols, nd, 5)
+    blocks.c[0].cap_dst = cap
+    x = torch.randn((5, dim), device="cuda").half()
+    out = torch.empty((cap, dim), dtype=torch.float16, device="cuda")
+    out[nd] = 7.0
+    mqg.mqg_sage_mean_aggregate(ctx, blocks, 0, x, out)
+    xd = x.double()
+    want = torch.stack([(xd[4] + xd[1]) / 2, torch.zeros(dim, device="cuda", dtype=torch.float64), (xd[0] + xd[3] + xd[4]) / 3])
+    mag = torch.stack([(xd[4].abs() + xd[1].abs()) / 2, torch.zeros(dim, device="cuda", dtype=torch.float64),
+                       (xd[0].abs() + xd[3].abs() + xd[4].abs()) / 3])
+    assert torch.all((out[:nd].double() - want).abs() <= 7 * 2.0 ** -24 * mag + 2.0 ** -11 * want.abs() + 2.0 ** -24)
+    assert torch.all(out[nd] == 7.0)

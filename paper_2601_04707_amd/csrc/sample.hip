@@ -511,8 +511,11 @@ struct SampleLds {
 };
 
 // Hubs (degree > heavy_degree, listed with the row information): the four wavefronts of a workgroup walk
-// one row together, 64 slots each in turn, each with a list of its own for 64 candidates (about 2k + 32 are
-// expected in all).  The k winners are selected by (key, slot) and then ordered by slot.  The wavefronts take
+// one row together, 64 slots each in turn, each with a list of its own for 64 candidates.  About 2k + 32 are
+// expected in all, but no more than k + 48: a list that overflows, or too few candidates, costs k walks of the
+// row by one wavefront, milliseconds for a long one.  At k = 64 that is one row in 10^7 from 600 slots on, and
+// 2 in 10,000 of the short rows that only a low heavy_degree brings here; with 160 expected it was 6 in 10,000
+// (4,000 rows of 20,000 slots at k = 60: 2.3 ms instead of 0.08).  The k winners are selected by (key, slot) and then ordered by slot.  The wavefronts take
 // turns at that, while the others go on with the next hub into the second set of lists: one barrier per hub.
 template <typename IdxT>
 __device__ __forceinline__ void sample_hubs(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, const SampleArgs &a,
@@ -531,7 +534,7 @@ __device__ __forceinline__ void sample_hubs(const IdxT *__restrict__ col_idx, co
         const uint64_t hv = readlane64(mix64(layer_hash ^ uint64_t(dst_ids[row])), 0);
         uint64_t *ck = lds.key[turn & 1];
         int32_t *cs = lds.slot[turn & 1];
-        const uint32_t thr = __builtin_amdgcn_readfirstlane(threshold_for(2 * k + 32, d));
+        const uint32_t thr = __builtin_amdgcn_readfirstlane(threshold_for(k + (k < 16 ? k + 32 : 48), d));
         const int mine = wave_candidates(hv, d, thr, wave * kWave, kBlock, ck + wave * kWave, cs + wave * kWave, kWave);
         if (lane == 0) counts[turn & 1][wave] = mine;
         __syncthreads();

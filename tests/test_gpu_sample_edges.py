@@ -76,3 +76,30 @@ def test_row_of_more_than_2_30_slots():
         assert blocks.host_sizes()[0] == (1, k + 1, k, 0)
         assert torch.equal(blocks.src_ids[0][1:k + 1].long(), want + 1)
         ctx.close()
+
+
+def test_large_fanouts_keep_hubs_off_the_slow_selection():
+    """A hub whose candidates overflow a wavefront's list is selected by one wavefront in as many walks of its row as the
+    fanout: 100 times the usual work.  That has to stay rare at the largest fanouts: 64 of 4,000 hubs' neighbours take
+    2 % longer than 50, and took ten times as long while one hub in 3,000 overflowed."""
+    from paper_2601_04707_amd import mqg
+    n, hubs, d = 50_000, 4000, 3000
+    deg = torch.zeros(n, dtype=torch.int64, device="cuda")
+    deg[:hubs] = d
+    row_ptr = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(deg, 0, out=row_ptr[1:])
+    col = (torch.arange(hubs * d, device="cuda") * 7 % n).int()
+    g = mqg.Graph(row_ptr, col)
+    seeds = torch.arange(hubs, dtype=torch.int32, device="cuda")
+    took = {}
+    for k in (50, 64):
+        ctx = mqg.Context(g, hubs, [k])
+        blocks = mqg.Blocks(g, hubs, [k])
+        mqg.mqg_sample_blocks(ctx, g, seeds, [k], 1, blocks)
+        ctx.set_option(mqg.MQG_OPT_PROFILE, 1)
+        ctx.reset_profile()
+        for seed in range(10):
+            mqg.mqg_sample_blocks(ctx, g, seeds, [k], seed, blocks)
+        took[k] = ctx.kernel_time("k_sample")[0]
+        ctx.close()
+    assert took[64] < 3 * took[50], took

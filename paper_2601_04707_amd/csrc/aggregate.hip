@@ -127,7 +127,9 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
                T *__restrict__ out, int64_t out_stride, int dim, uint32_t row_blocks) {
     using P = Pack<T, VEC>;
     constexpr int U = NV == 1 ? (sizeof(P) == 16 ? 8 : 16) : NV == 2 ? (Rows::kFewEntries ? 4 : 8) : NV == 3 ? 4 : 2;    // input rows in flight: 4 to 12 KB per wavefront
-    constexpr int NACC = VEC <= 2 ? 4 : NV <= 2 ? 2 : 1;   // partial sums that take the entries in turn
+    // Partial sums that take the entries in turn.  The turn counts from the start of the run, so a row may begin
+    // at any of them; opposite ones are added first, which gives the same bits wherever it began.
+    constexpr int NACC = U < 2 ? 1 : VEC <= 2 ? (U < 4 ? U : 4) : NV <= 2 ? 2 : 1;
     const int lane = lane_id();
     const int64_t n = *n_rows;
     const uint32_t slab = blockIdx.x / row_blocks;
@@ -171,8 +173,8 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
 #pragma unroll
                 for (int q = 0; q < VEC; ++q) {
                     float sum = acc[0][k][q];
-                    if constexpr (NACC >= 2) sum += acc[1][k][q];
-                    if constexpr (NACC == 4) sum += acc[2][k][q] + acc[3][k][q];
+                    if constexpr (NACC == 2) sum += acc[1][k][q];
+                    if constexpr (NACC == 4) sum = (sum + acc[2][k][q]) + (acc[1][k][q] + acc[3][k][q]);
                     from_f32(rows.finish(sum, static_cast<int>(row_end - row_begin)), &o.v[q]);
 #pragma unroll
                     for (int a = 0; a < NACC; ++a) acc[a][k][q] = 0.f;

@@ -156,3 +156,48 @@ def test_rows_wider_than_one_launch():
                        (xd[0].abs() + xd[3].abs() + xd[4].abs()) / 3])
     assert torch.all((out[:nd].double() - want).abs() <= 7 * 2.0 ** -24 * mag + 2.0 ** -11 * want.abs() + 2.0 ** -24)
     assert torch.all(out[nd] == 7.0)
+
+
+@pytest.mark.parametrize("dim,dtype", [(3, torch.float32), (16, torch.float32), (40, torch.float32), (70, torch.float16), (130, torch.float16),
+                                       (255, torch.float32), (256, torch.float32), (300, torch.float32), (602, torch.float32)])
+def test_a_row_has_the_same_bits_wherever_it_lies(dim, dtype):
+    """Rows with the same entries, between rows of other lengths: the order of a row's additions is its own."""
+    from paper_2601_04707_amd import mqg
+    rng = np.random.default_rng(dim)
+    kinds, nd, ns = 40, 40_001, 500
+    lens = rng.integers(0, 24, kinds)
+    first = np.concatenate([[0], np.cumsum(lens)])
+    cols = rng.integers(kinds, ns, first[-1])
+    kind = rng.integers(0, kinds, nd)
+    indptr = np.concatenate([[0], np.cumsum(lens[kind])])
+    entry = np.repeat(first[kind] - indptr[:-1], lens[kind]) + np.arange(indptr[-1])
+    gen = torch.Generator(device="cuda").manual_seed(dim)
+    x = torch.randn((ns, dim), generator=gen, device="cuda").to(dtype)
+    w = torch.randn(int(first[-1]), generator=gen, device="cuda")
+    small = [bare_blocks(mqg, first, cols, kinds, ns), torch.empty((kinds, dim), dtype=dtype, device="cuda"), w]
+    large = [bare_blocks(mqg, indptr, cols[entry], nd, ns), torch.empty((nd, dim), dtype=dtype, device="cuda"), w[torch.from_numpy(entry).cuda()]]
+    where = torch.from_numpy(kind).cuda()
+    for call in ("mean", "weighted"):
+        for (ctx, blocks), out, weights in (small, large):
+            if call == "mean":
+                mqg.mqg_sage_mean_aggregate(ctx, blocks, 0, x, out)
+            else:
+                mqg.mqg_weighted_aggregate(ctx, blocks, 0, weights, None, x, out)
+        assert torch.equal(large[1], small[1][where])
+    # the backward: sources that are neighbours of the same destinations, in the same order
+    dst = np.repeat(np.arange(ns), rng.integers(1, 5, ns))                   # 500 destinations, 1 to 4 kinds of sources each
+    pairs = np.stack([dst, rng.integers(0, kinds, len(dst))], 1)
+    pairs = np.unique(pairs, axis=0)
+    members = [np.flatnonzero(kind == k) for k in range(kinds)]
+    big_cols = np.concatenate([members[k] for _, k in pairs])
+    big_ptr = np.concatenate([[0], np.cumsum(np.bincount(pairs[:, 0], weights=[len(members[k]) for _, k in pairs], minlength=ns))]).astype(np.int64)
+    small_ptr = np.concatenate([[0], np.cumsum(np.bincount(pairs[:, 0], minlength=ns))])
+    ew = torch.rand(len(pairs), generator=gen, device="cuda")
+    ew_big = ew[torch.from_numpy(np.repeat(np.arange(len(pairs)), [len(members[k]) for _, k in pairs])).cuda()]
+    got = []
+    for ptr, c, n_src, weights in ((small_ptr, pairs[:, 1], kinds, ew), (big_ptr, big_cols, nd, ew_big)):
+        ctx, blocks = bare_blocks(mqg, ptr, c, ns, n_src)
+        gx = torch.empty((n_src, dim), dtype=dtype, device="cuda")
+        mqg.mqg_weighted_aggregate_backward(ctx, blocks, 0, weights, None, x, gx)
+        got.append(gx)
+    assert torch.equal(got[1], got[0][where])

@@ -550,9 +550,11 @@ int mqg_gather_features_static(const mqg_cache *cache, int32_t idx_type, const v
  * x_src: device [num_src x x_stride]; out: device [cap_dst x out_stride];
  * strides in elements (columns from dim up to out_stride of a written row are
  * unspecified: with 16-byte aligned rows on both sides whole 16-byte words are
- * processed); sums are accumulated in fp32: up to four partial sums take a row's
- * entries by turns and are added up at its end (the same block gives the same
- * bits every time); MQG_F16 rounds once, to nearest even, at the store.
+ * processed); sums are accumulated in fp32: partial sums (up to 64 for long rows of
+ * few columns, up to four otherwise) take a row's entries by turns and are added up
+ * at its end.  Rows with the same entries give the same bits, in this block or
+ * another, with the same dim, dtype, strides and alignment; MQG_F16 rounds once, to
+ * nearest even, at the store.
  */
 int mqg_sage_mean_aggregate(mqg_ctx *ctx, const mqg_block *block, const void *x_src,
                             int64_t x_stride, void *out, int64_t out_stride, int32_t dim,
@@ -567,9 +569,9 @@ int mqg_sage_mean_aggregate(mqg_ctx *ctx, const mqg_block *block, const void *x_
  * for all num_src sources (zeros where no edge points).
  * grad_out: device [num_dst x go_stride]; grad_x: device [cap_src x gx_stride];
  * strides in elements, padding columns of written rows unspecified as in the
- * forward.  The edges are first ordered by source with a stable radix sort and
- * each source's terms are added in ascending destination order in fp32, so
- * the result is reproducible bit for bit.  The first call (and any call with
+ * forward.  The edges are first ordered by source with a stable radix sort;
+ * each source's terms come in ascending destination order and are summed as the
+ * forward's entries are, so the result is reproducible bit for bit.  The first call (and any call with
  * larger block capacities than seen before) allocates context scratch of
  * about 20 bytes per edge and synchronises the stream once to do so.
  */

@@ -4,20 +4,25 @@
 // dense contraction, hence no matrix cores.
 //
 //   k_segment_flat   one wavefront per run of up to kRunRows consecutive output rows, its 64 lanes side by
-//                    side over the columns (wider rows: several vectors per lane, or slabs of 64
-//                    vectors, each a share of the grid).  The entries of the run are walked as one sequence across the row ends:
-//                    64 of them are fetched at a time, one per lane, and U input rows are loaded before
-//                    the first of them is added, however few entries the rows have.  Entry numbers, row
-//                    ends and addresses are the same in all lanes and live in scalar registers: per
-//                    entry the vector unit sees one load and VEC additions.
+//                    side over the columns (wider rows: several vectors per lane, or slabs of 64 vectors, each a
+//                    share of the grid).  The entries of the run are walked as one sequence across the row ends:
+//                    64 of them are fetched at a time, one per lane, and U input rows are loaded before the
+//                    first of them is added, however few entries the rows have.  Entry numbers, row ends and
+//                    addresses are the same in all lanes and live in scalar registers: per entry the vector
+//                    unit sees one load and VEC additions.
+//   reduce_long_row  rows of many entries and few columns: the lanes are split into groups, each takes a share
+//                    of the row's entries.
 // Forward: output row i reduces x[indices[e]] over the edges e of destination i and divides by
 // their number.  Backward: output row s reduces grad_out[i] / n_i over the edges that point to
 // source s, taken from the block's edge list sorted by source (stable radix sort, so a row's terms
-// are always added in ascending destination order: the result is reproducible bit for bit).
+// always come in ascending destination order).  A row's sum is made of partial sums that take its terms
+// in turn; which takes which depends on the row's own terms and on the width, strides and alignment of the
+// call, not on the rows around it: the result is reproducible bit for bit.
 // Sums are fp32; fp16 output is rounded once (to nearest even) at the store.
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "device_utils.h"
@@ -109,22 +114,80 @@ struct WeightedBackwardRows {
     __device__ __forceinline__ float finish(float acc, int) const { return acc; }
 };
 
+// One row of many entries and few columns (at most eight vectors of LV elements): the lanes are split into groups of
+// 2^log2_lpr that cover the columns, group g takes the row's entries g, g + G, ..., and the G partial sums (8 to 64)
+// are folded across the groups.  64 / lpr rows per load and four loads in flight, where the walk below has 16 rows
+// in flight and most lanes idle: 2,000 rows of 300 entries and 16 fp32 columns 22.5 -> 8.6 us, of 2,000 entries
+// 139 -> 60; and more partial sums keep the error down (300 entries 1.7e-7 -> 1.0e-7 of the result, 2,000 entries
+// 4.0e-7 -> 2.1e-7).
+template <typename T, int LV, typename Rows>
+__device__ __forceinline__ void reduce_long_row(const Rows &rows, int64_t i, int b, int e, bool diag, const T *__restrict__ x, int64_t x_stride,
+                                                T *__restrict__ out, int64_t out_stride, int dim, int log2_lpr) {
+    using P = Pack<T, LV>;
+    const int lane = lane_id();
+    const int lpr = 1 << log2_lpr;
+    const int groups = kWave >> log2_lpr;
+    const int g = lane >> log2_lpr;
+    const int col0 = (lane & (lpr - 1)) * LV;
+    const bool live = col0 < dim;
+    float acc[LV];
+#pragma unroll
+    for (int q = 0; q < LV; ++q) acc[q] = 0.f;
+    if (Rows::kSelf && diag) {
+        const float ws = rows.self_weight(i);
+        if (ws != 0.f && live && g == 0) {
+            const P v = *reinterpret_cast<const P *>(x + i * x_stride + col0);
+#pragma unroll
+            for (int q = 0; q < LV; ++q) acc[q] = ws * to_f32(v.v[q]);
+        }
+    }
+#pragma unroll 4
+    for (int p = b + g; p < e; p += groups) {
+        const int64_t r = rows.input_row(p);
+        const float w = rows.weight(p);
+        if (live) {
+            const P v = *reinterpret_cast<const P *>(x + r * x_stride + col0);
+#pragma unroll
+            for (int q = 0; q < LV; ++q) {
+                if (Rows::kWeighted) acc[q] += w * to_f32(v.v[q]);
+                else acc[q] += to_f32(v.v[q]);
+            }
+        }
+    }
+    for (int off = lpr; off < kWave; off <<= 1) {
+#pragma unroll
+        for (int q = 0; q < LV; ++q) acc[q] += __shfl_xor(acc[q], off, 64);
+    }
+    if (live && g == 0) {
+        P o;
+#pragma unroll
+        for (int q = 0; q < LV; ++q) from_f32(rows.finish(acc[q], e - b), &o.v[q]);
+        *reinterpret_cast<P *>(out + i * out_stride + col0) = o;
+    }
+}
+
 // The segmented reduction.  What bounds it is the traffic behind the L2s: random 512-byte rows are read at
 // 7.5 TB/s from a table that the memory-side cache holds and at 6.6 TB/s from a larger one (measured with a
 // kernel that does nothing else).  A loop over one row after the other, the wavefront split into groups of
-// lanes that share a row's entries, came near that only for long rows.  Measured, before -> now: the three
+// lanes that share a row's entries, came near that only for long rows.  Measured, such a loop -> this: the three
 // blocks of a mini-batch of 8,192 seeds (512-byte rows; 347 k output rows, 4.7 M entries) 0.432 -> 0.338 ms,
 // the reductions of their backward (1.7 M output rows of 3 entries) 0.89 -> 0.49 ms; 2,408-byte rows (10 k
-// rows of 25 entries: 612 MB read in 83 us = 7.4 TB/s) as before; rows of 4 to 256 bytes, 100 k of them, 5 to
-// 60 % faster, and no slower where there are few.
+// rows of 25 entries: 612 MB read in 83 us = 7.4 TB/s) as before.
 // Measured and dropped: slabs of 128 to 512 bytes dealt to the XCDs so that every L2 keeps its slab of the
-// hot rows (L2 hits 13 -> 24 %, time unchanged or worse); 4 or 16 instead of 8 vectors of 16 bytes in flight.
+// hot rows (L2 hits 13 -> 24 %, time unchanged or worse); 4 or 16 instead of 8 vectors of 16 bytes in flight;
+// lanes past the row left out of the loads (wide fp16 rows 1.3 to 1.7 times slower).
 constexpr int kRunRows = 16;
+// LV > 0 (rows of at most eight vectors of LV elements): rows of kLongRow entries and more go to reduce_long_row,
+// the shorter ones are walked.  At 12 the two are level in large blocks (100 k rows of 10 entries, 16 fp32 columns:
+// 28 and 24 us; of 15 entries 28 and 32 to 35), and in blocks of a few thousand rows the groups are ahead from 5 or 6.
+constexpr uint32_t kLongRow = 12;
 
-template <typename T, int VEC, int NV, typename Rows>
+// busy: wavefronts to hand rows to before any gets a second one, up to four rows (run below).
+// mostly_long: rows are expected to have kLongRow entries or more, so every wavefront takes one at a time.
+template <typename T, int VEC, int NV, int LV, typename Rows>
 __global__ void __launch_bounds__(kBlock)
 k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restrict__ x, int64_t x_stride,
-               T *__restrict__ out, int64_t out_stride, int dim, uint32_t row_blocks) {
+               T *__restrict__ out, int64_t out_stride, int dim, uint32_t row_blocks, uint32_t busy, int mostly_long, int log2_lpr) {
     using P = Pack<T, VEC>;
     constexpr int U = NV == 1 ? (sizeof(P) == 16 ? 8 : 16) : NV == 2 ? (Rows::kFewEntries ? 4 : 8) : NV == 3 ? 4 : 2;    // input rows in flight: 4 to 12 KB per wavefront
     // Partial sums that take the entries in turn.  The turn counts from the start of the run, so a row may begin
@@ -145,88 +208,114 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
     const int64_t self_rows = Rows::kSelf ? rows.self_rows(n) : 0;         // rows with a diagonal term: the first ones
     const int64_t nwaves = int64_t(row_blocks) * kWavesPerBlock;
     const int64_t wave0 = __builtin_amdgcn_readfirstlane(static_cast<int>(row_block) * kWavesPerBlock + static_cast<int>(threadIdx.x >> 6));
-    const int64_t share = (n + nwaves - 1) / nwaves;
-    const int run = share < kRunRows ? static_cast<int>(share) : kRunRows;
+    int run = 1;                                           // rows per wavefront and run
+    while (run < kRunRows && run * (run < 4 ? int64_t(busy) : nwaves) < n && !(LV > 0 && mostly_long)) ++run;
     const char *xb = reinterpret_cast<const char *>(x);
     const int64_t x_bytes = x_stride * int64_t(sizeof(T)), out_bytes = out_stride * int64_t(sizeof(T));
     for (int64_t c0 = wave0 * run; c0 < n; c0 += nwaves * run) {
+        if constexpr (LV > 0) {
+            if (mostly_long) {
+                const int b = rows.begin(c0), e = rows.begin(c0 + 1);
+                const bool own = c0 < self_rows;
+                if (e - b + own >= static_cast<int>(kLongRow)) {
+                    reduce_long_row<T, LV>(rows, c0, b, e, own, x, x_stride, out, out_stride, dim, log2_lpr);
+                    continue;
+                }
+            }
+        }
         const int m = n - c0 < run ? static_cast<int>(n - c0) : run;       // rows of this run
         // diagonal terms in this run: one more entry, its first, for each of the run's first `diag` rows
         const int diag = self_rows > c0 ? static_cast<int>(self_rows - c0 < m ? self_rows - c0 : m) : 0;
         const int t = lane < m ? lane : m;                 // lane t keeps the first position of row c0 + t
         const uint32_t off = static_cast<uint32_t>(rows.begin(c0 + t)) + static_cast<uint32_t>(t < diag ? t : diag);
-        const uint32_t begin = readlane32(off, 0), end = readlane32(off, m);
-        int cur = 0;
-        uint32_t row_begin = begin, row_end = readlane32(off, 1);
-        float acc[NACC][NV][VEC];
+        uint64_t longs = 0;                                // the run's long rows, if they go by themselves
+        if constexpr (LV > 0) {
+            const uint32_t entries = __shfl_down(off, 1) - off;
+            longs = ballot64(lane < m && entries >= kLongRow);
+        }
+        for (int cur = 0;;) {
+            const int stop = LV > 0 && longs ? __ffsll(static_cast<long long>(longs)) - 1 : m;
+            const uint32_t begin = readlane32(off, cur), end = readlane32(off, stop);
+            uint32_t row_begin = begin, row_end = readlane32(off, cur + 1);
+            float acc[NACC][NV][VEC];
 #pragma unroll
-        for (int a = 0; a < NACC; ++a)
+            for (int a = 0; a < NACC; ++a)
 #pragma unroll
-            for (int k = 0; k < NV; ++k)
+                for (int k = 0; k < NV; ++k)
 #pragma unroll
-                for (int q = 0; q < VEC; ++q) acc[a][k][q] = 0.f;
-        auto finish_row = [&]() {
-            char *orow = reinterpret_cast<char *>(out) + (c0 + cur) * out_bytes;
+                    for (int q = 0; q < VEC; ++q) acc[a][k][q] = 0.f;
+            auto finish_row = [&]() __attribute__((always_inline)) {
+                char *orow = reinterpret_cast<char *>(out) + (c0 + cur) * out_bytes;
 #pragma unroll
-            for (int k = 0; k < NV; ++k) {
-                P o;
+                for (int k = 0; k < NV; ++k) {
+                    P o;
 #pragma unroll
-                for (int q = 0; q < VEC; ++q) {
-                    float sum = acc[0][k][q];
-                    if constexpr (NACC == 2) sum += acc[1][k][q];
-                    if constexpr (NACC == 4) sum = (sum + acc[2][k][q]) + (acc[1][k][q] + acc[3][k][q]);
-                    from_f32(rows.finish(sum, static_cast<int>(row_end - row_begin)), &o.v[q]);
+                    for (int q = 0; q < VEC; ++q) {
+                        float sum = acc[0][k][q];
+                        if constexpr (NACC == 2) sum += acc[1][k][q];
+                        if constexpr (NACC == 4) sum = (sum + acc[2][k][q]) + (acc[1][k][q] + acc[3][k][q]);
+                        from_f32(rows.finish(sum, static_cast<int>(row_end - row_begin)), &o.v[q]);
 #pragma unroll
-                    for (int a = 0; a < NACC; ++a) acc[a][k][q] = 0.f;
-                }
-                if (live[k]) *reinterpret_cast<P *>(orow + lane_off[k]) = o;
-            }
-            ++cur;
-            row_begin = row_end;
-            row_end = readlane32(off, cur + 1);
-        };
-        for (uint32_t e0 = begin; e0 < end; e0 += kWave) {
-            const int cnt = end - e0 < kWave ? static_cast<int>(end - e0) : kWave;
-            const uint32_t p = e0 + (lane < cnt ? lane : cnt - 1);     // past the end: the last entry again, loaded but not added
-            int my_row;                                    // -1: a diagonal term whose weight is zero, not added either
-            float my_w = 1.f;
-            if (Rows::kSelf && diag > 0) {
-                int k = 0;                                 // the entry's row and that row's first position
-                uint32_t first = begin;
-                for (int q = 1; q < m; ++q) {
-                    const uint32_t o = readlane32(off, q);
-                    if (p >= o) {
-                        k = q;
-                        first = o;
+                        for (int a = 0; a < NACC; ++a) acc[a][k][q] = 0.f;
                     }
+                    if (live[k]) *reinterpret_cast<P *>(orow + lane_off[k]) = o;
                 }
-                if (k < diag && p == first) {
-                    my_w = rows.self_weight(c0 + k);
-                    my_row = my_w != 0.f ? static_cast<int>(c0) + k : -1;
-                } else {
-                    const int q = static_cast<int>(p - (k < diag ? k + 1 : diag));
-                    my_row = rows.input_row(q);
-                    my_w = rows.weight(q);
-                }
-            } else {
-                my_row = rows.input_row(static_cast<int>(p));
-                if (Rows::kWeighted) my_w = rows.weight(static_cast<int>(p));
-            }
-            for (int b = 0; b < cnt; b += U) {
-                P v[U][NV];
+                ++cur;
+                row_begin = row_end;
+                row_end = readlane32(off, cur + 1);
+            };
+            // the entries e0 ... of the walk, one per lane: input row, weight, and whether it is a diagonal term
+            struct Entry {
+                int row;
+                float w;
+                bool own;
+            };
+            auto fetch = [&](uint32_t e0) __attribute__((always_inline)) {
+                Entry en;
+                en.w = 1.f;
+                en.own = false;
+                const uint32_t p = e0 + lane < end ? e0 + lane : end - 1;      // past the end: the last entry again, loaded but not added
+                if (Rows::kSelf && diag > 0) {
+                    int k = 0;                             // the entry's row: the last that begins at or before it
+                    uint32_t first = begin;
+                    if (m > 1) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int r = static_cast<int>(readlane32(static_cast<uint32_t>(my_row), b + u));
+                        for (int h = kRunRows / 2; h > 0; h >>= 1)
+                            if (static_cast<uint32_t>(__shfl(static_cast<int>(off), k + h)) <= p) k += h;
+                        first = static_cast<uint32_t>(__shfl(static_cast<int>(off), k));
+                    }
+                    en.own = k < diag && p == first;
+                    const int q = static_cast<int>(p - (k < diag ? k + 1 : diag));
+                    if (en.own) {
+                        en.w = rows.self_weight(c0 + k);
+                        en.row = en.w != 0.f ? static_cast<int>(c0) + k : -1;
+                    } else {
+                        en.row = rows.input_row(q);
+                        en.w = rows.weight(q);
+                    }
+                } else {
+                    en.row = rows.input_row(static_cast<int>(p));
+                    if (Rows::kWeighted) en.w = rows.weight(static_cast<int>(p));
+                }
+                return en;
+            };
+            // W entries from position b of the 64 on: all their loads, then their additions
+            auto batch = [&](const Entry &en, uint32_t e0, int cnt, int b, auto width) __attribute__((always_inline)) {
+                constexpr int W = decltype(width)::value;
+                P v[W][NV];
+#pragma unroll
+                for (int u = 0; u < W; ++u) {
+                    const int r = static_cast<int>(readlane32(static_cast<uint32_t>(en.row), b + u));
                     const char *row = xb + (Rows::kSelf && r < 0 ? 0 : r) * x_bytes;
 #pragma unroll
                     for (int k = 0; k < NV; ++k) v[u][k] = *reinterpret_cast<const P *>(row + lane_off[k]);
                 }
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
+                for (int u = 0; u < W; ++u) {
                     if (b + u >= cnt) continue;
                     while (e0 + static_cast<uint32_t>(b + u) >= row_end) finish_row();
-                    if (Rows::kSelf && static_cast<int>(readlane32(static_cast<uint32_t>(my_row), b + u)) < 0) continue;
-                    const float w = __uint_as_float(readlane32(__float_as_uint(my_w), b + u));
+                    if (Rows::kSelf && static_cast<int>(readlane32(static_cast<uint32_t>(en.row), b + u)) < 0) continue;
+                    const float w = __uint_as_float(readlane32(__float_as_uint(en.w), b + u));
 #pragma unroll
                     for (int k = 0; k < NV; ++k)
 #pragma unroll
@@ -236,21 +325,38 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
                             else a += to_f32(v[u][k].v[q]);
                         }
                 }
-            }
+            };
+            auto walk = [&](auto width) __attribute__((always_inline)) {
+                constexpr int W = decltype(width)::value;
+                for (uint32_t e0 = begin; e0 < end; e0 += kWave) {
+                    const int cnt = end - e0 < kWave ? static_cast<int>(end - e0) : kWave;
+                    const Entry en = fetch(e0);
+                    for (int b = 0; b < cnt; b += W) batch(en, e0, cnt, b, width);
+                }
+            };
+            if (begin < end) walk(std::integral_constant<int, U>());
+            while (cur < stop) finish_row();
+            if (stop == m) break;
+            const int b = static_cast<int>(readlane32(off, stop)) - (stop < diag ? stop : diag);
+            const int e = static_cast<int>(readlane32(off, stop + 1)) - (stop + 1 < diag ? stop + 1 : diag);
+            if constexpr (LV > 0) reduce_long_row<T, LV>(rows, c0 + stop, b, e, stop < diag, x, x_stride, out, out_stride, dim, log2_lpr);
+            longs &= longs - 1;
+            cur = stop + 1;
+            if (cur == m) break;
         }
-        while (cur < m) finish_row();
     }
 }
 
 // columns [0, dim) of all rows, nv vectors of vec elements per lane
 template <typename T, typename Rows>
 int launch_columns(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_rows, int64_t row_blocks, const T *x,
-                   int64_t x_stride, T *out, int64_t out_stride, int dim, int vec, int nv, hipStream_t s) {
+                   int64_t x_stride, T *out, int64_t out_stride, int dim, int vec, int nv, uint32_t busy, int mostly_long, int long_vec, int log2_lpr, hipStream_t s) {
     const int64_t slabs = ceil_div(ceil_div(dim, vec), int64_t(nv) * kWave);
     const int grid = static_cast<int>(row_blocks * slabs);
-#define MQG_AGG(V, NV)                                                                                          \
+#define MQG_AGG_LV(V, NV, LV)                                                                                          \
     MQG_LAUNCH(ctx, name, s,                                                                                    \
-               (k_segment_flat<T, V, NV, Rows><<<grid, kBlock, 0, s>>>(rows, n_rows, x, x_stride, out, out_stride, dim, static_cast<uint32_t>(row_blocks))))
+               (k_segment_flat<T, V, NV, LV, Rows><<<grid, kBlock, 0, s>>>(rows, n_rows, x, x_stride, out, out_stride, dim, static_cast<uint32_t>(row_blocks), busy, mostly_long, log2_lpr)))
+#define MQG_AGG(V, NV) MQG_AGG_LV(V, NV, 0)
 #define MQG_AGG_PICK(V)                        \
     switch (nv) {                              \
         case 1: MQG_AGG(V, 1); break;          \
@@ -261,7 +367,15 @@ int launch_columns(mqg_ctx *ctx, const char *name, const Rows &rows, const int64
         default: MQG_AGG(V, 6); break;         \
     }
     constexpr int kWidest = 16 / static_cast<int>(sizeof(T));
-    if (vec == kWidest) {
+    if (long_vec == 8) {
+        if constexpr (kWidest == 8) MQG_AGG_LV(1, 1, 8);
+    } else if (long_vec == 4) {
+        MQG_AGG_LV(1, 1, 4);
+    } else if (long_vec == 2) {
+        MQG_AGG_LV(1, 1, 2);
+    } else if (long_vec == 1) {
+        MQG_AGG_LV(1, 1, 1);
+    } else if (vec == kWidest) {
         MQG_AGG_PICK(kWidest);
     } else if (vec == kWidest / 2) {
         MQG_AGG_PICK(kWidest / 2);
@@ -272,11 +386,12 @@ int launch_columns(mqg_ctx *ctx, const char *name, const Rows &rows, const int64
     }
 #undef MQG_AGG_PICK
 #undef MQG_AGG
+#undef MQG_AGG_LV
     return MQG_OK;
 }
 
 template <typename T, typename Rows>
-int launch(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_rows, int64_t cap_rows, const T *x,
+int launch(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_rows, int64_t cap_rows, int64_t cap_nnz, const T *x,
            int64_t x_stride, T *out, int64_t out_stride, int dim, hipStream_t s) {
     // widest vector (<= 16 bytes) that divides dim and both strides and keeps the bases aligned.
     // When both strides leave room, dim is first rounded up to whole 16-byte words: the extra
@@ -292,19 +407,30 @@ int launch(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_ro
                reinterpret_cast<uintptr_t>(x) % bytes == 0 && reinterpret_cast<uintptr_t>(out) % bytes == 0;
     };
     while (vec > 1 && !ok(vec)) vec >>= 1;
+    // Up to eight of these vectors: rows of many entries go by themselves, see k_segment_flat.
+    const int wide_lanes = static_cast<int>(ceil_div(dim, vec));
+    const int long_vec = wide_lanes <= 8 ? vec : 0;
+    int log2_lpr = 0;
+    while ((1 << log2_lpr) < wide_lanes && log2_lpr < 3) ++log2_lpr;
     // the narrowest vector with which the 64 lanes still cover the row (wider rows: the widest, in slabs)
     while (vec > 1 && ceil_div(dim, vec / 2) <= kWave) vec >>= 1;
     // Rows of more than 64 vectors: NV vectors per lane, or slabs of 64 vectors with a wavefront each.  More
     // vectors per lane share the walk over the entries, slabs spread few rows over more wavefronts and
     // leave a row's last, partly filled vector to a wavefront of its own.  Output rows of few entries (the
     // backward) want the first up to six vectors (513 to 800 fp32 columns: 236 to 345 us against 295 to
-    // 367 us), output rows of many entries the second if the vectors are well filled (602 columns, 79 %: 198
-    // against 204 us; 513 columns, 67 %: 214 against 188 us).
+    // 367 us).  Output rows of many entries want slabs if the vectors are well
+    // filled (602 columns, 79 %: 198 against 204 us; 513 columns, 67 %: 214 against 188 us).
     const int64_t lanes = ceil_div(dim, vec);
     const int64_t units = ceil_div(lanes, kWave);
-    const bool spread = units > 6 || vec < 8 / static_cast<int>(sizeof(T)) || (!Rows::kFewEntries && units >= 2 && lanes * 100 >= units * kWave * 78);
+    const bool filled = units >= 2 && lanes * 100 >= units * kWave * 78;
+    const bool spread = units > 6 || vec < 8 / static_cast<int>(sizeof(T)) || (!Rows::kFewEntries && filled);
     const int nv = spread ? 1 : static_cast<int>(units);
     const int64_t row_blocks = std::min<int64_t>(std::max<int64_t>(1, ceil_div(cap_rows, kWavesPerBlock)), 256 * 32);
+    // Narrow rows of few entries are handed out two to four at a time once the chip's 8,192 wavefronts have one
+    // each (10 k rows of 5 entries, 16 fp32 columns: 5.1 -> 4.6 us, 30 k of 10: 13.2 -> 9.6; rows of 25: the other
+    // way round).  Their expected length is what the block's capacities say, a sampled block's fanout.
+    const int mostly_long = cap_nnz >= kLongRow * cap_rows ? 1 : 0;
+    const uint32_t busy = long_vec && !mostly_long ? 8192 : static_cast<uint32_t>(row_blocks * kWavesPerBlock);
     // A launch has fewer than 2^32 threads and the kernel's column offsets are 32 bits: very wide rows take
     // several launches over pieces of their columns, 64 MB of a row at most each.
     const int64_t slabs_at_once = std::min<int64_t>((int64_t(1) << 22) / row_blocks, int64_t(1) << 16);
@@ -312,12 +438,12 @@ int launch(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_ro
         const int64_t piece = slabs_at_once * kWave * vec;
         for (int64_t c0 = 0; c0 < dim; c0 += piece) {
             const int cols = static_cast<int>(std::min<int64_t>(piece, dim - c0));
-            int rc = launch_columns(ctx, name, rows, n_rows, row_blocks, x + c0, x_stride, out + c0, out_stride, cols, vec, nv, s);
+            int rc = launch_columns(ctx, name, rows, n_rows, row_blocks, x + c0, x_stride, out + c0, out_stride, cols, vec, nv, busy, 0, 0, 0, s);
             if (rc != MQG_OK) return rc;
         }
         return MQG_OK;
     }
-    return launch_columns(ctx, name, rows, n_rows, row_blocks, x, x_stride, out, out_stride, dim, vec, nv, s);
+    return launch_columns(ctx, name, rows, n_rows, row_blocks, x, x_stride, out, out_stride, dim, vec, nv, busy, mostly_long, long_vec, log2_lpr, s);
 }
 
 // ---------------------------------------------------------------- edges ordered by source
@@ -479,9 +605,9 @@ int run_weighted_aggregate(mqg_ctx *ctx, const mqg_block *b, const float *edge_w
                            int64_t x_stride, void *out, int64_t out_stride, int32_t dim, int32_t dtype, hipStream_t s) {
     WeightedRows rows{b->indptr, b->indices, edge_w, self_w};
     if (dtype == MQG_F16)
-        return launch<_Float16>(ctx, "k_weighted_aggregate", rows, &b->sizes[0], b->cap_dst, static_cast<const _Float16 *>(x),
+        return launch<_Float16>(ctx, "k_weighted_aggregate", rows, &b->sizes[0], b->cap_dst, b->cap_nnz, static_cast<const _Float16 *>(x),
                                 x_stride, static_cast<_Float16 *>(out), out_stride, dim, s);
-    return launch<float>(ctx, "k_weighted_aggregate", rows, &b->sizes[0], b->cap_dst, static_cast<const float *>(x), x_stride,
+    return launch<float>(ctx, "k_weighted_aggregate", rows, &b->sizes[0], b->cap_dst, b->cap_nnz, static_cast<const float *>(x), x_stride,
                          static_cast<float *>(out), out_stride, dim, s);
 }
 
@@ -489,9 +615,9 @@ int run_mean_aggregate(mqg_ctx *ctx, const mqg_block *b, const void *x, int64_t 
                        int64_t out_stride, int32_t dim, int32_t dtype, hipStream_t s) {
     ForwardRows rows{b->indptr, b->indices};
     if (dtype == MQG_F16)
-        return launch<_Float16>(ctx, "k_mean_aggregate", rows, &b->sizes[0], b->cap_dst, static_cast<const _Float16 *>(x),
+        return launch<_Float16>(ctx, "k_mean_aggregate", rows, &b->sizes[0], b->cap_dst, b->cap_nnz, static_cast<const _Float16 *>(x),
                                 x_stride, static_cast<_Float16 *>(out), out_stride, dim, s);
-    return launch<float>(ctx, "k_mean_aggregate", rows, &b->sizes[0], b->cap_dst, static_cast<const float *>(x), x_stride,
+    return launch<float>(ctx, "k_mean_aggregate", rows, &b->sizes[0], b->cap_dst, b->cap_nnz, static_cast<const float *>(x), x_stride,
                          static_cast<float *>(out), out_stride, dim, s);
 }
 
@@ -556,16 +682,16 @@ int run_aggregate_backward(mqg_ctx *ctx, const mqg_block *b, const float *edge_w
                    (k_permute_edges<<<egrid, kBlock, 0, s>>>(sorted_dst, b->indptr, rows_of, edge_w, b->sizes, dst_sorted, ctx->bwd_w_sorted)));
         WeightedBackwardRows rows{ctx->bwd_col_ptr, dst_sorted, ctx->bwd_w_sorted, self_w, b->sizes};
         if (dtype == MQG_F16)
-            return launch<_Float16>(ctx, "k_weighted_aggregate_backward", rows, &b->sizes[1], src_cap,
+            return launch<_Float16>(ctx, "k_weighted_aggregate_backward", rows, &b->sizes[1], src_cap, nnz_cap,
                                     static_cast<const _Float16 *>(grad_out), go_stride, static_cast<_Float16 *>(grad_x), gx_stride, dim, s);
-        return launch<float>(ctx, "k_weighted_aggregate_backward", rows, &b->sizes[1], src_cap, static_cast<const float *>(grad_out),
+        return launch<float>(ctx, "k_weighted_aggregate_backward", rows, &b->sizes[1], src_cap, nnz_cap, static_cast<const float *>(grad_out),
                              go_stride, static_cast<float *>(grad_x), gx_stride, dim, s);
     }
     BackwardRows rows{ctx->bwd_col_ptr, sorted_dst, b->indptr};
     if (dtype == MQG_F16)
-        return launch<_Float16>(ctx, "k_mean_aggregate_backward", rows, &b->sizes[1], src_cap,
+        return launch<_Float16>(ctx, "k_mean_aggregate_backward", rows, &b->sizes[1], src_cap, nnz_cap,
                                 static_cast<const _Float16 *>(grad_out), go_stride, static_cast<_Float16 *>(grad_x), gx_stride, dim, s);
-    return launch<float>(ctx, "k_mean_aggregate_backward", rows, &b->sizes[1], src_cap, static_cast<const float *>(grad_out),
+    return launch<float>(ctx, "k_mean_aggregate_backward", rows, &b->sizes[1], src_cap, nnz_cap, static_cast<const float *>(grad_out),
                          go_stride, static_cast<float *>(grad_x), gx_stride, dim, s);
 }
 

@@ -173,6 +173,9 @@ __device__ __forceinline__ void reduce_long_row(const Rows &rows, int64_t i, int
 // blocks of a mini-batch of 8,192 seeds (512-byte rows; 347 k output rows, 4.7 M entries) 0.432 -> 0.338 ms,
 // the reductions of their backward (1.7 M output rows of 3 entries) 0.89 -> 0.49 ms; 2,408-byte rows (10 k
 // rows of 25 entries: 612 MB read in 83 us = 7.4 TB/s) as before.
+// Few short rows are bound by the instructions of a wavefront and the chain of loads in it: the last entries of
+// a run take a batch of 4 or 8 rows if that will do (3,000 rows of 3 entries, 128 fp32 columns: 4.3 us with 16
+// loads for three entries, 3.3 now; the loop 3.3).
 // Measured and dropped: slabs of 128 to 512 bytes dealt to the XCDs so that every L2 keeps its slab of the
 // hot rows (L2 hits 13 -> 24 %, time unchanged or worse); 4 or 16 instead of 8 vectors of 16 bytes in flight;
 // lanes past the row left out of the loads (wide fp16 rows 1.3 to 1.7 times slower).
@@ -195,7 +198,7 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
     constexpr int NACC = U < 2 ? 1 : VEC <= 2 ? (U < 4 ? U : 4) : NV <= 2 ? 2 : 1;
     const int lane = lane_id();
     const int64_t n = *n_rows;
-    const uint32_t slab = blockIdx.x / row_blocks;
+    const uint32_t slab = gridDim.x == row_blocks ? 0 : blockIdx.x / row_blocks;
     const uint32_t row_block = blockIdx.x - slab * row_blocks;
     bool live[NV];
     uint32_t lane_off[NV];                                 // lanes past the row read its start and store nothing
@@ -331,7 +334,12 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
                 for (uint32_t e0 = begin; e0 < end; e0 += kWave) {
                     const int cnt = end - e0 < kWave ? static_cast<int>(end - e0) : kWave;
                     const Entry en = fetch(e0);
-                    for (int b = 0; b < cnt; b += W) batch(en, e0, cnt, b, width);
+                    int b = 0;
+                    for (; b + W <= cnt; b += W) batch(en, e0, cnt, b, width);
+                    const int left = cnt - b;
+                    if (left > 8 && W > 8) batch(en, e0, cnt, b, width);
+                    else if (left > 4 && W > 4) batch(en, e0, cnt, b, std::integral_constant<int, W < 8 ? W : 8>());
+                    else if (left > 0) batch(en, e0, cnt, b, std::integral_constant<int, W < 4 ? W : 4>());
                 }
             };
             if (begin < end) walk(std::integral_constant<int, U>());

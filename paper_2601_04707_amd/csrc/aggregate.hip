@@ -371,8 +371,8 @@ int launch_columns(mqg_ctx *ctx, const char *name, const Rows &rows, const int64
         case 2: MQG_AGG(V, 2); break;          \
         case 3: MQG_AGG(V, 3); break;          \
         case 4: MQG_AGG(V, 4); break;          \
-        case 5: MQG_AGG(V, 5); break;          \
-        default: MQG_AGG(V, 6); break;         \
+        case 5: if constexpr (Rows::kFewEntries) MQG_AGG(V, 5); break;          /* the others' are filled: slabs */ \
+        default: if constexpr (Rows::kFewEntries) MQG_AGG(V, 6); break;         \
     }
     constexpr int kWidest = 16 / static_cast<int>(sizeof(T));
     if (long_vec == 8) {
@@ -426,11 +426,13 @@ int launch(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_ro
     // vectors per lane share the walk over the entries, slabs spread few rows over more wavefronts and
     // leave a row's last, partly filled vector to a wavefront of its own.  Output rows of few entries (the
     // backward) want the first up to six vectors (513 to 800 fp32 columns: 236 to 345 us against 295 to
-    // 367 us).  Output rows of many entries want slabs if the vectors are well
-    // filled (602 columns, 79 %: 198 against 204 us; 513 columns, 67 %: 214 against 188 us).
+    // 367 us).  Output rows of many entries want slabs if the vectors are well filled, in time over that with
+    // vectors per lane, three mini-batches of fanouts 4 to 25: 67 % filled 1.14 to 1.16, 71 to 75 % 0.97 to 1.07,
+    // 77 % 1.01 to 1.05, 79 to 84 % 0.90 to 1.03, full 0.88 to 0.97.  Two vectors only if both are full: two slabs
+    // share the cache lines in the middle of a row (500 columns 1.05 to 1.07, 512 0.93 to 0.98).
     const int64_t lanes = ceil_div(dim, vec);
     const int64_t units = ceil_div(lanes, kWave);
-    const bool filled = units >= 2 && lanes * 100 >= units * kWave * 78;
+    const bool filled = units == 2 ? lanes == 2 * kWave : units > 2 && lanes * 100 >= units * kWave * 78;
     const bool spread = units > 6 || vec < 8 / static_cast<int>(sizeof(T)) || (!Rows::kFewEntries && filled);
     const int nv = spread ? 1 : static_cast<int>(units);
     const int64_t row_blocks = std::min<int64_t>(std::max<int64_t>(1, ceil_div(cap_rows, kWavesPerBlock)), 256 * 32);

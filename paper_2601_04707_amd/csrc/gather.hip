@@ -4,7 +4,7 @@
 // by the kernel itself) when it is not.
 //
 //   k_classify        slot_of lookup, ballot-compacted (output row, source row) lists for hits and
-//                     misses, one atomic per wavefront and list
+//                     misses, one atomic per tile of ids and list
 //   k_gather_rows<.,0> hits:   HBM cache -> HBM output, widest aligned loads; rows of up to 64 vectors
 //                     as one flat sequence of vectors (every lane carries one), longer rows two at a
 //                     time by a wavefront
@@ -43,25 +43,27 @@ __global__ void k_direct_stats(int64_t *stats, const int64_t *num_ids, int64_t c
 
 // Splits the ids into a hit list (output row, cache slot) and a miss list (output row, node id).
 // A workgroup classifies a tile of 256 * ITEMS ids and reserves its share of both lists with one atomic
-// each: atomics on one address are served one after the other, at 13 ns, so large batches take tiles of
-// 4,096 ids (1.35 M ids: 41 -> 20 us; batches of up to 512 k keep 1,024, enough workgroups to hide the
-// slot lookups).  Positions inside a share come from ballots, so that a wavefront writes consecutive
-// entries.  The order of the list entries is arbitrary; the gather does not depend on it.  An id outside
-// [0, num_nodes) is never used as an index: it goes on neither list, so its output row stays untouched and
-// hits + misses fall short of the number of ids.
+// each: atomics on one address are served one after the other, at 13 ns, so more than 512 k ids go in tiles of
+// 4,096 (1.35 M ids: 41 -> 20 us); fewer keep tiles of 1,024, enough workgroups to hide the slot lookups (100 k ids
+// 7.9 us, in tiles of 4,096 14.3; level at 500 k with 16.5 and 17.5).  The number of ids decides, which only
+// the device knows; the capacity is often twice that and more.  Positions inside a share come from ballots, so that
+// a wavefront writes consecutive entries.  The order of the list entries is arbitrary; the gather does not depend on
+// it.  An id outside [0, num_nodes) is never used as an index: it goes on neither list, so its output row stays
+// untouched and hits + misses fall short of the number of ids.
 constexpr int64_t kClassifyLarge = int64_t(1) << 19;
-template <typename IdxT, int ITEMS>
-__global__ void __launch_bounds__(kBlock)
-k_classify(const IdxT *__restrict__ ids, const int64_t *__restrict__ num_ids, int64_t cap,
-           const int32_t *__restrict__ slot_of, int64_t num_nodes, int2 *__restrict__ hit_list,
-           int2 *__restrict__ miss_list, unsigned long long *__restrict__ counters) {
+struct ClassifyLds {
+    int totals[2][kWavesPerBlock];
+    unsigned long long base[2];
+};
+template <int ITEMS, typename IdxT>
+__device__ __forceinline__ void classify_tiles(const IdxT *__restrict__ ids, int64_t n, const int32_t *__restrict__ slot_of, int64_t num_nodes,
+                                               int2 *__restrict__ hit_list, int2 *__restrict__ miss_list,
+                                               unsigned long long *__restrict__ counters, ClassifyLds &lds) {
     constexpr int kTile = kBlock * ITEMS;
-    __shared__ int totals[2][kWavesPerBlock];
-    __shared__ unsigned long long base[2];
+    int (&totals)[2][kWavesPerBlock] = lds.totals;
+    unsigned long long (&base)[2] = lds.base;
     const int lane = lane_id();
     const int wave = static_cast<int>(threadIdx.x) >> 6;
-    int64_t n = *num_ids;
-    if (n > cap) n = cap;
     for (int64_t t0 = int64_t(blockIdx.x) * kTile; t0 < n; t0 += int64_t(gridDim.x) * kTile) {
         int32_t id[ITEMS], slot[ITEMS];
 #pragma unroll
@@ -107,6 +109,18 @@ k_classify(const IdxT *__restrict__ ids, const int64_t *__restrict__ num_ids, in
         }
         __syncthreads();                                // totals[] and base[] are rewritten by the next tile
     }
+}
+
+template <typename IdxT>
+__global__ void __launch_bounds__(kBlock)
+k_classify(const IdxT *__restrict__ ids, const int64_t *__restrict__ num_ids, int64_t cap,
+           const int32_t *__restrict__ slot_of, int64_t num_nodes, int2 *__restrict__ hit_list,
+           int2 *__restrict__ miss_list, unsigned long long *__restrict__ counters) {
+    __shared__ ClassifyLds lds;
+    int64_t n = *num_ids;
+    if (n > cap) n = cap;
+    if (n > kClassifyLarge) classify_tiles<16>(ids, n, slot_of, num_nodes, hit_list, miss_list, counters, lds);
+    else classify_tiles<4>(ids, n, slot_of, num_nodes, hit_list, miss_list, counters, lds);
 }
 
 // Which rows to copy: entry r of a (output row, source row) list, or row ids[r] to output row r.
@@ -563,16 +577,13 @@ int run_gather(mqg_ctx *ctx, const mqg_cache *c, int32_t idx_type, const void *i
     // (hits, misses) counters: zero between gathers (the miss launch clears them when it is done)
     unsigned long long *counters = ctx->counters;
     if (phases & kGatherCached) {
-        const bool large = cap_ids > kClassifyLarge;
-        const int cgrid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(cap_ids, kBlock * (large ? 16 : 4))), 1024));
-#define MQG_CLASSIFY(IT, ITEMS)                                                                                        \
+        const int cgrid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(cap_ids, kBlock * 4)), 1024));
+#define MQG_CLASSIFY(IT)                                                                                               \
     MQG_LAUNCH(ctx, "k_classify", s,                                                                                   \
-               (k_classify<IT, ITEMS><<<cgrid, kBlock, 0, s>>>(static_cast<const IT *>(ids), num_ids, cap_ids, c->slot_of, c->num_nodes, \
-                                                               ctx->hit_list, ctx->miss_list, counters)))
-        if (idx_type == MQG_I64 && large) MQG_CLASSIFY(int64_t, 16);
-        else if (idx_type == MQG_I64) MQG_CLASSIFY(int64_t, 4);
-        else if (large) MQG_CLASSIFY(int32_t, 16);
-        else MQG_CLASSIFY(int32_t, 4);
+               (k_classify<IT><<<cgrid, kBlock, 0, s>>>(static_cast<const IT *>(ids), num_ids, cap_ids, c->slot_of, c->num_nodes, \
+                                                        ctx->hit_list, ctx->miss_list, counters)))
+        if (idx_type == MQG_I64) MQG_CLASSIFY(int64_t);
+        else MQG_CLASSIFY(int32_t);
 #undef MQG_CLASSIFY
         int rc = launch_rows<0>(ctx, "k_gather_hit", ctx->hit_list, &counters[0], cap_ids, c->cache_rows,
                                 c->cache_stride * elt, out, out_stride * elt, row_bytes, stats, counters, s);

@@ -1,5 +1,5 @@
-"""The split of the ids into hits and misses at the edges of its tiles (1,024 ids, 4,096 above 512 k) and of its
-workgroups' loop, with ids outside the graph among them.  Bytes and counts are exact."""
+"""The split of the ids into hits and misses at the edges of its tiles (1,024 ids, 4,096 for more than 512 k) and of its
+workgroups' loop (1,024 tiles at a time), with ids outside the graph among them.  Bytes and counts are exact."""
 import pytest
 import torch
 
@@ -39,3 +39,65 @@ def test_tiles_of_ids(num_ids, cap, idx):
         torch.cuda.synchronize()
         assert torch.equal(out, want)
         assert stats.tolist() == [hits, int(valid.sum()) - hits]
+
+
+@pytest.mark.parametrize("idx", [torch.int32, torch.int64])
+def test_workgroups_take_a_second_tile(idx):
+    """More than 1,024 tiles of 4,096: workgroups go round again, some to a tile of hits only, of misses only, or of ids
+    outside the graph only."""
+    from paper_2601_04707_amd import mqg
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    n, cap = 50_000, 1024 * 4096 + 3 * 4096 + 77
+    deg = torch.randint(0, 9, (n,), generator=gen, device="cuda")
+    row_ptr = torch.zeros(n + 1, dtype=idx, device="cuda")
+    row_ptr[1:] = torch.cumsum(deg, 0).to(idx)
+    g = mqg.Graph(row_ptr, torch.zeros(int(row_ptr[-1]), dtype=idx, device="cuda"))
+    ctx = mqg.Context(g, cap, [1])
+    feats = torch.randn((n, 2), generator=gen, device="cuda")
+    cache = mqg.Cache(g, feats, n // 3)
+    mqg.mqg_build_cache(ctx, g, cache)
+    cached = cache.slot_of >= 0
+    hit_ids, miss_ids = torch.nonzero(cached).flatten(), torch.nonzero(~cached).flatten()
+    ids = torch.randint(-500, n + 500, (cap,), generator=gen, device="cuda")
+    second = ids[1024 * 4096:]
+    second[:4096] = hit_ids[torch.randint(0, len(hit_ids), (4096,), generator=gen, device="cuda")]
+    second[4096:8192] = miss_ids[torch.randint(0, len(miss_ids), (4096,), generator=gen, device="cuda")]
+    second[8192:12288] = -7
+    valid = (ids >= 0) & (ids < n)
+    want = torch.full((cap, 2), 9.0, device="cuda")
+    want[valid] = feats[ids[valid]]
+    hits = int(cached[ids[valid]].sum())
+    out = torch.empty((cap, 2), device="cuda")
+    stats = torch.zeros(2, dtype=torch.int64, device="cuda")
+    for _ in range(2):
+        out.fill_(9.0)
+        mqg.mqg_gather_features(ctx, cache, ids.to(idx), torch.tensor([cap], device="cuda"), out, stats)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        assert stats.tolist() == [hits, int(valid.sum()) - hits]
+
+
+def test_tiles_follow_the_number_of_ids():
+    """100,000 ids are classified in as many workgroups whether the buffers hold 100,000 or a million (8 us; 14 us in the
+    tiles of 4,096 that a million ids take)."""
+    from paper_2601_04707_amd import mqg
+    n, ids_cap = 400_000, 1 << 20
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    row_ptr = torch.clamp(torch.arange(n + 1, device="cuda"), max=1000)
+    g = mqg.Graph(row_ptr, torch.zeros(1000, dtype=torch.int64, device="cuda"))
+    ctx = mqg.Context(g, ids_cap, [1])
+    cache = mqg.Cache(g, torch.zeros((n, 4), device="cuda"), n // 2)
+    mqg.mqg_build_cache(ctx, g, cache)
+    ids = torch.randint(0, n, (ids_cap,), generator=gen, device="cuda")
+    out = torch.empty((ids_cap, 4), device="cuda")
+    count = torch.tensor([100_000], device="cuda")
+    ctx.set_option(mqg.MQG_OPT_PROFILE, 1)
+    took = {100_000: [], ids_cap: []}
+    for _ in range(8):
+        for cap in took:
+            mqg.mqg_gather_features(ctx, cache, ids, count, out, None, cap_ids=cap)
+            ctx.reset_profile()
+            for _ in range(5):
+                mqg.mqg_gather_features(ctx, cache, ids, count, out, None, cap_ids=cap)
+            took[cap].append(ctx.kernel_time("k_classify")[0])
+    assert min(took[ids_cap]) < 1.35 * min(took[100_000]), took

@@ -475,21 +475,23 @@ __device__ __forceinline__ int64_t wave_count_below(const V *__restrict__ v, int
     return lo;
 }
 
-// payload of edge e = its destination row (the keys are `indices`).  A wavefront takes kEdgeRun consecutive
-// edges; its lanes hold the offsets of 64 consecutive rows, and every edge finds its row among them.  The
+// payload of edge e = its destination row (the keys are `indices`).  A wavefront takes a run of consecutive edges,
+// 64 or as many more as give every wavefront of the chip one run (runs of 512 left 38 k edges to 74 wavefronts:
+// 5.9 us, 2.4 in runs of 64; a bisection per edge 3.4); its lanes hold the offsets of 64 consecutive rows, and every edge finds its row among them.  The
 // window of rows only moves forward and ends at the last row, which takes every edge past the last offset
 // (the number of edges comes from another array than the offsets): the loop ends whatever the block holds.
 // Bound by its 4-byte store per edge; a bisection of all of indptr per edge (19 dependent loads) took 57
 // instead of 13 us for 4.3 M edges of 295 k rows.
-constexpr int kEdgeRun = 512;
+constexpr int kEdgeWaves = 8192;
 constexpr int64_t kPickRowsEdges = int64_t(3) << 19;     // see run_aggregate_backward
 __global__ void __launch_bounds__(kBlock)
 k_edge_dst_rows(const int32_t *__restrict__ indptr, const int64_t *__restrict__ sizes, int32_t *__restrict__ dst_row) {
     const int lane = lane_id();
     const int64_t num_dst = sizes[0], nnz = sizes[2];
-    const int64_t step = int64_t(gridDim.x) * kWavesPerBlock * kEdgeRun;
-    for (int64_t e0 = (int64_t(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6)) * kEdgeRun; e0 < nnz; e0 += step) {
-        const int64_t e1 = e0 + kEdgeRun < nnz ? e0 + kEdgeRun : nnz;
+    const int64_t run = nnz > kEdgeWaves * kWave ? (nnz + kEdgeWaves * kWave - 1) / (kEdgeWaves * kWave) * kWave : kWave;
+    const int64_t step = int64_t(gridDim.x) * kWavesPerBlock * run;
+    for (int64_t e0 = (int64_t(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6)) * run; e0 < nnz; e0 += step) {
+        const int64_t e1 = e0 + run < nnz ? e0 + run : nnz;
         auto row_of = [&](int64_t e) {
             const int64_t r = wave_count_below<false>(indptr, num_dst, e) - 1;
             return r > 0 ? r : 0;
@@ -669,7 +671,7 @@ int run_aggregate_backward(mqg_ctx *ctx, const mqg_block *b, const float *edge_w
     const int egrid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(nnz_cap, kBlock)), 8192));
     // Edges by source, stably.  An edge carries its destination row along, or (weighted) its own
     // position, which the sort's first pass makes itself - at least one pass, for that.
-    const int rgrid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(nnz_cap, int64_t(kWavesPerBlock) * kEdgeRun)), 8192));
+    const int rgrid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(nnz_cap, kBlock)), kEdgeWaves / kWavesPerBlock));
     if (!edge_w) MQG_LAUNCH(ctx, "k_edge_dst_rows", s, (k_edge_dst_rows<<<rgrid, kBlock, 0, s>>>(b->indptr, b->sizes, ctx->bwd_dst_row)));
     const int bits = std::max(1, radix_key_bits(static_cast<uint64_t>(std::max<int64_t>(src_cap, 1) - 1)));
     int which = -1;

@@ -192,7 +192,7 @@ __global__ void __launch_bounds__(kBlock)
 k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restrict__ x, int64_t x_stride,
                T *__restrict__ out, int64_t out_stride, int dim, uint32_t row_blocks, uint32_t busy, int mostly_long, int log2_lpr) {
     using P = Pack<T, VEC>;
-    constexpr int U = NV == 1 ? (sizeof(P) == 16 ? 8 : 16) : NV == 2 ? (Rows::kFewEntries ? 4 : 8) : NV == 3 ? 4 : 2;    // input rows in flight: 4 to 12 KB per wavefront
+    constexpr int U = NV == 1 ? (sizeof(P) == 16 ? 8 : 16) : NV <= 3 ? 4 : 2;    // input rows in flight: 4 to 12 KB per wavefront
     // Partial sums that take the entries in turn.  The turn counts from the start of the run, so a row may begin
     // at any of them; opposite ones are added first, which gives the same bits wherever it began.
     constexpr int NACC = U < 2 ? 1 : VEC <= 2 ? (U < 4 ? U : 4) : NV <= 2 ? 2 : 1;

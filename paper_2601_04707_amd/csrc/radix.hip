@@ -311,6 +311,22 @@ k_radix_scatter(const uint32_t *__restrict__ keys_in, RadixPayload payload, int6
         }
         mine += cnt[q];
     }
+    if constexpr (SELF) {
+        // small sorts: each key straight to its place, without the second scan and the sorted tile
+#pragma unroll
+        for (int q = 0; q < PER; ++q) gbase[tid * PER + q] = out0[q];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            if (r < items && wave_first + r * kWave + lane < tile_n) {
+                const int digit = (key[r] >> shift) & (D - 1);
+                const int o = gbase[digit] + wcnt[wave][digit] + rank[r];
+                keys_out[o] = key[r];
+                vals_out[o] = val[r];
+            }
+        }
+        return;
+    }
     int total;
     int ex = block_excl_scan<kWavesPerBlock>(mine, &total, scan_lds);
 #pragma unroll

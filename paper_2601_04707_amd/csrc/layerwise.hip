@@ -1005,8 +1005,10 @@ static int sample_layerwise_impl(mqg_ctx *ctx, const mqg_graph *g, const void *s
         MQG_LAUNCH(ctx, "k_lw_keys", s,
                    (k_lw_keys<PtrT><<<key_grid, kBlock, 0, s>>>(row_ptr, cand, n_keys_dev, n, mass, tag_hash, flat, w.key64, w.q_part, w.sel_hist,
                                                                 dense ? w.counters : nullptr, w.sel_state, layer_sizes[l], bcount)));
-        // (every workgroup adds up 32 KB of digit counts first: 911 workgroups on 233 k keys took 2 us more per launch)
-        const int sel_grid = static_cast<int>(std::min<int64_t>(cand_grid, n <= (int64_t(1) << 20) ? 256 : 1024));
+        // Every workgroup adds up 32 KB of digit counts first, so no more of them than the keys need.  Whole calls (two
+        // layers of 512) with 256 / 512 / 1,024: 233 k nodes 115 / 116 / 121 us, 524 k 137 / 137 / 141, 1 M 170 / 167 / 170,
+        // 2 M 131 / 131 / 135; layers of 2,048 on 1 M nodes 206 / 200 / 202.
+        const int sel_grid = static_cast<int>(std::min<int64_t>(cand_grid, n <= (int64_t(1) << 19) ? 256 : 512));
         for (int pass = 1; pass < kSelPasses; ++pass)
             MQG_LAUNCH(ctx, "k_lw_select", s,
                        (k_lw_select<<<sel_grid, kBlock, 0, s>>>(w.key64, n_keys_dev, n, layer_sizes[l], w.sel_state, w.sel_hist, pass)));

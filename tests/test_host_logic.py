@@ -83,3 +83,16 @@ def test_aligned_row_stride_rule():
         st = synth.aligned_row_stride(dim, dt)
         elt = 2 if dt == torch.float16 else 4
         assert st >= dim and (st * elt) % 16 == 0
+
+
+def test_current_stream_with_and_without_torchs_raw_handle(monkeypatch):
+    from types import SimpleNamespace
+
+    from paper_2601_04707_amd import mqg
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=123))
+    monkeypatch.setattr(mqg, "_raw_stream", {3: 77}.get)
+    assert mqg._stream(None) == 77
+    monkeypatch.setattr(mqg, "_raw_stream", None)
+    assert mqg._stream(None) == 123
+    assert mqg._stream(55) == 55

@@ -25,6 +25,18 @@ def spmm(rows, cols, w, x, n):
                                                (70_001, 33, torch.float32), (70_001, 130, torch.float16), (40_000, 260, torch.float32),
                                                (3_000, 1030, torch.float32), (530_000, 16, torch.float16), (600_000, 9, torch.float32)])
 def test_runs_of_rows(num_dst, dim, dtype):
+    check_runs(num_dst, dim, dtype, dim)
+
+
+# several vectors of 16 bytes per lane: two to four forward, up to six backward; slabs
+@pytest.mark.parametrize("dim,dtype", [(390, torch.float32), (516, torch.float32), (602, torch.float32), (780, torch.float32), (1150, torch.float32),
+                                       (1500, torch.float32), (600, torch.float16), (1100, torch.float16), (1570, torch.float16),
+                                       (2100, torch.float16), (2900, torch.float16), (3100, torch.float16)])
+def test_runs_of_wide_padded_rows(dim, dtype):
+    check_runs(2_100, dim, dtype, -(-dim // 8) * 8)
+
+
+def check_runs(num_dst, dim, dtype, stride):
     from paper_2601_04707_amd import mqg
     gen = torch.Generator(device="cuda").manual_seed(num_dst + dim)
     lens = torch.randint(0, 7, (num_dst,), generator=gen, device="cuda")
@@ -38,16 +50,16 @@ def test_runs_of_rows(num_dst, dim, dtype):
     cols = torch.randint(0, num_src, (nnz,), generator=gen, device="cuda")
     cols[: nnz // 4] = num_src // 3                        # one source that a quarter of the edges point to
     ctx, blocks = bare_blocks(mqg, indptr.cpu().numpy(), cols.cpu().numpy(), num_dst, num_src)
-    x = torch.randn((num_src, dim), generator=gen, device="cuda").to(dtype)
-    g = torch.randn((num_dst, dim), generator=gen, device="cuda").to(dtype)
+    x = torch.randn((num_src, stride), generator=gen, device="cuda").to(dtype)[:, :dim]
+    g = torch.randn((num_dst, stride), generator=gen, device="cuda").to(dtype)[:, :dim]
     ew = torch.randn(max(nnz, 1), generator=gen, device="cuda")
     sw = torch.randn(num_dst, generator=gen, device="cuda")
     sw[::3] = 0                                            # a diagonal term of zero is no term:
-    xi = x.clone()
+    xi = torch.empty((num_src, stride), dtype=dtype, device="cuda")[:, :dim].copy_(x)
     xi[:num_dst:3] = float("inf")                          # its input row may hold anything, as long as no edge reads it
     keep = ~((cols < num_dst) & (cols % 3 == 0))
-    out = torch.full((num_dst + 1, dim), 7.0, dtype=dtype, device="cuda")
-    gx = torch.full((num_src + 1, dim), 7.0, dtype=dtype, device="cuda")
+    out = torch.full((num_dst + 1, stride), 7.0, dtype=dtype, device="cuda")[:, :dim]
+    gx = torch.full((num_src + 1, stride), 7.0, dtype=dtype, device="cuda")[:, :dim]
 
     def check(got, rows, cols, w, x, n, scale=None, diag=None):
         ref, mag = spmm(rows, cols, w, x.double(), n), spmm(rows, cols, w.abs(), x.double().abs(), n)
@@ -79,10 +91,10 @@ def test_runs_of_rows(num_dst, dim, dtype):
     assert torch.all(torch.isfinite(out[:num_dst][~dirty & (sw == 0)]))
 
 
-@pytest.mark.parametrize("scale", [1, 60])
+@pytest.mark.parametrize("scale", [1, 60, 80])
 def test_edges_find_their_rows(scale):
     """The backward's order of edges where rows are empty in long stretches, hold one edge each, or thousands
-    (scale 60: enough edges for the weighted backward to write all rows down first)."""
+    (scale 80: enough edges for the weighted backward to write all rows down first)."""
     from paper_2601_04707_amd import mqg
     rng = np.random.default_rng(scale)
     lens = np.concatenate([np.zeros(70), [3], np.zeros(5000), np.ones(700), [9000, 0, 0, 64, 1], np.zeros(64), np.full(300, 2),
@@ -90,6 +102,7 @@ def test_edges_find_their_rows(scale):
     lens = np.tile(lens, scale)
     indptr = np.concatenate([[0], np.cumsum(lens)])
     nd, nnz, ns = len(lens), int(indptr[-1]), 3000
+    assert (nnz > 3 << 19) == (scale == 80)
     cols = rng.integers(0, ns, nnz)
     cols[cols == 17] = 18                                  # a source without edges
     ctx, blocks = bare_blocks(mqg, indptr, cols, nd, ns)

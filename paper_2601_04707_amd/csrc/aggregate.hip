@@ -185,12 +185,22 @@ constexpr int kRunRows = 16;
 // 28 and 24 us; of 15 entries 28 and 32 to 35), and in blocks of a few thousand rows the groups are ahead from 5 or 6.
 constexpr uint32_t kLongRow = 12;
 
-// busy: wavefronts to hand rows to before any gets a second one, up to four rows (run below).
-// mostly_long: rows are expected to have kLongRow entries or more, so every wavefront takes one at a time.
+struct FlatShape {
+    int dim;
+    uint32_t row_blocks;          // workgroups per slab
+    int one_slab;                 // (the grid's size, which would tell, is an argument that the launch has to fill in)
+    uint32_t busy;                // wavefronts to hand rows to before any gets a second one, up to four rows (run below)
+    int mostly_long;              // rows are expected to have kLongRow entries or more: a wavefront takes one at a time
+    int log2_lpr;                 // lanes per row in reduce_long_row
+};
+
 template <typename T, int VEC, int NV, int LV, typename Rows>
 __global__ void __launch_bounds__(kBlock)
 k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restrict__ x, int64_t x_stride,
-               T *__restrict__ out, int64_t out_stride, int dim, uint32_t row_blocks, uint32_t busy, int mostly_long, int log2_lpr) {
+               T *__restrict__ out, int64_t out_stride, FlatShape sh) {
+    const int dim = sh.dim, log2_lpr = sh.log2_lpr;
+    const uint32_t row_blocks = sh.row_blocks;
+    const bool mostly_long = LV > 0 && sh.mostly_long;
     using P = Pack<T, VEC>;
     constexpr int U = NV == 1 ? (sizeof(P) == 16 ? 8 : 16) : NV <= 3 ? 4 : 2;    // input rows in flight: 4 to 12 KB per wavefront
     // Partial sums that take the entries in turn.  The turn counts from the start of the run, so a row may begin
@@ -198,7 +208,7 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
     constexpr int NACC = U < 2 ? 1 : VEC <= 2 ? (U < 4 ? U : 4) : NV <= 2 ? 2 : 1;
     const int lane = lane_id();
     const int64_t n = *n_rows;
-    const uint32_t slab = gridDim.x == row_blocks ? 0 : blockIdx.x / row_blocks;
+    const uint32_t slab = sh.one_slab ? 0 : blockIdx.x / row_blocks;
     const uint32_t row_block = blockIdx.x - slab * row_blocks;
     bool live[NV];
     uint32_t lane_off[NV];                                 // lanes past the row read its start and store nothing
@@ -212,7 +222,7 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
     const int64_t nwaves = int64_t(row_blocks) * kWavesPerBlock;
     const int64_t wave0 = __builtin_amdgcn_readfirstlane(static_cast<int>(row_block) * kWavesPerBlock + static_cast<int>(threadIdx.x >> 6));
     int run = 1;                                           // rows per wavefront and run
-    while (run < kRunRows && run * (run < 4 ? int64_t(busy) : nwaves) < n && !(LV > 0 && mostly_long)) ++run;
+    while (run < kRunRows && run * (run < 4 ? int64_t(sh.busy) : nwaves) < n && !mostly_long) ++run;
     const char *xb = reinterpret_cast<const char *>(x);
     const int64_t x_bytes = x_stride * int64_t(sizeof(T)), out_bytes = out_stride * int64_t(sizeof(T));
     for (int64_t c0 = wave0 * run; c0 < n; c0 += nwaves * run) {
@@ -355,15 +365,16 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
     }
 }
 
-// columns [0, dim) of all rows, nv vectors of vec elements per lane
+// columns [0, shape.dim) of all rows, nv vectors of vec elements per lane; long_vec: the kernel's LV
 template <typename T, typename Rows>
-int launch_columns(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_rows, int64_t row_blocks, const T *x,
-                   int64_t x_stride, T *out, int64_t out_stride, int dim, int vec, int nv, uint32_t busy, int mostly_long, int long_vec, int log2_lpr, hipStream_t s) {
-    const int64_t slabs = ceil_div(ceil_div(dim, vec), int64_t(nv) * kWave);
-    const int grid = static_cast<int>(row_blocks * slabs);
+int launch_columns(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_rows, const T *x,
+                   int64_t x_stride, T *out, int64_t out_stride, FlatShape shape, int vec, int nv, int long_vec, hipStream_t s) {
+    const int64_t slabs = ceil_div(ceil_div(shape.dim, vec), int64_t(nv) * kWave);
+    shape.one_slab = slabs == 1 ? 1 : 0;
+    const int grid = static_cast<int>(shape.row_blocks * slabs);
 #define MQG_AGG_LV(V, NV, LV)                                                                                          \
     MQG_LAUNCH(ctx, name, s,                                                                                    \
-               (k_segment_flat<T, V, NV, LV, Rows><<<grid, kBlock, 0, s>>>(rows, n_rows, x, x_stride, out, out_stride, dim, static_cast<uint32_t>(row_blocks), busy, mostly_long, log2_lpr)))
+               (k_segment_flat<T, V, NV, LV, Rows><<<grid, kBlock, 0, s>>>(rows, n_rows, x, x_stride, out, out_stride, shape)))
 #define MQG_AGG(V, NV) MQG_AGG_LV(V, NV, 0)
 #define MQG_AGG_PICK(V)                        \
     switch (nv) {                              \
@@ -439,21 +450,26 @@ int launch(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_ro
     // Narrow rows of few entries are handed out two to four at a time once the chip's 8,192 wavefronts have one
     // each (10 k rows of 5 entries, 16 fp32 columns: 5.1 -> 4.6 us, 30 k of 10: 13.2 -> 9.6; rows of 25: the other
     // way round).  Their expected length is what the block's capacities say, a sampled block's fanout.
-    const int mostly_long = cap_nnz >= kLongRow * cap_rows ? 1 : 0;
-    const uint32_t busy = long_vec && !mostly_long ? 8192 : static_cast<uint32_t>(row_blocks * kWavesPerBlock);
+    const bool mostly_long = cap_nnz >= kLongRow * cap_rows;
+    FlatShape shape;
+    shape.dim = dim;
+    shape.row_blocks = static_cast<uint32_t>(row_blocks);
+    shape.busy = long_vec && !mostly_long ? 8192 : static_cast<uint32_t>(row_blocks * kWavesPerBlock);
+    shape.mostly_long = mostly_long ? 1 : 0;
+    shape.log2_lpr = log2_lpr;
     // A launch has fewer than 2^32 threads and the kernel's column offsets are 32 bits: very wide rows take
     // several launches over pieces of their columns, 64 MB of a row at most each.
     const int64_t slabs_at_once = std::min<int64_t>((int64_t(1) << 22) / row_blocks, int64_t(1) << 16);
     if (nv == 1 && units > slabs_at_once) {
         const int64_t piece = slabs_at_once * kWave * vec;
         for (int64_t c0 = 0; c0 < dim; c0 += piece) {
-            const int cols = static_cast<int>(std::min<int64_t>(piece, dim - c0));
-            int rc = launch_columns(ctx, name, rows, n_rows, row_blocks, x + c0, x_stride, out + c0, out_stride, cols, vec, nv, busy, 0, 0, 0, s);
+            shape.dim = static_cast<int>(std::min<int64_t>(piece, dim - c0));
+            int rc = launch_columns(ctx, name, rows, n_rows, x + c0, x_stride, out + c0, out_stride, shape, vec, nv, 0, s);
             if (rc != MQG_OK) return rc;
         }
         return MQG_OK;
     }
-    return launch_columns(ctx, name, rows, n_rows, row_blocks, x, x_stride, out, out_stride, dim, vec, nv, busy, mostly_long, long_vec, log2_lpr, s);
+    return launch_columns(ctx, name, rows, n_rows, x, x_stride, out, out_stride, shape, vec, nv, long_vec, s);
 }
 
 // ---------------------------------------------------------------- edges ordered by source

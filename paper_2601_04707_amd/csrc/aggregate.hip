@@ -116,12 +116,13 @@ struct WeightedBackwardRows {
 
 // One row of many entries and few columns (at most eight vectors of LV elements): the lanes are split into groups of
 // 2^log2_lpr that cover the columns, group g takes the row's entries g, g + G, ..., and the G partial sums (8 to 64)
-// are folded across the groups.  64 / lpr rows per load and four loads in flight, where the walk below has 16 rows
-// in flight and most lanes idle: 2,000 rows of 300 entries and 16 fp32 columns 22.5 -> 8.6 us, of 2,000 entries
-// 139 -> 60; and more partial sums keep the error down (300 entries 1.7e-7 -> 1.0e-7 of the result, 2,000 entries
-// 4.0e-7 -> 2.1e-7).
+// are folded across the groups.  ws: the weight of the diagonal term, 0 if there is none.  G rows per load and, in
+// long rows, four loads in flight, where the walk below has 16 rows in flight and most lanes idle: 2,000 rows of 300
+// entries and 16 fp32 columns 22.5 -> 6.7 us (8.7 with one load at a time), of 2,000 entries 139 -> 33 (60); and
+// more partial sums keep the error down (300 entries 1.7e-7 -> 1.0e-7 of the result, 2,000 entries 4.0e-7 -> 2.1e-7).
+// Four loads where one or two will do cost 5 to 40 % on rows of G entries and fewer.
 template <typename T, int LV, typename Rows>
-__device__ __forceinline__ void reduce_long_row(const Rows &rows, int64_t i, int b, int e, bool diag, const T *__restrict__ x, int64_t x_stride,
+__device__ __forceinline__ void reduce_long_row(const Rows &rows, int64_t i, int b, int e, float ws, const T *__restrict__ x, int64_t x_stride,
                                                 T *__restrict__ out, int64_t out_stride, int dim, int log2_lpr) {
     using P = Pack<T, LV>;
     const int lane = lane_id();
@@ -133,27 +134,41 @@ __device__ __forceinline__ void reduce_long_row(const Rows &rows, int64_t i, int
     float acc[LV];
 #pragma unroll
     for (int q = 0; q < LV; ++q) acc[q] = 0.f;
-    if (Rows::kSelf && diag) {
-        const float ws = rows.self_weight(i);
-        if (ws != 0.f && live && g == 0) {
-            const P v = *reinterpret_cast<const P *>(x + i * x_stride + col0);
+    if (Rows::kSelf && ws != 0.f && live && g == 0) {
+        const P v = *reinterpret_cast<const P *>(x + i * x_stride + col0);
 #pragma unroll
-            for (int q = 0; q < LV; ++q) acc[q] = ws * to_f32(v.v[q]);
-        }
+        for (int q = 0; q < LV; ++q) acc[q] = ws * to_f32(v.v[q]);
     }
-#pragma unroll 4
-    for (int p = b + g; p < e; p += groups) {
-        const int64_t r = rows.input_row(p);
-        const float w = rows.weight(p);
-        if (live) {
-            const P v = *reinterpret_cast<const P *>(x + r * x_stride + col0);
+    // F entries of every group from position p0 on: all their loads, then their additions
+    auto batch = [&](int p0, auto flight) __attribute__((always_inline)) {
+        constexpr int F = decltype(flight)::value;
+        const int p = p0 + g;
+        if (p >= e) return;
+        int r[F];
+        float w[F];
+        P v[F];
 #pragma unroll
-            for (int q = 0; q < LV; ++q) {
-                if (Rows::kWeighted) acc[q] += w * to_f32(v.v[q]);
-                else acc[q] += to_f32(v.v[q]);
+        for (int u = 0; u < F; ++u) {
+            const int pu = p + u * groups < e ? p + u * groups : p;        // past the end: the first again, not added
+            r[u] = rows.input_row(pu);
+            w[u] = Rows::kWeighted ? rows.weight(pu) : 1.f;
+        }
+#pragma unroll
+        for (int u = 0; u < F; ++u) v[u] = *reinterpret_cast<const P *>(x + r[u] * x_stride + (live ? col0 : 0));
+#pragma unroll
+        for (int u = 0; u < F; ++u)
+            if (p + u * groups < e) {
+#pragma unroll
+                for (int q = 0; q < LV; ++q) {
+                    if (Rows::kWeighted) acc[q] += w[u] * to_f32(v[u].v[q]);
+                    else acc[q] += to_f32(v[u].v[q]);
+                }
             }
-        }
-    }
+    };
+    int p0 = b;
+    for (; e - p0 > 2 * groups; p0 += 4 * groups) batch(p0, std::integral_constant<int, 4>());
+    if (e - p0 > groups) batch(p0, std::integral_constant<int, 2>());
+    else if (e - p0 > 0) batch(p0, std::integral_constant<int, 1>());
     for (int off = lpr; off < kWave; off <<= 1) {
 #pragma unroll
         for (int q = 0; q < LV; ++q) acc[q] += __shfl_xor(acc[q], off, 64);
@@ -181,9 +196,11 @@ __device__ __forceinline__ void reduce_long_row(const Rows &rows, int64_t i, int
 // lanes past the row left out of the loads (wide fp16 rows 1.3 to 1.7 times slower).
 constexpr int kRunRows = 16;
 // LV > 0 (rows of at most eight vectors of LV elements): rows of kLongRow entries and more go to reduce_long_row,
-// the shorter ones are walked.  At 12 the two are level in large blocks (100 k rows of 10 entries, 16 fp32 columns:
-// 28 and 24 us; of 15 entries 28 and 32 to 35), and in blocks of a few thousand rows the groups are ahead from 5 or 6.
-constexpr uint32_t kLongRow = 12;
+// the shorter ones are walked.  fp32, 16 columns, walk and groups: 100 k rows of 10 entries 24 and 28 us, of 15 32 and 28;
+// in blocks of a few thousand rows the groups are ahead from 5 or 6 entries.  fp16, 32 columns, where a vector of 16 bytes
+// has more additions: 100 k rows of 15 entries 32 and 43 us, 30 k of 20 20.6 and 16.6.
+template <typename T>
+constexpr int kLongRow = sizeof(T) == 4 ? 12 : 16;
 
 struct FlatShape {
     int dim;
@@ -201,6 +218,7 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
     const int dim = sh.dim, log2_lpr = sh.log2_lpr;
     const uint32_t row_blocks = sh.row_blocks;
     const bool mostly_long = LV > 0 && sh.mostly_long;
+    constexpr int kLong = kLongRow<T>;
     using P = Pack<T, VEC>;
     constexpr int U = NV == 1 ? (sizeof(P) == 16 ? 8 : 16) : NV <= 3 ? 4 : 2;    // input rows in flight: 4 to 12 KB per wavefront
     // Partial sums that take the entries in turn.  The turn counts from the start of the run, so a row may begin
@@ -230,8 +248,9 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
             if (mostly_long) {
                 const int b = rows.begin(c0), e = rows.begin(c0 + 1);
                 const bool own = c0 < self_rows;
-                if (e - b + own >= static_cast<int>(kLongRow)) {
-                    reduce_long_row<T, LV>(rows, c0, b, e, own, x, x_stride, out, out_stride, dim, log2_lpr);
+                const float ws = Rows::kSelf && own ? rows.self_weight(c0) : 0.f;      // on its way with the two offsets
+                if (e - b >= kLong) {
+                    reduce_long_row<T, LV>(rows, c0, b, e, ws, x, x_stride, out, out_stride, dim, log2_lpr);
                     continue;
                 }
             }
@@ -243,8 +262,8 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
         const uint32_t off = static_cast<uint32_t>(rows.begin(c0 + t)) + static_cast<uint32_t>(t < diag ? t : diag);
         uint64_t longs = 0;                                // the run's long rows, if they go by themselves
         if constexpr (LV > 0) {
-            const uint32_t entries = __shfl_down(off, 1) - off;
-            longs = ballot64(lane < m && entries >= kLongRow);
+            const int entries = static_cast<int>(__shfl_down(off, 1) - off) - (lane < diag ? 1 : 0);
+            longs = ballot64(lane < m && entries >= kLong);
         }
         for (int cur = 0;;) {
             const int stop = LV > 0 && longs ? __ffsll(static_cast<long long>(longs)) - 1 : m;
@@ -357,7 +376,8 @@ k_segment_flat(Rows rows, const int64_t *__restrict__ n_rows, const T *__restric
             if (stop == m) break;
             const int b = static_cast<int>(readlane32(off, stop)) - (stop < diag ? stop : diag);
             const int e = static_cast<int>(readlane32(off, stop + 1)) - (stop + 1 < diag ? stop + 1 : diag);
-            if constexpr (LV > 0) reduce_long_row<T, LV>(rows, c0 + stop, b, e, stop < diag, x, x_stride, out, out_stride, dim, log2_lpr);
+            const float ws = Rows::kSelf && stop < diag ? rows.self_weight(c0 + stop) : 0.f;
+            if constexpr (LV > 0) reduce_long_row<T, LV>(rows, c0 + stop, b, e, ws, x, x_stride, out, out_stride, dim, log2_lpr);
             longs &= longs - 1;
             cur = stop + 1;
             if (cur == m) break;
@@ -450,7 +470,7 @@ int launch(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_ro
     // Narrow rows of few entries are handed out two to four at a time once the chip's 8,192 wavefronts have one
     // each (10 k rows of 5 entries, 16 fp32 columns: 5.1 -> 4.6 us, 30 k of 10: 13.2 -> 9.6; rows of 25: the other
     // way round).  Their expected length is what the block's capacities say, a sampled block's fanout.
-    const bool mostly_long = cap_nnz >= kLongRow * cap_rows;
+    const bool mostly_long = cap_nnz >= kLongRow<T> * cap_rows;
     FlatShape shape;
     shape.dim = dim;
     shape.row_blocks = static_cast<uint32_t>(row_blocks);

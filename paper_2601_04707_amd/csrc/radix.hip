@@ -358,9 +358,11 @@ k_radix_scatter(const uint32_t *__restrict__ keys_in, RadixPayload payload, int6
 
 // Digits: as few passes as the widest digit allows, then the digit just wide enough for them (8 bits
 // at least).  The widest digit is 11 bits for inputs of up to kRadixWideKeys keys, where a pass is
-// mostly its launches, and 9 bits above, where it is mostly its per-key work (the LDS counters to
-// clear and add up per round grow with the digit: the 4.5 M edges of a "stress" block sorted faster
-// in three 8-bit passes than in two of 11 bits).
+// mostly its launches, and 9 bits above, where it is mostly its scatter: a tile of 2,048 keys has about
+// one of each of 2,048 digits, so its runs are single words.  All launches of a sort, keys spread evenly:
+// 11 bits in one pass or in two of 8, 300 k keys 30 and 44 us, 1 M 40 and 50, 2 M 55 and 56, 4.3 M 104 and 79;
+// 20 bits in two passes of 10 or in three of 8, 300 k 49 and 67, 2 M 84 and 87, 4.3 M 136 and 118; 22 bits in two
+// of 11 or in three of 8, 300 k 59 and 67, 1 M 81 and 75, 2 M 112 and 87, 4.3 M 207 and 118.
 static int max_digit_bits(int64_t n_cap) { return n_cap <= kRadixWideKeys ? kRadixMaxDigitBits : 9; }
 int radix_passes(int bits, int64_t n_cap) { return bits <= 0 ? 0 : (bits + max_digit_bits(n_cap) - 1) / max_digit_bits(n_cap); }
 int radix_digit_bits(int bits, int64_t n_cap) {

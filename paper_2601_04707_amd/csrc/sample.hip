@@ -193,7 +193,7 @@ k_row_offsets(const int32_t *__restrict__ row_deg, int fanout, int64_t *sizes,
 }
 
 // ------------------------------------------------------------------------------------------
-// Neighbour selection.  One wavefront owns one destination node.
+// Neighbour selection.  A wavefront takes destinations one by one, a workgroup the hubs.
 
 struct SampleArgs {
     const int64_t *row_start;

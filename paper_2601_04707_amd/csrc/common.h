@@ -74,7 +74,8 @@ struct mqg_ctx {
     int64_t max_dst = 0, max_src = 0, max_nnz = 0;
 
     // scratch (device)
-    int32_t *local_of = nullptr;         // [num_nodes] position of a node in the current source list, -1 if absent
+    int32_t *local_of = nullptr;         // [num_nodes] position of a node in the current source list plus the call's offset; less if absent
+    int64_t pos_next = 0;                // offset of the next call's positions (take_positions)
     uint32_t *bitmap = nullptr;          // [bitmap_words] nodes first seen in the current layer
     int64_t bitmap_words = 0;            // padded to a multiple of kBitmapTileWords
     int32_t *tile_vals = nullptr;        // [max_tiles] per-tile sums of the rows, then their exclusive scan
@@ -189,6 +190,9 @@ int hash_put_seeds(mqg_ctx *ctx, const void *seeds, int idx_type, int64_t need_d
 int hash_dedup_block(mqg_ctx *ctx, const int32_t *nbr, int64_t need_nnz, int64_t num_nodes, int idx_type, void *src_ids,
                      int64_t *sizes, int64_t *sizes_next, int32_t *indices, hipStream_t s);
 int hash_clear(mqg_ctx *ctx, hipStream_t s);
+
+// A range of `count` offset positions for local_of; take_back: the call's last launch has to set its entries to -1.
+int take_positions(mqg_ctx *ctx, int64_t count, hipStream_t s, int32_t *base, bool *take_back);
 
 // Exclusive scan of vals[0..n) in place by one workgroup; the total (plus *addend if given) is
 // stored to *total_a and *total_b where non-null.

@@ -194,7 +194,7 @@ k_lw_tile_counts(const uint32_t *__restrict__ bitmap, int32_t *__restrict__ tile
 template <typename OutT, int WPT>
 __global__ void __launch_bounds__(kBlock)
 k_lw_emit(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_vals, int scanned, OutT *__restrict__ out,
-          int32_t *__restrict__ local_of, int64_t *count_a, int64_t *count_b) {
+          int32_t *__restrict__ local_of, int32_t pos_base, int64_t *count_a, int64_t *count_b) {
     __shared__ int lds[kWavesPerBlock];
     __shared__ int32_t staged[WPT == 1 ? kBlock * 32 : 1];   // every id of the tile, ascending
     const int tile_base = scanned ? tile_vals[blockIdx.x] : tiles_before(tile_vals, lds);
@@ -235,7 +235,7 @@ k_lw_emit(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_vals, 
         for (int k = threadIdx.x; k < total; k += kBlock) {
             const int32_t v = staged[k];
             out[tile_base + k] = static_cast<OutT>(v);
-            if (local_of) local_of[v] = tile_base + k;
+            if (local_of) local_of[v] = pos_base + tile_base + k;
         }
     } else {
         if (c == 0) return;
@@ -250,7 +250,7 @@ k_lw_emit(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_vals, 
                 bits &= bits - 1;
                 const int64_t v = (w0 + q) * 32 + b;
                 out[pos] = static_cast<OutT>(v);
-                if (local_of) local_of[v] = pos;
+                if (local_of) local_of[v] = pos_base + pos;
                 ++pos;
             }
         }
@@ -618,7 +618,7 @@ __device__ __forceinline__ double lw_raw_weight(const PtrT *__restrict__ row_ptr
 template <typename PtrT, typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_lw_count(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst,
-           const int64_t *__restrict__ sizes, const int32_t *__restrict__ local_of, const unsigned long long *__restrict__ mass,
+           const int64_t *__restrict__ sizes, const int32_t *__restrict__ local_of, int32_t pos_base, const unsigned long long *__restrict__ mass,
            const double *__restrict__ q_total, const double *__restrict__ beta, int flat, int32_t *__restrict__ counts,
            double *__restrict__ psum) {
     const int lane = lane_id();
@@ -635,9 +635,9 @@ k_lw_count(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ col_idx, c
         const double dv = static_cast<double>(d + 1);
         int cnt = 0;
         double acc = 0.0;
-        if (c == 0 && local_of[v] >= 0) {
+        if (c == 0 && local_of[v] >= pos_base) {
             cnt = 1;
-            if (lane == 0) acc = lw_raw_weight(row_ptr, mass, scale, dv, v, beta, local_of[v], flat);
+            if (lane == 0) acc = lw_raw_weight(row_ptr, mass, scale, dv, v, beta, local_of[v] - pos_base, flat);
         }
         int64_t jb, je;
         chunk_range(d, c, &jb, &je);
@@ -646,7 +646,7 @@ k_lw_count(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ col_idx, c
             bool in = false;
             if (j < je) {
                 const int64_t i = static_cast<int64_t>(col_idx[start + j]);
-                const int32_t li = local_of[i];
+                const int32_t li = local_of[i] - pos_base;
                 in = li >= 0;
                 if (in) acc += lw_raw_weight(row_ptr, mass, scale, dv, i, beta, li, flat);
             }
@@ -664,7 +664,7 @@ k_lw_count(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ col_idx, c
 template <typename PtrT, typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_lw_fill(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst,
-          int64_t *sizes, const int32_t *__restrict__ local_of, const unsigned long long *__restrict__ mass,
+          int64_t *sizes, const int32_t *__restrict__ local_of, int32_t pos_base, const unsigned long long *__restrict__ mass,
           const double *__restrict__ q_total, const double *__restrict__ beta, int flat, const int32_t *__restrict__ offs,
           const double *__restrict__ psum, int32_t *__restrict__ indptr, int32_t *__restrict__ indices,
           float *__restrict__ edge_w, int normalise, int64_t cap_nnz, const int32_t *__restrict__ seed_flags) {
@@ -697,7 +697,7 @@ k_lw_fill(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ col_idx, co
         }
         int64_t pos = offs[u];
         if (c == 0) {
-            const int32_t self_pos = local_of[v];
+            const int32_t self_pos = local_of[v] - pos_base;
             if (self_pos >= 0) {
                 if (lane == 0 && pos < cap_nnz) {
                     indices[pos] = self_pos;
@@ -714,7 +714,7 @@ k_lw_fill(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ col_idx, co
             int32_t li = -1;
             if (j < je) {
                 i = static_cast<int64_t>(col_idx[start + j]);
-                li = local_of[i];
+                li = local_of[i] - pos_base;
             }
             const uint64_t m = ballot64(li >= 0);
             if (li >= 0) {
@@ -848,7 +848,7 @@ template <typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_lw_reset(const int32_t *__restrict__ cand, const int64_t *__restrict__ n_cand, int64_t all_nodes,
            unsigned long long *__restrict__ mass, const IdxT *__restrict__ src_ids, const int64_t *__restrict__ sizes,
-           int32_t *__restrict__ local_of, int32_t *__restrict__ flags, int32_t *__restrict__ sel_hist, int hist_len) {
+           int32_t *__restrict__ local_of, int take_back, int32_t *__restrict__ flags, int32_t *__restrict__ sel_hist, int hist_len) {
     if (flags && blockIdx.x == 0 && threadIdx.x == 0) *flags = 0;     // the seed check's word, for the next call
     const int64_t ns = sizes[1];
     const int64_t stride = int64_t(gridDim.x) * kBlock;
@@ -859,6 +859,7 @@ k_lw_reset(const int32_t *__restrict__ cand, const int64_t *__restrict__ n_cand,
     } else {
         for (int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x; k < all_nodes; k += stride) mass[k] = 0;
     }
+    if (!take_back) return;                                // positions: see take_positions
     for (int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x; k < ns; k += stride) local_of[src_ids[k]] = -1;
 }
 
@@ -930,16 +931,16 @@ static int sample_layerwise_impl(mqg_ctx *ctx, const mqg_graph *g, const void *s
         else MQG_LAUNCH(ctx, "k_lw_tile_counts", s, (k_lw_tile_counts<4><<<tiles, kBlock, 0, s>>>(ctx->bitmap, w.word_offs)));
         return MQG_OK;
     };
-    auto emit_list = [&](auto *out, int32_t *local_of, int64_t *count_a, int64_t *count_b) -> int {
+    auto emit_list = [&](auto *out, int32_t *local_of, int32_t pos_base, int64_t *count_a, int64_t *count_b) -> int {
         using OutT = std::remove_pointer_t<decltype(out)>;
         if (tiles_scanned) {
             int rc = device_scan(ctx, w.word_offs, tiles, w.scan_tiles, s);
             if (rc != MQG_OK) return rc;
         }
         if (wpt == 1)
-            MQG_LAUNCH(ctx, "k_lw_emit", s, (k_lw_emit<OutT, 1><<<tiles, kBlock, 0, s>>>(ctx->bitmap, w.word_offs, tiles_scanned, out, local_of, count_a, count_b)));
+            MQG_LAUNCH(ctx, "k_lw_emit", s, (k_lw_emit<OutT, 1><<<tiles, kBlock, 0, s>>>(ctx->bitmap, w.word_offs, tiles_scanned, out, local_of, pos_base, count_a, count_b)));
         else
-            MQG_LAUNCH(ctx, "k_lw_emit", s, (k_lw_emit<OutT, 4><<<tiles, kBlock, 0, s>>>(ctx->bitmap, w.word_offs, tiles_scanned, out, local_of, count_a, count_b)));
+            MQG_LAUNCH(ctx, "k_lw_emit", s, (k_lw_emit<OutT, 4><<<tiles, kBlock, 0, s>>>(ctx->bitmap, w.word_offs, tiles_scanned, out, local_of, pos_base, count_a, count_b)));
         return MQG_OK;
     };
     const int cand_grid = static_cast<int>(std::max<int64_t>(1, ceil_div(n, kBlock)));
@@ -979,7 +980,10 @@ static int sample_layerwise_impl(mqg_ctx *ctx, const mqg_graph *g, const void *s
         const int64_t rows_cap = l == L - 1 ? num_seeds : std::min<int64_t>(n, layer_sizes[l + 1]);
         const uint64_t tag_hash = host_mix64(seed_hash ^ static_cast<uint64_t>(int64_t(kLayerwiseTag + l)));
 
-        int rc = MQG_OK;
+        int32_t pos_base = 0;
+        bool take_back = false;
+        int rc = take_positions(ctx, std::min<int64_t>(n, layer_sizes[l]), s, &pos_base, &take_back);
+        if (rc != MQG_OK) return rc;
         if (!fastgcn) {
             const int mass_grid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(rows_cap * kRowChunks, kWavesPerBlock)), 256 * 64));
             // list of candidates: marked slot by slot in the node bitmap, or, on graphs of up to
@@ -994,7 +998,7 @@ static int sample_layerwise_impl(mqg_ctx *ctx, const mqg_graph *g, const void *s
                     MQG_LAUNCH(ctx, "k_lw_mass_bits", s, (k_lw_mass_bits<<<tiles, kBlock, 0, s>>>(w.mass, n, ctx->bitmap, w.word_offs)));
                 else
                     rc = count_tiles();
-                if (rc == MQG_OK) rc = emit_list(w.cand, nullptr, n_cand, nullptr);
+                if (rc == MQG_OK) rc = emit_list(w.cand, nullptr, 0, n_cand, nullptr);
                 if (rc != MQG_OK) return rc;
             }
         }
@@ -1019,7 +1023,7 @@ static int sample_layerwise_impl(mqg_ctx *ctx, const mqg_graph *g, const void *s
                    (k_lw_finish<<<1, kBlock, 0, s>>>(cand, n_keys_dev, n, n_cand, layer_sizes[l], w.sel_state, w.bkey, w.bpos, bcount,
                                                      ctx->bitmap)));
         rc = count_tiles();
-        if (rc == MQG_OK) rc = emit_list(src_ids, ctx->local_of, &b.sizes[1], l > 0 ? &blocks[l - 1].sizes[0] : nullptr);
+        if (rc == MQG_OK) rc = emit_list(src_ids, ctx->local_of, pos_base, &b.sizes[1], l > 0 ? &blocks[l - 1].sizes[0] : nullptr);
         if (rc != MQG_OK) return rc;
         const double *beta = nullptr;
         if (debias) {
@@ -1038,7 +1042,7 @@ static int sample_layerwise_impl(mqg_ctx *ctx, const mqg_graph *g, const void *s
         // (entries of chunk_offs past the block's rows are not cleared: an exclusive scan's values up to
         // the last row's end, the only ones read, do not depend on them)
         MQG_LAUNCH(ctx, "k_lw_count", s,
-                   (k_lw_count<PtrT, IdxT><<<chunk_grid, kBlock, 0, s>>>(row_ptr, col_idx, dst, b.sizes, ctx->local_of, mass, w.q_total,
+                   (k_lw_count<PtrT, IdxT><<<chunk_grid, kBlock, 0, s>>>(row_ptr, col_idx, dst, b.sizes, ctx->local_of, pos_base, mass, w.q_total,
                                                                          beta, flat, w.chunk_offs, w.chunk_sum)));
         // one launch when the table is small (the scan goes to a second array), else in place
         const int32_t *offs = w.chunk_offs;
@@ -1050,12 +1054,12 @@ static int sample_layerwise_impl(mqg_ctx *ctx, const mqg_graph *g, const void *s
         }
         if (rc != MQG_OK) return rc;
         MQG_LAUNCH(ctx, "k_lw_fill", s,
-                   (k_lw_fill<PtrT, IdxT><<<chunk_grid, kBlock, 0, s>>>(row_ptr, col_idx, dst, b.sizes, ctx->local_of, mass, w.q_total,
+                   (k_lw_fill<PtrT, IdxT><<<chunk_grid, kBlock, 0, s>>>(row_ptr, col_idx, dst, b.sizes, ctx->local_of, pos_base, mass, w.q_total,
                                                                         beta, flat, offs, w.chunk_sum, b.indptr, b.indices, edge_w[l],
                                                                         normalise, b.cap_nnz, l == L - 1 ? w.flags : nullptr)));
         const int reset_grid = static_cast<int>(std::min<int64_t>(cand_grid, 4096));
         MQG_LAUNCH(ctx, "k_lw_reset", s,
-                   (k_lw_reset<IdxT><<<reset_grid, kBlock, 0, s>>>(cand, n_cand, dense ? n : 0, w.mass, src_ids, b.sizes, ctx->local_of,
+                   (k_lw_reset<IdxT><<<reset_grid, kBlock, 0, s>>>(cand, n_cand, dense ? n : 0, w.mass, src_ids, b.sizes, ctx->local_of, take_back ? 1 : 0,
                                                                    l == L - 1 ? w.flags : nullptr, w.sel_hist, kSelHistLen)));
     }
     return MQG_OK;

@@ -44,9 +44,10 @@ struct LayerwiseScratch {
     int64_t xcap = 0;
     unsigned long long *sel_state = nullptr;   // [18] radix select: prefix and wanted count per pass
     int32_t *sel_hist = nullptr;         // [passes][digits] counts of the radix select
-    int32_t *chunk_offs = nullptr;       // [rows_cap * 16 + 1] edges per (row, chunk), then their scan
-    int32_t *chunk_scan = nullptr;       // the scan of a small chunk_offs table (one-launch scan, out of place)
-    double *chunk_sum = nullptr;         // [rows_cap * 16] raw weight sums per (row, chunk)
+    int32_t *sure = nullptr;             // [2048] drawn nodes of a layer of few nodes, in no order, without the last bin's
+    int32_t *chunk_counts = nullptr;     // [rows_cap * 16] edges per (row, chunk)
+    double *chunk_sum = nullptr;         // [rows_cap * 16] sums of their factors
+    int32_t *row_count = nullptr;        // [rows_cap + 4] edges per row, or their scan
     int32_t *word_offs = nullptr;        // [bitmap_words + 1] set bits per tile of the bitmap
     int32_t *scan_tiles = nullptr;
     double *q_part = nullptr;            // per-workgroup partial sums of q
@@ -55,7 +56,8 @@ struct LayerwiseScratch {
     int64_t *seeds_copy = nullptr;       // [rows_cap] the checked seeds
     int32_t *flags = nullptr;
     uint64_t *dkey = nullptr;            // [rows_cap] race keys of the drawn nodes (debiased coefficients)
-    double *dq = nullptr, *beta = nullptr;
+    double *dq = nullptr;
+    double *factor = nullptr;            // [rows_cap] the drawn nodes' share of their edges' weights
     int32_t *order = nullptr;            // [rows_cap] source positions in draw order
     unsigned long long *fg_mass = nullptr;     // [num_nodes] masses over all rows of the graph (FastGCN)
     bool fg_ready = false;

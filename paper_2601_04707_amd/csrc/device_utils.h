@@ -184,21 +184,27 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
 // fractional bits (r = 0 counts as 1).  With m = r << lz in [2^63, 2^64) the integer part is
 // lz + 1; the fraction of log2(m / 2^63) comes bit by bit from repeated squaring (a square that
 // reaches 2 emits a one and is halved), squares truncated to 64 bits.  The step is written without
-// a data-dependent branch (the renormalising shift is 0 or 1) so that the loop compiles to straight
+// a data-dependent branch (selects) so that the loop compiles to straight
 // vector code: with a branch the compiler wraps the low product in an exec-mask save/restore, and
 // one build of a kernel around that form returned wrong tickets, different from run to run, in
 // every workgroup but the first of a compute unit.
+// The square of m = hi 2^32 + lo takes three multiplications: with t = hi lo + floor(lo^2 / 2^33) its upper word is
+// hi^2 + floor(t / 2^31), and bit 63 of its lower one is bit 30 of t.
 __device__ __forceinline__ uint64_t exp_ticket64(uint64_t r) {
     if (r == 0) r = 1;
     const int lz = __clzll(static_cast<long long>(r));
-    uint64_t m = r << lz, frac = 0;
-#pragma unroll 4
+    const uint64_t m = r << lz;
+    uint32_t hi = static_cast<uint32_t>(m >> 32), lo = static_cast<uint32_t>(m), frac = 0;
+#pragma unroll 8
     for (int b = 0; b < 32; ++b) {
-        const uint64_t hi = __umul64hi(m, m), lo = m * m;
-        const uint64_t one = hi >> 63;
-        frac = (frac << 1) | one;
-        const uint64_t sh = one ^ 1;                       // not yet at 2: renormalise by one bit
-        m = (hi << sh) | ((lo >> 63) & sh);
+        const uint64_t t = static_cast<uint64_t>(hi) * lo + (__umulhi(lo, lo) >> 1);
+        const uint64_t top = static_cast<uint64_t>(hi) * hi + (t >> 31);
+        const uint32_t th = static_cast<uint32_t>(top >> 32), tl = static_cast<uint32_t>(top);
+        const uint32_t below = static_cast<uint32_t>(t) >> 30 & 1u;
+        const bool one = static_cast<int32_t>(th) < 0;     // the square reached 2
+        frac = frac << 1 | (one ? 1u : 0u);
+        hi = one ? th : __builtin_amdgcn_alignbit(th, tl, 31);        // not yet at 2: renormalise by one bit
+        lo = one ? tl : tl << 1 | below;
     }
     return (static_cast<uint64_t>(lz + 1) << 32) - frac;
 }

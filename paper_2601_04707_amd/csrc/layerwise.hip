@@ -15,6 +15,12 @@
 //   k_lw_keys        exponential race: key = ticket * (deg_i + 1) / mass[i] in doubles (the "flat"
 //                    variants, Eq. 10, draw in proportion to sqrt(q_i): ticket^2 in place of ticket), ticket from
 //                    exp_ticket64; partial sums of q per workgroup, added up in a fixed order
+//   layers of up to kPickMost nodes:
+//   k_lw_list        the keys' leading bits, sixteen bins to the octave, are counted by k_lw_keys itself; this
+//                    launch finds the threshold's bin and lists the nodes of the bins before it and of the bin
+//   k_lw_pick        ranks the bin's nodes by (key, id) and all that are drawn by id: the block's sources,
+//                    their positions into local_of[], their columns' share of the weights
+//   larger layers:
 //   k_lw_select      radix select of the s-th smallest 64-bit key pattern, most significant digit
 //                    first: the leading 12 bits are counted by k_lw_keys itself, the next 13 by
 //                    this launch, whose workgroups derive the digit found so far from the
@@ -27,13 +33,12 @@
 //   bitmap -> list   the drawn nodes ascending = the block's sources, positions into local_of[]
 //   k_lw_count/fill  row v lists the drawn nodes among v and its adjacency row (self edge first,
 //                    then slot order) with weight P_vi / (s p_i), optionally divided by the row sum;
-//                    k_lw_fill also writes indptr and the block's sizes
+//                    k_lw_fill also writes indptr and the block's sizes, k_lw_count sets the masses and the
+//                    histogram back to zero
 // A row is shared by kRowChunks wavefronts, each with a contiguous range of adjacency slots, so
-// that a hub does not become a kernel's tail; counts and partial weight sums are kept per (row,
-// chunk) and one scan over all of them gives every wavefront its first edge position.
+// that a hub does not become a kernel's tail.
 //   k_lw_drawn_keys / k_lw_draw_order / k_lw_debias   (the "+debias" variants, Eq. 12) the drawn nodes in
 //                    the order of the race and their debiased coefficients, three scans in one workgroup
-//   k_lw_reset       masses and positions back to their idle values
 #include <algorithm>
 #include <type_traits>
 
@@ -66,14 +71,13 @@ __device__ __forceinline__ void set_bit(uint32_t *bitmap, uint32_t i) {
         (void)__hip_atomic_fetch_or(w, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// the caller's seeds, checked: an id outside the graph is replaced by node 0 and flagged; also clears
-// the histograms of the radix select
+// the caller's seeds, checked: an id outside the graph is replaced by node 0 and flagged (FastGCN; the other
+// methods do it in k_lw_mass)
 template <typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_lw_seeds(const IdxT *__restrict__ seeds, int64_t n, int64_t num_nodes, IdxT *__restrict__ dst, int64_t *sizes,
-           int32_t *__restrict__ flags, int32_t *__restrict__ sel_hist, int hist_len) {
+           int32_t *__restrict__ flags) {
     const int64_t t = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-    for (int64_t k = t; k < hist_len; k += int64_t(gridDim.x) * kBlock) sel_hist[k] = 0;    // for the first block's select
     if (t == 0) sizes[0] = n;
     if (t >= n) return;
     IdxT v = seeds[t];
@@ -84,29 +88,60 @@ k_lw_seeds(const IdxT *__restrict__ seeds, int64_t n, int64_t num_nodes, IdxT *_
     dst[t] = v;
 }
 
-constexpr int kRowChunks = 16;      // wavefronts that share one row
+// A row is shared by kRowChunks wavefronts, each with a contiguous range of adjacency slots: LEAST, or
+// more where the row is longer than all chunks of that size.
+constexpr int kRowChunks = 16;
+constexpr int kSlotUnroll = 4;      // groups of 64 slots whose loads are issued together
 
-// the contiguous range of adjacency slots of chunk c of a row of d slots (multiples of 64)
+template <int LEAST>
 __device__ __forceinline__ void chunk_range(int64_t d, int c, int64_t *begin, int64_t *end) {
-    const int64_t len = ((d + kRowChunks - 1) / kRowChunks + kWave - 1) / kWave * kWave;
+    int64_t len = ((d + kRowChunks - 1) / kRowChunks + kWave - 1) / kWave * kWave;
+    len = len < LEAST ? LEAST : len;
     *begin = len * c < d ? len * c : d;
     *end = len * (c + 1) < d ? len * (c + 1) : d;
 }
 
+// The ticket of node i (integer below 2^39, exact in a double).
+__device__ __forceinline__ double lw_ticket(uint64_t tag_hash, int64_t i) {
+    return static_cast<double>(exp_ticket64(mix64(mix64(tag_hash ^ static_cast<uint64_t>(i)))));
+}
+
+// The rows are the seeds (n_seeds >= 0: checked here and written to `checked`), a block's destinations, or, without
+// a list, every node of the graph.  Bound by the atomics (23 G/s); a hub's chunk of more than a thousand slots is a
+// chain of loads, four groups at a time.  The workgroups past `grid` make the tickets of all nodes, 32 squarings each, while the
+// atomics of the others are under way: they add nothing (first in the grid 2 us) and take 3.5 of k_lw_keys' 11.7 us away.
 template <typename PtrT, typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_lw_mass(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst,
-          const int64_t *__restrict__ sizes, unsigned long long *__restrict__ mass, uint32_t *__restrict__ bitmap,
-          int64_t *__restrict__ zero_me) {
+          int64_t *sizes, int64_t n_seeds, int64_t num_nodes, IdxT *__restrict__ checked, int32_t *__restrict__ flags,
+          unsigned long long *__restrict__ mass, uint32_t *__restrict__ bitmap, int64_t *__restrict__ zero_me, int grid,
+          uint64_t tag_hash, double *__restrict__ tickets) {
     const int lane = lane_id();
-    if (zero_me && blockIdx.x == 0 && threadIdx.x == 0) *zero_me = 0;     // the candidate count k_lw_keys adds up
-    const int64_t n = sizes[0] * kRowChunks;
-    const int64_t wave0 = int64_t(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
-    const int64_t nwaves = int64_t(gridDim.x) * kWavesPerBlock;
+    const int block = static_cast<int>(blockIdx.x);
+    if (block >= grid) {
+        const int64_t i = int64_t(block - grid) * kBlock + threadIdx.x;
+        if (i < num_nodes) tickets[i] = lw_ticket(tag_hash, i);
+        return;
+    }
+    if (block == 0 && threadIdx.x == 0) {
+        if (zero_me) *zero_me = 0;                         // the candidate count k_lw_keys adds up
+        if (n_seeds >= 0) sizes[0] = n_seeds;
+    }
+    const int64_t n = (n_seeds >= 0 ? n_seeds : sizes[0]) * kRowChunks;
+    const int64_t wave0 = int64_t(block) * kWavesPerBlock + (threadIdx.x >> 6);
+    const int64_t nwaves = int64_t(grid) * kWavesPerBlock;
     for (int64_t u = wave0; u < n; u += nwaves) {
         const int64_t t = u / kRowChunks;
         const int c = static_cast<int>(u % kRowChunks);
-        const int64_t v = dst ? static_cast<int64_t>(dst[t]) : t;      // no row list: every node of the graph
+        int64_t v = dst ? static_cast<int64_t>(dst[t]) : t;
+        if (n_seeds >= 0) {
+            const bool bad = v < 0 || v >= num_nodes;
+            if (bad) v = 0;
+            if (c == 0 && lane == 0) {
+                checked[t] = static_cast<IdxT>(v);
+                if (bad) atomicOr(flags, 1);
+            }
+        }
         const int64_t start = static_cast<int64_t>(row_ptr[v]);
         const int64_t d = static_cast<int64_t>(row_ptr[v + 1]) - start;
         const unsigned long long add = (1ull << 40) / static_cast<unsigned long long>(d + 1);
@@ -115,11 +150,20 @@ k_lw_mass(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ col_idx, co
             if (bitmap) set_bit(bitmap, static_cast<uint32_t>(v));
         }
         int64_t jb, je;
-        chunk_range(d, c, &jb, &je);
-        for (int64_t j = jb + lane; j < je; j += kWave) {
-            const uint32_t i = static_cast<uint32_t>(col_idx[start + j]);
-            atomicAdd(&mass[i], add);
-            if (bitmap) set_bit(bitmap, i);
+        chunk_range<kWave>(d, c, &jb, &je);
+        for (int64_t j0 = jb + lane; j0 < je; j0 += kSlotUnroll * kWave) {
+            uint32_t id[kSlotUnroll];
+#pragma unroll
+            for (int q = 0; q < kSlotUnroll; ++q) {
+                const int64_t j = j0 + q * kWave;
+                id[q] = static_cast<uint32_t>(col_idx[start + (j < je ? j : j0)]);
+            }
+#pragma unroll
+            for (int q = 0; q < kSlotUnroll; ++q) {
+                if (j0 + q * kWave >= je) continue;
+                atomicAdd(&mass[id[q]], add);
+                if (bitmap) set_bit(bitmap, id[q]);
+            }
         }
     }
 }
@@ -189,12 +233,30 @@ k_lw_tile_counts(const uint32_t *__restrict__ bitmap, int32_t *__restrict__ tile
     }
 }
 
+// What a drawn node's column contributes to the weights of its edges: Eq. 8 with p_i = q_i / q_total,
+// q_i = mass_i / di, gives P_vi / (s p_i) = (q_total / s) / sqrt(dv) * f_i with f_i = di / (mass_i sqrt(di)); flat
+// (p_i = sqrt(q_i) / total): f_i = 1 / (sqrt(q_i) sqrt(di)).  With debiased coefficients (paper Eq. 12) the weight is
+// beta_i / sqrt(dv di): 1 / sqrt(di) here, and k_lw_debias multiplies by beta_i.
+struct LwColumns {
+    const void *row_ptr;                 // of PtrT
+    const unsigned long long *mass;
+    int flat, debias;
+    double *factor;                      // [sources]; null: a list of candidates, no factors
+    template <typename PtrT>
+    __device__ __forceinline__ double value(int64_t i) const {
+        const PtrT *rp = static_cast<const PtrT *>(row_ptr);
+        const double di = static_cast<double>(static_cast<int64_t>(rp[i + 1]) - static_cast<int64_t>(rp[i]) + 1);
+        const double m = static_cast<double>(mass[i]);
+        return debias ? 1.0 / sqrt(di) : flat ? 1.0 / (sqrt(m / di) * sqrt(di)) : di / (m * sqrt(di));
+    }
+};
+
 // ids of the set bits, ascending, into out[0..total); the words are cleared; total to count_a/b.
 // scanned: tile_vals holds the exclusive scan of the tile counts, otherwise the counts themselves.
-template <typename OutT, int WPT>
+template <typename PtrT, typename OutT, int WPT>
 __global__ void __launch_bounds__(kBlock)
 k_lw_emit(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_vals, int scanned, OutT *__restrict__ out,
-          int32_t *__restrict__ local_of, int32_t pos_base, int64_t *count_a, int64_t *count_b) {
+          int32_t *__restrict__ local_of, int32_t pos_base, LwColumns columns, int64_t *count_a, int64_t *count_b) {
     __shared__ int lds[kWavesPerBlock];
     __shared__ int32_t staged[WPT == 1 ? kBlock * 32 : 1];   // every id of the tile, ascending
     const int tile_base = scanned ? tile_vals[blockIdx.x] : tiles_before(tile_vals, lds);
@@ -236,6 +298,7 @@ k_lw_emit(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_vals, 
             const int32_t v = staged[k];
             out[tile_base + k] = static_cast<OutT>(v);
             if (local_of) local_of[v] = pos_base + tile_base + k;
+            if (columns.factor) columns.factor[tile_base + k] = columns.value<PtrT>(v);
         }
     } else {
         if (c == 0) return;
@@ -251,6 +314,7 @@ k_lw_emit(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_vals, 
                 const int64_t v = (w0 + q) * 32 + b;
                 out[pos] = static_cast<OutT>(v);
                 if (local_of) local_of[v] = pos_base + pos;
+                if (columns.factor) columns.factor[pos] = columns.value<PtrT>(v);
                 ++pos;
             }
         }
@@ -277,20 +341,37 @@ constexpr int kSelBins = 8192;
 constexpr int kSelHistLen = kSelPasses * kSelBins;
 __host__ __device__ constexpr int sel_shift(int pass) { return 52 - 13 * pass; }
 
+// Layers of up to kPickMost nodes take k_lw_list and k_lw_pick, two launches (6.6 and 6.4 us for 512 of 233 k nodes) in place of
+// five (select 7.1, mark 6.8, finish 3.9, tile counts 2.7, list 3.4).  k_lw_pick compares every id with every other: whole calls
+// with two layers of 2,048 nodes 0.90 to 0.98 of the time of the other way, of 4,096 1.0 to 1.16.  Bins of a sixteenth of an octave, so that the threshold's bin holds at most
+// about a sixteenth of the nodes drawn.  The bin ascends with the key whatever the key; the race keys lie in
+// 2^-62 .. 2^98, well inside.
+constexpr int kPickMost = 2048;
+constexpr int kFineBins = 4096;
+__device__ __forceinline__ int fine_bin(uint64_t key) {
+    const int b = static_cast<int>(key >> 48) - ((1023 - 128) << 4);
+    return b < 0 ? 0 : b < kFineBins ? b : kFineBins - 1;
+}
+
 // Race keys of the candidates and the per-workgroup partial sums of q (a fixed launch shape, so the
-// sums are the same from run to run); the keys' leading 12 bits are counted into hist[0..4096) - the
-// first pass of the radix select.  Candidates: cand[0..n) if given, otherwise the nodes 0..n-1
+// sums are the same from run to run); the keys are counted into hist[0..4096): by fine_bin (fine), or by
+// their leading 12 bits, the first pass of the radix select.  have_tickets: key64[i] holds node i's ticket.  (A wavefront per SIMD, 256 workgroups of 256, left
+// the 32 squarings of a ticket a bare chain.  233 k nodes 11.7 us, 8.1 with the tickets at hand; what is left is the chain of loads,
+// the LDS counts and their way into hist.)  Candidates: cand[0..n) if given, otherwise the nodes 0..n-1
 // themselves, of which those with no mass are none (key = all ones, not counted); their number is
 // added to *count_out then.  n = *n_dev if given, else n_fixed.  hist must be clear.
 constexpr uint64_t kNoKey = ~uint64_t(0);
+constexpr int kKeyThreads = 1024;          // at most; `threads` of them: as many wavefronts per SIMD as the nodes give all compute units
 template <typename PtrT>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kKeyThreads)
 k_lw_keys(const PtrT *__restrict__ row_ptr, const int32_t *__restrict__ cand, const int64_t *__restrict__ n_dev, int64_t n_fixed,
           const unsigned long long *__restrict__ mass, uint64_t tag_hash, int flat, uint64_t *__restrict__ key64,
           double *__restrict__ q_part, int32_t *__restrict__ hist, int64_t *__restrict__ count_out,
-          unsigned long long *__restrict__ state, int64_t layer_size, unsigned long long *__restrict__ bcount) {
-    __shared__ double lds[kWavesPerBlock];
-    __shared__ int cnt_lds[kWavesPerBlock];
+          unsigned long long *__restrict__ state, int64_t layer_size, unsigned long long *__restrict__ bcount, int fine, int grid, int threads, int have_tickets,
+          int32_t *__restrict__ row_count, int64_t row_counts) {
+    constexpr int kWaves = kKeyThreads / kWave;
+    __shared__ double lds[kWaves];
+    __shared__ int cnt_lds[kWaves];
     __shared__ int h[4096];
     if (blockIdx.x == 0 && threadIdx.x == 0) {             // the select's state before its first pass
         state[0] = 0;
@@ -298,13 +379,13 @@ k_lw_keys(const PtrT *__restrict__ row_ptr, const int32_t *__restrict__ cand, co
         *bcount = 0;                                       // the boundary list is empty
     }
     const int64_t n = n_dev ? *n_dev : n_fixed;
-    const int64_t stride = int64_t(gridDim.x) * kBlock;
-#pragma unroll
-    for (int q = 0; q < 4096 / kBlock; ++q) h[q * kBlock + threadIdx.x] = 0;
+    const int64_t stride = int64_t(grid) * threads;
+    for (int64_t k = int64_t(blockIdx.x) * threads + threadIdx.x; k < row_counts; k += stride) row_count[k] = 0;      // for k_lw_count
+    for (int d = threadIdx.x; d < 4096; d += threads) h[d] = 0;
     __syncthreads();
     double q = 0.0;
     int cnt = 0;
-    for (int64_t c = int64_t(blockIdx.x) * kBlock + threadIdx.x; c < n; c += stride) {
+    for (int64_t c = int64_t(blockIdx.x) * threads + threadIdx.x; c < n; c += stride) {
         const int64_t i = cand ? cand[c] : c;
         const unsigned long long mi = mass[i];
         if (mi == 0) {
@@ -313,10 +394,10 @@ k_lw_keys(const PtrT *__restrict__ row_ptr, const int32_t *__restrict__ cand, co
         }
         const double deg1 = static_cast<double>(static_cast<int64_t>(row_ptr[i + 1]) - static_cast<int64_t>(row_ptr[i]) + 1);
         const double m = static_cast<double>(mi);
-        const double ticket = static_cast<double>(exp_ticket64(mix64(mix64(tag_hash ^ static_cast<uint64_t>(i)))));
+        const double ticket = have_tickets ? __longlong_as_double(static_cast<long long>(key64[c])) : lw_ticket(tag_hash, i);
         const uint64_t key = static_cast<uint64_t>(__double_as_longlong(lw_race_key(ticket, deg1, m, flat)));
         key64[c] = key;
-        atomicAdd(&h[key >> 52], 1);
+        atomicAdd(&h[fine ? fine_bin(key) : static_cast<int>(key >> 52)], 1);
         q += lw_measure(m, deg1, flat);
         ++cnt;
     }
@@ -329,15 +410,17 @@ k_lw_keys(const PtrT *__restrict__ row_ptr, const int32_t *__restrict__ cand, co
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        q_part[blockIdx.x] = ((lds[0] + lds[1]) + lds[2]) + lds[3];
-        const int total = cnt_lds[0] + cnt_lds[1] + cnt_lds[2] + cnt_lds[3];
+        double sum = 0.0;
+        int total = 0;
+        for (int w = 0; w < threads / kWave; ++w) {
+            sum += lds[w];
+            total += cnt_lds[w];
+        }
+        q_part[blockIdx.x] = sum;
         if (count_out && total) atomicAdd(reinterpret_cast<unsigned long long *>(count_out), static_cast<unsigned long long>(total));
     }
-#pragma unroll
-    for (int q4 = 0; q4 < 4096 / kBlock; ++q4) {
-        const int d = q4 * kBlock + threadIdx.x;
+    for (int d = threadIdx.x; d < 4096; d += threads)
         if (h[d]) atomicAdd(&hist[d], h[d]);
-    }
 }
 
 // q_total = sum of the partial sums, in a fixed order (one workgroup; `lds` needs kBlock doubles)
@@ -496,11 +579,54 @@ k_lw_mark(const int32_t *__restrict__ cand, const uint64_t *__restrict__ key64, 
     }
 }
 
+// Of the m (key, position) pairs of a list in memory, whose keys equal kp from bit `known` on (known = 64:
+// nothing is known), the last of the `want` first ones in (key, position) order: 1 <= want <= m.  A radix select,
+// eight bits at a time, over the key bits and, among the keys equal to the threshold, over the 32 position
+// bits.  Every thread of the workgroup (256) calls it; h: 256 ints, lds: kWavesPerBlock, pick: 2.
+__device__ __forceinline__ void lw_select_pairs(const uint64_t *__restrict__ bkey, const int32_t *__restrict__ bpos, int64_t m, long long want,
+                                                uint64_t &kp, int known, uint32_t &pp, int *h, int *lds, long long *pick) {
+    const int tid = threadIdx.x;
+    int pknown = 32;
+    pp = 0;
+    while (known > 0 || pknown > 0) {
+        const bool on_key = known > 0;
+        const int shift = on_key ? ((known - 1) & ~7) : pknown - 8;
+        h[tid] = 0;
+        __syncthreads();
+        for (int64_t e = tid; e < m; e += kBlock) {
+            const uint64_t k = bkey[e];
+            if (on_key) {
+                if (known == 64 || (k >> known) == (kp >> known)) atomicAdd(&h[(k >> shift) & ((1 << (known - shift)) - 1)], 1);
+            } else if (k == kp) {
+                const uint32_t ps = static_cast<uint32_t>(bpos[e]);
+                if (pknown == 32 || (ps >> pknown) == (pp >> pknown)) atomicAdd(&h[(ps >> shift) & 255], 1);
+            }
+        }
+        __syncthreads();
+        const int c = h[tid];
+        int total;
+        const int before = block_excl_scan<kWavesPerBlock>(c, &total, lds);
+        if (before < want && want <= static_cast<long long>(before) + c) {      // exactly one digit
+            pick[0] = tid;
+            pick[1] = want - before;
+        }
+        __syncthreads();
+        const uint64_t digit = static_cast<uint64_t>(pick[0]);
+        want = pick[1];
+        if (on_key) {
+            kp |= digit << shift;
+            known = shift;
+        } else {
+            pp |= static_cast<uint32_t>(digit) << shift;
+            pknown = shift;
+        }
+        __syncthreads();                                   // pick[] and h[] are rewritten by the next pass
+    }
+}
+
 // The boundary list: m keys that share the 25 known leading bits, of which the state[5] smallest in
 // (key, position) order are drawn (positions ascend with the ids).  One workgroup.  Up to
-// kBoundaryRanked entries: every entry counts the entries ahead of it.  More (many equal keys):
-// a radix select over the remaining 39 key bits and, among the keys equal to the threshold, over the
-// 32 position bits, eight bits at a time.
+// kBoundaryRanked entries: every entry counts the entries ahead of it.  More (many equal keys): lw_select_pairs.
 constexpr int kBoundaryRanked = 1024;
 __global__ void __launch_bounds__(kBlock)
 k_lw_finish(const int32_t *__restrict__ cand, const int64_t *__restrict__ n_dev, int64_t n_fixed,
@@ -516,7 +642,7 @@ k_lw_finish(const int32_t *__restrict__ cand, const int64_t *__restrict__ n_dev,
     const int64_t n = n_dev ? *n_dev : n_fixed;
     if ((n_cand ? *n_cand : n) <= layer_size) return;      // every candidate was drawn by k_lw_mark
     const int64_t m = static_cast<int64_t>(*bcount);
-    long long want = static_cast<long long>(state[5]);
+    const long long want = static_cast<long long>(state[5]);
     if (m <= kBoundaryRanked) {
         for (int e = tid; e < m; e += kBlock) {
             lk[e] = bkey[e];
@@ -547,45 +673,9 @@ k_lw_finish(const int32_t *__restrict__ cand, const int64_t *__restrict__ n_dev,
         }
         return;
     }
-    // radix select: first the key (bits 38..0: seven bits, then four times eight), then the position
-    uint64_t kp = state[4] << kSelKnownShift;              // the threshold key as far as known
-    int known = kSelKnownShift;                            // its bits from here up are known
-    uint32_t pp = 0;                                       // the threshold position as far as known
-    int pknown = 32;
-    for (int pass = 0; pass < 9; ++pass) {
-        const bool on_key = pass < 5;
-        const int shift = on_key ? 32 - 8 * pass : 24 - 8 * (pass - 5);
-        h[tid] = 0;
-        __syncthreads();
-        for (int64_t e = tid; e < m; e += kBlock) {
-            const uint64_t k = bkey[e];
-            if (on_key) {
-                if ((k >> known) == (kp >> known)) atomicAdd(&h[(k >> shift) & 255], 1);
-            } else if (k == kp) {
-                const uint32_t ps = static_cast<uint32_t>(bpos[e]);
-                if (pknown == 32 || (ps >> pknown) == (pp >> pknown)) atomicAdd(&h[(ps >> shift) & 255], 1);
-            }
-        }
-        __syncthreads();
-        const int c = h[tid];
-        int total;
-        const int before = block_excl_scan<kWavesPerBlock>(c, &total, lds);
-        if (before < want && want <= static_cast<long long>(before) + c) {      // exactly one digit
-            pick[0] = tid;
-            pick[1] = want - before;
-        }
-        __syncthreads();
-        const uint64_t digit = static_cast<uint64_t>(pick[0]);
-        want = pick[1];
-        if (on_key) {
-            kp |= digit << shift;
-            known = shift;
-        } else {
-            pp |= static_cast<uint32_t>(digit) << shift;
-            pknown = shift;
-        }
-        __syncthreads();                                   // pick[] and h[] are rewritten by the next pass
-    }
+    uint64_t kp = state[4] << kSelKnownShift;
+    uint32_t pp;
+    lw_select_pairs(bkey, bpos, m, want, kp, kSelKnownShift, pp, h, lds, pick);
     // kp, pp: the last drawn entry
     for (int64_t e = tid; e < m; e += kBlock) {
         const uint64_t k = bkey[e];
@@ -600,131 +690,402 @@ k_lw_zero_i32(int32_t *__restrict__ p, int64_t n) {
     if (i < n) p[i] = 0;
 }
 
-// Eq. 8 with p_i = q_i / q_total, q_i = mass_i / di: P_vi / (s p_i) = (q_total / s) * di / (mass_i sqrt(dv di))
-// With debiased coefficients (paper Eq. 12) the column of the drawn node at source position li is scaled
-// by beta[li] instead: P_vi * beta.
-template <typename PtrT>
-__device__ __forceinline__ double lw_raw_weight(const PtrT *__restrict__ row_ptr, const unsigned long long *__restrict__ mass,
-                                                double scale, double dv, int64_t i, const double *__restrict__ beta, int32_t li,
-                                                int flat) {
-    const double di = static_cast<double>(static_cast<int64_t>(row_ptr[i + 1]) - static_cast<int64_t>(row_ptr[i]) + 1);
-    if (beta) return beta[li] / sqrt(dv * di);
-    if (flat) return scale / (sqrt(static_cast<double>(mass[i]) / di) * sqrt(dv * di));   // p_i = sqrt(q_i) / total
-    return scale * di / (static_cast<double>(mass[i]) * sqrt(dv * di));
+// Layers of up to kPickMost nodes.  hist holds the candidates' keys by fine_bin.  Every workgroup finds the threshold's
+// bin (the first at which the running count reaches layer_size; past all bins if there are no more candidates
+// than that) and classifies tiles of 1,024 keys: nodes of the bins before it are drawn and listed in `sure`,
+// nodes of the bin go to the boundary list (key, id), of which *want are drawn.  One atomic per tile that
+// has any: count = listed as sure | listed as boundary << 32 (zero before).  Workgroup 0 also adds up the partial
+// sums of q and stores the number of candidates.
+constexpr int kListItems = 4;
+__global__ void __launch_bounds__(kBlock)
+k_lw_list(const int32_t *__restrict__ cand, const uint64_t *__restrict__ key64, const int64_t *__restrict__ n_dev, int64_t n_fixed, int layer_size,
+          const int32_t *__restrict__ hist, const double *__restrict__ q_part, int parts, double *__restrict__ q_total,
+          int64_t *__restrict__ n_cand, int32_t *__restrict__ sure, uint64_t *__restrict__ bkey, int32_t *__restrict__ bpos,
+          unsigned long long *__restrict__ count, unsigned long long *__restrict__ want, int grid) {
+    __shared__ double qlds[kBlock];
+    __shared__ int lds[kWavesPerBlock];
+    __shared__ int totals[2][kWavesPerBlock];
+    __shared__ unsigned long long base;
+    __shared__ int threshold[2];
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    if (blockIdx.x == 0) lw_sum_parts(q_part, parts, q_total, qlds);
+    const int64_t n = n_dev ? *n_dev : n_fixed;
+    constexpr int kTile = kBlock * kListItems;
+    uint64_t key[kListItems];                              // of the first tile, on their way already
+    auto load = [&](int64_t t0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < kListItems; ++q) {
+            const int64_t c = t0 + q * kBlock + tid;
+            key[q] = c < n ? key64[c] : kNoKey;
+        }
+    };
+    load(int64_t(blockIdx.x) * kTile);
+    {
+        constexpr int kPer = kFineBins / kBlock;           // consecutive bins per thread
+        const int4 *hp = reinterpret_cast<const int4 *>(hist + tid * kPer);
+        int v[kPer], c = 0, all;
+#pragma unroll
+        for (int q = 0; q < kPer / 4; ++q) {
+            const int4 x = hp[q];
+            v[4 * q] = x.x;
+            v[4 * q + 1] = x.y;
+            v[4 * q + 2] = x.z;
+            v[4 * q + 3] = x.w;
+            c += x.x + x.y + x.z + x.w;
+        }
+        int run = block_excl_scan<kWavesPerBlock>(c, &all, lds);
+        if (all <= layer_size) {
+            if (tid == 0) {
+                threshold[0] = kFineBins;
+                threshold[1] = 0;
+            }
+        } else if (run < layer_size && layer_size <= run + c) {      // exactly one thread, and one of its bins
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) {
+                if (run < layer_size && layer_size <= run + v[q]) {
+                    threshold[0] = tid * kPer + q;
+                    threshold[1] = layer_size - run;
+                }
+                run += v[q];
+            }
+        }
+        __syncthreads();
+        if (blockIdx.x == 0 && tid == 0) {
+            *n_cand = all;
+            *want = static_cast<unsigned long long>(threshold[1]);
+        }
+    }
+    const int bin = threshold[0];
+    for (int64_t t0 = int64_t(blockIdx.x) * kTile; t0 < n; t0 += int64_t(grid) * kTile) {
+        uint64_t sm[kListItems], bm[kListItems];
+        int ns = 0, nb = 0;
+#pragma unroll
+        for (int q = 0; q < kListItems; ++q) {
+            const int b = fine_bin(key[q]);
+            sm[q] = ballot64(key[q] != kNoKey && b < bin);
+            bm[q] = ballot64(key[q] != kNoKey && b == bin);
+            ns += popc64(sm[q]);
+            nb += popc64(bm[q]);
+        }
+        if (lane == 0) {
+            totals[0][wave] = ns;
+            totals[1][wave] = nb;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            unsigned long long all = 0;
+#pragma unroll
+            for (int w = 0; w < kWavesPerBlock; ++w)
+                all += static_cast<unsigned long long>(totals[0][w]) | static_cast<unsigned long long>(totals[1][w]) << 32;
+            if (all) base = atomicAdd(count, all);
+        }
+        __syncthreads();
+        uint32_t ps = static_cast<uint32_t>(base), pb = static_cast<uint32_t>(base >> 32);
+        for (int w = 0; w < wave; ++w) {
+            ps += totals[0][w];
+            pb += totals[1][w];
+        }
+#pragma unroll
+        for (int q = 0; q < kListItems; ++q) {
+            const int64_t c = t0 + q * kBlock + tid;
+            if ((sm[q] >> lane) & 1) sure[ps + popc64(sm[q] & lanes_below(lane))] = cand ? cand[c] : static_cast<int32_t>(c);
+            if ((bm[q] >> lane) & 1) {
+                const uint32_t o = pb + popc64(bm[q] & lanes_below(lane));
+                bkey[o] = key[q];
+                bpos[o] = cand ? cand[c] : static_cast<int32_t>(c);
+            }
+            ps += popc64(sm[q]);
+            pb += popc64(bm[q]);
+        }
+        load(t0 + int64_t(grid) * kTile);
+        __syncthreads();                                   // totals[] and base are rewritten by the next tile
+    }
 }
 
-// per (row, chunk): the number of drawn nodes in the chunk's slots (chunk 0 also counts the self
-// edge) and the sum of their raw weights
+// The drawn nodes, ascending, are the block's sources.  Every workgroup ranks the boundary list by (key, id) for
+// itself, which completes the list of drawn ids in LDS; then four threads count the ids below each.
+constexpr int kPickThreads = 4;
+template <typename PtrT, typename IdxT>
+__global__ void __launch_bounds__(kBlock)
+k_lw_pick(const int32_t *__restrict__ sure, const uint64_t *__restrict__ bkey, const int32_t *__restrict__ bpos,
+          const unsigned long long *__restrict__ count, const unsigned long long *__restrict__ want_dev, int layer_size, int64_t list_cap,
+          IdxT *__restrict__ src_ids, int32_t *__restrict__ local_of, int32_t pos_base, LwColumns columns, int64_t *count_a, int64_t *count_b) {
+    __shared__ __align__(16) int32_t ids[kPickMost + 8];
+    __shared__ __align__(16) uint64_t lk[kBoundaryRanked + 4];
+    __shared__ __align__(16) int32_t lp[kBoundaryRanked + 4];
+    __shared__ int h[256];
+    __shared__ int lds[kWavesPerBlock];
+    __shared__ long long pick[2];
+    const int tid = threadIdx.x;
+    // the lists' first entries are loaded whether they are filled or not, together with the counts
+    for (int e = tid; e < layer_size; e += kBlock) ids[e] = sure[e];
+    lk[tid] = tid < list_cap ? bkey[tid] : 0;
+    lp[tid] = tid < list_cap ? bpos[tid] : 0;
+    const unsigned long long cnt = *count;
+    const int ns = static_cast<int>(cnt & 0xFFFFFFFFu), want = static_cast<int>(*want_dev);
+    const int64_t m = static_cast<int64_t>(cnt >> 32);
+    const int total = ns + want;                           // at most the layer's size, and that at most kPickMost
+    __syncthreads();
+    if (want > 0 && m <= kBoundaryRanked) {
+        for (int e = kBlock + tid; e < m; e += kBlock) {
+            lk[e] = bkey[e];
+            lp[e] = bpos[e];
+        }
+        if (tid < 4) {                                     // ahead of none
+            lk[m + tid] = ~uint64_t(0);
+            lp[m + tid] = 0x7FFFFFFF;
+        }
+        __syncthreads();
+        for (int e = tid; e < m; e += kBlock) {
+            const uint64_t k = lk[e];
+            const int32_t p = lp[e];
+            int rank = 0;
+#pragma unroll 2
+            for (int j = 0; j < m; j += 4) {
+                const ulonglong2 a = *reinterpret_cast<const ulonglong2 *>(lk + j), b = *reinterpret_cast<const ulonglong2 *>(lk + j + 2);
+                const int4 o = *reinterpret_cast<const int4 *>(lp + j);
+                rank += (a.x < k || (a.x == k && o.x < p)) + (a.y < k || (a.y == k && o.y < p)) + (b.x < k || (b.x == k && o.z < p)) +
+                        (b.y < k || (b.y == k && o.w < p));
+            }
+            if (rank < want) ids[ns + rank] = p;
+        }
+    } else if (want > 0) {                                 // many keys of nearly the same size
+        uint64_t kp = 0;
+        uint32_t pp;
+        lw_select_pairs(bkey, bpos, m, want, kp, 64, pp, h, lds, pick);
+        int at = ns;                                       // in the list's order, which is the same for all workgroups
+        for (int64_t e0 = 0; e0 < m; e0 += kBlock) {
+            const int64_t e = e0 + tid;
+            const uint64_t k = e < m ? bkey[e] : 0;
+            const int32_t p = e < m ? bpos[e] : 0;
+            const bool in = e < m && (k < kp || (k == kp && static_cast<uint32_t>(p) <= pp));
+            int found;
+            const int o = block_excl_scan<kWavesPerBlock>(in ? 1 : 0, &found, lds);
+            if (in) ids[at + o] = p;
+            at += found;
+        }
+    }
+    if (tid < 4) ids[total + tid] = 0x7FFFFFFF;
+    if (blockIdx.x == 0 && tid == 0) {
+        if (count_a) *count_a = total;
+        if (count_b) *count_b = total;
+    }
+    __syncthreads();
+    const int e = (static_cast<int>(blockIdx.x) * kBlock + tid) / kPickThreads;
+    const int part = tid % kPickThreads;
+    if (e >= total) return;
+    const int32_t id = ids[e];
+    const double f = columns.value<PtrT>(id);              // its loads ahead of the counting
+    int pos = 0;
+#pragma unroll 8
+    for (int j = 4 * part; j < total; j += 4 * kPickThreads) {
+        const int4 o = *reinterpret_cast<const int4 *>(ids + j);
+        pos += (o.x < id) + (o.y < id) + (o.z < id) + (o.w < id);
+    }
+    pos += __shfl_xor(pos, 1, 64);
+    pos += __shfl_xor(pos, 2, 64);
+    if (part == 0) {
+        src_ids[pos] = static_cast<IdxT>(id);
+        local_of[id] = pos_base + pos;
+        columns.factor[pos] = f;
+    }
+}
+
+// Rows up to which k_lw_fill adds up the edges of the rows before its own; more are scanned in launches of their own.
+constexpr int64_t kSelfOffsetRows = 2048;
+
+// A wavefront per (row, chunk): the number of drawn nodes in the chunk's slots (chunk 0 also counts the self edge) and the
+// sum of their columns' factors; the rows' edges (row_count is zero before).  `cleared` workgroups more set
+// the masses of the candidates (of all nodes without a list of them) and the histogram back to zero; the
+// block's flags word.  Bound by the lookups behind its caches: the two layers of a batch of 1,024 seeds on a graph of 233 k
+// nodes and mean degree 490 15.8 + 12.9 us, then 5.8 + 4.2
+// for a scan of the counts -> 13.6 + 9.1 (a workgroup per row 20 + 15: a hub's lookups take a 128-byte line each, and a compute
+// unit fetches 64 bytes per cycle).
 template <typename PtrT, typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_lw_count(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst,
-           const int64_t *__restrict__ sizes, const int32_t *__restrict__ local_of, int32_t pos_base, const unsigned long long *__restrict__ mass,
-           const double *__restrict__ q_total, const double *__restrict__ beta, int flat, int32_t *__restrict__ counts,
-           double *__restrict__ psum) {
+           int64_t *sizes, const int32_t *__restrict__ local_of, int32_t pos_base, const double *__restrict__ factor,
+           int32_t *__restrict__ counts, double *__restrict__ psum, int32_t *__restrict__ row_count, int row_blocks, int cleared,
+           const int32_t *__restrict__ cand, const int64_t *__restrict__ n_cand, int64_t all_nodes, unsigned long long *__restrict__ mass,
+           int32_t *__restrict__ sel_hist, int hist_len, int32_t *__restrict__ seed_flags) {
     const int lane = lane_id();
-    const int64_t n = sizes[0] * kRowChunks;
-    const double scale = *q_total / static_cast<double>(sizes[1]);
+    if (static_cast<int>(blockIdx.x) >= row_blocks) {
+        const int64_t first = int64_t(static_cast<int>(blockIdx.x) - row_blocks) * kBlock + threadIdx.x;
+        const int64_t stride = int64_t(cleared) * kBlock;
+        for (int64_t k = first; k < hist_len; k += stride) sel_hist[k] = 0;
+        if (cand) {
+            const int64_t nc = *n_cand;
+            for (int64_t k = first; k < nc; k += stride) mass[cand[k]] = 0;
+        } else {
+            for (int64_t k = first; k < all_nodes; k += stride) mass[k] = 0;
+        }
+        return;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        sizes[3] = seed_flags ? *seed_flags : 0;
+        if (seed_flags) *seed_flags = 0;                   // for the next call
+    }
+    const int64_t rows = sizes[0];
     const int64_t wave0 = int64_t(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
-    const int64_t nwaves = int64_t(gridDim.x) * kWavesPerBlock;
-    for (int64_t u = wave0; u < n; u += nwaves) {
+    const int64_t nwaves = int64_t(row_blocks) * kWavesPerBlock;
+    for (int64_t u = wave0; u < rows * kRowChunks; u += nwaves) {
         const int64_t t = u / kRowChunks;
         const int c = static_cast<int>(u % kRowChunks);
         const int64_t v = static_cast<int64_t>(dst[t]);
         const int64_t start = static_cast<int64_t>(row_ptr[v]);
         const int64_t d = static_cast<int64_t>(row_ptr[v + 1]) - start;
-        const double dv = static_cast<double>(d + 1);
         int cnt = 0;
         double acc = 0.0;
-        if (c == 0 && local_of[v] >= pos_base) {
-            cnt = 1;
-            if (lane == 0) acc = lw_raw_weight(row_ptr, mass, scale, dv, v, beta, local_of[v] - pos_base, flat);
+        if (c == 0) {
+            const int32_t li = local_of[v] - pos_base;
+            if (li >= 0) {
+                cnt = 1;
+                if (lane == 0) acc = factor[li];
+            }
         }
         int64_t jb, je;
-        chunk_range(d, c, &jb, &je);
-        for (int64_t base = jb; base < je; base += kWave) {
-            const int64_t j = base + lane;
-            bool in = false;
-            if (j < je) {
-                const int64_t i = static_cast<int64_t>(col_idx[start + j]);
-                const int32_t li = local_of[i] - pos_base;
-                in = li >= 0;
-                if (in) acc += lw_raw_weight(row_ptr, mass, scale, dv, i, beta, li, flat);
+        chunk_range<kSlotUnroll * kWave>(d, c, &jb, &je);
+        // a batch's ids are on their way while the positions of the batch before are looked up, and a batch's
+        // factors while the next one's are
+        int64_t id[kSlotUnroll];
+        double f[kSlotUnroll];
+        auto load = [&](int64_t j0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < kSlotUnroll; ++q) {
+                const int64_t j = j0 + q * kWave + lane;
+                id[q] = static_cast<int64_t>(col_idx[start + (j < je ? j : jb)]);
             }
-            cnt += popc64(ballot64(in));
+        };
+#pragma unroll
+        for (int q = 0; q < kSlotUnroll; ++q) f[q] = 0.0;
+        if (jb < je) load(jb);
+        for (int64_t j0 = jb; j0 < je; j0 += kSlotUnroll * kWave) {
+            int32_t li[kSlotUnroll];
+#pragma unroll
+            for (int q = 0; q < kSlotUnroll; ++q) li[q] = local_of[id[q]] - pos_base;
+            if (j0 + kSlotUnroll * kWave < je) load(j0 + kSlotUnroll * kWave);
+#pragma unroll
+            for (int q = 0; q < kSlotUnroll; ++q) {
+                const bool in = li[q] >= 0 && j0 + q * kWave + lane < je;
+                cnt += popc64(ballot64(in));
+                acc += f[q];
+                f[q] = 0.0;
+                if (in) f[q] = factor[li[q]];
+            }
         }
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+        for (int q = 0; q < kSlotUnroll; ++q) acc += f[q];
+        if (cnt > 0) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+        }
         if (lane == 0) {
             counts[u] = cnt;
             psum[u] = acc;
+            if (cnt > 0) atomicAdd(&row_count[t], cnt);
         }
     }
 }
 
+// scanned: row_count holds its exclusive scan, one entry past the last row too; otherwise every wavefront that needs a
+// row's first edge position adds up the counts before it (a launch of its own for that took 4 to 6 us per block).
 template <typename PtrT, typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_lw_fill(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst,
-          int64_t *sizes, const int32_t *__restrict__ local_of, int32_t pos_base, const unsigned long long *__restrict__ mass,
-          const double *__restrict__ q_total, const double *__restrict__ beta, int flat, const int32_t *__restrict__ offs,
+          int64_t *sizes, const int32_t *__restrict__ local_of, int32_t pos_base, const double *__restrict__ q_total,
+          const double *__restrict__ factor, int debias, const int32_t *__restrict__ counts, const int32_t *__restrict__ row_count, int scanned,
           const double *__restrict__ psum, int32_t *__restrict__ indptr, int32_t *__restrict__ indices,
-          float *__restrict__ edge_w, int normalise, int64_t cap_nnz, const int32_t *__restrict__ seed_flags) {
+          float *__restrict__ edge_w, int normalise, int64_t cap_nnz, int grid) {
     const int lane = lane_id();
     const int64_t rows = sizes[0];
-    const int64_t n = rows * kRowChunks;
-    const double scale = *q_total / static_cast<double>(sizes[1]);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {             // the end of indptr, the block's nnz and flags
-        const int64_t nnz = offs[n];
-        indptr[rows] = static_cast<int32_t>(nnz);
-        sizes[2] = nnz < cap_nnz ? nnz : cap_nnz;
-        sizes[3] = (seed_flags ? *seed_flags : 0) | (nnz > cap_nnz ? 4 : 0);
-    }
     const int64_t wave0 = int64_t(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
-    const int64_t nwaves = int64_t(gridDim.x) * kWavesPerBlock;
-    for (int64_t u = wave0; u < n; u += nwaves) {
+    const int64_t nwaves = int64_t(grid) * kWavesPerBlock;
+    if (rows == 0 && wave0 == 0 && lane == 0) {
+        indptr[0] = 0;
+        sizes[2] = 0;
+    }
+    for (int64_t u = wave0; u < rows * kRowChunks; u += nwaves) {
         const int64_t t = u / kRowChunks;
         const int c = static_cast<int>(u % kRowChunks);
-        if (c == 0 && lane == 0) indptr[t] = offs[u];      // first edge position of row t
-        if (offs[u + 1] == offs[u]) continue;              // nothing drawn in this chunk (wavefront-uniform)
+        // the row's chunks, one per lane
+        const int of_chunk = lane < kRowChunks ? counts[t * kRowChunks + lane] : 0;
+        const int mine = static_cast<int>(readlane32(static_cast<uint32_t>(of_chunk), c));
+        if (mine == 0 && c != 0) continue;                 // nothing drawn in this chunk
+        int64_t pos = 0;                                   // first edge position of the row
+        if (scanned) {
+            pos = row_count[t];
+        } else {
+            int part = 0;
+#pragma unroll 2
+            for (int64_t k = 4 * lane; k < t; k += 4 * kWave) {
+                const int4 x = *reinterpret_cast<const int4 *>(row_count + k);
+                part += x.x + (k + 1 < t ? x.y : 0) + (k + 2 < t ? x.z : 0) + (k + 3 < t ? x.w : 0);
+            }
+            pos = wave_sum(part);
+        }
+        if (c == 0 && lane == 0) indptr[t] = static_cast<int32_t>(pos);
+        if (c == 0 && t == rows - 1) {                     // the end of indptr, the block's nnz, its flags
+            const int64_t nnz = pos + wave_sum(of_chunk);
+            if (lane == 0) {
+                indptr[rows] = static_cast<int32_t>(nnz);
+                sizes[2] = nnz < cap_nnz ? nnz : cap_nnz;
+                if (nnz > cap_nnz) sizes[3] |= 4;
+            }
+        }
+        if (mine == 0) continue;
+        pos += wave_sum(lane < c ? of_chunk : 0);
+        const int64_t end = pos + mine;
         const int64_t v = static_cast<int64_t>(dst[t]);
         const int64_t start = static_cast<int64_t>(row_ptr[v]);
         const int64_t d = static_cast<int64_t>(row_ptr[v + 1]) - start;
-        const double dv = static_cast<double>(d + 1);
-        double inv_sum = 1.0;
+        double scale;
         if (normalise) {                                   // the row's sum: its chunks' partial sums in order
+            const double part = lane < kRowChunks ? psum[t * kRowChunks + lane] : 0.0;
             double row_sum = 0.0;
-            for (int k = 0; k < kRowChunks; ++k) row_sum += psum[t * kRowChunks + k];
-            inv_sum = 1.0 / row_sum;
+            for (int k = 0; k < kRowChunks; ++k) row_sum += __shfl(part, k, 64);
+            scale = 1.0 / row_sum;
+        } else {
+            scale = (debias ? 1.0 : *q_total / static_cast<double>(sizes[1])) / sqrt(static_cast<double>(d + 1));
         }
-        int64_t pos = offs[u];
         if (c == 0) {
             const int32_t self_pos = local_of[v] - pos_base;
             if (self_pos >= 0) {
                 if (lane == 0 && pos < cap_nnz) {
                     indices[pos] = self_pos;
-                    edge_w[pos] = static_cast<float>(lw_raw_weight(row_ptr, mass, scale, dv, v, beta, self_pos, flat) * inv_sum);
+                    edge_w[pos] = static_cast<float>(factor[self_pos] * scale);
                 }
                 pos += 1;
             }
         }
         int64_t jb, je;
-        chunk_range(d, c, &jb, &je);
-        for (int64_t base = jb; base < je; base += kWave) {
-            const int64_t j = base + lane;
-            int64_t i = 0;
-            int32_t li = -1;
-            if (j < je) {
-                i = static_cast<int64_t>(col_idx[start + j]);
-                li = local_of[i] - pos_base;
+        chunk_range<kSlotUnroll * kWave>(d, c, &jb, &je);
+        int64_t id[kSlotUnroll];
+        auto load = [&](int64_t j0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < kSlotUnroll; ++q) {
+                const int64_t j = j0 + q * kWave + lane;
+                id[q] = static_cast<int64_t>(col_idx[start + (j < je ? j : jb)]);
             }
-            const uint64_t m = ballot64(li >= 0);
-            if (li >= 0) {
-                const int64_t p = pos + popc64(m & lanes_below(lane));
-                if (p < cap_nnz) {
-                    indices[p] = li;
-                    edge_w[p] = static_cast<float>(lw_raw_weight(row_ptr, mass, scale, dv, i, beta, li, flat) * inv_sum);
+        };
+        if (jb < je) load(jb);
+        for (int64_t j0 = jb; j0 < je && pos < end; j0 += kSlotUnroll * kWave) {
+            int32_t li[kSlotUnroll];
+#pragma unroll
+            for (int q = 0; q < kSlotUnroll; ++q) li[q] = local_of[id[q]] - pos_base;
+            if (j0 + kSlotUnroll * kWave < je) load(j0 + kSlotUnroll * kWave);
+#pragma unroll
+            for (int q = 0; q < kSlotUnroll; ++q) {
+                const bool in = li[q] >= 0 && j0 + q * kWave + lane < je;
+                const uint64_t m = ballot64(in);
+                if (in) {
+                    const int64_t p = pos + popc64(m & lanes_below(lane));
+                    if (p < cap_nnz) {
+                        indices[p] = li[q];
+                        edge_w[p] = static_cast<float>(factor[li[q]] * scale);
+                    }
                 }
+                pos += popc64(m);
             }
-            pos += popc64(m);
         }
     }
 }
@@ -743,7 +1104,7 @@ k_lw_drawn_keys(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ src_i
     const int64_t i = static_cast<int64_t>(src_ids[pos]);
     const double deg1 = static_cast<double>(static_cast<int64_t>(row_ptr[i + 1]) - static_cast<int64_t>(row_ptr[i]) + 1);
     const double m = static_cast<double>(mass[i]);
-    const double ticket = static_cast<double>(exp_ticket64(mix64(mix64(tag_hash ^ static_cast<uint64_t>(i)))));
+    const double ticket = lw_ticket(tag_hash, i);
     dkey[pos] = static_cast<uint64_t>(__double_as_longlong(lw_race_key(ticket, deg1, m, flat)));
     dq[pos] = lw_measure(m, deg1, flat);
 }
@@ -795,19 +1156,16 @@ __device__ __forceinline__ double lw_block_scan_incl(double v, double *total, do
 //   beta_r = b0_r G_r + H_r,  G_r = prod_{u > r} (1 - a_u),  H_r = sum_{u > r} a_u G_u.
 // One workgroup: a prefix sum over the draws for b0, then, from the last draw backwards, a prefix
 // product for G and a prefix sum of a_u G_u for H, 256 draws at a time with running carries.
-// Every candidate drawn: beta = 1.
+// Every candidate drawn: beta = 1.  The coefficients go into the drawn nodes' factors (LwColumns).
 __global__ void __launch_bounds__(kBlock)
 k_lw_debias(const int32_t *__restrict__ order, const double *__restrict__ dq, const double *__restrict__ q_total,
             const int64_t *__restrict__ sizes, const int64_t *__restrict__ n_cand, double *__restrict__ b0,
-            double *__restrict__ beta) {
+            double *__restrict__ factor) {
     __shared__ double lds[kWavesPerBlock];
     __shared__ double incl_of[kBlock];
     const int64_t s = sizes[1];
     const int64_t n = *n_cand;
-    if (s >= n) {
-        for (int64_t r = threadIdx.x; r < s; r += kBlock) beta[r] = 1.0;
-        return;
-    }
+    if (s >= n) return;
     const double total = *q_total;
     const double nd = static_cast<double>(n);
     double drawn = 0.0;                                    // probability mass of the draws before this chunk
@@ -837,30 +1195,20 @@ k_lw_debias(const int32_t *__restrict__ order, const double *__restrict__ dq, co
         const double Gr = G * (threadIdx.x == 0 ? 1.0 : incl_of[threadIdx.x - 1]);
         const double term = alpha * Gr;
         const double h_incl = lw_block_scan_incl<false>(term, &hsum, lds);
-        if (in) beta[order[r]] = b0[r] * Gr + (H + (h_incl - term));
+        if (in) factor[order[r]] *= b0[r] * Gr + (H + (h_incl - term));
         H += hsum;
         G *= gprod;
         __syncthreads();                                   // incl_of[] is rewritten by the next chunk
     }
 }
 
+// Calls that are being recorded take their positions back, see take_positions.
 template <typename IdxT>
 __global__ void __launch_bounds__(kBlock)
-k_lw_reset(const int32_t *__restrict__ cand, const int64_t *__restrict__ n_cand, int64_t all_nodes,
-           unsigned long long *__restrict__ mass, const IdxT *__restrict__ src_ids, const int64_t *__restrict__ sizes,
-           int32_t *__restrict__ local_of, int take_back, int32_t *__restrict__ flags, int32_t *__restrict__ sel_hist, int hist_len) {
-    if (flags && blockIdx.x == 0 && threadIdx.x == 0) *flags = 0;     // the seed check's word, for the next call
+k_lw_reset(const IdxT *__restrict__ src_ids, const int64_t *__restrict__ sizes, int32_t *__restrict__ local_of) {
     const int64_t ns = sizes[1];
-    const int64_t stride = int64_t(gridDim.x) * kBlock;
-    for (int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x; k < hist_len; k += stride) sel_hist[k] = 0;   // for the next block
-    if (cand) {
-        const int64_t nc = *n_cand;
-        for (int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x; k < nc; k += stride) mass[cand[k]] = 0;
-    } else {
-        for (int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x; k < all_nodes; k += stride) mass[k] = 0;
-    }
-    if (!take_back) return;                                // positions: see take_positions
-    for (int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x; k < ns; k += stride) local_of[src_ids[k]] = -1;
+    const int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+    if (k < ns) local_of[src_ids[k]] = -1;
 }
 
 __global__ void k_lw_store_i64(int64_t *p, int64_t v, int64_t *zero) {
@@ -881,7 +1229,7 @@ bool dev_alloc(T **p, int64_t count) {
 void free_layerwise_scratch(mqg_ctx *ctx) {
     LayerwiseScratch &w = ctx->lw;
     void *ptrs[] = {w.mass, w.cand, w.key64, w.bkey, w.bpos, w.xkey, w.xpos, w.word_offs, w.scan_tiles, w.q_part, w.counters, w.q_total, w.seeds_copy, w.flags,
-                    w.sel_state, w.sel_hist, w.chunk_offs, w.chunk_scan, w.chunk_sum, w.fg_mass, w.dkey, w.dq, w.order, w.beta};
+                    w.sel_state, w.sel_hist, w.sure, w.chunk_counts, w.row_count, w.chunk_sum, w.fg_mass, w.dkey, w.dq, w.order, w.factor};
     for (void *p : ptrs) (void)hipFree(p);
     w = LayerwiseScratch{};
 }
@@ -895,16 +1243,16 @@ int ensure_layerwise_scratch(mqg_ctx *ctx, int64_t rows_cap, hipStream_t s) {
     free_layerwise_scratch(ctx);
     const int64_t n = std::max<int64_t>(ctx->num_nodes, 1);
     const int64_t chunks = rows_cap * kRowChunks;
-    const int64_t scan_len = std::max<int64_t>(ctx->bitmap_words + 1, chunks + 1);
+    const int64_t scan_len = std::max<int64_t>(ctx->bitmap_words + 1, rows_cap + 1);
     bool ok = dev_alloc(&w.mass, n) && dev_alloc(&w.cand, n) && dev_alloc(&w.key64, n) && dev_alloc(&w.bkey, n) && dev_alloc(&w.bpos, n) && dev_alloc(&w.word_offs, ctx->bitmap_words + 1) &&
               dev_alloc(&w.scan_tiles, ceil_div(scan_len, kScanTile) + 2) && dev_alloc(&w.q_part, ceil_div(n, kBlock) + 1) &&
               dev_alloc(&w.counters, 4) && dev_alloc(&w.q_total, 1) && dev_alloc(&w.seeds_copy, rows_cap) && dev_alloc(&w.flags, 1) &&
-              dev_alloc(&w.sel_state, 18) && dev_alloc(&w.sel_hist, kSelHistLen) && dev_alloc(&w.chunk_offs, chunks + 1) &&
-              dev_alloc(&w.chunk_scan, std::min<int64_t>(chunks + 1, int64_t(kScanSelfTiles) * kScanTile)) &&
-              dev_alloc(&w.chunk_sum, chunks) && dev_alloc(&w.dkey, rows_cap) && dev_alloc(&w.dq, rows_cap) &&
-              dev_alloc(&w.order, rows_cap) && dev_alloc(&w.beta, rows_cap);
+              dev_alloc(&w.sel_state, 18) && dev_alloc(&w.sel_hist, kSelHistLen) && dev_alloc(&w.sure, kPickMost) && dev_alloc(&w.chunk_counts, chunks) &&
+              dev_alloc(&w.row_count, rows_cap + 4) && dev_alloc(&w.chunk_sum, chunks) && dev_alloc(&w.dkey, rows_cap) && dev_alloc(&w.dq, rows_cap) &&
+              dev_alloc(&w.order, rows_cap) && dev_alloc(&w.factor, rows_cap);
     if (ok) ok = hipMemset(w.mass, 0, static_cast<size_t>(n) * sizeof(unsigned long long)) == hipSuccess &&
-                 hipMemset(w.flags, 0, sizeof(int32_t)) == hipSuccess && hipDeviceSynchronize() == hipSuccess;
+                 hipMemset(w.flags, 0, sizeof(int32_t)) == hipSuccess &&
+                 hipMemset(w.sel_hist, 0, kSelHistLen * sizeof(int32_t)) == hipSuccess && hipDeviceSynchronize() == hipSuccess;
     if (!ok) {
         free_layerwise_scratch(ctx);
         return fail(ctx, MQG_ERR_HIP, "mqg_sample_layerwise: scratch allocation failed");
@@ -931,16 +1279,16 @@ static int sample_layerwise_impl(mqg_ctx *ctx, const mqg_graph *g, const void *s
         else MQG_LAUNCH(ctx, "k_lw_tile_counts", s, (k_lw_tile_counts<4><<<tiles, kBlock, 0, s>>>(ctx->bitmap, w.word_offs)));
         return MQG_OK;
     };
-    auto emit_list = [&](auto *out, int32_t *local_of, int32_t pos_base, int64_t *count_a, int64_t *count_b) -> int {
+    auto emit_list = [&](auto *out, int32_t *local_of, int32_t pos_base, LwColumns columns, int64_t *count_a, int64_t *count_b) -> int {
         using OutT = std::remove_pointer_t<decltype(out)>;
         if (tiles_scanned) {
             int rc = device_scan(ctx, w.word_offs, tiles, w.scan_tiles, s);
             if (rc != MQG_OK) return rc;
         }
         if (wpt == 1)
-            MQG_LAUNCH(ctx, "k_lw_emit", s, (k_lw_emit<OutT, 1><<<tiles, kBlock, 0, s>>>(ctx->bitmap, w.word_offs, tiles_scanned, out, local_of, pos_base, count_a, count_b)));
+            MQG_LAUNCH(ctx, "k_lw_emit", s, (k_lw_emit<PtrT, OutT, 1><<<tiles, kBlock, 0, s>>>(ctx->bitmap, w.word_offs, tiles_scanned, out, local_of, pos_base, columns, count_a, count_b)));
         else
-            MQG_LAUNCH(ctx, "k_lw_emit", s, (k_lw_emit<OutT, 4><<<tiles, kBlock, 0, s>>>(ctx->bitmap, w.word_offs, tiles_scanned, out, local_of, pos_base, count_a, count_b)));
+            MQG_LAUNCH(ctx, "k_lw_emit", s, (k_lw_emit<PtrT, OutT, 4><<<tiles, kBlock, 0, s>>>(ctx->bitmap, w.word_offs, tiles_scanned, out, local_of, pos_base, columns, count_a, count_b)));
         return MQG_OK;
     };
     const int cand_grid = static_cast<int>(std::max<int64_t>(1, ceil_div(n, kBlock)));
@@ -962,16 +1310,15 @@ static int sample_layerwise_impl(mqg_ctx *ctx, const mqg_graph *g, const void *s
         MQG_LAUNCH(ctx, "k_lw_store_i64", s, (k_lw_store_i64<<<1, 64, 0, s>>>(w.counters + 2, n, nullptr)));
         const int grid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(n * kRowChunks, kWavesPerBlock)), 256 * 64));
         MQG_LAUNCH(ctx, "k_lw_mass", s,
-                   (k_lw_mass<PtrT, IdxT><<<grid, kBlock, 0, s>>>(row_ptr, col_idx, nullptr, w.counters + 2, w.fg_mass, nullptr, nullptr)));
+                   (k_lw_mass<PtrT, IdxT><<<grid, kBlock, 0, s>>>(row_ptr, col_idx, nullptr, w.counters + 2, -1, n, nullptr, nullptr, w.fg_mass, nullptr, nullptr, grid, 0, nullptr)));
         w.fg_ready = true;
     }
 
     IdxT *dst0 = reinterpret_cast<IdxT *>(w.seeds_copy);
-    {
+    if (fastgcn) {
         const int grid = static_cast<int>(std::max<int64_t>(1, ceil_div(num_seeds, kBlock)));
         MQG_LAUNCH(ctx, "k_lw_seeds", s,
-                   (k_lw_seeds<IdxT><<<grid, kBlock, 0, s>>>(static_cast<const IdxT *>(seeds_v), num_seeds, n, dst0,
-                                                             blocks[L - 1].sizes, w.flags, w.sel_hist, kSelHistLen)));
+                   (k_lw_seeds<IdxT><<<grid, kBlock, 0, s>>>(static_cast<const IdxT *>(seeds_v), num_seeds, n, dst0, blocks[L - 1].sizes, w.flags)));
     }
     for (int l = L - 1; l >= 0; --l) {
         mqg_block &b = blocks[l];
@@ -980,87 +1327,100 @@ static int sample_layerwise_impl(mqg_ctx *ctx, const mqg_graph *g, const void *s
         const int64_t rows_cap = l == L - 1 ? num_seeds : std::min<int64_t>(n, layer_sizes[l + 1]);
         const uint64_t tag_hash = host_mix64(seed_hash ^ static_cast<uint64_t>(int64_t(kLayerwiseTag + l)));
 
+        const int64_t src_cap = std::min<int64_t>(n, layer_sizes[l]);
         int32_t pos_base = 0;
         bool take_back = false;
-        int rc = take_positions(ctx, std::min<int64_t>(n, layer_sizes[l]), s, &pos_base, &take_back);
+        int rc = take_positions(ctx, src_cap, s, &pos_base, &take_back);
         if (rc != MQG_OK) return rc;
+        // tickets in the shadow of the masses' atomics, if the rows have more slots than the graph has nodes (most nodes
+        // are candidates then; fewer would make their tickets themselves)
+        const bool shadow = dense && g->num_edges / std::max<int64_t>(n, 1) * rows_cap >= n;
+        const int ticket_blocks = shadow ? cand_grid : 0;
         if (!fastgcn) {
             const int mass_grid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(rows_cap * kRowChunks, kWavesPerBlock)), 256 * 64));
             // list of candidates: marked slot by slot in the node bitmap, or, on graphs of up to
             // kMassScanNodes nodes, read off the masses afterwards
             const bool scan_masses = how == 0 ? n <= kMassScanNodes : how == 2;
             MQG_LAUNCH(ctx, "k_lw_mass", s,
-                       (k_lw_mass<PtrT, IdxT><<<mass_grid, kBlock, 0, s>>>(row_ptr, col_idx, dst, b.sizes, w.mass,
+                       (k_lw_mass<PtrT, IdxT><<<mass_grid + ticket_blocks, kBlock, 0, s>>>(row_ptr, col_idx, l == L - 1 ? static_cast<const IdxT *>(seeds_v) : dst, b.sizes,
+                                                                           l == L - 1 ? int64_t(num_seeds) : int64_t(-1), n, dst0, w.flags, w.mass,
                                                                            dense || scan_masses ? nullptr : ctx->bitmap,
-                                                                           dense ? w.counters : nullptr)));
+                                                                           dense ? w.counters : nullptr, mass_grid, tag_hash,
+                                                                           reinterpret_cast<double *>(w.key64))));
             if (!dense) {
                 if (scan_masses)
                     MQG_LAUNCH(ctx, "k_lw_mass_bits", s, (k_lw_mass_bits<<<tiles, kBlock, 0, s>>>(w.mass, n, ctx->bitmap, w.word_offs)));
                 else
                     rc = count_tiles();
-                if (rc == MQG_OK) rc = emit_list(w.cand, nullptr, 0, n_cand, nullptr);
+                if (rc == MQG_OK) rc = emit_list(w.cand, nullptr, 0, LwColumns{}, n_cand, nullptr);
                 if (rc != MQG_OK) return rc;
             }
         }
-        // race keys and the first digit's counts, then the other digits, then the drawn nodes
-        // (few workgroups: the keys' leading digits take a handful of values, and every workgroup adds its
-        // counts to the same few words - 911 workgroups spent 9 us of 15 queueing there)
-        const int key_grid = static_cast<int>(std::min<int64_t>(cand_grid, n <= (int64_t(1) << 22) ? 256 : 2048));
+        // Race keys and the first digit's counts, then the drawn nodes.  (Few workgroups: every one of them adds its
+        // counts to the same words - 911 workgroups spent 9 us of 15 queueing there.)
+        const bool pick = layer_sizes[l] <= kPickMost;
+        const int key_threads = n <= 256 * 256 ? 256 : n <= 256 * 512 ? 512 : kKeyThreads;
+        const int key_grid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(n, key_threads)), n <= (int64_t(1) << 22) ? 256 : 512));
         MQG_LAUNCH(ctx, "k_lw_keys", s,
-                   (k_lw_keys<PtrT><<<key_grid, kBlock, 0, s>>>(row_ptr, cand, n_keys_dev, n, mass, tag_hash, flat, w.key64, w.q_part, w.sel_hist,
-                                                                dense ? w.counters : nullptr, w.sel_state, layer_sizes[l], bcount)));
-        // Every workgroup adds up 32 KB of digit counts first, so no more of them than the keys need.  Whole calls (two
-        // layers of 512) with 256 / 512 / 1,024: 233 k nodes 115 / 116 / 121 us, 524 k 137 / 137 / 141, 1 M 170 / 167 / 170,
-        // 2 M 131 / 131 / 135; layers of 2,048 on 1 M nodes 206 / 200 / 202.
-        const int sel_grid = static_cast<int>(std::min<int64_t>(cand_grid, n <= (int64_t(1) << 19) ? 256 : 512));
-        for (int pass = 1; pass < kSelPasses; ++pass)
-            MQG_LAUNCH(ctx, "k_lw_select", s,
-                       (k_lw_select<<<sel_grid, kBlock, 0, s>>>(w.key64, n_keys_dev, n, layer_sizes[l], w.sel_state, w.sel_hist, pass)));
-        MQG_LAUNCH(ctx, "k_lw_mark", s,
-                   (k_lw_mark<<<sel_grid, kBlock, 0, s>>>(cand, w.key64, n_keys_dev, n, n_cand, dense ? 1 : 0, layer_sizes[l], w.sel_state,
-                                                          w.sel_hist, ctx->bitmap, w.q_part, key_grid, w.q_total, w.bkey, w.bpos, bcount)));
-        MQG_LAUNCH(ctx, "k_lw_finish", s,
-                   (k_lw_finish<<<1, kBlock, 0, s>>>(cand, n_keys_dev, n, n_cand, layer_sizes[l], w.sel_state, w.bkey, w.bpos, bcount,
-                                                     ctx->bitmap)));
-        rc = count_tiles();
-        if (rc == MQG_OK) rc = emit_list(src_ids, ctx->local_of, pos_base, &b.sizes[1], l > 0 ? &blocks[l - 1].sizes[0] : nullptr);
-        if (rc != MQG_OK) return rc;
-        const double *beta = nullptr;
+                   (k_lw_keys<PtrT><<<key_grid, key_threads, 0, s>>>(row_ptr, cand, n_keys_dev, n, mass, tag_hash, flat, w.key64, w.q_part, w.sel_hist,
+                                                                    dense && !pick ? w.counters : nullptr, w.sel_state, layer_sizes[l], bcount,
+                                                                    pick ? 1 : 0, key_grid, key_threads, ticket_blocks > 0 ? 1 : 0, w.row_count, rows_cap + 1)));
+        const LwColumns columns{row_ptr, mass, flat, debias ? 1 : 0, w.factor};
+        int64_t *next_rows = l > 0 ? &blocks[l - 1].sizes[0] : nullptr;
+        if (pick) {
+            const int list_grid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(n, kBlock * kListItems)), 1024));
+            MQG_LAUNCH(ctx, "k_lw_list", s,
+                       (k_lw_list<<<list_grid, kBlock, 0, s>>>(cand, w.key64, n_keys_dev, n, layer_sizes[l], w.sel_hist, w.q_part, key_grid, w.q_total,
+                                                               w.counters + 1, w.sure, w.bkey, w.bpos, bcount, w.sel_state + 5, list_grid)));
+            MQG_LAUNCH(ctx, "k_lw_pick", s,
+                       (k_lw_pick<PtrT, IdxT><<<static_cast<int>(std::max<int64_t>(1, ceil_div(src_cap * kPickThreads, kBlock))), kBlock, 0, s>>>(
+                           w.sure, w.bkey, w.bpos, bcount, w.sel_state + 5, layer_sizes[l], std::max<int64_t>(n, 1), src_ids, ctx->local_of, pos_base, columns, &b.sizes[1], next_rows)));
+        } else {
+            // Every workgroup adds up 32 KB of digit counts first, so no more of them than the keys need.  Whole calls (two
+            // layers of 512) with 256 / 512 / 1,024: 233 k nodes 115 / 116 / 121 us, 524 k 137 / 137 / 141, 1 M 170 / 167 / 170,
+            // 2 M 131 / 131 / 135; layers of 2,048 on 1 M nodes 206 / 200 / 202.
+            const int sel_grid = static_cast<int>(std::min<int64_t>(cand_grid, n <= (int64_t(1) << 19) ? 256 : 512));
+            for (int pass = 1; pass < kSelPasses; ++pass)
+                MQG_LAUNCH(ctx, "k_lw_select", s,
+                           (k_lw_select<<<sel_grid, kBlock, 0, s>>>(w.key64, n_keys_dev, n, layer_sizes[l], w.sel_state, w.sel_hist, pass)));
+            MQG_LAUNCH(ctx, "k_lw_mark", s,
+                       (k_lw_mark<<<sel_grid, kBlock, 0, s>>>(cand, w.key64, n_keys_dev, n, n_cand, dense ? 1 : 0, layer_sizes[l], w.sel_state,
+                                                              w.sel_hist, ctx->bitmap, w.q_part, key_grid, w.q_total, w.bkey, w.bpos, bcount)));
+            MQG_LAUNCH(ctx, "k_lw_finish", s,
+                       (k_lw_finish<<<1, kBlock, 0, s>>>(cand, n_keys_dev, n, n_cand, layer_sizes[l], w.sel_state, w.bkey, w.bpos, bcount,
+                                                         ctx->bitmap)));
+            rc = count_tiles();
+            if (rc == MQG_OK) rc = emit_list(src_ids, ctx->local_of, pos_base, columns, &b.sizes[1], next_rows);
+            if (rc != MQG_OK) return rc;
+        }
         if (debias) {
-            const int64_t src_cap = std::min<int64_t>(n, layer_sizes[l]);
             const int sgrid = static_cast<int>(std::max<int64_t>(1, ceil_div(src_cap, kBlock)));
             MQG_LAUNCH(ctx, "k_lw_drawn_keys", s,
                        (k_lw_drawn_keys<PtrT, IdxT><<<sgrid, kBlock, 0, s>>>(row_ptr, src_ids, b.sizes, mass, tag_hash, flat, w.dkey, w.dq)));
             MQG_LAUNCH(ctx, "k_lw_draw_order", s, (k_lw_draw_order<<<sgrid, kBlock, 0, s>>>(w.dkey, b.sizes, w.order)));
             MQG_LAUNCH(ctx, "k_lw_debias", s,
-                       (k_lw_debias<<<1, kBlock, 0, s>>>(w.order, w.dq, w.q_total, b.sizes, n_cand, w.chunk_sum, w.beta)));
-            beta = w.beta;
+                       (k_lw_debias<<<1, kBlock, 0, s>>>(w.order, w.dq, w.q_total, b.sizes, pick ? w.counters + 1 : n_cand, w.chunk_sum, w.factor)));
         }
-        // rows: per (row, chunk) counts and weight sums, one scan, then the edges
-        const int64_t chunks_cap = rows_cap * kRowChunks;
-        const int chunk_grid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(chunks_cap, kWavesPerBlock)), 256 * 64));
-        // (entries of chunk_offs past the block's rows are not cleared: an exclusive scan's values up to
-        // the last row's end, the only ones read, do not depend on them)
+        // rows: edges and weight sums per (row, chunk), then the edges
+        const int row_grid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(rows_cap * kRowChunks, kWavesPerBlock)), 256 * 64));
+        const int clear_grid = static_cast<int>(std::min<int64_t>(ceil_div(fastgcn ? 0 : n, kBlock * 8) + 8, 1024));
         MQG_LAUNCH(ctx, "k_lw_count", s,
-                   (k_lw_count<PtrT, IdxT><<<chunk_grid, kBlock, 0, s>>>(row_ptr, col_idx, dst, b.sizes, ctx->local_of, pos_base, mass, w.q_total,
-                                                                         beta, flat, w.chunk_offs, w.chunk_sum)));
-        // one launch when the table is small (the scan goes to a second array), else in place
-        const int32_t *offs = w.chunk_offs;
-        if (chunks_cap + 1 <= int64_t(kScanSelfTiles) * kScanTile) {
-            rc = device_scan_copy(ctx, w.chunk_offs, w.chunk_scan, chunks_cap + 1, s);
-            offs = w.chunk_scan;
-        } else {
-            rc = device_scan(ctx, w.chunk_offs, chunks_cap + 1, w.scan_tiles, s);
+                   (k_lw_count<PtrT, IdxT><<<row_grid + clear_grid, kBlock, 0, s>>>(row_ptr, col_idx, dst, b.sizes, ctx->local_of, pos_base, w.factor,
+                                                                                   w.chunk_counts, w.chunk_sum, w.row_count, row_grid, clear_grid, cand, n_cand,
+                                                                                   dense ? n : 0, w.mass, w.sel_hist, pick ? kFineBins : kSelHistLen,
+                                                                                   l == L - 1 ? w.flags : nullptr)));
+        const int scanned = rows_cap > kSelfOffsetRows ? 1 : 0;
+        if (scanned) {
+            rc = device_scan(ctx, w.row_count, rows_cap + 1, w.scan_tiles, s);
+            if (rc != MQG_OK) return rc;
         }
-        if (rc != MQG_OK) return rc;
         MQG_LAUNCH(ctx, "k_lw_fill", s,
-                   (k_lw_fill<PtrT, IdxT><<<chunk_grid, kBlock, 0, s>>>(row_ptr, col_idx, dst, b.sizes, ctx->local_of, pos_base, mass, w.q_total,
-                                                                        beta, flat, offs, w.chunk_sum, b.indptr, b.indices, edge_w[l],
-                                                                        normalise, b.cap_nnz, l == L - 1 ? w.flags : nullptr)));
-        const int reset_grid = static_cast<int>(std::min<int64_t>(cand_grid, 4096));
-        MQG_LAUNCH(ctx, "k_lw_reset", s,
-                   (k_lw_reset<IdxT><<<reset_grid, kBlock, 0, s>>>(cand, n_cand, dense ? n : 0, w.mass, src_ids, b.sizes, ctx->local_of, take_back ? 1 : 0,
-                                                                   l == L - 1 ? w.flags : nullptr, w.sel_hist, kSelHistLen)));
+                   (k_lw_fill<PtrT, IdxT><<<row_grid, kBlock, 0, s>>>(row_ptr, col_idx, dst, b.sizes, ctx->local_of, pos_base, w.q_total, w.factor,
+                                                                     debias ? 1 : 0, w.chunk_counts, w.row_count, scanned, w.chunk_sum, b.indptr,
+                                                                     b.indices, edge_w[l], normalise, b.cap_nnz, row_grid)));
+        if (take_back)
+            MQG_LAUNCH(ctx, "k_lw_reset", s,
+                       (k_lw_reset<IdxT><<<static_cast<int>(std::max<int64_t>(1, ceil_div(src_cap, kBlock))), kBlock, 0, s>>>(src_ids, b.sizes, ctx->local_of)));
     }
     return MQG_OK;
 }
@@ -1098,7 +1458,6 @@ int run_select_smallest_keys(mqg_ctx *ctx, const uint64_t *keys, int64_t n, int6
     if (words > 0)
         MQG_LAUNCH(ctx, "k_lw_zero_i32", s,
                    (k_lw_zero_i32<<<static_cast<int>(ceil_div(words, kBlock)), kBlock, 0, s>>>(reinterpret_cast<int32_t *>(out_bitmap), words)));
-    MQG_LAUNCH(ctx, "k_lw_zero_i32", s, (k_lw_zero_i32<<<kSelHistLen / kBlock, kBlock, 0, s>>>(w.sel_hist, kSelHistLen)));
     const int grid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(n, kBlock)), 1024));
     for (int pass = 0; pass < kSelPasses; ++pass)
         MQG_LAUNCH(ctx, "k_lw_select", s, (k_lw_select<<<grid, kBlock, 0, s>>>(keys, n_dev, 0, k, w.sel_state, w.sel_hist, pass)));
@@ -1108,6 +1467,8 @@ int run_select_smallest_keys(mqg_ctx *ctx, const uint64_t *keys, int64_t n, int6
                                                   bkey, bpos, bcount)));
     MQG_LAUNCH(ctx, "k_lw_finish", s,
                (k_lw_finish<<<1, kBlock, 0, s>>>(nullptr, n_dev, 0, nullptr, k, w.sel_state, bkey, bpos, bcount, out_bitmap)));
+    // the histogram is clear between calls
+    MQG_LAUNCH(ctx, "k_lw_zero_i32", s, (k_lw_zero_i32<<<kSelHistLen / kBlock, kBlock, 0, s>>>(w.sel_hist, kSelHistLen)));
     return MQG_OK;
 }
 

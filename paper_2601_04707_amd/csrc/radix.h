@@ -12,8 +12,6 @@ constexpr int kRadixSelfBlocks = 32;                 // up to this many tiles th
 constexpr int kRadixMaxDigitBits = 11;
 constexpr int kRadixTotals = 1 << kRadixMaxDigitBits;  // entries of RadixBufs::totals
 
-constexpr int kScanSelfTiles = 32;                   // up to this many tiles device_scan_copy scans in one launch
-
 constexpr int64_t kRadixWideKeys = int64_t(2) << 20;  // inputs above this many keys use digits of at most 9 bits
 // n_cap keys of `bits` significant bits are sorted in radix_passes passes of radix_digit_bits bits.
 int radix_passes(int bits, int64_t n_cap);
@@ -25,9 +23,6 @@ int64_t radix_hist_len_max(int64_t n_cap);            // enough for every sort o
 
 // exclusive scan of data[0..n) in place; tile_sums needs ceil(n / kScanTile) + 1 ints
 int device_scan(mqg_ctx *ctx, int32_t *data, int64_t n, int32_t *tile_sums, hipStream_t s);
-
-// exclusive scan of in[0..n) into out[0..n) (out != in), one launch; n <= kScanSelfTiles * kScanTile
-int device_scan_copy(mqg_ctx *ctx, const int32_t *in, int32_t *out, int64_t n, hipStream_t s);
 
 // Sorts the first min(n_cap, *n_dev) pairs by the low `bits` bits of the key, stably.  The input
 // arrays are only read; *result tells which of b.keys/b.vals holds the output (-1: bits == 0,

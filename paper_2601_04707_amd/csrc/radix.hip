@@ -155,40 +155,6 @@ k_scan_apply(int32_t *__restrict__ data, int64_t n, const int32_t *__restrict__ 
     }
 }
 
-// Exclusive scan of up to kScanSelfTiles tiles in one launch, out of place: every workgroup adds up
-// the elements of the tiles before its own (at most 31 x 4 KB, from L2) and scans its tile.
-__global__ void __launch_bounds__(kBlock)
-k_scan_self(const int32_t *__restrict__ in, int64_t n, int32_t *__restrict__ out) {
-    __shared__ int lds[kWavesPerBlock];
-    const int64_t tile0 = int64_t(blockIdx.x) * kScanTile;
-    int part = 0;
-    for (int64_t i = int64_t(threadIdx.x) * 4; i < tile0; i += kBlock * 4) {    // tile0 is a multiple of kBlock * 4
-        const int4 x = *reinterpret_cast<const int4 *>(in + i);
-        part += x.x + x.y + x.z + x.w;
-    }
-    part = wave_sum(part);
-    if (lane_id() == 0) lds[threadIdx.x >> 6] = part;
-    __syncthreads();
-    int tile_base = 0;
-#pragma unroll
-    for (int k = 0; k < kWavesPerBlock; ++k) tile_base += lds[k];
-    const int64_t base = tile0 + threadIdx.x * 4;
-    int v[4];
-    int c = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        v[q] = base + q < n ? in[base + q] : 0;
-        c += v[q];
-    }
-    int total;
-    int ex = block_excl_scan<kWavesPerBlock>(c, &total, lds) + tile_base;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        if (base + q < n) out[base + q] = ex;
-        ex += v[q];
-    }
-}
-
 // What a key carries along: vals_in[i], or (vals_in == nullptr, first pass only) its own position i.
 struct RadixPayload {
     const int32_t *vals_in;
@@ -397,13 +363,6 @@ int device_scan(mqg_ctx *ctx, int32_t *data, int64_t n, int32_t *tile_sums, hipS
         if (rc != MQG_OK) return rc;
     }
     MQG_LAUNCH(ctx, "k_scan_apply", s, (k_scan_apply<<<tiles, kBlock, 0, s>>>(data, n, tile_sums, scanned)));
-    return MQG_OK;
-}
-
-int device_scan_copy(mqg_ctx *ctx, const int32_t *in, int32_t *out, int64_t n, hipStream_t s) {
-    const int tiles = static_cast<int>(std::max<int64_t>(1, ceil_div(n, kScanTile)));
-    if (tiles > kScanSelfTiles || in == out) return fail(ctx, MQG_ERR_INVALID_ARG, "device_scan_copy: too many tiles, or in place");
-    MQG_LAUNCH(ctx, "k_scan_self", s, (k_scan_self<<<tiles, kBlock, 0, s>>>(in, n, out)));
     return MQG_OK;
 }
 

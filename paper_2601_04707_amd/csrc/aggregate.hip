@@ -494,23 +494,6 @@ int launch(mqg_ctx *ctx, const char *name, const Rows &rows, const int64_t *n_ro
 
 // ---------------------------------------------------------------- edges ordered by source
 
-// Number of the entries of the ascending list v[0..n) that are below x (STRICT) or not above it, found by a
-// whole wavefront: 64 probes per step instead of one, so that a million entries take four dependent loads.
-template <bool STRICT, typename V>
-__device__ __forceinline__ int64_t wave_count_below(const V *__restrict__ v, int64_t n, int64_t x) {
-    int64_t lo = 0, hi = n;                                // the answer lies in [lo, hi]
-    while (lo < hi) {
-        const int64_t step = (hi - lo + kWave - 1) / kWave;
-        const int64_t i = lo + (lane_id() + 1) * step - 1;
-        const bool below = i < hi && (STRICT ? static_cast<int64_t>(v[i]) < x : static_cast<int64_t>(v[i]) <= x);
-        const int64_t c = popc64(ballot64(below));         // v ascends: the first c probes
-        const int64_t next = lo + (c + 1) * step - 1;      // the first probe that is not
-        lo += c * step;
-        hi = next < hi ? next : hi;
-    }
-    return lo;
-}
-
 // payload of edge e = its destination row (the keys are `indices`).  A wavefront takes a run of consecutive edges,
 // 64 or as many more as give every wavefront of the chip one run (runs of 512 left 38 k edges to 74 wavefronts:
 // 5.9 us, 2.4 in runs of 64; a bisection per edge 3.4); its lanes hold the offsets of 64 consecutive rows, and every edge finds its row among them.  The
@@ -681,7 +664,7 @@ int ensure_backward_scratch(mqg_ctx *ctx, int64_t nnz_cap, int64_t src_cap, hipS
     auto alloc = [&](void **p, int64_t bytes) { return hipMalloc(p, static_cast<size_t>(std::max<int64_t>(bytes, 4))) == hipSuccess; };
     bool ok = alloc(reinterpret_cast<void **>(&ctx->bwd.keys[0]), nn * 4) && alloc(reinterpret_cast<void **>(&ctx->bwd.keys[1]), nn * 4) &&
               alloc(reinterpret_cast<void **>(&ctx->bwd.vals[0]), nn * 4) && alloc(reinterpret_cast<void **>(&ctx->bwd.vals[1]), nn * 4) &&
-              alloc(reinterpret_cast<void **>(&ctx->bwd.hist), radix_hist_len_max(nn) * 4) &&
+              alloc(reinterpret_cast<void **>(&ctx->bwd.hist), std::max(radix_hist_len_max(nn), order_hist_len(nn)) * 4) &&
               alloc(reinterpret_cast<void **>(&ctx->bwd.totals), kRadixTotals * 4) &&
               alloc(reinterpret_cast<void **>(&ctx->bwd_dst_row), nn * 4) &&
               alloc(reinterpret_cast<void **>(&ctx->bwd_w_sorted), nn * 4) &&
@@ -704,8 +687,31 @@ int run_aggregate_backward(mqg_ctx *ctx, const mqg_block *b, const float *edge_w
     int rc0 = ensure_backward_scratch(ctx, nnz_cap, src_cap, s, who);
     if (rc0 != MQG_OK) return rc0;
 
+    auto reduce_weighted = [&](const int32_t *dst_sorted) -> int {
+        WeightedBackwardRows rows{ctx->bwd_col_ptr, dst_sorted, ctx->bwd_w_sorted, self_w, b->sizes};
+        if (dtype == MQG_F16)
+            return launch<_Float16>(ctx, "k_weighted_aggregate_backward", rows, &b->sizes[1], src_cap, nnz_cap,
+                                    static_cast<const _Float16 *>(grad_out), go_stride, static_cast<_Float16 *>(grad_x), gx_stride, dim, s);
+        return launch<float>(ctx, "k_weighted_aggregate_backward", rows, &b->sizes[1], src_cap, nnz_cap, static_cast<const float *>(grad_out),
+                             go_stride, static_cast<float *>(grad_x), gx_stride, dim, s);
+    };
+    auto reduce_mean = [&](const int32_t *dst_sorted) -> int {
+        BackwardRows rows{ctx->bwd_col_ptr, dst_sorted, b->indptr};
+        if (dtype == MQG_F16)
+            return launch<_Float16>(ctx, "k_mean_aggregate_backward", rows, &b->sizes[1], src_cap, nnz_cap,
+                                    static_cast<const _Float16 *>(grad_out), go_stride, static_cast<_Float16 *>(grad_x), gx_stride, dim, s);
+        return launch<float>(ctx, "k_mean_aggregate_backward", rows, &b->sizes[1], src_cap, nnz_cap, static_cast<const float *>(grad_out),
+                             go_stride, static_cast<float *>(grad_x), gx_stride, dim, s);
+    };
+
+    if (can_order_edges(src_cap)) {
+        // bwd.vals[0] and bwd.keys hold the partitioned edges on the way
+        rc0 = order_edges_by_source(ctx, b, edge_w, ctx->bwd_col_ptr, ctx->bwd_dst_row, ctx->bwd_w_sorted, s);
+        if (rc0 != MQG_OK) return rc0;
+        return edge_w ? reduce_weighted(ctx->bwd_dst_row) : reduce_mean(ctx->bwd_dst_row);
+    }
     const int egrid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(nnz_cap, kBlock)), 8192));
-    // Edges by source, stably.  An edge carries its destination row along, or (weighted) its own
+    // More sources than that: edges by source by a radix sort, stably.  An edge carries its destination row along, or (weighted) its own
     // position, which the sort's first pass makes itself - at least one pass, for that.
     const int rgrid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(nnz_cap, kBlock)), kEdgeWaves / kWavesPerBlock));
     if (!edge_w) MQG_LAUNCH(ctx, "k_edge_dst_rows", s, (k_edge_dst_rows<<<rgrid, kBlock, 0, s>>>(b->indptr, b->sizes, ctx->bwd_dst_row)));
@@ -728,19 +734,9 @@ int run_aggregate_backward(mqg_ctx *ctx, const mqg_block *b, const float *edge_w
         if (rows_of) MQG_LAUNCH(ctx, "k_edge_dst_rows", s, (k_edge_dst_rows<<<rgrid, kBlock, 0, s>>>(b->indptr, b->sizes, rows_of)));
         MQG_LAUNCH(ctx, "k_permute_edges", s,
                    (k_permute_edges<<<egrid, kBlock, 0, s>>>(sorted_dst, b->indptr, rows_of, edge_w, b->sizes, dst_sorted, ctx->bwd_w_sorted)));
-        WeightedBackwardRows rows{ctx->bwd_col_ptr, dst_sorted, ctx->bwd_w_sorted, self_w, b->sizes};
-        if (dtype == MQG_F16)
-            return launch<_Float16>(ctx, "k_weighted_aggregate_backward", rows, &b->sizes[1], src_cap, nnz_cap,
-                                    static_cast<const _Float16 *>(grad_out), go_stride, static_cast<_Float16 *>(grad_x), gx_stride, dim, s);
-        return launch<float>(ctx, "k_weighted_aggregate_backward", rows, &b->sizes[1], src_cap, nnz_cap, static_cast<const float *>(grad_out),
-                             go_stride, static_cast<float *>(grad_x), gx_stride, dim, s);
+        return reduce_weighted(dst_sorted);
     }
-    BackwardRows rows{ctx->bwd_col_ptr, sorted_dst, b->indptr};
-    if (dtype == MQG_F16)
-        return launch<_Float16>(ctx, "k_mean_aggregate_backward", rows, &b->sizes[1], src_cap, nnz_cap,
-                                static_cast<const _Float16 *>(grad_out), go_stride, static_cast<_Float16 *>(grad_x), gx_stride, dim, s);
-    return launch<float>(ctx, "k_mean_aggregate_backward", rows, &b->sizes[1], src_cap, nnz_cap, static_cast<const float *>(grad_out),
-                         go_stride, static_cast<float *>(grad_x), gx_stride, dim, s);
+    return reduce_mean(sorted_dst);
 }
 
 }  // namespace mqg

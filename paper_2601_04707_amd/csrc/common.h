@@ -171,6 +171,10 @@ int run_aggregate_backward(mqg_ctx *ctx, const mqg_block *b, const float *edge_w
 int run_gcn_edge_weights(mqg_ctx *ctx, const mqg_graph *g, const mqg_block *b, float *edge_w, float *self_w, hipStream_t s);
 int run_weighted_aggregate(mqg_ctx *ctx, const mqg_block *b, const float *edge_w, const float *self_w, const void *x,
                            int64_t x_stride, void *out, int64_t out_stride, int32_t dim, int32_t dtype, hipStream_t s);
+bool can_order_edges(int64_t src_cap);
+int64_t order_hist_len(int64_t nnz_cap);
+int order_edges_by_source(mqg_ctx *ctx, const mqg_block *b, const float *edge_w, int32_t *col_ptr, int32_t *rows_out, float *w_out,
+                          hipStream_t s);
 void free_backward_scratch(mqg_ctx *ctx);
 int ensure_backward_scratch(mqg_ctx *ctx, int64_t nnz_cap, int64_t src_cap, hipStream_t s, const char *who);
 int ensure_layerwise_scratch(mqg_ctx *ctx, int64_t rows_cap, hipStream_t s);

@@ -170,6 +170,23 @@ __device__ __forceinline__ int tiles_before(const int32_t *__restrict__ tile_sum
     return tiles_before(tile_sums, lds, static_cast<int>(blockIdx.x));
 }
 
+// Number of the entries of the ascending list v[0..n) that are below x (STRICT) or not above it, found by a
+// whole wavefront: 64 probes per step instead of one, so that a million entries take four dependent loads.
+template <bool STRICT, typename V>
+__device__ __forceinline__ int64_t wave_count_below(const V *__restrict__ v, int64_t n, int64_t x) {
+    int64_t lo = 0, hi = n;                                // the answer lies in [lo, hi]
+    while (lo < hi) {
+        const int64_t step = (hi - lo + kWave - 1) / kWave;
+        const int64_t i = lo + (lane_id() + 1) * step - 1;
+        const bool below = i < hi && (STRICT ? static_cast<int64_t>(v[i]) < x : static_cast<int64_t>(v[i]) <= x);
+        const int64_t c = popc64(ballot64(below));         // v ascends: the first c probes
+        const int64_t next = lo + (c + 1) * step - 1;      // the first probe that is not
+        lo += c * step;
+        hi = next < hi ? next : hi;
+    }
+    return lo;
+}
+
 // SplitMix64 finaliser (Steele, Lea, Flood 2014): the mixing function of the sampling keys.
 __device__ __forceinline__ uint64_t mix64(uint64_t z) {
     z ^= z >> 30;

@@ -1,0 +1,512 @@
+// The edges of a block ordered by source, stably, for the backward aggregation: the transposed operator's row offsets
+// (col_ptr), and per edge its destination row and, weighted, its weight.
+//
+//   k_order_hist     digit histogram of every tile of edges, digit = the leading bits of the source position
+//   (k_radix_scan    exclusive scan of every digit's counts over the tiles, and their totals; up to kRadixSelfBlocks
+//                    tiles the scatter adds the counts up itself)
+//   k_order_scatter  stable partition by that digit; an edge's destination row is found here, by its wavefront, among
+//                    the offsets of 64 consecutive rows
+//   k_order_buckets  a workgroup per range of up to 2,048 sources: counts its edges per source, which gives col_ptr,
+//                    and writes them to their places in order
+//
+// One partition and one pass over each bucket in place of two or three passes of a radix sort (a histogram, a scan and a
+// scatter each), a launch for the destination rows, a bisection for col_ptr and, weighted, a gather of the
+// weights.  Measured, all launches: 4.3 M edges into 1.35 M sources MEASURE.
+// How many leading bits there are depends on the number of sources, which only the device knows.
+#include <algorithm>
+
+#include "common.h"
+#include "device_utils.h"
+#include "radix.h"
+
+namespace mqg {
+
+namespace {
+
+constexpr int kOrderBits = 9;                        // of the partition's digit
+constexpr int kOrderDigits = 1 << kOrderBits;
+constexpr int kOrderThreads = 512;                   // workgroup of a tile of many edges; few edges: kBlock
+constexpr int kSubBits = 11;                         // of a source within its workgroup's range
+constexpr int kSub = 1 << kSubBits;
+constexpr int kBucketThreads = 512;
+constexpr int kBucketWaves = kBucketThreads / kWave;
+constexpr int kBucketChunk = 16384;                  // edges of a bucket placed by one workgroup; fits 16 bits
+constexpr int kStageWords = 8192;                    // of a range's edges, for a coalesced store
+constexpr int kBucketGrid = 1024;
+
+// bits of a source position below the partition's digit
+__host__ __device__ inline int order_shift(int64_t num_src) {
+    int bits = 0;
+    while (bits < 32 && ((num_src > 0 ? num_src - 1 : 0) >> bits) != 0) ++bits;
+    return bits > kOrderBits ? bits - kOrderBits : 0;
+}
+
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS)
+k_order_hist(const int32_t *__restrict__ indices, const int64_t *__restrict__ sizes, int64_t cap, int32_t *__restrict__ hist, int nblocks, int items,
+             int tile_major) {
+    __shared__ int h[kOrderDigits];
+    const int64_t n = sizes[2] < cap ? sizes[2] : cap;
+    const int me = tile_major ? static_cast<int>(blockIdx.x) : xcd_tile(live_tiles(n, THREADS * items));
+    if (me >= nblocks) return;
+    const int shift = order_shift(sizes[1]);
+#pragma unroll
+    for (int q = 0; q < kOrderDigits / THREADS; ++q) h[q * THREADS + threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t base = int64_t(me) * THREADS * items;
+    uint32_t key[kRadixItems];
+#pragma unroll
+    for (int r = 0; r < kRadixItems; ++r) {
+        const int64_t i = base + r * THREADS + threadIdx.x;
+        key[r] = r < items && i < n ? static_cast<uint32_t>(indices[i]) : 0;
+    }
+#pragma unroll
+    for (int r = 0; r < kRadixItems; ++r) {
+        const int64_t i = base + r * THREADS + threadIdx.x;
+        if (r < items && i < n) atomicAdd(&h[(key[r] >> shift) & (kOrderDigits - 1)], 1);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kOrderDigits / THREADS; ++q) {
+        const int d = q * THREADS + threadIdx.x;
+        if (tile_major) hist[int64_t(me) * kOrderDigits + d] = h[d];
+        else hist[int64_t(d) * nblocks + me] = h[d];
+    }
+}
+
+// The destination rows of consecutive edges, 64 at a time, for one wavefront: the last row that begins at or before an
+// edge.  The lanes hold the offsets of 64 consecutive rows; the window only moves forward and ends at the last row,
+// which takes every edge past the last offset.
+struct RowWindow {
+    const int32_t *indptr;
+    int64_t num_dst, r0;
+    int off, end;
+    __device__ __forceinline__ int offset(int64_t r) const { return indptr[r < num_dst ? r : num_dst]; }
+    __device__ __forceinline__ int64_t row_of(int64_t e) const {
+        const int64_t r = wave_count_below<false>(indptr, num_dst, e) - 1;
+        return r > 0 ? r : 0;
+    }
+    __device__ __forceinline__ RowWindow(const int32_t *p, int64_t n, int64_t first) : indptr(p), num_dst(n) {
+        r0 = row_of(first);
+        off = offset(r0 + lane_id());
+        end = offset(r0 + kWave);
+    }
+    // edge e of every lane (ascending over the lanes and from call to call); only `open` ones count
+    __device__ __forceinline__ int32_t rows(int64_t e, bool open) {
+        int32_t row = 0;
+        const int64_t e0 = e - lane_id();
+        for (;;) {
+            int k = 0;
+#pragma unroll
+            for (int h = 32; h > 0; h >>= 1)
+                if (__shfl(off, k + h, 64) <= e) k += h;
+            if (open && (e < end || r0 + kWave >= num_dst)) {
+                const int64_t r = r0 + k < num_dst ? r0 + k : num_dst - 1;
+                row = static_cast<int32_t>(r > 0 ? r : 0);
+                open = false;
+            }
+            const uint64_t left = ballot64(open);
+            if (!left) return row;
+            r0 += kWave;
+            const int64_t first = e0 + __ffsll(static_cast<long long>(left)) - 1;
+            if (offset(r0 + kWave) <= first) {             // past a stretch of empty rows
+                const int64_t r = row_of(first);
+                r0 = r > r0 ? r : r0;
+            }
+            off = offset(r0 + lane_id());
+            end = offset(r0 + kWave);
+        }
+    }
+};
+
+// SELF: hist is the [tile][digit] table of counts, added up here (and the totals stored); otherwise it is the
+// [digit][tile] table, scanned row by row, and `totals` the edges of every digit.  The tile lies sorted by digit in LDS
+// before it is written, every digit's run to consecutive addresses; see k_radix_scatter.
+template <bool SELF, bool WEIGHTED, int THREADS>
+__global__ void __launch_bounds__(THREADS)
+k_order_scatter(const int32_t *__restrict__ indices, const int32_t *__restrict__ indptr, const float *__restrict__ edge_w,
+                const int64_t *__restrict__ sizes, int64_t cap, const int32_t *__restrict__ hist, int32_t *__restrict__ totals, int nblocks, int items,
+                uint16_t *__restrict__ key_out, int32_t *__restrict__ row_out, float *__restrict__ w_out) {
+    constexpr int ITEMS = kRadixItems, WAVES = THREADS / kWave, PER = kOrderDigits / THREADS;
+    __shared__ uint16_t wcnt[WAVES][kOrderDigits];     // edges of this digit so far, then those of the wavefronts before
+    __shared__ int first[kOrderDigits];                    // first place of the digit in the sorted tile ...
+    __shared__ int gbase[kOrderDigits];                    // ... and in the output, less that
+    __shared__ uint32_t skeys[THREADS * ITEMS];
+    __shared__ int32_t srows[THREADS * ITEMS];
+    __shared__ float sw[WEIGHTED ? THREADS * ITEMS : 1];
+    __shared__ int scan_lds[WAVES];
+    const int tid = threadIdx.x;
+    const int lane = lane_id();
+    const int wave = tid >> 6;
+    const int64_t n = sizes[2] < cap ? sizes[2] : cap;
+    const int shift = order_shift(sizes[1]);
+    const uint32_t low = (1u << shift) - 1;
+    const int me = SELF ? static_cast<int>(blockIdx.x) : xcd_tile(live_tiles(n, THREADS * items));
+    if (me >= nblocks) return;
+    const int64_t base = int64_t(me) * THREADS * items;
+    if (base >= n && !(SELF && me == 0)) return;
+    const int tile_n = n - base < THREADS * items ? static_cast<int>(n > base ? n - base : 0) : THREADS * items;
+    const int wave_first = wave * kWave * items;
+    uint32_t key[ITEMS];
+    float w[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const int i = wave_first + r * kWave + lane;
+        const bool in = r < items && i < tile_n;
+        key[r] = in ? static_cast<uint32_t>(indices[base + i]) : 0;
+        w[r] = WEIGHTED && in ? edge_w[base + i] : 0.f;
+    }
+    int out0[PER], all[PER], sum = 0, total;   // first output places of digits tid * PER ... for this tile
+    if (!SELF) {
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            out0[q] = hist[int64_t(tid * PER + q) * nblocks + me];
+            all[q] = totals[tid * PER + q];
+            sum += all[q];
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < PER; ++q) all[q] = out0[q] = 0;
+#pragma unroll 4
+        for (int t = 0; t < nblocks; ++t) {
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                const int c = hist[int64_t(t) * kOrderDigits + tid * PER + q];
+                all[q] += c;
+                out0[q] += t < me ? c : 0;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            if (me == 0) totals[tid * PER + q] = all[q];
+            sum += all[q];
+        }
+    }
+    int ex = block_excl_scan<WAVES>(sum, &total, scan_lds);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        out0[q] += ex;
+        ex += all[q];
+    }
+#pragma unroll
+    for (int q = 0; q < kOrderDigits / kWave; ++q) wcnt[wave][q * kWave + lane] = 0;
+    wave_lds_sync();
+    int rank[ITEMS];                                       // among the edges of its digit in this wavefront
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        if (r < items) {                                   // uniform
+            const bool in = wave_first + r * kWave + lane < tile_n;
+            const int digit = (key[r] >> shift) & (kOrderDigits - 1);
+            uint64_t peers = ballot64(in);                 // lanes that hold the same digit
+#pragma unroll
+            for (int bit = 0; bit < kOrderBits; ++bit) {
+                const int b = __builtin_amdgcn_sbfe(digit, bit, 1);              // all ones or zero
+                peers &= ~(ballot64(b != 0) ^ static_cast<uint64_t>(int64_t(b)));
+            }
+            const int in_group = popc64(peers & lanes_below(lane));
+            const int so_far = wcnt[wave][digit];
+            rank[r] = so_far + in_group;
+            wave_lds_sync();
+            if (in && in_group == 0) wcnt[wave][digit] = static_cast<uint16_t>(so_far + popc64(peers));
+            wave_lds_sync();
+        }
+    }
+    int32_t row[ITEMS];
+    if (wave_first < tile_n) {
+        RowWindow window(indptr, sizes[0], base + wave_first);
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            const int i = wave_first + r * kWave + lane;
+            row[r] = r < items && wave_first + r * kWave < tile_n ? window.rows(base + i, i < tile_n) : 0;
+        }
+    }
+    __syncthreads();
+    int cnt[PER];
+    sum = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        cnt[q] = 0;
+#pragma unroll
+        for (int v = 0; v < WAVES; ++v) {
+            const int c = wcnt[v][tid * PER + q];
+            wcnt[v][tid * PER + q] = static_cast<uint16_t>(cnt[q]);
+            cnt[q] += c;
+        }
+        sum += cnt[q];
+    }
+    if constexpr (SELF) {                                  // few edges: each straight to its place
+#pragma unroll
+        for (int q = 0; q < PER; ++q) gbase[tid * PER + q] = out0[q];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            if (r < items && wave_first + r * kWave + lane < tile_n) {
+                const int digit = (key[r] >> shift) & (kOrderDigits - 1);
+                const int o = gbase[digit] + wcnt[wave][digit] + rank[r];
+                key_out[o] = static_cast<uint16_t>(key[r] & low);
+                row_out[o] = row[r];
+                if (WEIGHTED) w_out[o] = w[r];
+            }
+        }
+        return;
+    }
+    ex = block_excl_scan<WAVES>(sum, &total, scan_lds);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        first[tid * PER + q] = ex;
+        gbase[tid * PER + q] = out0[q] - ex;
+        ex += cnt[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        if (r < items && wave_first + r * kWave + lane < tile_n) {
+            const int digit = (key[r] >> shift) & (kOrderDigits - 1);
+            const int p = first[digit] + wcnt[wave][digit] + rank[r];
+            skeys[p] = key[r];
+            srows[p] = row[r];
+            if (WEIGHTED) sw[p] = w[r];
+        }
+    }
+    __syncthreads();
+    for (int p = tid; p < tile_n; p += THREADS) {
+        const uint32_t k = skeys[p];
+        const int o = gbase[(k >> shift) & (kOrderDigits - 1)] + p;
+        key_out[o] = static_cast<uint16_t>(k & low);
+        row_out[o] = srows[p];
+        if (WEIGHTED) w_out[o] = sw[p];
+    }
+}
+
+// A bucket's sources are cut into ranges of up to kSub, and a bucket of more than kBucketChunk edges is cut into chunks: a
+// workgroup takes one (bucket, range, chunk) after the other, `grid` apart.  It reads the keys of the whole bucket, counts
+// its range's edges per source, which gives the places, and places its own chunk's: the chunk's edges in order are cut
+// among the wavefronts, so that counts per wavefront and running places keep the order.  A range in one chunk is put
+// together in LDS and stored coalesced (single 4-byte stores go at about 100 G/s: 4.3 M of them 40 us).
+template <bool WEIGHTED>
+__global__ void __launch_bounds__(kBucketThreads)
+k_order_buckets(const uint16_t *__restrict__ keys, const int32_t *__restrict__ rows, const float *__restrict__ w, const int64_t *__restrict__ sizes,
+                int64_t cap, const int32_t *__restrict__ totals, int grid, int32_t *__restrict__ col_ptr, int32_t *__restrict__ row_out,
+                float *__restrict__ w_out) {
+    __shared__ uint32_t pairs[kBucketWaves][kSub / 2];     // two 16-bit counts a word: edges per wavefront and source
+    __shared__ int base_of[kSub];                          // of the other chunks; then the first place of the source's edges
+    __shared__ int32_t stage[kStageWords];                 // edges of the range; or, in several chunks, counts of the chunks before
+    __shared__ int start_of[kOrderDigits + 1], item_of[kOrderDigits + 1];        // first edge and first item of every bucket
+    __shared__ int lds[kBucketWaves];
+    __shared__ int below_of[kBucketWaves];
+    static_assert(kOrderDigits == kBucketThreads, "a bucket per thread");
+    static_assert(kSub == 4 * kBucketThreads, "four sources per thread");
+    constexpr int kStage = WEIGHTED ? kStageWords / 2 : kStageWords;
+    uint16_t (&wcnt)[kBucketWaves][kSub] = reinterpret_cast<uint16_t (&)[kBucketWaves][kSub]>(pairs);
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t num_src = sizes[1];
+    const int shift = order_shift(num_src);
+    const int range_bits = shift > kSubBits ? shift - kSubBits : 0;
+    const int subs = 1 << (shift < kSubBits ? shift : kSubBits);           // sources of a range
+    const int used = num_src > 0 ? static_cast<int>((num_src - 1) >> shift) + 1 : 0;      // buckets
+    if (blockIdx.x == 0 && tid == 0) col_ptr[num_src] = static_cast<int32_t>(sizes[2] < cap ? sizes[2] : cap);
+    int items;
+    {
+        const int mine = totals[tid];
+        int total;
+        start_of[tid] = block_excl_scan<kBucketWaves>(mine, &total, lds);
+        if (tid == 0) start_of[kOrderDigits] = total;
+        const int chunks = tid < used ? (mine > kBucketChunk ? (mine + kBucketChunk - 1) / kBucketChunk : 1) : 0;
+        item_of[tid] = block_excl_scan<kBucketWaves>(chunks << range_bits, &items, lds);
+        if (tid == 0) item_of[kOrderDigits] = items;
+    }
+    __syncthreads();
+    for (int item = static_cast<int>(blockIdx.x); item < items; item += grid) {
+        int b = 0;                                         // the last bucket that begins at or before the item
+#pragma unroll
+        for (int h = kOrderDigits / 2; h > 0; h >>= 1)
+            if (item_of[b + h] <= item) b += h;
+        b = __builtin_amdgcn_readfirstlane(b);
+        const int k = item - item_of[b];
+        const int range = k & ((1 << range_bits) - 1), chunk = k >> range_bits;
+        const int start = start_of[b], n = start_of[b + 1] - start;
+        const bool whole = n <= kBucketChunk;
+        for (int q = lane; 2 * q < subs + 2; q += kWave) pairs[wave][q < kSub / 2 ? q : 0] = 0;
+        for (int q = tid; q < subs; q += kBucketThreads) {
+            base_of[q] = 0;
+            if (!whole) stage[q] = 0;
+        }
+        __syncthreads();
+        const int c0 = chunk * kBucketChunk, c1 = n - c0 < kBucketChunk ? n : c0 + kBucketChunk;
+        const int share = ((c1 - c0 + kBucketWaves - 1) / kBucketWaves + kWave - 1) / kWave * kWave;
+        const int my0 = c0 + wave * share < c1 ? c0 + wave * share : c1, my1 = my0 + share < c1 ? my0 + share : c1;
+        const uint16_t *bk = keys + start;
+        constexpr int U = 8;
+        constexpr int kNone = -(1 << 16);                  // in no range
+        int below = 0;                                     // edges of the ranges before
+        for (int i0 = my0; i0 < my1; i0 += U * kWave) {
+            int key[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * kWave + lane;
+                key[u] = i < my1 ? bk[i] : kNone;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int r = key[u] >> kSubBits;
+                if (r == range) atomicAdd(&pairs[wave][(key[u] & (kSub - 1)) >> 1], (key[u] & 1) ? 0x10000u : 1u);
+                below += r >= 0 && r < range ? 1 : 0;
+            }
+        }
+        for (int i0 = 0; !whole && i0 < n; i0 += U * kBucketThreads) {         // the other chunks
+            int key[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * kBucketThreads + tid;
+                key[u] = i < n && (i < c0 || i >= c1) ? bk[i] : kNone;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int r = key[u] >> kSubBits, d = key[u] & (kSub - 1);
+                if (r == range) {
+                    atomicAdd(&base_of[d], 1);
+                    if (i0 + u * kBucketThreads + tid < c0) atomicAdd(&stage[d], 1);
+                }
+                below += r >= 0 && r < range ? 1 : 0;
+            }
+        }
+        below = wave_sum(below);
+        if (lane == 0) below_of[wave] = below;
+        __syncthreads();
+        int held, first = start;                           // the range's edges and the first one's place
+        {
+            const int d = 4 * tid;
+            int all[4] = {0, 0, 0, 0};
+            if (d < subs) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    uint32_t run = 0;                      // both halves: a chunk's edges fit 16 bits
+#pragma unroll
+                    for (int v = 0; v < kBucketWaves; ++v) {
+                        const uint32_t c = pairs[v][2 * tid + h];
+                        pairs[v][2 * tid + h] = run;
+                        run += c;
+                    }
+                    all[2 * h] = static_cast<int>(run & 0xFFFF);
+                    all[2 * h + 1] = static_cast<int>(run >> 16);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) all[q] = d + q < subs ? all[q] + base_of[d + q] : 0;      // (ranges of one or two sources)
+            int at = block_excl_scan<kBucketWaves>((all[0] + all[1]) + (all[2] + all[3]), &held, lds);
+#pragma unroll
+            for (int v = 0; v < kBucketWaves; ++v) first += below_of[v];
+            const int64_t source = (int64_t(b) << shift) + (int64_t(range) << kSubBits) + d;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (d + q < subs) {
+                    if (chunk == 0 && source + q < num_src) col_ptr[source + q] = first + at;
+                    base_of[d + q] = at + (whole ? 0 : stage[d + q]);
+                }
+                at += all[q];
+            }
+        }
+        __syncthreads();
+        // every wavefront its own edges, in order
+        const bool staged = whole && held <= kStage;
+        const int32_t *br = rows + start;
+        const float *bw = w + start;
+        for (int i0 = my0; i0 < my1; i0 += U * kWave) {
+            int key[U];
+            int32_t row[U];
+            float weight[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * kWave + lane;
+                key[u] = i < my1 ? bk[i] : kNone;
+                row[u] = i < my1 ? br[i] : 0;
+                weight[u] = WEIGHTED && i < my1 ? bw[i] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool in = (key[u] >> kSubBits) == range;
+                uint64_t peers = ballot64(in);
+                if (!peers) continue;
+                const int d = key[u] & (kSub - 1);
+#pragma unroll
+                for (int bit = 0; bit < kSubBits; ++bit) {
+                    const int m = __builtin_amdgcn_sbfe(d, bit, 1);            // all ones or zero
+                    peers &= ~(ballot64(m != 0) ^ static_cast<uint64_t>(int64_t(m)));
+                }
+                const int in_group = popc64(peers & lanes_below(lane));
+                const int so_far = wcnt[wave][d];
+                const int o = base_of[d] + so_far + in_group;
+                wave_lds_sync();
+                if (in && in_group == 0) wcnt[wave][d] = static_cast<uint16_t>(so_far + popc64(peers));
+                wave_lds_sync();
+                if (in && staged) {
+                    stage[o] = row[u];
+                    if (WEIGHTED) stage[kStage + o] = __float_as_int(weight[u]);
+                } else if (in) {
+                    row_out[first + o] = row[u];
+                    if (WEIGHTED) w_out[first + o] = weight[u];
+                }
+            }
+        }
+        __syncthreads();
+        if (staged) {
+            for (int q = tid; q < held; q += kBucketThreads) {
+                row_out[first + q] = stage[q];
+                if (WEIGHTED) w_out[first + q] = __int_as_float(stage[kStage + q]);
+            }
+            __syncthreads();                               // stage[] is the next item's
+        }
+    }
+}
+
+}  // namespace
+
+// Sources up to which the order is made this way: 16-bit keys and 8 ranges a bucket.
+bool can_order_edges(int64_t src_cap) { return src_cap <= (int64_t(1) << 22); }
+
+// entries of bwd.hist for blocks of at most nnz_cap edges
+int64_t order_hist_len(int64_t nnz_cap) { return kOrderDigits * std::max<int64_t>(radix_blocks(nnz_cap), kRadixSelfBlocks); }
+
+// Edges of block b by source into rows_out (destination rows), w_out (weights, if edge_w is given) and col_ptr.
+int order_edges_by_source(mqg_ctx *ctx, const mqg_block *b, const float *edge_w, int32_t *col_ptr, int32_t *rows_out, float *w_out, hipStream_t s) {
+    const int64_t cap = b->cap_nnz;
+    const RadixBufs &t = ctx->bwd;
+    uint16_t *keys = reinterpret_cast<uint16_t *>(t.keys[0]);
+    int32_t *rows = t.vals[0];
+    float *w = reinterpret_cast<float *>(t.keys[1]);
+    // up to kRadixSelfBlocks tiles of kBlock threads without a scan launch; more edges in tiles of kOrderThreads
+    const bool self = cap <= int64_t(kRadixTile) * kRadixSelfBlocks;
+    const int items = self ? radix_items(cap) : kRadixItems;
+    const int nblocks = static_cast<int>(std::max<int64_t>(1, ceil_div(cap, int64_t(self ? kBlock : kOrderThreads) * items)));
+    const int grid = self ? nblocks : xcd_grid(nblocks);
+    if (self)
+        MQG_LAUNCH(ctx, "k_order_hist", s, (k_order_hist<kBlock><<<grid, kBlock, 0, s>>>(b->indices, b->sizes, cap, t.hist, nblocks, items, 1)));
+    else
+        MQG_LAUNCH(ctx, "k_order_hist", s, (k_order_hist<kOrderThreads><<<grid, kOrderThreads, 0, s>>>(b->indices, b->sizes, cap, t.hist, nblocks, items, 0)));
+    if (!self) {
+        int rc = launch_radix_scan(ctx, t.hist, nblocks, kOrderDigits, t.totals, cap, &b->sizes[2], kOrderThreads * items, s);
+        if (rc != MQG_OK) return rc;
+    }
+#define MQG_ORDER(SELF, W, T)                                                                                            \
+    MQG_LAUNCH(ctx, "k_order_scatter", s,                                                                                \
+               (k_order_scatter<SELF, W, T><<<grid, T, 0, s>>>(b->indices, b->indptr, edge_w, b->sizes, cap, t.hist, t.totals, nblocks, items, keys, rows, w)))
+    if (self && edge_w) MQG_ORDER(true, true, kBlock);
+    else if (self) MQG_ORDER(true, false, kBlock);
+    else if (edge_w) MQG_ORDER(false, true, kOrderThreads);
+    else MQG_ORDER(false, false, kOrderThreads);
+#undef MQG_ORDER
+    // one workgroup per bucket, range and chunk if there are fewer of them than kBucketGrid
+    const int shift = order_shift(b->cap_src);
+    const int64_t pieces = (int64_t(kOrderDigits) + cap / kBucketChunk) << (shift > kSubBits ? shift - kSubBits : 0);
+    const int bgrid = static_cast<int>(std::min<int64_t>(pieces, kBucketGrid));
+    if (edge_w)
+        MQG_LAUNCH(ctx, "k_order_buckets", s,
+                   (k_order_buckets<true><<<bgrid, kBucketThreads, 0, s>>>(keys, rows, w, b->sizes, cap, t.totals, bgrid, col_ptr, rows_out, w_out)));
+    else
+        MQG_LAUNCH(ctx, "k_order_buckets", s,
+                   (k_order_buckets<false><<<bgrid, kBucketThreads, 0, s>>>(keys, rows, nullptr, b->sizes, cap, t.totals, bgrid, col_ptr, rows_out, nullptr)));
+    return MQG_OK;
+}
+
+}  // namespace mqg

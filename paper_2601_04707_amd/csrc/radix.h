@@ -5,6 +5,22 @@
 
 namespace mqg {
 
+// Tiles that hold any of n keys.
+__device__ __forceinline__ int live_tiles(int64_t n, int tile) { return static_cast<int>((n + tile - 1) / tile); }
+
+// An XCD's workgroups (every eighth) take neighbouring tiles: their runs of one digit, and their counts of it,
+// share cache lines, and the scatter finds in its L2 the keys that the histogram read (histograms of the seven
+// passes of a 4.3 M-edge backward 77 -> 71 us, of a degree sort of 1 M nodes 23 -> 19).  The live tiles are dealt, not the
+// capacity's: with half of it in use four of the XCDs went without work (a pass of 4.3 M keys in room for 8.1 M, scatter 52 -> 36 us).
+// A result of kNoTile: no tile for this workgroup.  The grid is the number of tiles rounded up to a multiple of eight.
+constexpr int kNoTile = 0x7FFFFFFF;
+__device__ __forceinline__ int xcd_tile(int live) {
+    const int share = (live + 7) >> 3, k = static_cast<int>(blockIdx.x >> 3);
+    const int me = static_cast<int>(blockIdx.x & 7) * share + k;
+    return k < share && me < live ? me : kNoTile;
+}
+__host__ inline int xcd_grid(int nblocks) { return (nblocks + 7) & ~7; }
+
 constexpr int kRadixItems = 8;                      // rounds per tile
 constexpr int kRadixTile = kBlock * kRadixItems;     // keys per workgroup
 constexpr int kScanTile = 1024;                      // elements per workgroup in the generic scan
@@ -20,6 +36,12 @@ int radix_key_bits(uint64_t max_key);                // significant bits of the 
 int64_t radix_blocks(int64_t n_cap);
 int64_t radix_hist_len(int64_t n_cap, int bits);     // table of one sort of exactly this shape
 int64_t radix_hist_len_max(int64_t n_cap);            // enough for every sort of at most n_cap keys, any key width
+
+int radix_items(int64_t n_cap);                       // rounds per tile
+// exclusive scan of every row of the [digits][nblocks] table, in place, up to the last tile of min(n_cap, *n_dev) keys, and the
+// rows' totals
+int launch_radix_scan(mqg_ctx *ctx, int32_t *hist, int nblocks, int digits, int32_t *totals, int64_t n_cap, const int64_t *n_dev, int tile,
+                      hipStream_t s);
 
 // exclusive scan of data[0..n) in place; tile_sums needs ceil(n / kScanTile) + 1 ints
 int device_scan(mqg_ctx *ctx, int32_t *data, int64_t n, int32_t *tile_sums, hipStream_t s);

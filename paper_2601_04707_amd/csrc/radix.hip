@@ -25,15 +25,6 @@ namespace mqg {
 
 namespace {
 
-// An XCD's workgroups (every eighth) take neighbouring tiles: their runs of one digit, and their counts of it,
-// share cache lines, and the scatter finds in its L2 the keys that the histogram read (histograms of the seven
-// passes of a 4.3 M-edge backward 77 -> 71 us, of a degree sort of 1 M nodes 23 -> 19).  The grid is nblocks
-// rounded up to a multiple of eight; a result of nblocks or more has no tile.
-__device__ __forceinline__ int xcd_tile(int nblocks) {
-    return static_cast<int>(blockIdx.x & 7) * ((nblocks + 7) >> 3) + static_cast<int>(blockIdx.x >> 3);
-}
-__host__ inline int xcd_grid(int nblocks) { return (nblocks + 7) & ~7; }
-
 // tile_major: the table is [tile][digit] (for the scatter that adds the counts up itself), otherwise
 // [digit][tile] (so that a scan of every row gives every tile its places among the keys of the digit).
 // DB = bits per digit.
@@ -43,9 +34,9 @@ k_radix_hist(const uint32_t *__restrict__ keys, int64_t n, const int64_t *__rest
              int32_t *__restrict__ hist, int nblocks, int items, int tile_major) {
     constexpr int D = 1 << DB, PER = D / kBlock;
     __shared__ int h[D];
-    const int me = tile_major ? static_cast<int>(blockIdx.x) : xcd_tile(nblocks);
-    if (me >= nblocks) return;
     if (n_dev && *n_dev < n) n = *n_dev;
+    const int me = tile_major ? static_cast<int>(blockIdx.x) : xcd_tile(live_tiles(n, kBlock * items));
+    if (me >= nblocks) return;
 #pragma unroll
     for (int q = 0; q < PER; ++q) h[q * kBlock + threadIdx.x] = 0;
     __syncthreads();
@@ -78,9 +69,11 @@ k_radix_hist(const uint32_t *__restrict__ keys, int64_t n, const int64_t *__rest
 // launches, three on large ones: 4.3 M keys by 8 bits 12.9 -> 7.6 us, 100 M 63 -> 48, 1 M 13.3 -> 7.5.)
 constexpr int kScanRounds = 8;
 __global__ void __launch_bounds__(kBlock)
-k_radix_scan(int32_t *__restrict__ hist, int nblocks, int32_t *__restrict__ totals) {
+k_radix_scan(int32_t *__restrict__ hist, int stride, int32_t *__restrict__ totals, int64_t n, const int64_t *__restrict__ n_dev, int tile) {
+    if (n_dev && *n_dev < n) n = *n_dev;
+    const int nblocks = live_tiles(n, tile);
     __shared__ int lds[2][kWavesPerBlock];
-    int32_t *row = hist + int64_t(blockIdx.x) * nblocks;
+    int32_t *row = hist + int64_t(blockIdx.x) * stride;
     const int mine = (static_cast<int>(threadIdx.x) >> 6) * (kWave * kScanRounds) + lane_id();
     const int wave = threadIdx.x >> 6;
     int next[kScanRounds];
@@ -186,7 +179,7 @@ k_radix_scatter(const uint32_t *__restrict__ keys_in, RadixPayload payload, int6
     const int lane = lane_id();
     const int wave = tid >> 6;
     if (n_dev && *n_dev < n) n = *n_dev;
-    const int me = SELF ? static_cast<int>(blockIdx.x) : xcd_tile(nblocks);
+    const int me = SELF ? static_cast<int>(blockIdx.x) : xcd_tile(live_tiles(n, kBlock * items));
     if (me >= nblocks) return;
     const int64_t base = int64_t(me) * kBlock * items;
     if (base >= n) return;
@@ -368,8 +361,13 @@ int device_scan(mqg_ctx *ctx, int32_t *data, int64_t n, int32_t *tile_sums, hipS
 
 // rounds per tile: 8, fewer for small inputs (a round is a serial step of a workgroup; 32 tiles of
 // one round sort 8 k keys faster than 4 tiles of eight)
-static int radix_items(int64_t n_cap) {
+int radix_items(int64_t n_cap) {
     return static_cast<int>(std::min<int64_t>(kRadixItems, std::max<int64_t>(1, ceil_div(n_cap, int64_t(kBlock) * kRadixSelfBlocks))));
+}
+
+int launch_radix_scan(mqg_ctx *ctx, int32_t *hist, int nblocks, int digits, int32_t *totals, int64_t n_cap, const int64_t *n_dev, int tile, hipStream_t s) {
+    MQG_LAUNCH(ctx, "k_radix_scan", s, (k_radix_scan<<<digits, kBlock, 0, s>>>(hist, nblocks, totals, n_cap, n_dev, tile)));
+    return MQG_OK;
 }
 
 template <int DB>
@@ -391,7 +389,8 @@ static int radix_sort_pairs_t(mqg_ctx *ctx, const uint32_t *keys_in, RadixPayloa
             MQG_LAUNCH(ctx, "k_radix_scatter", s,
                        (k_radix_scatter<true, DB, kRadixItems><<<nblocks, kBlock, 0, s>>>(kin, pay, n_cap, n_dev, shift, b.hist, b.totals, nblocks, items, b.keys[out], b.vals[out])));
         } else {
-            MQG_LAUNCH(ctx, "k_radix_scan", s, (k_radix_scan<<<D, kBlock, 0, s>>>(b.hist, nblocks, b.totals)));
+            int rc = launch_radix_scan(ctx, b.hist, nblocks, D, b.totals, n_cap, n_dev, kBlock * items, s);
+            if (rc != MQG_OK) return rc;
             MQG_LAUNCH(ctx, "k_radix_scatter", s,
                        (k_radix_scatter<false, DB, kRadixItems><<<xcd_grid(nblocks), kBlock, 0, s>>>(kin, pay, n_cap, n_dev, shift, b.hist, b.totals, nblocks, items, b.keys[out], b.vals[out])));
         }

@@ -11,7 +11,8 @@
 //
 // One partition and one pass over each bucket in place of two or three passes of a radix sort (a histogram, a scan and a
 // scatter each), a launch for the destination rows, a bisection for col_ptr and, weighted, a gather of the
-// weights.  Measured, all launches: 4.3 M edges into 1.35 M sources MEASURE.
+// weights.  All launches: 4.3 M edges of 295 k rows into 1.35 M sources 191 -> 99 us (9 + 5 + 33 + 52); 245 k edges into
+// 134 k 52 -> 35; 255 k weighted ones into 109 k 49 -> 33.
 // How many leading bits there are depends on the number of sources, which only the device knows.
 #include <algorithm>
 
@@ -25,7 +26,10 @@ namespace {
 
 constexpr int kOrderBits = 9;                        // of the partition's digit
 constexpr int kOrderDigits = 1 << kOrderBits;
-constexpr int kOrderThreads = 512;                   // workgroup of a tile of many edges; few edges: kBlock
+// Workgroups of 512 cut more than kLargeOrder edges into tiles of 4,096: half the counts to scan and runs twice as long.  Fewer
+// edges take tiles of 2,048, more workgroups (histogram, scan and partition of 245 k edges 22.0 and 23.7 us, of 4.3 M 75 and 72).
+constexpr int kOrderThreads = 512;
+constexpr int64_t kLargeOrder = int64_t(1) << 20;
 constexpr int kSubBits = 11;                         // of a source within its workgroup's range
 constexpr int kSub = 1 << kSubBits;
 constexpr int kBucketThreads = 512;
@@ -282,7 +286,10 @@ k_order_scatter(const int32_t *__restrict__ indices, const int32_t *__restrict__
 // workgroup takes one (bucket, range, chunk) after the other, `grid` apart.  It reads the keys of the whole bucket, counts
 // its range's edges per source, which gives the places, and places its own chunk's: the chunk's edges in order are cut
 // among the wavefronts, so that counts per wavefront and running places keep the order.  A range in one chunk is put
-// together in LDS and stored coalesced (single 4-byte stores go at about 100 G/s: 4.3 M of them 40 us).
+// together in LDS and stored coalesced.  Bound by what a wavefront does per 64 keys, of which the other ranges' are done for
+// nothing: ballots over all bits of every key in place of the places taken and corrected 79 us, now 52 (sources of like
+// degree 38); chunks of 8,192 edges 55, of 32,768 63 (the crowded buckets of earlier frontiers hold 100 k edges, which every
+// chunk's workgroup counts); digits of 8 and 10 bits in the partition, with 4 ranges and 1, 14 and 7 us more in all.
 template <bool WEIGHTED>
 __global__ void __launch_bounds__(kBucketThreads)
 k_order_buckets(const uint16_t *__restrict__ keys, const int32_t *__restrict__ rows, const float *__restrict__ w, const int64_t *__restrict__ sizes,
@@ -297,7 +304,6 @@ k_order_buckets(const uint16_t *__restrict__ keys, const int32_t *__restrict__ r
     static_assert(kOrderDigits == kBucketThreads, "a bucket per thread");
     static_assert(kSub == 4 * kBucketThreads, "four sources per thread");
     constexpr int kStage = WEIGHTED ? kStageWords / 2 : kStageWords;
-    uint16_t (&wcnt)[kBucketWaves][kSub] = reinterpret_cast<uint16_t (&)[kBucketWaves][kSub]>(pairs);
     const int tid = threadIdx.x, lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t num_src = sizes[1];
@@ -425,21 +431,27 @@ k_order_buckets(const uint16_t *__restrict__ keys, const int32_t *__restrict__ r
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
+                // Every lane takes the next place of its source.  Lanes of the same source take them in any order: a lane
+                // that did not get the first place free tells that there are some, and then ballots put them in order.
                 const bool in = (key[u] >> kSubBits) == range;
-                uint64_t peers = ballot64(in);
-                if (!peers) continue;
-                const int d = key[u] & (kSub - 1);
-#pragma unroll
-                for (int bit = 0; bit < kSubBits; ++bit) {
-                    const int m = __builtin_amdgcn_sbfe(d, bit, 1);            // all ones or zero
-                    peers &= ~(ballot64(m != 0) ^ static_cast<uint64_t>(int64_t(m)));
+                const uint64_t live = ballot64(in);
+                if (!live) continue;
+                const int d = key[u] & (kSub - 1), half = (d & 1) << 4;
+                int o = 0;
+                bool later = false;
+                if (in) {
+                    const uint32_t so_far = pairs[wave][d >> 1] >> half & 0xFFFF;
+                    wave_lds_sync();
+                    const uint32_t got = atomicAdd(&pairs[wave][d >> 1], 1u << half) >> half & 0xFFFF;
+                    later = got != so_far;
+                    o = base_of[d] + static_cast<int>(so_far);
                 }
-                const int in_group = popc64(peers & lanes_below(lane));
-                const int so_far = wcnt[wave][d];
-                const int o = base_of[d] + so_far + in_group;
-                wave_lds_sync();
-                if (in && in_group == 0) wcnt[wave][d] = static_cast<uint16_t>(so_far + popc64(peers));
-                wave_lds_sync();
+                for (uint64_t left = ballot64(later); left;) {                  // one source after the other
+                    const int source = static_cast<int>(readlane32(static_cast<uint32_t>(d), __ffsll(static_cast<long long>(left)) - 1));
+                    const uint64_t peers = ballot64(in && d == source);
+                    if (d == source) o += popc64(peers & lanes_below(lane));
+                    left &= ~peers;
+                }
                 if (in && staged) {
                     stage[o] = row[u];
                     if (WEIGHTED) stage[kStage + o] = __float_as_int(weight[u]);
@@ -475,26 +487,34 @@ int order_edges_by_source(mqg_ctx *ctx, const mqg_block *b, const float *edge_w,
     uint16_t *keys = reinterpret_cast<uint16_t *>(t.keys[0]);
     int32_t *rows = t.vals[0];
     float *w = reinterpret_cast<float *>(t.keys[1]);
-    // up to kRadixSelfBlocks tiles of kBlock threads without a scan launch; more edges in tiles of kOrderThreads
-    const bool self = cap <= int64_t(kRadixTile) * kRadixSelfBlocks;
-    const int items = self ? radix_items(cap) : kRadixItems;
-    const int nblocks = static_cast<int>(std::max<int64_t>(1, ceil_div(cap, int64_t(self ? kBlock : kOrderThreads) * items)));
+    // up to kRadixSelfBlocks tiles: no scan launch
+    const bool self = cap <= int64_t(kRadixTile) * kRadixSelfBlocks, large = cap > kLargeOrder;
+    const int threads = large ? kOrderThreads : kBlock;
+    const int items = radix_items(cap);
+    const int nblocks = static_cast<int>(std::max<int64_t>(1, ceil_div(cap, int64_t(threads) * items)));
     const int grid = self ? nblocks : xcd_grid(nblocks);
-    if (self)
-        MQG_LAUNCH(ctx, "k_order_hist", s, (k_order_hist<kBlock><<<grid, kBlock, 0, s>>>(b->indices, b->sizes, cap, t.hist, nblocks, items, 1)));
+    if (large)
+        MQG_LAUNCH(ctx, "k_order_hist", s, (k_order_hist<kOrderThreads><<<grid, threads, 0, s>>>(b->indices, b->sizes, cap, t.hist, nblocks, items, 0)));
     else
-        MQG_LAUNCH(ctx, "k_order_hist", s, (k_order_hist<kOrderThreads><<<grid, kOrderThreads, 0, s>>>(b->indices, b->sizes, cap, t.hist, nblocks, items, 0)));
+        MQG_LAUNCH(ctx, "k_order_hist", s, (k_order_hist<kBlock><<<grid, threads, 0, s>>>(b->indices, b->sizes, cap, t.hist, nblocks, items, self ? 1 : 0)));
     if (!self) {
-        int rc = launch_radix_scan(ctx, t.hist, nblocks, kOrderDigits, t.totals, cap, &b->sizes[2], kOrderThreads * items, s);
+        int rc = launch_radix_scan(ctx, t.hist, nblocks, kOrderDigits, t.totals, cap, &b->sizes[2], threads * items, s);
         if (rc != MQG_OK) return rc;
     }
-#define MQG_ORDER(SELF, W, T)                                                                                            \
-    MQG_LAUNCH(ctx, "k_order_scatter", s,                                                                                \
-               (k_order_scatter<SELF, W, T><<<grid, T, 0, s>>>(b->indices, b->indptr, edge_w, b->sizes, cap, t.hist, t.totals, nblocks, items, keys, rows, w)))
-    if (self && edge_w) MQG_ORDER(true, true, kBlock);
-    else if (self) MQG_ORDER(true, false, kBlock);
-    else if (edge_w) MQG_ORDER(false, true, kOrderThreads);
-    else MQG_ORDER(false, false, kOrderThreads);
+#define MQG_ORDER(SELF, T)                                                                                                                  \
+    do {                                                                                                                                    \
+        if (edge_w)                                                                                                                         \
+            MQG_LAUNCH(ctx, "k_order_scatter", s,                                                                                           \
+                       (k_order_scatter<SELF, true, T><<<grid, T, 0, s>>>(b->indices, b->indptr, edge_w, b->sizes, cap, t.hist, t.totals,    \
+                                                                          nblocks, items, keys, rows, w)));                                 \
+        else                                                                                                                                \
+            MQG_LAUNCH(ctx, "k_order_scatter", s,                                                                                           \
+                       (k_order_scatter<SELF, false, T><<<grid, T, 0, s>>>(b->indices, b->indptr, edge_w, b->sizes, cap, t.hist, t.totals,   \
+                                                                           nblocks, items, keys, rows, w)));                                \
+    } while (0)
+    if (self) MQG_ORDER(true, kBlock);
+    else if (large) MQG_ORDER(false, kOrderThreads);
+    else MQG_ORDER(false, kBlock);
 #undef MQG_ORDER
     // one workgroup per bucket, range and chunk if there are fewer of them than kBucketGrid
     const int shift = order_shift(b->cap_src);

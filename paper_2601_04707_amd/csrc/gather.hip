@@ -4,12 +4,12 @@
 // by the kernel itself) when it is not.
 //
 //   k_classify        slot_of lookup, ballot-compacted (output row, source row) lists for hits and
-//                     misses, one atomic per tile of ids and list
-//   k_gather_rows<.,0> hits:   HBM cache -> HBM output, widest aligned loads; rows of up to 64 vectors
+//                     misses, one atomic per tile of ids
+//   k_gather_rows     hits: HBM cache -> HBM output, widest aligned loads; rows of up to 64 vectors
 //                     as one flat sequence of vectors (every lane carries one), longer rows two at a
-//                     time by a wavefront
-//   k_gather_rows<.,1> misses: feature matrix -> HBM output (same code, separate symbol so that
-//                     profiles tell the HBM-bound from the link-bound launch)
+//                     time by a wavefront; misses: feature matrix -> HBM output.  One launch for both, the few
+//                     workgroups that keep the host link busy first; in halves, and while profiling, a launch
+//                     each (<., 0> hits, <., 1> misses, so that profiles tell the HBM-bound from the link-bound)
 //   k_gather_direct   no cache: every row straight from the feature matrix
 #include <hip/hip_ext.h>
 
@@ -23,7 +23,13 @@ namespace mqg {
 
 namespace {
 
-// Stats of a gather without a cache: every valid id is a row served from feats.  counters[3] holds
+// Words of a context's (or the static array's) counters; all but the last two are zero between gathers.
+constexpr int kCountSplit = 0;         // hits, misses and tiles so far, see classify_tiles
+constexpr int kCountBad = 1;           // ids outside the graph
+constexpr int kCountMissed = 2;        // finished workgroups that copy misses
+constexpr int kCountHits = 4, kCountMisses = 5;    // entries of the lists of the last split; misses are zero again once they are copied
+
+// Stats of a gather without a cache: every valid id is a row served from feats.  counters[kCountBad] holds
 // the number of ids outside the graph that the copy skipped; it is left at zero for the next call.
 __global__ void k_direct_stats(int64_t *stats, const int64_t *num_ids, int64_t cap, unsigned long long *counters) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -31,8 +37,8 @@ __global__ void k_direct_stats(int64_t *stats, const int64_t *num_ids, int64_t c
         if (n > cap) n = cap;
         if (n < 0) n = 0;
         if (counters) {
-            n -= static_cast<int64_t>(counters[3]);
-            counters[3] = 0;
+            n -= static_cast<int64_t>(counters[kCountBad]);
+            counters[kCountBad] = 0;
         }
         if (stats) {
             stats[0] = 0;
@@ -42,35 +48,45 @@ __global__ void k_direct_stats(int64_t *stats, const int64_t *num_ids, int64_t c
 }
 
 // Splits the ids into a hit list (output row, cache slot) and a miss list (output row, node id).
-// A workgroup classifies a tile of 256 * ITEMS ids and reserves its share of both lists with one atomic
-// each: atomics on one address are served one after the other, at 13 ns, so more than 512 k ids go in tiles of
+// A workgroup classifies a tile of 256 * ITEMS ids and reserves its share of both lists with one atomic.  Atomics on one
+// address are served one after the other, at 13 ns, so more than 512 k ids go in tiles of
 // 4,096 (1.35 M ids: 41 -> 20 us); fewer keep tiles of 1,024, enough workgroups to hide the slot lookups (100 k ids
-// 7.9 us, in tiles of 4,096 14.3; level at 500 k with 16.5 and 17.5).  The number of ids decides, which only
+// 7.9 us, in tiles of 4,096 14.3; level at 500 k with 16.5 and 17.5), and up to 32 k ids go in tiles of 256.
+// The number of ids decides, which only
 // the device knows; the capacity is often twice that and more.  Positions inside a share come from ballots, so that
 // a wavefront writes consecutive entries.  The order of the list entries is arbitrary; the gather does not depend on
 // it.  An id outside [0, num_nodes) is never used as an index: it goes on neither list, so its output row stays
 // untouched and hits + misses fall short of the number of ids.
+// The word that the atomics go to holds the hits, the misses and the tiles so far, 21 bits each, and whoever adds the last
+// tile hands the numbers on.  In tiles of 4,096 it holds the hits and the tiles: there all that is no hit
+// goes on the miss list, so that the misses before a tile are the ids of the tiles before it less their hits; ids outside the
+// graph, and the places past the ids in the last tile, hold node -1, which the copy passes over.
 constexpr int64_t kClassifyLarge = int64_t(1) << 19;
+constexpr int64_t kClassifySmall = int64_t(1) << 15;
 struct ClassifyLds {
-    int totals[2][kWavesPerBlock];
+    int hits[kWavesPerBlock], misses[kWavesPerBlock];
     unsigned long long base[2];
 };
 template <int ITEMS, typename IdxT>
 __device__ __forceinline__ void classify_tiles(const IdxT *__restrict__ ids, int64_t n, const int32_t *__restrict__ slot_of, int64_t num_nodes,
                                                int2 *__restrict__ hit_list, int2 *__restrict__ miss_list,
-                                               unsigned long long *__restrict__ counters, ClassifyLds &lds) {
+                                               unsigned long long *__restrict__ counters, int64_t *__restrict__ stats, ClassifyLds &lds, int grid) {
     constexpr int kTile = kBlock * ITEMS;
-    int (&totals)[2][kWavesPerBlock] = lds.totals;
-    unsigned long long (&base)[2] = lds.base;
+    constexpr bool kHoles = ITEMS == 16;                   // more than kClassifyLarge ids
+    static_assert(kClassifyLarge < (1 << 21), "ids and tiles fit 21 bits");
     const int lane = lane_id();
     const int wave = static_cast<int>(threadIdx.x) >> 6;
-    for (int64_t t0 = int64_t(blockIdx.x) * kTile; t0 < n; t0 += int64_t(gridDim.x) * kTile) {
+    const int64_t tiles = n > 0 ? (n + kTile - 1) / kTile : 1;             // of no ids one, for the numbers
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += grid) {
+        const int64_t t0 = tile * kTile;
         int32_t id[ITEMS], slot[ITEMS];
+        int bad = 0;
 #pragma unroll
         for (int q = 0; q < ITEMS; ++q) {
             const int64_t i = t0 + q * kBlock + threadIdx.x;
             const int64_t raw = i < n ? static_cast<int64_t>(ids[i]) : -1;
-            id[q] = raw >= 0 && raw < num_nodes ? static_cast<int32_t>(raw) : -1;    // an id outside the graph is on neither list
+            id[q] = raw >= 0 && raw < num_nodes ? static_cast<int32_t>(raw) : -1;
+            bad += i < n && id[q] < 0 ? 1 : 0;
         }
 #pragma unroll
         for (int q = 0; q < ITEMS; ++q) slot[q] = id[q] >= 0 ? slot_of[id[q]] : -1;
@@ -78,36 +94,62 @@ __device__ __forceinline__ void classify_tiles(const IdxT *__restrict__ ids, int
 #pragma unroll
         for (int q = 0; q < ITEMS; ++q) {
             h += popc64(ballot64(slot[q] >= 0));
-            m += popc64(ballot64(slot[q] < 0 && id[q] >= 0));
+            m += popc64(ballot64(slot[q] < 0 && (kHoles || id[q] >= 0)));
         }
         if (lane == 0) {
-            totals[0][wave] = h;
-            totals[1][wave] = m;
+            lds.hits[wave] = h;
+            lds.misses[wave] = m;
         }
-        __syncthreads();
-        if (threadIdx.x < 2) {
-            int t = 0;
+        if (kHoles) {
+            // (a workgroup's bad ids are counted before its tile is; nearly always there are none)
+            if (bad) atomicAdd(&counters[kCountBad], static_cast<unsigned long long>(bad));
+            if (__syncthreads_or(bad)) __threadfence();
+        } else {
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) {
+            unsigned long long th = 0, tm = 0;
 #pragma unroll
-            for (int w = 0; w < kWavesPerBlock; ++w) t += totals[threadIdx.x][w];
-            if (t) base[threadIdx.x] = atomicAdd(&counters[threadIdx.x], static_cast<unsigned long long>(t));
+            for (int w = 0; w < kWavesPerBlock; ++w) {
+                th += static_cast<unsigned>(lds.hits[w]);
+                tm += static_cast<unsigned>(lds.misses[w]);
+            }
+            const unsigned long long before = atomicAdd(&counters[kCountSplit], kHoles ? th | 1ull << 32 : th | tm << 21 | 1ull << 42);
+            const unsigned long long tiles_before = before >> (kHoles ? 32 : 42), hits_before = before & (kHoles ? 0xFFFFFFFFull : 0x1FFFFFull);
+            const unsigned long long misses_before = kHoles ? tiles_before * kTile - hits_before : before >> 21 & 0x1FFFFFull;
+            lds.base[0] = hits_before;
+            lds.base[1] = misses_before;
+            if (static_cast<int64_t>(tiles_before) == tiles - 1) {
+                // the last tile: the words are left at zero, so that the call is self-contained and can be replayed from
+                // a recorded graph
+                const unsigned long long all = hits_before + th, missed = misses_before + tm;
+                const unsigned long long skipped = kHoles ? atomicExch(&counters[kCountBad], 0ull) : 0ull;
+                counters[kCountSplit] = 0;
+                counters[kCountHits] = all;
+                counters[kCountMisses] = missed;
+                if (stats) {
+                    stats[0] = static_cast<int64_t>(all);
+                    stats[1] = kHoles ? n - static_cast<int64_t>(all + skipped) : static_cast<int64_t>(missed);
+                }
+            }
         }
         __syncthreads();
-        unsigned long long ph = base[0], pm = base[1];
+        int64_t ph = static_cast<int64_t>(lds.base[0]), pm = static_cast<int64_t>(lds.base[1]);
         for (int w = 0; w < wave; ++w) {
-            ph += totals[0][w];
-            pm += totals[1][w];
+            ph += lds.hits[w];
+            pm += lds.misses[w];
         }
 #pragma unroll
         for (int q = 0; q < ITEMS; ++q) {
             const int i = static_cast<int>(t0 + q * kBlock + threadIdx.x);
-            const bool hit = slot[q] >= 0, miss = slot[q] < 0 && id[q] >= 0;
+            const bool hit = slot[q] >= 0, miss = !hit && (kHoles || id[q] >= 0);
             const uint64_t hb = ballot64(hit), mb = ballot64(miss);
             if (hit) hit_list[ph + popc64(hb & lanes_below(lane))] = make_int2(i, slot[q]);
             if (miss) miss_list[pm + popc64(mb & lanes_below(lane))] = make_int2(i, id[q]);
             ph += popc64(hb);
             pm += popc64(mb);
         }
-        __syncthreads();                                // totals[] and base[] are rewritten by the next tile
+        __syncthreads();                                // hits[], misses[] and base are rewritten by the next tile
     }
 }
 
@@ -115,33 +157,38 @@ template <typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_classify(const IdxT *__restrict__ ids, const int64_t *__restrict__ num_ids, int64_t cap,
            const int32_t *__restrict__ slot_of, int64_t num_nodes, int2 *__restrict__ hit_list,
-           int2 *__restrict__ miss_list, unsigned long long *__restrict__ counters) {
+           int2 *__restrict__ miss_list, unsigned long long *__restrict__ counters, int64_t *__restrict__ stats, int grid) {
     __shared__ ClassifyLds lds;
     int64_t n = *num_ids;
     if (n > cap) n = cap;
-    if (n > kClassifyLarge) classify_tiles<16>(ids, n, slot_of, num_nodes, hit_list, miss_list, counters, lds);
-    else classify_tiles<4>(ids, n, slot_of, num_nodes, hit_list, miss_list, counters, lds);
+    if (n > kClassifyLarge) classify_tiles<16>(ids, n, slot_of, num_nodes, hit_list, miss_list, counters, stats, lds, grid);
+    else if (n > kClassifySmall) classify_tiles<4>(ids, n, slot_of, num_nodes, hit_list, miss_list, counters, stats, lds, grid);
+    else classify_tiles<1>(ids, n, slot_of, num_nodes, hit_list, miss_list, counters, stats, lds, grid);
 }
 
 // Which rows to copy: entry r of a (output row, source row) list, or row ids[r] to output row r.
 // get() returns false for a row that must not be written (an id outside the feature matrix); the
 // source row is then 0, so that a load issued before the check stays inside the matrix.  skipped()
 // is called once per such row.
+template <bool HOLES>
 struct ListRows {
+    static constexpr bool kHoles = HOLES;        // entries without a row
     const int2 *list;
     __device__ __forceinline__ bool get(int64_t r, int64_t *src_row, int64_t *dst_row) const {
         int2 e = list[r];
-        *src_row = e.y;
+        *src_row = HOLES && e.y < 0 ? 0 : e.y;
         *dst_row = e.x;
-        return true;
+        return !HOLES || e.y >= 0;
     }
     __device__ __forceinline__ void skipped() const {}
 };
-template <typename IdxT>
+template <typename IdxT, bool IN_LDS>
 struct DirectRows {
+    static constexpr bool kHoles = false;
     const IdxT *ids;
     int64_t num_rows;                    // rows of the source matrix
-    unsigned long long *bad;             // counter of skipped rows, may be null
+    unsigned long long *bad;             // counter of skipped rows, may be null ...
+    int *bad_lds;                        // ... or the workgroup's own (IN_LDS)
     __device__ __forceinline__ bool get(int64_t r, int64_t *src_row, int64_t *dst_row) const {
         const int64_t id = static_cast<int64_t>(ids[r]);
         const bool ok = id >= 0 && id < num_rows;
@@ -150,7 +197,8 @@ struct DirectRows {
         return ok;
     }
     __device__ __forceinline__ void skipped() const {
-        if (bad) atomicAdd(bad, 1ull);
+        if (IN_LDS) atomicAdd(bad_lds, 1);
+        else if (bad) atomicAdd(bad, 1ull);
     }
 };
 
@@ -173,14 +221,15 @@ constexpr int kRowUnroll = 4;                            // row loads in flight 
 // Longer rows: all 64 lanes walk WR rows at a time, NCH 64-vector chunks of each, so that up to
 // eight loads per lane are issued before the first store (a row's last, partial chunk rides along
 // instead of trailing alone).  NCH is the number of chunks a row needs, at most four; loads are
-// unconditional (an index past the row re-reads its last vector), only the stores are predicated.
+// unconditional (an index past the row re-reads its last vector), only the stores are predicated; rows of a list with holes are
+// loaded if they are rows.
 template <typename VecT, int NCH, int WR, bool STREAM, typename Rows>
 __device__ __forceinline__ void copy_rows_wide(const Rows &rows, int64_t n, const char *__restrict__ src,
                                                int64_t src_stride_bytes, char *__restrict__ dst,
-                                               int64_t dst_stride_bytes, int vecs) {
+                                               int64_t dst_stride_bytes, int vecs, int vb, int nb) {
     const int lane = lane_id();
-    const int64_t wave0 = int64_t(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
-    const int64_t nwaves = int64_t(gridDim.x) * kWavesPerBlock;
+    const int64_t wave0 = int64_t(vb) * kWavesPerBlock + (threadIdx.x >> 6);
+    const int64_t nwaves = int64_t(nb) * kWavesPerBlock;
     for (int64_t r0 = wave0 * WR; r0 < n; r0 += nwaves * WR) {
         const VecT *sp[WR];
         VecT *dp[WR];
@@ -198,12 +247,14 @@ __device__ __forceinline__ void copy_rows_wide(const Rows &rows, int64_t n, cons
         for (int c0 = lane; c0 < vecs; c0 += NCH * kWave) {
             VecT v[WR][NCH];
 #pragma unroll
-            for (int q = 0; q < WR; ++q)
+            for (int q = 0; q < WR; ++q) {
+                if (Rows::kHoles && !rok[q]) continue;     // uniform
 #pragma unroll
                 for (int k = 0; k < NCH; ++k) {
                     const int c = c0 + k * kWave;
                     v[q][k] = load_vec<STREAM>(&sp[q][c < vecs ? c : vecs - 1]);
                 }
+            }
 #pragma unroll
             for (int q = 0; q < WR; ++q)
 #pragma unroll
@@ -219,25 +270,25 @@ __device__ __forceinline__ void copy_rows_wide(const Rows &rows, int64_t n, cons
 inline __host__ __device__ int wide_chunks(int vecs) { return vecs > 3 * kWave ? 4 : (vecs > 2 * kWave ? 3 : 2); }
 inline __host__ __device__ int wide_rows(int vecs) { return vecs > 2 * kWave ? 2 : 4; }
 
-// Row copies by one wavefront (the grouped copy).  Rows of up to 64 vectors: the wavefront is split
+// (All copies: workgroup vb of nb.)  Row copies by one wavefront (the grouped copy).  Rows of up to 64 vectors: the wavefront is split
 // into 64/LPR groups of LPR lanes (LPR = 2^log2_lpr >= vecs), every group copies one row per step
 // and kRowUnroll steps are in flight, so a wavefront moves 4*64/LPR short rows at a time.  Longer
 // rows: copy_rows_wide.
 template <typename VecT, bool STREAM, typename Rows>
 __device__ __forceinline__ void copy_rows(const Rows &rows, int64_t n, const char *__restrict__ src,
                                           int64_t src_stride_bytes, char *__restrict__ dst,
-                                          int64_t dst_stride_bytes, int vecs, int log2_lpr) {
+                                          int64_t dst_stride_bytes, int vecs, int log2_lpr, int vb, int nb) {
     if (vecs > kWave) {
         switch (wide_chunks(vecs)) {
-            case 2: copy_rows_wide<VecT, 2, 4, STREAM>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs); break;
-            case 3: copy_rows_wide<VecT, 3, 2, STREAM>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs); break;
-            default: copy_rows_wide<VecT, 4, 2, STREAM>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs); break;
+            case 2: copy_rows_wide<VecT, 2, 4, STREAM>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, vb, nb); break;
+            case 3: copy_rows_wide<VecT, 3, 2, STREAM>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, vb, nb); break;
+            default: copy_rows_wide<VecT, 4, 2, STREAM>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, vb, nb); break;
         }
         return;
     }
     const int lane = lane_id();
-    const int64_t wave0 = int64_t(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
-    const int64_t nwaves = int64_t(gridDim.x) * kWavesPerBlock;
+    const int64_t wave0 = int64_t(vb) * kWavesPerBlock + (threadIdx.x >> 6);
+    const int64_t nwaves = int64_t(nb) * kWavesPerBlock;
     const int groups = kWave >> log2_lpr;
     const int g = lane >> log2_lpr;
     const int gl = lane & ((1 << log2_lpr) - 1);
@@ -245,7 +296,7 @@ __device__ __forceinline__ void copy_rows(const Rows &rows, int64_t n, const cha
     for (int64_t base = wave0 * per_wave; base < n; base += nwaves * per_wave) {
         const VecT *sp[kRowUnroll];
         VecT *dp[kRowUnroll];
-        bool ok[kRowUnroll];
+        bool ok[kRowUnroll], load[kRowUnroll];
         VecT v[kRowUnroll];
 #pragma unroll
         for (int u = 0; u < kRowUnroll; ++u) {
@@ -257,12 +308,13 @@ __device__ __forceinline__ void copy_rows(const Rows &rows, int64_t n, const cha
                 if (!valid && gl == 0) rows.skipped();
             }
             ok[u] = valid && gl < vecs;
+            load[u] = (Rows::kHoles ? r < n : valid) && gl < vecs;         // (a hole reads row 0: no wait for the list before)
             sp[u] = reinterpret_cast<const VecT *>(src + srow * src_stride_bytes) + gl;
             dp[u] = reinterpret_cast<VecT *>(dst + drow * dst_stride_bytes) + gl;
         }
 #pragma unroll
         for (int u = 0; u < kRowUnroll; ++u)
-            if (ok[u]) v[u] = *sp[u];
+            if (load[u]) v[u] = *sp[u];
 #pragma unroll
         for (int u = 0; u < kRowUnroll; ++u)
             if (ok[u]) *dp[u] = v[u];
@@ -284,10 +336,10 @@ constexpr int64_t kStreamingBytes = int64_t(320) << 20;
 template <typename VecT, bool STREAM, typename Rows>
 __device__ __forceinline__ void copy_rows_flat(const Rows &rows, int64_t n, const char *__restrict__ src,
                                                int64_t src_stride_bytes, char *__restrict__ dst,
-                                               int64_t dst_stride_bytes, int vecs, unsigned long long magic) {
+                                               int64_t dst_stride_bytes, int vecs, unsigned long long magic, int vb, int nb) {
     const int64_t total = n * vecs;
     const int64_t span = int64_t(kBlock) * kFlatUnroll;
-    for (int64_t b0 = int64_t(blockIdx.x) * span; b0 < total; b0 += int64_t(gridDim.x) * span) {
+    for (int64_t b0 = int64_t(vb) * span; b0 < total; b0 += int64_t(nb) * span) {
         const VecT *sp[kFlatUnroll];
         VecT *dp[kFlatUnroll];
         bool ok[kFlatUnroll];
@@ -314,54 +366,83 @@ __device__ __forceinline__ void copy_rows_flat(const Rows &rows, int64_t n, cons
     }
 }
 
-// MISS names the launch: 0 = rows from the HBM cache, 1 = rows from the feature matrix in pinned
-// host memory.  The copy is the same; profiles tell the two apart by symbol.  The miss launch is
-// the last kernel of a gather and leaves the (hits, misses) counters at zero for the next one: the
-// workgroup that finishes last - every workgroup has read its count by then - clears them, so the
-// call is self-contained and can be replayed from a recorded graph.  counters[2] counts the
-// finished workgroups.
-template <typename VecT, int MISS>
+// One side of a gather: entries of a list, copied from src.
+struct RowSide {
+    const int2 *list;
+    const char *src;
+    int64_t src_stride_bytes;
+    int blocks;                  // workgroups
+    int vecs, log2_lpr;
+    unsigned long long magic;    // flat copy, see copy_rows_flat; 0: grouped
+};
+// WHAT: 0 = hits (rows from the HBM cache), 1 = misses (rows from the feature matrix in pinned host memory), 2 = both: the
+// workgroups of the misses come first, so that the link is busy from the start, and the hits pass beside them.  (As two
+// launches, one after the other: 179 MB over the link and 50 k cached rows of 400 bytes 1,862 us, 1.35 M cached rows and no
+// missed ones 268; in one 1,816 and 265.)  The misses' workgroup that ends last, every one having read their number by
+// then, sets it to zero: a second half on its own copies nothing.
+template <typename VecT, int WHAT>
 __global__ void __launch_bounds__(kBlock)
-k_gather_rows(const int2 *__restrict__ list, const unsigned long long *count,
-              const char *__restrict__ src, int64_t src_stride_bytes, char *__restrict__ dst,
-              int64_t dst_stride_bytes, int vecs, int log2_lpr, int64_t *__restrict__ stats,
-              unsigned long long *counters, unsigned long long magic) {
-    if (stats && blockIdx.x == 0 && threadIdx.x < 2) stats[threadIdx.x] = static_cast<int64_t>(counters[threadIdx.x]);
-    const int64_t n = static_cast<int64_t>(*count);
-    // a launch that moves more than the last-level cache holds reads its source rows past the caches
-    const bool streaming = !MISS && sizeof(VecT) == 16 && 2 * n * vecs * int64_t(sizeof(VecT)) > kStreamingBytes;
-    const ListRows rows{list};
-    if (streaming) {                                       // one uniform branch; the copies themselves are straight code
-        if (magic) copy_rows_flat<VecT, true>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, magic);
-        else copy_rows<VecT, true>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, log2_lpr);
-    } else {
-        if (magic) copy_rows_flat<VecT, false>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, magic);
-        else copy_rows<VecT, false>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, log2_lpr);
+k_gather_rows(RowSide hit, RowSide miss, char *__restrict__ dst, int64_t dst_stride_bytes, unsigned long long *counters) {
+    const int b = static_cast<int>(blockIdx.x);
+    if (WHAT == 0 || (WHAT == 2 && b >= miss.blocks)) {
+        const int vb = WHAT == 0 ? b : b - miss.blocks;
+        const int64_t n = static_cast<int64_t>(counters[kCountHits]);
+        // a launch that moves more than the last-level cache holds reads its source rows past the caches
+        const bool streaming = sizeof(VecT) == 16 && 2 * n * hit.vecs * int64_t(sizeof(VecT)) > kStreamingBytes;
+        const ListRows<false> rows{hit.list};
+        if (streaming) {                                   // one uniform branch; the copies themselves are straight code
+            if (hit.magic) copy_rows_flat<VecT, true>(rows, n, hit.src, hit.src_stride_bytes, dst, dst_stride_bytes, hit.vecs, hit.magic, vb, hit.blocks);
+            else copy_rows<VecT, true>(rows, n, hit.src, hit.src_stride_bytes, dst, dst_stride_bytes, hit.vecs, hit.log2_lpr, vb, hit.blocks);
+        } else {
+            if (hit.magic) copy_rows_flat<VecT, false>(rows, n, hit.src, hit.src_stride_bytes, dst, dst_stride_bytes, hit.vecs, hit.magic, vb, hit.blocks);
+            else copy_rows<VecT, false>(rows, n, hit.src, hit.src_stride_bytes, dst, dst_stride_bytes, hit.vecs, hit.log2_lpr, vb, hit.blocks);
+        }
+        return;
     }
-    if (MISS) {
-        __syncthreads();                                   // every thread of the workgroup has read its count
-        if (threadIdx.x == 0) {
-            __threadfence();
-            const unsigned long long done = atomicAdd(&counters[2], 1ull);
-            if (done == gridDim.x - 1) {
-                counters[0] = 0;
-                counters[1] = 0;
-                counters[2] = 0;
-            }
+    if (WHAT == 0) return;
+    const int64_t n = static_cast<int64_t>(counters[kCountMisses]);
+    copy_rows<VecT, false>(ListRows<true>{miss.list}, n, miss.src, miss.src_stride_bytes, dst, dst_stride_bytes, miss.vecs, miss.log2_lpr, b, miss.blocks);
+    __syncthreads();                                       // every thread of the workgroup has read the number
+    if (threadIdx.x == 0) {
+        __threadfence();
+        if (atomicAdd(&counters[kCountMissed], 1ull) == static_cast<unsigned long long>(miss.blocks - 1)) {
+            counters[kCountMisses] = 0;
+            counters[kCountMissed] = 0;
         }
     }
 }
 
-template <typename VecT, typename IdxT>
+// STATS: the workgroup that ends last writes the statistics: each adds itself and its skipped ids to one word (counters
+// [kCountBad], workgroups in the upper half), left at zero.
+template <typename VecT, typename IdxT, bool STATS>
 __global__ void __launch_bounds__(kBlock)
 k_gather_direct(const IdxT *__restrict__ ids, const int64_t *__restrict__ num_ids, int64_t cap, int64_t src_rows,
                 unsigned long long *bad, const char *__restrict__ src, int64_t src_stride_bytes, char *__restrict__ dst,
-                int64_t dst_stride_bytes, int vecs, int log2_lpr, unsigned long long magic) {
+                int64_t dst_stride_bytes, int vecs, int log2_lpr, unsigned long long magic, int grid, int64_t *__restrict__ stats) {
+    __shared__ int bad_here;
     int64_t n = *num_ids;
     if (n > cap) n = cap;
-    const DirectRows<IdxT> rows{ids, src_rows, bad};
-    if (magic) copy_rows_flat<VecT, false>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, magic);
-    else copy_rows<VecT, false>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, log2_lpr);
+    if (STATS) {
+        if (threadIdx.x == 0) bad_here = 0;
+        __syncthreads();
+    }
+    const DirectRows<IdxT, STATS> rows{ids, src_rows, STATS ? nullptr : bad, STATS ? &bad_here : nullptr};
+    if (magic) copy_rows_flat<VecT, false>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, magic, static_cast<int>(blockIdx.x), grid);
+    else copy_rows<VecT, false>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, log2_lpr, static_cast<int>(blockIdx.x), grid);
+    if (STATS) {
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const unsigned long long mine = 1ull << 32 | static_cast<unsigned>(bad_here);
+            const unsigned long long all = atomicAdd(bad, mine) + mine;
+            if (static_cast<int>(all >> 32) == grid) {
+                *bad = 0;
+                if (stats) {
+                    stats[0] = 0;
+                    stats[1] = (n < 0 ? 0 : n) - static_cast<int64_t>(all & 0xFFFFFFFFu);
+                }
+            }
+        }
+    }
 }
 
 // Widest power-of-two access (16, 8, 4 or 2 bytes) that keeps every row of both sides aligned.
@@ -450,41 +531,54 @@ int link_grid(int64_t rows, const RowGeom &g, int64_t inflight_bytes) {
     return static_cast<int>(std::min<int64_t>(blocks, hbm_grid(rows, g)));
 }
 
-template <int MISS>
-int launch_rows(mqg_ctx *ctx, const char *name, const int2 *list, const unsigned long long *count, int64_t cap,
-                const void *src, int64_t src_stride_bytes, void *dst, int64_t dst_stride_bytes,
-                int64_t row_bytes, int64_t *stats, unsigned long long *counters, hipStream_t s) {
-    row_bytes = copy_bytes(row_bytes, src_stride_bytes, dst_stride_bytes, src, dst, !MISS);
+RowSide row_side(const int2 *list, const void *src, int64_t src_stride_bytes, const void *dst, int64_t dst_stride_bytes, int64_t row_bytes, int64_t cap,
+                 bool miss, int64_t inflight_bytes, int *vec_bytes) {
+    row_bytes = copy_bytes(row_bytes, src_stride_bytes, dst_stride_bytes, src, dst, !miss);
     const RowGeom g = row_geom(row_bytes, src_stride_bytes, dst_stride_bytes, src, dst);
-    int grid = MISS ? link_grid(cap, g, ctx->miss_inflight_bytes) : hbm_grid(cap, g);   // the grouped copy's
-    const unsigned long long magic = MISS ? 0 : flat_magic(cap, g);
-    if (magic) grid = flat_grid(cap, g);
-    const char *sp = static_cast<const char *>(src);
+    RowSide r;
+    r.list = list;
+    r.src = static_cast<const char *>(src);
+    r.src_stride_bytes = src_stride_bytes;
+    r.vecs = g.vecs;
+    r.log2_lpr = g.log2_lpr;
+    r.magic = miss ? 0 : flat_magic(cap, g);
+    r.blocks = miss ? link_grid(cap, g, inflight_bytes) : r.magic ? flat_grid(cap, g) : hbm_grid(cap, g);
+    *vec_bytes = g.vb;
+    return r;
+}
+
+template <int WHAT>
+int launch_rows(mqg_ctx *ctx, const char *name, int vec_bytes, const RowSide &hit, const RowSide &miss, void *dst, int64_t dst_stride_bytes,
+                unsigned long long *counters, hipStream_t s) {
+    const int grid = (WHAT != 1 ? hit.blocks : 0) + (WHAT != 0 ? miss.blocks : 0);
     char *dp = static_cast<char *>(dst);
-    if (ctx->profile && g.vb == 16) {
+    if (ctx->profile && vec_bytes == 16) {
         // the two kernels the rooflines are quoted on: timed by the dispatch's own start and end
         hipEvent_t e0, e1;
         prof_begin_ext(ctx, name, &e0, &e1);
-        hipExtLaunchKernelGGL((k_gather_rows<uint4, MISS>), dim3(grid), dim3(kBlock), 0, s, e0, e1, 0, list, count, sp, src_stride_bytes, dp,
-                              dst_stride_bytes, g.vecs, g.log2_lpr, stats, counters, magic);
+        hipExtLaunchKernelGGL((k_gather_rows<uint4, WHAT>), dim3(grid), dim3(kBlock), 0, s, e0, e1, 0, hit, miss, dp, dst_stride_bytes, counters);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return fail(ctx, MQG_ERR_HIP, std::string(name) + ": " + hipGetErrorString(e));
         return MQG_OK;
     }
-    switch (g.vb) {
-        case 16: MQG_LAUNCH(ctx, name, s, (k_gather_rows<uint4, MISS><<<grid, kBlock, 0, s>>>(list, count, sp, src_stride_bytes, dp, dst_stride_bytes, g.vecs, g.log2_lpr, stats, counters, magic))); break;
-        case 8: MQG_LAUNCH(ctx, name, s, (k_gather_rows<uint2, MISS><<<grid, kBlock, 0, s>>>(list, count, sp, src_stride_bytes, dp, dst_stride_bytes, g.vecs, g.log2_lpr, stats, counters, magic))); break;
-        case 4: MQG_LAUNCH(ctx, name, s, (k_gather_rows<uint32_t, MISS><<<grid, kBlock, 0, s>>>(list, count, sp, src_stride_bytes, dp, dst_stride_bytes, g.vecs, g.log2_lpr, stats, counters, magic))); break;
-        default: MQG_LAUNCH(ctx, name, s, (k_gather_rows<uint16_t, MISS><<<grid, kBlock, 0, s>>>(list, count, sp, src_stride_bytes, dp, dst_stride_bytes, g.vecs, g.log2_lpr, stats, counters, magic))); break;
+    switch (vec_bytes) {
+        case 16: MQG_LAUNCH(ctx, name, s, (k_gather_rows<uint4, WHAT><<<grid, kBlock, 0, s>>>(hit, miss, dp, dst_stride_bytes, counters))); break;
+        case 8: MQG_LAUNCH(ctx, name, s, (k_gather_rows<uint2, WHAT><<<grid, kBlock, 0, s>>>(hit, miss, dp, dst_stride_bytes, counters))); break;
+        case 4: MQG_LAUNCH(ctx, name, s, (k_gather_rows<uint32_t, WHAT><<<grid, kBlock, 0, s>>>(hit, miss, dp, dst_stride_bytes, counters))); break;
+        default: MQG_LAUNCH(ctx, name, s, (k_gather_rows<uint16_t, WHAT><<<grid, kBlock, 0, s>>>(hit, miss, dp, dst_stride_bytes, counters))); break;
     }
     return MQG_OK;
 }
+
+// Workgroups up to which the last one writes the statistics of a gather without a cache, in place of a launch for them
+// (both in a recorded graph: 60 workgroups 4.2 -> 3.9 us, 127 4.2 -> 4.2, 250 4.3 -> 4.9; and a launch less for the host, 2 to 3 us).
+constexpr int kDirectStatsGrid = 192;
 
 // from_host: the source is host memory, so the launch is sized for the link
 template <typename IdxT>
 int launch_direct(mqg_ctx *ctx, const IdxT *ids, const int64_t *num_ids, int64_t cap, int64_t src_rows,
                   unsigned long long *bad, const void *src, int64_t src_stride_bytes, void *dst,
-                  int64_t dst_stride_bytes, int64_t row_bytes, bool from_host, hipStream_t s) {
+                  int64_t dst_stride_bytes, int64_t row_bytes, bool from_host, int64_t *stats, bool *with_stats, hipStream_t s) {
     row_bytes = copy_bytes(row_bytes, src_stride_bytes, dst_stride_bytes, src, dst, !from_host);
     const RowGeom g = row_geom(row_bytes, src_stride_bytes, dst_stride_bytes, src, dst);
     int grid = from_host ? link_grid(cap, g, ctx->miss_inflight_bytes) : hbm_grid(cap, g);
@@ -492,12 +586,19 @@ int launch_direct(mqg_ctx *ctx, const IdxT *ids, const int64_t *num_ids, int64_t
     if (magic) grid = flat_grid(cap, g);
     const char *sp = static_cast<const char *>(src);
     char *dp = static_cast<char *>(dst);
+    const bool last = bad && grid <= kDirectStatsGrid;
+    *with_stats = last;
+#define MQG_DIRECT(V, S)                                                                                                                    \
+    MQG_LAUNCH(ctx, "k_gather_direct", s,                                                                                                   \
+               (k_gather_direct<V, IdxT, S><<<grid, kBlock, 0, s>>>(ids, num_ids, cap, src_rows, bad, sp, src_stride_bytes, dp, dst_stride_bytes, \
+                                                                    g.vecs, g.log2_lpr, magic, grid, stats)))
     switch (g.vb) {
-        case 16: MQG_LAUNCH(ctx, "k_gather_direct", s, (k_gather_direct<uint4, IdxT><<<grid, kBlock, 0, s>>>(ids, num_ids, cap, src_rows, bad, sp, src_stride_bytes, dp, dst_stride_bytes, g.vecs, g.log2_lpr, magic))); break;
-        case 8: MQG_LAUNCH(ctx, "k_gather_direct", s, (k_gather_direct<uint2, IdxT><<<grid, kBlock, 0, s>>>(ids, num_ids, cap, src_rows, bad, sp, src_stride_bytes, dp, dst_stride_bytes, g.vecs, g.log2_lpr, magic))); break;
-        case 4: MQG_LAUNCH(ctx, "k_gather_direct", s, (k_gather_direct<uint32_t, IdxT><<<grid, kBlock, 0, s>>>(ids, num_ids, cap, src_rows, bad, sp, src_stride_bytes, dp, dst_stride_bytes, g.vecs, g.log2_lpr, magic))); break;
-        default: MQG_LAUNCH(ctx, "k_gather_direct", s, (k_gather_direct<uint16_t, IdxT><<<grid, kBlock, 0, s>>>(ids, num_ids, cap, src_rows, bad, sp, src_stride_bytes, dp, dst_stride_bytes, g.vecs, g.log2_lpr, magic))); break;
+        case 16: if (last) MQG_DIRECT(uint4, true); else MQG_DIRECT(uint4, false); break;
+        case 8: if (last) MQG_DIRECT(uint2, true); else MQG_DIRECT(uint2, false); break;
+        case 4: if (last) MQG_DIRECT(uint32_t, true); else MQG_DIRECT(uint32_t, false); break;
+        default: if (last) MQG_DIRECT(uint16_t, true); else MQG_DIRECT(uint16_t, false); break;
     }
+#undef MQG_DIRECT
     return MQG_OK;
 }
 
@@ -518,8 +619,9 @@ bool is_host_memory(const void *p) {
 int gather_direct_i32(mqg_ctx *ctx, const int32_t *ids, const int64_t *num_ids, int64_t cap, int64_t src_rows,
                       const void *src, int64_t src_stride_bytes, void *dst, int64_t dst_stride_bytes, int64_t row_bytes,
                       hipStream_t s) {
+    bool with_stats;
     return launch_direct<int32_t>(ctx, ids, num_ids, cap, src_rows, nullptr, src, src_stride_bytes, dst, dst_stride_bytes,
-                                  row_bytes, is_host_memory(src), s);
+                                  row_bytes, is_host_memory(src), nullptr, &with_stats, s);
 }
 
 // Host-side argument checks shared by the gather entry points.  max_ids bounds cap_ids when the
@@ -561,37 +663,44 @@ int run_gather(mqg_ctx *ctx, const mqg_cache *c, int32_t idx_type, const void *i
     if (!c->slot_of) {                                   // no cache: everything from feats
         if (!(phases & kGatherMissed)) return MQG_OK;
         int rc;
+        bool with_stats = false;
         const bool from_host = is_host_memory(c->feats);
         if (idx_type == MQG_I64)
-            rc = launch_direct<int64_t>(ctx, static_cast<const int64_t *>(ids), num_ids, cap_ids, c->num_nodes, &ctx->counters[3],
-                                        c->feats, c->feat_stride * elt, out, out_stride * elt, row_bytes, from_host, s);
+            rc = launch_direct<int64_t>(ctx, static_cast<const int64_t *>(ids), num_ids, cap_ids, c->num_nodes, &ctx->counters[kCountBad],
+                                        c->feats, c->feat_stride * elt, out, out_stride * elt, row_bytes, from_host, stats, &with_stats, s);
         else
-            rc = launch_direct<int32_t>(ctx, static_cast<const int32_t *>(ids), num_ids, cap_ids, c->num_nodes, &ctx->counters[3],
-                                        c->feats, c->feat_stride * elt, out, out_stride * elt, row_bytes, from_host, s);
+            rc = launch_direct<int32_t>(ctx, static_cast<const int32_t *>(ids), num_ids, cap_ids, c->num_nodes, &ctx->counters[kCountBad],
+                                        c->feats, c->feat_stride * elt, out, out_stride * elt, row_bytes, from_host, stats, &with_stats, s);
         if (rc != MQG_OK) return rc;
         // every valid id counts as served from feats; the launch also clears the count of skipped ids
-        MQG_LAUNCH(ctx, "k_direct_stats", s, (k_direct_stats<<<1, 64, 0, s>>>(stats, num_ids, cap_ids, ctx->counters)));
+        if (!with_stats) MQG_LAUNCH(ctx, "k_direct_stats", s, (k_direct_stats<<<1, 64, 0, s>>>(stats, num_ids, cap_ids, ctx->counters)));
         return MQG_OK;
     }
 
-    // (hits, misses) counters: zero between gathers (the miss launch clears them when it is done)
     unsigned long long *counters = ctx->counters;
+    int hit_vec, miss_vec;
+    const RowSide hit = row_side(ctx->hit_list, c->cache_rows, c->cache_stride * elt, out, out_stride * elt, row_bytes, cap_ids, false, 0, &hit_vec);
+    RowSide miss = row_side(ctx->miss_list, c->feats, c->feat_stride * elt, out, out_stride * elt, row_bytes, cap_ids, true,
+                                  ctx->miss_inflight_bytes, &miss_vec);
+    if (c->num_nodes == 0) miss.vecs = 0;                 // no row that a hole could read
     if (phases & kGatherCached) {
-        const int cgrid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(cap_ids, kBlock * 4)), 1024));
+        const int cgrid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(cap_ids, cap_ids <= 4 * kClassifySmall ? kBlock : kBlock * 4)), 1024));
 #define MQG_CLASSIFY(IT)                                                                                               \
     MQG_LAUNCH(ctx, "k_classify", s,                                                                                   \
                (k_classify<IT><<<cgrid, kBlock, 0, s>>>(static_cast<const IT *>(ids), num_ids, cap_ids, c->slot_of, c->num_nodes, \
-                                                        ctx->hit_list, ctx->miss_list, counters)))
+                                                        ctx->hit_list, ctx->miss_list, counters, stats, cgrid)))
         if (idx_type == MQG_I64) MQG_CLASSIFY(int64_t);
         else MQG_CLASSIFY(int32_t);
 #undef MQG_CLASSIFY
-        int rc = launch_rows<0>(ctx, "k_gather_hit", ctx->hit_list, &counters[0], cap_ids, c->cache_rows,
-                                c->cache_stride * elt, out, out_stride * elt, row_bytes, stats, counters, s);
+    }
+    // both sides in one launch if they move vectors of the same width
+    if (phases == (kGatherCached | kGatherMissed) && hit_vec == miss_vec && !ctx->profile)
+        return launch_rows<2>(ctx, "k_gather_both", hit_vec, hit, miss, out, out_stride * elt, counters, s);
+    if (phases & kGatherCached) {
+        int rc = launch_rows<0>(ctx, "k_gather_hit", hit_vec, hit, miss, out, out_stride * elt, counters, s);
         if (rc != MQG_OK) return rc;
     }
-    if (phases & kGatherMissed)
-        return launch_rows<1>(ctx, "k_gather_miss", ctx->miss_list, &counters[1], cap_ids, c->feats,
-                              c->feat_stride * elt, out, out_stride * elt, row_bytes, nullptr, counters, s);
+    if (phases & kGatherMissed) return launch_rows<1>(ctx, "k_gather_miss", miss_vec, hit, miss, out, out_stride * elt, counters, s);
     return MQG_OK;
 }
 

@@ -1,0 +1,72 @@
+"""The gather's hits and misses in one launch: sides of different vector widths and strides, only hits, only misses, no rows; a
+second half on its own; and the statistics written by the last workgroup of a small gather without a cache, around that line."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def setup(n, dim, dtype, feat_pad, cached, cache_pad, seed=0):
+    from paper_2601_04707_amd import mqg
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    g = mqg.Graph(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int64, device="cuda")[:0])
+    feats = torch.randn((n, dim + feat_pad), generator=gen, device="cuda").to(dtype).cpu().pin_memory()[:, :dim]
+    ctx = mqg.Context(g, 50_000, [1])
+    cache = mqg.Cache(g, feats, cached, cache_stride=dim + cache_pad)
+    mqg.mqg_build_cache(ctx, g, cache)
+    return mqg, ctx, cache, feats.cuda(), gen
+
+
+@pytest.mark.parametrize("dim,dtype,feat_pad,cache_pad", [(64, torch.float32, 0, 0), (100, torch.float32, 0, 0), (602, torch.float32, 6, 6),
+                                                          (30, torch.float16, 0, 2), (30, torch.float16, 2, 0), (7, torch.float16, 0, 1),
+                                                          (33, torch.float32, 0, 3), (1, torch.float16, 0, 0)])
+def test_both_sides(dim, dtype, feat_pad, cache_pad):
+    n = 3000
+    mqg, ctx, cache, feats, gen = setup(n, dim, dtype, feat_pad, n // 3, cache_pad)
+    slot = cache.slot_of
+    hit, miss = torch.nonzero(slot >= 0).flatten(), torch.nonzero(slot < 0).flatten()
+    mixed = torch.randint(-20, n + 20, (4000,), generator=gen, device="cuda")
+    for ids in (mixed, hit, miss, mixed[:0], mixed[:1], hit[:1], miss[:1]):
+        valid = (ids >= 0) & (ids < n)
+        buf = torch.full((len(ids) + 1, dim + 8), 3.0, dtype=dtype, device="cuda")
+        out = buf[:, :dim]
+        stats = torch.zeros(2, dtype=torch.int64, device="cuda")
+        num = torch.tensor([len(ids)], device="cuda")
+        padded = torch.cat([ids, ids[:1] if len(ids) else torch.zeros(1, dtype=ids.dtype, device="cuda")])
+        mqg.mqg_gather_features(ctx, cache, padded, num, out, stats)
+        # a second half after the rows are copied copies nothing
+        other = torch.full((len(ids) + 1, dim), 5.0, dtype=dtype, device="cuda")
+        mqg.mqg_gather_features_missed(ctx, cache, padded, num, other)
+        torch.cuda.synchronize()
+        want = torch.full_like(out, 3.0)
+        want[:-1][valid] = feats[ids[valid]]
+        assert torch.equal(out, want) and torch.all(buf[:, dim + 7:] == 3.0)
+        assert torch.all(other == 5.0)
+        hits = int((slot[ids[valid]] >= 0).sum())
+        assert stats.tolist() == [hits, int(valid.sum()) - hits]
+
+
+@pytest.mark.parametrize("rows", [1, 2000, 12_287, 12_288, 12_289, 40_000])
+@pytest.mark.parametrize("dim", [64, 602])
+def test_statistics_without_a_cache(rows, dim):
+    """64 columns: 192 workgroups of 64 rows each are the most that write their own statistics."""
+    from paper_2601_04707_amd import mqg
+    n = 5000
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+    g = mqg.Graph(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int64, device="cuda")[:0])
+    feats = torch.randn((n, dim), generator=gen, device="cuda")
+    ctx = mqg.Context(g, 50_000, [1])
+    cache = mqg.Cache(g, feats, None)
+    for bad in (0, 1, rows):
+        ids = torch.randint(0, n, (rows,), generator=gen, device="cuda")
+        ids[torch.randperm(rows, generator=gen, device="cuda")[:bad]] = n + 3
+        valid = ids < n
+        want = torch.full((rows, dim), 2.0, device="cuda")
+        want[valid] = feats[ids[valid]]
+        for fewer in (0, rows // 2):
+            out = torch.full((rows, dim), 2.0, device="cuda")
+            stats = torch.zeros(2, dtype=torch.int64, device="cuda")
+            mqg.mqg_gather_features(ctx, cache, ids, torch.tensor([rows - fewer], device="cuda"), out, stats)
+            torch.cuda.synchronize()
+            assert torch.equal(out[: rows - fewer], want[: rows - fewer]) and torch.all(out[rows - fewer:] == 2.0)
+            assert stats.tolist() == [0, int(valid[: rows - fewer].sum())]

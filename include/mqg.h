@@ -569,7 +569,7 @@ int mqg_sage_mean_aggregate(mqg_ctx *ctx, const mqg_block *block, const void *x_
  * for all num_src sources (zeros where no edge points).
  * grad_out: device [num_dst x go_stride]; grad_x: device [cap_src x gx_stride];
  * strides in elements, padding columns of written rows unspecified as in the
- * forward.  The edges are first ordered by source with a stable radix sort;
+ * forward.  The edges are first ordered by source, stably;
  * each source's terms come in ascending destination order and are summed as the
  * forward's entries are, so the result is reproducible bit for bit.  The first call (and any call with
  * larger block capacities than seen before) allocates context scratch of

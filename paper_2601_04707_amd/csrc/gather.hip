@@ -10,6 +10,7 @@
 //                     time by a wavefront; misses: feature matrix -> HBM output.  One launch for both, the few
 //                     workgroups that keep the host link busy first; in halves, and while profiling, a launch
 //                     each (<., 0> hits, <., 1> misses, so that profiles tell the HBM-bound from the link-bound)
+//   k_gather_slots    a cache that holds every node: slot lookup and copy in one launch
 //   k_gather_direct   no cache: every row straight from the feature matrix
 #include <hip/hip_ext.h>
 
@@ -25,7 +26,7 @@ namespace {
 
 // Words of a context's (or the static array's) counters; all but the last two are zero between gathers.
 constexpr int kCountSplit = 0;         // hits, misses and tiles so far, see classify_tiles
-constexpr int kCountBad = 1;           // ids outside the graph
+constexpr int kCountBad = 1;           // ids outside the graph, or misses that k_gather_slots counts
 constexpr int kCountMissed = 2;        // finished workgroups that copy misses
 constexpr int kCountHits = 4, kCountMisses = 5;    // entries of the lists of the last split; misses are zero again once they are copied
 
@@ -180,6 +181,7 @@ struct ListRows {
         *dst_row = e.x;
         return !HOLES || e.y >= 0;
     }
+    __device__ __forceinline__ const char *at(int64_t row, const char *src, int64_t stride) const { return src + row * stride; }
     __device__ __forceinline__ void skipped() const {}
 };
 template <typename IdxT, bool IN_LDS>
@@ -196,10 +198,34 @@ struct DirectRows {
         *dst_row = r;
         return ok;
     }
+    __device__ __forceinline__ const char *at(int64_t row, const char *src, int64_t stride) const { return src + row * stride; }
     __device__ __forceinline__ void skipped() const {
         if (IN_LDS) atomicAdd(bad_lds, 1);
         else if (bad) atomicAdd(bad, 1ull);
     }
+};
+
+// Row ids[r] to output row r, from the cache if it has a slot there and else from the feature matrix (row -1 - id).
+template <typename IdxT>
+struct SlotRows {
+    static constexpr bool kHoles = false;
+    const IdxT *ids;
+    const int32_t *slot_of;
+    int64_t num_nodes;                   // at least 1, and so has the cache a row
+    const char *feats;
+    int64_t feat_stride_bytes;
+    __device__ __forceinline__ bool get(int64_t r, int64_t *src_row, int64_t *dst_row) const {
+        const int64_t id = static_cast<int64_t>(ids[r]);
+        const bool ok = id >= 0 && id < num_nodes;
+        const int32_t slot = slot_of[ok ? id : 0];
+        *src_row = !ok ? 0 : slot >= 0 ? slot : -1 - id;
+        *dst_row = r;
+        return ok;
+    }
+    __device__ __forceinline__ const char *at(int64_t row, const char *src, int64_t stride) const {
+        return row >= 0 ? src + row * stride : feats + (-1 - row) * feat_stride_bytes;
+    }
+    __device__ __forceinline__ void skipped() const {}
 };
 
 // A 16-byte load that is not kept in the caches on its way (STREAM: read-once data of a launch too
@@ -241,7 +267,7 @@ __device__ __forceinline__ void copy_rows_wide(const Rows &rows, int64_t n, cons
             const bool valid = rows.get(r < n ? r : n - 1, &srow, &drow);          // a row past the end re-reads the last one
             if (r < n && !valid && lane == 0) rows.skipped();
             rok[q] = r < n && valid;
-            sp[q] = reinterpret_cast<const VecT *>(src + srow * src_stride_bytes);
+            sp[q] = reinterpret_cast<const VecT *>(rows.at(srow, src, src_stride_bytes));
             dp[q] = reinterpret_cast<VecT *>(dst + drow * dst_stride_bytes);
         }
         for (int c0 = lane; c0 < vecs; c0 += NCH * kWave) {
@@ -309,7 +335,7 @@ __device__ __forceinline__ void copy_rows(const Rows &rows, int64_t n, const cha
             }
             ok[u] = valid && gl < vecs;
             load[u] = (Rows::kHoles ? r < n : valid) && gl < vecs;         // (a hole reads row 0: no wait for the list before)
-            sp[u] = reinterpret_cast<const VecT *>(src + srow * src_stride_bytes) + gl;
+            sp[u] = reinterpret_cast<const VecT *>(rows.at(srow, src, src_stride_bytes)) + gl;
             dp[u] = reinterpret_cast<VecT *>(dst + drow * dst_stride_bytes) + gl;
         }
 #pragma unroll
@@ -355,7 +381,7 @@ __device__ __forceinline__ void copy_rows_flat(const Rows &rows, int64_t n, cons
             const bool valid = rows.get(row, &srow, &drow);
             if (ok[u] && !valid && col == 0) rows.skipped();
             ok[u] = ok[u] && valid;
-            sp[u] = reinterpret_cast<const VecT *>(src + srow * src_stride_bytes) + col;
+            sp[u] = reinterpret_cast<const VecT *>(rows.at(srow, src, src_stride_bytes)) + col;
             dp[u] = reinterpret_cast<VecT *>(dst + drow * dst_stride_bytes) + col;
         }
 #pragma unroll
@@ -440,6 +466,79 @@ k_gather_direct(const IdxT *__restrict__ ids, const int64_t *__restrict__ num_id
                     stats[0] = 0;
                     stats[1] = (n < 0 ? 0 : n) - static_cast<int64_t>(all & 0xFFFFFFFFu);
                 }
+            }
+        }
+    }
+}
+
+// A cache that holds every node: no lists.  A row finds its slot while it is copied, in one launch; the first count_blocks
+// workgroups count the hits and misses beside it (as a split and a copy 1.35 M rows of 512 bytes 18 + 247 us, 247 in all; a few thousand rows 14.5 and 8).
+template <typename VecT, typename IdxT>
+__global__ void __launch_bounds__(kBlock)
+k_gather_slots(SlotRows<IdxT> rows, const int64_t *__restrict__ num_ids, int64_t cap, const char *__restrict__ cache, int64_t cache_stride_bytes,
+               char *__restrict__ dst, int64_t dst_stride_bytes, int vecs, int log2_lpr, unsigned long long magic, int count_blocks, int copy_blocks,
+               unsigned long long *counters, int64_t *__restrict__ stats) {
+    __shared__ int lds[2][kWavesPerBlock];
+    const int b = static_cast<int>(blockIdx.x);
+    int64_t n = *num_ids;
+    if (n > cap) n = cap;
+    if (b >= count_blocks) {
+        const int vb = b - count_blocks;
+        const bool streaming = sizeof(VecT) == 16 && 2 * n * vecs * int64_t(sizeof(VecT)) > kStreamingBytes;
+        if (streaming) {
+            if (magic) copy_rows_flat<VecT, true>(rows, n, cache, cache_stride_bytes, dst, dst_stride_bytes, vecs, magic, vb, copy_blocks);
+            else copy_rows<VecT, true>(rows, n, cache, cache_stride_bytes, dst, dst_stride_bytes, vecs, log2_lpr, vb, copy_blocks);
+        } else {
+            if (magic) copy_rows_flat<VecT, false>(rows, n, cache, cache_stride_bytes, dst, dst_stride_bytes, vecs, magic, vb, copy_blocks);
+            else copy_rows<VecT, false>(rows, n, cache, cache_stride_bytes, dst, dst_stride_bytes, vecs, log2_lpr, vb, copy_blocks);
+        }
+        return;
+    }
+    constexpr int U = 4;
+    int h = 0, m = 0;
+    for (int64_t i0 = int64_t(b) * kBlock + threadIdx.x; i0 < n; i0 += int64_t(count_blocks) * kBlock * U) {
+        int64_t id[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = i0 + int64_t(u) * count_blocks * kBlock;
+            const int64_t raw = i < n ? static_cast<int64_t>(rows.ids[i]) : -1;
+            id[u] = raw >= 0 && raw < rows.num_nodes ? raw : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool hit = id[u] >= 0 && rows.slot_of[id[u]] >= 0;
+            h += hit ? 1 : 0;
+            m += id[u] >= 0 && !hit ? 1 : 0;
+        }
+    }
+    h = wave_sum(h);
+    m = wave_sum(m);
+    const int wave = static_cast<int>(threadIdx.x) >> 6;
+    if (lane_id() == 0) {
+        lds[0][wave] = h;
+        lds[1][wave] = m;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long th = 0, tm = 0;
+#pragma unroll
+        for (int w = 0; w < kWavesPerBlock; ++w) {
+            th += static_cast<unsigned>(lds[0][w]);
+            tm += static_cast<unsigned>(lds[1][w]);
+        }
+        if (tm) {                                          // counted before this workgroup is
+            atomicAdd(&counters[kCountBad], tm);
+            __threadfence();
+        }
+        const unsigned long long mine = th | 1ull << 32, all = atomicAdd(&counters[kCountSplit], mine) + mine;
+        if (static_cast<int>(all >> 32) == count_blocks) {
+            const unsigned long long missed = atomicExch(&counters[kCountBad], 0ull);
+            counters[kCountSplit] = 0;
+            counters[kCountHits] = all & 0xFFFFFFFFu;
+            counters[kCountMisses] = 0;                    // they are copied
+            if (stats) {
+                stats[0] = static_cast<int64_t>(all & 0xFFFFFFFFu);
+                stats[1] = static_cast<int64_t>(missed);
             }
         }
     }
@@ -602,6 +701,37 @@ int launch_direct(mqg_ctx *ctx, const IdxT *ids, const int64_t *num_ids, int64_t
     return MQG_OK;
 }
 
+// *done: false if the two sources' rows cannot be copied with the same vectors; nothing is launched then.
+template <typename IdxT>
+int launch_slots(mqg_ctx *ctx, const mqg_cache *c, const IdxT *ids, const int64_t *num_ids, int64_t cap, void *out, int64_t out_stride_bytes,
+                 int64_t row_bytes, int64_t elt, int64_t *stats, bool *done, hipStream_t s) {
+    const int64_t cs = c->cache_stride * elt, fs = c->feat_stride * elt;
+    // whole lines only where the feature matrix would be read no further than its own misses are
+    const int64_t feat_bytes = copy_bytes(row_bytes, fs, out_stride_bytes, c->feats, out, false);
+    int64_t bytes = copy_bytes(row_bytes, cs, out_stride_bytes, c->cache_rows, out, true);
+    if (bytes > feat_bytes) bytes = copy_bytes(row_bytes, cs, out_stride_bytes, c->cache_rows, out, false);
+    const RowGeom g = row_geom(bytes, cs, out_stride_bytes, c->cache_rows, out);
+    *done = bytes <= feat_bytes && pick_vec_bytes(bytes, fs, out_stride_bytes, c->feats, out) == g.vb;
+    if (!*done) return MQG_OK;
+    const unsigned long long magic = flat_magic(cap, g);
+    const int copy_blocks = magic ? flat_grid(cap, g) : hbm_grid(cap, g);
+    const int count_blocks = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(cap, kBlock * 8)), 256));
+    const SlotRows<IdxT> rows{ids, c->slot_of, c->num_nodes, static_cast<const char *>(c->feats), fs};
+#define MQG_SLOTS(V)                                                                                                                        \
+    MQG_LAUNCH(ctx, "k_gather_slots", s,                                                                                                    \
+               (k_gather_slots<V, IdxT><<<count_blocks + copy_blocks, kBlock, 0, s>>>(rows, num_ids, cap, static_cast<const char *>(c->cache_rows), cs, \
+                                                                                      static_cast<char *>(out), out_stride_bytes, g.vecs, g.log2_lpr,   \
+                                                                                      magic, count_blocks, copy_blocks, ctx->counters, stats)))
+    switch (g.vb) {
+        case 16: MQG_SLOTS(uint4); break;
+        case 8: MQG_SLOTS(uint2); break;
+        case 4: MQG_SLOTS(uint32_t); break;
+        default: MQG_SLOTS(uint16_t); break;
+    }
+#undef MQG_SLOTS
+    return MQG_OK;
+}
+
 // Is p host memory (as opposed to memory of a GPU)?  Unknown pointers count as host.
 bool is_host_memory(const void *p) {
     hipPointerAttribute_t attr;
@@ -677,6 +807,12 @@ int run_gather(mqg_ctx *ctx, const mqg_cache *c, int32_t idx_type, const void *i
         return MQG_OK;
     }
 
+    if (phases == (kGatherCached | kGatherMissed) && c->num_cached == c->num_nodes && c->num_nodes > 0 && !ctx->profile) {
+        bool done = false;
+        const int rc = idx_type == MQG_I64 ? launch_slots(ctx, c, static_cast<const int64_t *>(ids), num_ids, cap_ids, out, out_stride * elt, row_bytes, elt, stats, &done, s)
+                                           : launch_slots(ctx, c, static_cast<const int32_t *>(ids), num_ids, cap_ids, out, out_stride * elt, row_bytes, elt, stats, &done, s);
+        if (rc != MQG_OK || done) return rc;
+    }
     unsigned long long *counters = ctx->counters;
     int hit_vec, miss_vec;
     const RowSide hit = row_side(ctx->hit_list, c->cache_rows, c->cache_stride * elt, out, out_stride * elt, row_bytes, cap_ids, false, 0, &hit_vec);

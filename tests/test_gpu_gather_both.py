@@ -46,6 +46,31 @@ def test_both_sides(dim, dtype, feat_pad, cache_pad):
         assert stats.tolist() == [hits, int(valid.sum()) - hits]
 
 
+@pytest.mark.parametrize("dim,dtype,feat_pad,cache_pad", [(64, torch.float32, 0, 0), (602, torch.float32, 6, 6), (602, torch.float32, 0, 14),
+                                                          (30, torch.float16, 2, 2), (7, torch.float16, 1, 1), (7, torch.float16, 0, 1)])
+@pytest.mark.parametrize("idx", [torch.int32, torch.int64])
+def test_every_node_cached(dim, dtype, feat_pad, cache_pad, idx):
+    """Also where the table of slots says otherwise for some nodes: their rows come from the feature matrix."""
+    n = 3000
+    mqg, ctx, cache, feats, gen = setup(n, dim, dtype, feat_pad, n, cache_pad)
+    for gone in (0, 700, n):
+        cache.slot_of[torch.randperm(n, generator=gen, device="cuda")[:gone]] = -1
+        for count in (0, 1, 255, 4000, 45_000):
+            ids = torch.randint(-20, n + 20, (max(count, 1) + 9,), generator=gen, device="cuda")
+            valid = (ids >= 0) & (ids < n)
+            valid[count:] = False
+            buf = torch.full((len(ids), dim + 8), 3.0, dtype=dtype, device="cuda")
+            stats = torch.full((2,), -1, dtype=torch.int64, device="cuda")
+            for _ in range(2):
+                mqg.mqg_gather_features(ctx, cache, ids.to(idx), torch.tensor([count], device="cuda"), buf[:, :dim], stats)
+            torch.cuda.synchronize()
+            want = torch.full((len(ids), dim), 3.0, dtype=dtype, device="cuda")
+            want[valid] = feats[ids[valid]]
+            assert torch.equal(buf[:, :dim], want) and torch.all(buf[:, dim + 7:] == 3.0)
+            hits = int((cache.slot_of[ids[valid]] >= 0).sum())
+            assert stats.tolist() == [hits, int(valid.sum()) - hits]
+
+
 @pytest.mark.parametrize("rows", [1, 2000, 12_287, 12_288, 12_289, 40_000])
 @pytest.mark.parametrize("dim", [64, 602])
 def test_statistics_without_a_cache(rows, dim):

@@ -662,7 +662,7 @@ int ensure_backward_scratch(mqg_ctx *ctx, int64_t nnz_cap, int64_t src_cap, hipS
     const int64_t nn = std::max<int64_t>(std::max(nnz_cap, ctx->max_nnz), 1);
     const int64_t ns = std::max<int64_t>(std::max(src_cap, ctx->max_src), 1);
     auto alloc = [&](void **p, int64_t bytes) { return hipMalloc(p, static_cast<size_t>(std::max<int64_t>(bytes, 4))) == hipSuccess; };
-    bool ok = alloc(reinterpret_cast<void **>(&ctx->bwd.keys[0]), nn * 4) && alloc(reinterpret_cast<void **>(&ctx->bwd.keys[1]), nn * 4) &&
+    bool ok = alloc(reinterpret_cast<void **>(&ctx->bwd.keys[0]), nn * 4 + 16) && alloc(reinterpret_cast<void **>(&ctx->bwd.keys[1]), nn * 4) &&
               alloc(reinterpret_cast<void **>(&ctx->bwd.vals[0]), nn * 4) && alloc(reinterpret_cast<void **>(&ctx->bwd.vals[1]), nn * 4) &&
               alloc(reinterpret_cast<void **>(&ctx->bwd.hist), std::max(radix_hist_len_max(nn), order_hist_len(nn)) * 4) &&
               alloc(reinterpret_cast<void **>(&ctx->bwd.totals), kRadixTotals * 4) &&

@@ -65,7 +65,7 @@ __global__ void k_direct_stats(int64_t *stats, const int64_t *num_ids, int64_t c
 constexpr int64_t kClassifyLarge = int64_t(1) << 19;
 constexpr int64_t kClassifySmall = int64_t(1) << 15;
 struct ClassifyLds {
-    int hits[kWavesPerBlock], misses[kWavesPerBlock];
+    int hits[kWavesPerBlock], misses[kWavesPerBlock], bad[kWavesPerBlock];
     unsigned long long base[2];
 };
 template <int ITEMS, typename IdxT>
@@ -97,23 +97,24 @@ __device__ __forceinline__ void classify_tiles(const IdxT *__restrict__ ids, int
             h += popc64(ballot64(slot[q] >= 0));
             m += popc64(ballot64(slot[q] < 0 && (kHoles || id[q] >= 0)));
         }
+        if (kHoles && ballot64(bad != 0)) bad = wave_sum(bad);       // nearly always there are none
         if (lane == 0) {
             lds.hits[wave] = h;
             lds.misses[wave] = m;
+            lds.bad[wave] = bad;
         }
-        if (kHoles) {
-            // (a workgroup's bad ids are counted before its tile is; nearly always there are none)
-            if (bad) atomicAdd(&counters[kCountBad], static_cast<unsigned long long>(bad));
-            if (__syncthreads_or(bad)) __threadfence();
-        } else {
-            __syncthreads();
-        }
+        __syncthreads();
         if (threadIdx.x == 0) {
-            unsigned long long th = 0, tm = 0;
+            unsigned long long th = 0, tm = 0, tb = 0;
 #pragma unroll
             for (int w = 0; w < kWavesPerBlock; ++w) {
                 th += static_cast<unsigned>(lds.hits[w]);
                 tm += static_cast<unsigned>(lds.misses[w]);
+                tb += static_cast<unsigned>(lds.bad[w]);
+            }
+            if (kHoles && tb) {                            // counted before the tile is, by the same thread
+                atomicAdd(&counters[kCountBad], tb);
+                __threadfence();
             }
             const unsigned long long before = atomicAdd(&counters[kCountSplit], kHoles ? th | 1ull << 32 : th | tm << 21 | 1ull << 42);
             const unsigned long long tiles_before = before >> (kHoles ? 32 : 42), hits_before = before & (kHoles ? 0xFFFFFFFFull : 0x1FFFFFull);

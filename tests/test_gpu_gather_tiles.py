@@ -101,3 +101,30 @@ def test_tiles_follow_the_number_of_ids():
                 mqg.mqg_gather_features(ctx, cache, ids, count, out, None, cap_ids=cap)
             took[cap].append(ctx.kernel_time("k_classify")[0])
     assert min(took[ids_cap]) < 1.35 * min(took[100_000]), took
+
+
+@pytest.mark.parametrize("share", [0.001, 0.5, 1.0])
+def test_counts_with_ids_outside_the_graph(share):
+    """More than 524,288 ids: the ids outside the graph are counted apart, each workgroup's before its tile, so that whoever
+    counts the last tile has all of them.  Many calls, each checked; a count left behind would show in the next one."""
+    from paper_2601_04707_amd import mqg
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    n, num = 20_000, 600_001
+    g = mqg.Graph(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(0, dtype=torch.int64, device="cuda"))
+    ctx = mqg.Context(g, num, [1])
+    cache = mqg.Cache(g, torch.ones((n, 2), device="cuda"), n // 2)
+    mqg.mqg_build_cache(ctx, g, cache)
+    out = torch.empty((num, 2), device="cuda")
+    count = torch.tensor([num], device="cuda")
+    stats = torch.zeros((40, 2), dtype=torch.int64, device="cuda")
+    want = []
+    for k in range(40):
+        ids = torch.randint(0, n, (num,), generator=gen, device="cuda")
+        bad = torch.rand(num, generator=gen, device="cuda") < share
+        ids[bad] = -1 - ids[bad]
+        out.fill_(3.0)
+        mqg.mqg_gather_features(ctx, cache, ids, count, out, stats[k])
+        hits = int((cache.slot_of[ids[~bad]] >= 0).sum())
+        want.append([hits, int((~bad).sum()) - hits])
+        assert torch.all(out[bad] == 3.0) and torch.all(out[~bad] == 1.0)
+    assert stats.tolist() == want

@@ -171,7 +171,7 @@ int mqg_ctx_create(mqg_ctx **out, const mqg_graph *g, int32_t max_seeds, const i
     ok = ok && dev_alloc(&c->heavy_rows, c->max_dst) == hipSuccess;
     ok = ok && dev_alloc(&c->heavy_count, MQG_MAX_LAYERS + 1) == hipSuccess;
     ok = ok && dev_alloc(&c->hit_list, c->max_src) == hipSuccess;
-    ok = ok && dev_alloc(&c->miss_list, c->max_src + mqg::kClassifyMostTile) == hipSuccess;
+    ok = ok && dev_alloc(&c->miss_list, c->max_src) == hipSuccess;
     ok = ok && dev_alloc(&c->counters, 8) == hipSuccess;
     if (ok) ok = hipMemset(c->local_of, 0xFF, std::max<int64_t>(c->num_nodes, 1) * sizeof(int32_t)) == hipSuccess;
     if (ok) ok = hipMemset(c->bitmap, 0, std::max<int64_t>(c->bitmap_words, 1) * sizeof(uint32_t)) == hipSuccess;

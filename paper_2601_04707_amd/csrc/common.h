@@ -15,7 +15,6 @@ constexpr int kWave = 64;                // CDNA wavefront width
 constexpr int kBlock = 256;              // default workgroup: 4 wavefronts
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kBitmapTileWords = 1024;   // the frontier bitmap is padded to a multiple of this many words
-constexpr int kClassifyMostTile = 4096;  // ids per tile of the gather's split, at most
 constexpr int kCandidates = 256;         // per-wavefront candidate slots of the threshold selection
 
 // Ping-pong buffers of the radix sort (see radix.h)
@@ -90,7 +89,7 @@ struct mqg_ctx {
     int32_t *heavy_rows = nullptr;       // [max_dst] destinations whose degree exceeds heavy_degree
     int32_t *heavy_count = nullptr;      // [MQG_MAX_LAYERS] their number, per block; [MQG_MAX_LAYERS] seed-check flags
     int2 *hit_list = nullptr;            // [max_src] (output row, cache slot)
-    int2 *miss_list = nullptr;           // [max_src + kClassifyMostTile] (output row, node id, or -1 for no row)
+    int2 *miss_list = nullptr;           // [max_src] (output row, node id)
     unsigned long long *counters = nullptr;  // [8] kCount* in gather.hip
     // backward aggregation: edges ordered by source; allocated at the first backward call
     mqg::RadixBufs bwd;

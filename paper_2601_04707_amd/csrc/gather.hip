@@ -27,6 +27,7 @@ namespace {
 // Words of a context's (or the static array's) counters; all but the last two are zero between gathers.
 constexpr int kCountSplit = 0;         // hits, misses and tiles so far, see classify_tiles
 constexpr int kCountBad = 1;           // ids outside the graph, or misses that k_gather_slots counts
+constexpr int kCountTiles = 3;         // tiles of a split into more than its word can count
 constexpr int kCountMissed = 2;        // finished workgroups that copy misses
 constexpr int kCountHits = 4, kCountMisses = 5;    // entries of the lists of the last split; misses are zero again once they are copied
 
@@ -58,36 +59,32 @@ __global__ void k_direct_stats(int64_t *stats, const int64_t *num_ids, int64_t c
 // a wavefront writes consecutive entries.  The order of the list entries is arbitrary; the gather does not depend on
 // it.  An id outside [0, num_nodes) is never used as an index: it goes on neither list, so its output row stays
 // untouched and hits + misses fall short of the number of ids.
-// The word that the atomics go to holds the hits, the misses and the tiles so far, 21 bits each, and whoever adds the last
-// tile hands the numbers on.  In tiles of 4,096 it holds the hits and the tiles: there all that is no hit
-// goes on the miss list, so that the misses before a tile are the ids of the tiles before it less their hits; ids outside the
-// graph, and the places past the ids in the last tile, hold node -1, which the copy passes over.
-constexpr int64_t kClassifyLarge = int64_t(1) << 19;
+// The word that the atomics go to holds the hits and the misses so far, BITS bits each, and above them the tiles: whoever adds the last
+// tile hands the numbers on.  2^25 ids and more leave no bits for the tiles: they are counted in a word of their own.
+constexpr int64_t kClassifyLarge = int64_t(1) << 19, kClassifyHuge = int64_t(1) << 25;
 constexpr int64_t kClassifySmall = int64_t(1) << 15;
 struct ClassifyLds {
-    int hits[kWavesPerBlock], misses[kWavesPerBlock], bad[kWavesPerBlock];
+    int hits[kWavesPerBlock], misses[kWavesPerBlock];
     unsigned long long base[2];
 };
-template <int ITEMS, typename IdxT>
+template <int ITEMS, int BITS, typename IdxT>
 __device__ __forceinline__ void classify_tiles(const IdxT *__restrict__ ids, int64_t n, const int32_t *__restrict__ slot_of, int64_t num_nodes,
                                                int2 *__restrict__ hit_list, int2 *__restrict__ miss_list,
                                                unsigned long long *__restrict__ counters, int64_t *__restrict__ stats, ClassifyLds &lds, int grid) {
     constexpr int kTile = kBlock * ITEMS;
-    constexpr bool kHoles = ITEMS == 16;                   // more than kClassifyLarge ids
-    static_assert(kClassifyLarge < (1 << 21), "ids and tiles fit 21 bits");
+    constexpr bool kTilesApart = BITS == 32;
+    constexpr unsigned long long kMask = (1ull << BITS) - 1;
     const int lane = lane_id();
     const int wave = static_cast<int>(threadIdx.x) >> 6;
     const int64_t tiles = n > 0 ? (n + kTile - 1) / kTile : 1;             // of no ids one, for the numbers
     for (int64_t tile = blockIdx.x; tile < tiles; tile += grid) {
         const int64_t t0 = tile * kTile;
         int32_t id[ITEMS], slot[ITEMS];
-        int bad = 0;
 #pragma unroll
         for (int q = 0; q < ITEMS; ++q) {
             const int64_t i = t0 + q * kBlock + threadIdx.x;
             const int64_t raw = i < n ? static_cast<int64_t>(ids[i]) : -1;
             id[q] = raw >= 0 && raw < num_nodes ? static_cast<int32_t>(raw) : -1;
-            bad += i < n && id[q] < 0 ? 1 : 0;
         }
 #pragma unroll
         for (int q = 0; q < ITEMS; ++q) slot[q] = id[q] >= 0 ? slot_of[id[q]] : -1;
@@ -95,45 +92,23 @@ __device__ __forceinline__ void classify_tiles(const IdxT *__restrict__ ids, int
 #pragma unroll
         for (int q = 0; q < ITEMS; ++q) {
             h += popc64(ballot64(slot[q] >= 0));
-            m += popc64(ballot64(slot[q] < 0 && (kHoles || id[q] >= 0)));
+            m += popc64(ballot64(slot[q] < 0 && id[q] >= 0));
         }
-        if (kHoles && ballot64(bad != 0)) bad = wave_sum(bad);       // nearly always there are none
         if (lane == 0) {
             lds.hits[wave] = h;
             lds.misses[wave] = m;
-            lds.bad[wave] = bad;
         }
         __syncthreads();
+        unsigned long long th = 0, tm = 0, before = 0;     // of thread 0
         if (threadIdx.x == 0) {
-            unsigned long long th = 0, tm = 0, tb = 0;
 #pragma unroll
             for (int w = 0; w < kWavesPerBlock; ++w) {
                 th += static_cast<unsigned>(lds.hits[w]);
                 tm += static_cast<unsigned>(lds.misses[w]);
-                tb += static_cast<unsigned>(lds.bad[w]);
             }
-            if (kHoles && tb) {                            // counted before the tile is, by the same thread
-                atomicAdd(&counters[kCountBad], tb);
-                __threadfence();
-            }
-            const unsigned long long before = atomicAdd(&counters[kCountSplit], kHoles ? th | 1ull << 32 : th | tm << 21 | 1ull << 42);
-            const unsigned long long tiles_before = before >> (kHoles ? 32 : 42), hits_before = before & (kHoles ? 0xFFFFFFFFull : 0x1FFFFFull);
-            const unsigned long long misses_before = kHoles ? tiles_before * kTile - hits_before : before >> 21 & 0x1FFFFFull;
-            lds.base[0] = hits_before;
-            lds.base[1] = misses_before;
-            if (static_cast<int64_t>(tiles_before) == tiles - 1) {
-                // the last tile: the words are left at zero, so that the call is self-contained and can be replayed from
-                // a recorded graph
-                const unsigned long long all = hits_before + th, missed = misses_before + tm;
-                const unsigned long long skipped = kHoles ? atomicExch(&counters[kCountBad], 0ull) : 0ull;
-                counters[kCountSplit] = 0;
-                counters[kCountHits] = all;
-                counters[kCountMisses] = missed;
-                if (stats) {
-                    stats[0] = static_cast<int64_t>(all);
-                    stats[1] = kHoles ? n - static_cast<int64_t>(all + skipped) : static_cast<int64_t>(missed);
-                }
-            }
+            before = atomicAdd(&counters[kCountSplit], th | tm << BITS | (kTilesApart ? 0ull : 1ull << (2 * BITS & 63)));
+            lds.base[0] = before & kMask;
+            lds.base[1] = before >> BITS & kMask;
         }
         __syncthreads();
         int64_t ph = static_cast<int64_t>(lds.base[0]), pm = static_cast<int64_t>(lds.base[1]);
@@ -144,12 +119,35 @@ __device__ __forceinline__ void classify_tiles(const IdxT *__restrict__ ids, int
 #pragma unroll
         for (int q = 0; q < ITEMS; ++q) {
             const int i = static_cast<int>(t0 + q * kBlock + threadIdx.x);
-            const bool hit = slot[q] >= 0, miss = !hit && (kHoles || id[q] >= 0);
+            const bool hit = slot[q] >= 0, miss = slot[q] < 0 && id[q] >= 0;
             const uint64_t hb = ballot64(hit), mb = ballot64(miss);
             if (hit) hit_list[ph + popc64(hb & lanes_below(lane))] = make_int2(i, slot[q]);
             if (miss) miss_list[pm + popc64(mb & lanes_below(lane))] = make_int2(i, id[q]);
             ph += popc64(hb);
             pm += popc64(mb);
+        }
+        if (threadIdx.x == 0) {
+            // (tiles apart: a tile is counted once its share is reserved, so whoever counts the last finds all reserved)
+            bool last;
+            unsigned long long all = before + (th | tm << BITS);
+            if (kTilesApart) {
+                __threadfence();
+                last = atomicAdd(&counters[kCountTiles], 1ull) == static_cast<unsigned long long>(tiles - 1);
+                if (last) all = atomicAdd(&counters[kCountSplit], 0ull);
+            } else {
+                last = static_cast<int64_t>(before >> (2 * BITS & 63)) == tiles - 1;
+            }
+            if (last) {
+                // the words are left at zero, so that the call is self-contained and can be replayed from a recorded graph
+                counters[kCountSplit] = 0;
+                if (kTilesApart) counters[kCountTiles] = 0;
+                counters[kCountHits] = all & kMask;
+                counters[kCountMisses] = all >> BITS & kMask;
+                if (stats) {
+                    stats[0] = static_cast<int64_t>(all & kMask);
+                    stats[1] = static_cast<int64_t>(all >> BITS & kMask);
+                }
+            }
         }
         __syncthreads();                                // hits[], misses[] and base are rewritten by the next tile
     }
@@ -163,31 +161,30 @@ k_classify(const IdxT *__restrict__ ids, const int64_t *__restrict__ num_ids, in
     __shared__ ClassifyLds lds;
     int64_t n = *num_ids;
     if (n > cap) n = cap;
-    if (n > kClassifyLarge) classify_tiles<16>(ids, n, slot_of, num_nodes, hit_list, miss_list, counters, stats, lds, grid);
-    else if (n > kClassifySmall) classify_tiles<4>(ids, n, slot_of, num_nodes, hit_list, miss_list, counters, stats, lds, grid);
-    else classify_tiles<1>(ids, n, slot_of, num_nodes, hit_list, miss_list, counters, stats, lds, grid);
+    // 4,096 ids a tile: fewer than 2^25 ids in at most 2^13 tiles, 25 + 25 + 14 bits; otherwise at most 2^19 ids and 2^9 tiles
+    if (n >= kClassifyHuge) classify_tiles<16, 32>(ids, n, slot_of, num_nodes, hit_list, miss_list, counters, stats, lds, grid);
+    else if (n > kClassifyLarge) classify_tiles<16, 25>(ids, n, slot_of, num_nodes, hit_list, miss_list, counters, stats, lds, grid);
+    else if (n > kClassifySmall) classify_tiles<4, 21>(ids, n, slot_of, num_nodes, hit_list, miss_list, counters, stats, lds, grid);
+    else classify_tiles<1, 21>(ids, n, slot_of, num_nodes, hit_list, miss_list, counters, stats, lds, grid);
 }
 
 // Which rows to copy: entry r of a (output row, source row) list, or row ids[r] to output row r.
 // get() returns false for a row that must not be written (an id outside the feature matrix); the
 // source row is then 0, so that a load issued before the check stays inside the matrix.  skipped()
 // is called once per such row.
-template <bool HOLES>
 struct ListRows {
-    static constexpr bool kHoles = HOLES;        // entries without a row
     const int2 *list;
     __device__ __forceinline__ bool get(int64_t r, int64_t *src_row, int64_t *dst_row) const {
         int2 e = list[r];
-        *src_row = HOLES && e.y < 0 ? 0 : e.y;
+        *src_row = e.y;
         *dst_row = e.x;
-        return !HOLES || e.y >= 0;
+        return true;
     }
     __device__ __forceinline__ const char *at(int64_t row, const char *src, int64_t stride) const { return src + row * stride; }
     __device__ __forceinline__ void skipped() const {}
 };
 template <typename IdxT, bool IN_LDS>
 struct DirectRows {
-    static constexpr bool kHoles = false;
     const IdxT *ids;
     int64_t num_rows;                    // rows of the source matrix
     unsigned long long *bad;             // counter of skipped rows, may be null ...
@@ -209,7 +206,6 @@ struct DirectRows {
 // Row ids[r] to output row r, from the cache if it has a slot there and else from the feature matrix (row -1 - id).
 template <typename IdxT>
 struct SlotRows {
-    static constexpr bool kHoles = false;
     const IdxT *ids;
     const int32_t *slot_of;
     int64_t num_nodes;                   // at least 1, and so has the cache a row
@@ -248,8 +244,7 @@ constexpr int kRowUnroll = 4;                            // row loads in flight 
 // Longer rows: all 64 lanes walk WR rows at a time, NCH 64-vector chunks of each, so that up to
 // eight loads per lane are issued before the first store (a row's last, partial chunk rides along
 // instead of trailing alone).  NCH is the number of chunks a row needs, at most four; loads are
-// unconditional (an index past the row re-reads its last vector), only the stores are predicated; rows of a list with holes are
-// loaded if they are rows.
+// unconditional (an index past the row re-reads its last vector), only the stores are predicated.
 template <typename VecT, int NCH, int WR, bool STREAM, typename Rows>
 __device__ __forceinline__ void copy_rows_wide(const Rows &rows, int64_t n, const char *__restrict__ src,
                                                int64_t src_stride_bytes, char *__restrict__ dst,
@@ -274,14 +269,12 @@ __device__ __forceinline__ void copy_rows_wide(const Rows &rows, int64_t n, cons
         for (int c0 = lane; c0 < vecs; c0 += NCH * kWave) {
             VecT v[WR][NCH];
 #pragma unroll
-            for (int q = 0; q < WR; ++q) {
-                if (Rows::kHoles && !rok[q]) continue;     // uniform
+            for (int q = 0; q < WR; ++q)
 #pragma unroll
                 for (int k = 0; k < NCH; ++k) {
                     const int c = c0 + k * kWave;
                     v[q][k] = load_vec<STREAM>(&sp[q][c < vecs ? c : vecs - 1]);
                 }
-            }
 #pragma unroll
             for (int q = 0; q < WR; ++q)
 #pragma unroll
@@ -323,7 +316,7 @@ __device__ __forceinline__ void copy_rows(const Rows &rows, int64_t n, const cha
     for (int64_t base = wave0 * per_wave; base < n; base += nwaves * per_wave) {
         const VecT *sp[kRowUnroll];
         VecT *dp[kRowUnroll];
-        bool ok[kRowUnroll], load[kRowUnroll];
+        bool ok[kRowUnroll];
         VecT v[kRowUnroll];
 #pragma unroll
         for (int u = 0; u < kRowUnroll; ++u) {
@@ -335,13 +328,12 @@ __device__ __forceinline__ void copy_rows(const Rows &rows, int64_t n, const cha
                 if (!valid && gl == 0) rows.skipped();
             }
             ok[u] = valid && gl < vecs;
-            load[u] = (Rows::kHoles ? r < n : valid) && gl < vecs;         // (a hole reads row 0: no wait for the list before)
             sp[u] = reinterpret_cast<const VecT *>(rows.at(srow, src, src_stride_bytes)) + gl;
             dp[u] = reinterpret_cast<VecT *>(dst + drow * dst_stride_bytes) + gl;
         }
 #pragma unroll
         for (int u = 0; u < kRowUnroll; ++u)
-            if (load[u]) v[u] = *sp[u];
+            if (ok[u]) v[u] = *sp[u];
 #pragma unroll
         for (int u = 0; u < kRowUnroll; ++u)
             if (ok[u]) *dp[u] = v[u];
@@ -416,7 +408,7 @@ k_gather_rows(RowSide hit, RowSide miss, char *__restrict__ dst, int64_t dst_str
         const int64_t n = static_cast<int64_t>(counters[kCountHits]);
         // a launch that moves more than the last-level cache holds reads its source rows past the caches
         const bool streaming = sizeof(VecT) == 16 && 2 * n * hit.vecs * int64_t(sizeof(VecT)) > kStreamingBytes;
-        const ListRows<false> rows{hit.list};
+        const ListRows rows{hit.list};
         if (streaming) {                                   // one uniform branch; the copies themselves are straight code
             if (hit.magic) copy_rows_flat<VecT, true>(rows, n, hit.src, hit.src_stride_bytes, dst, dst_stride_bytes, hit.vecs, hit.magic, vb, hit.blocks);
             else copy_rows<VecT, true>(rows, n, hit.src, hit.src_stride_bytes, dst, dst_stride_bytes, hit.vecs, hit.log2_lpr, vb, hit.blocks);
@@ -428,7 +420,7 @@ k_gather_rows(RowSide hit, RowSide miss, char *__restrict__ dst, int64_t dst_str
     }
     if (WHAT == 0) return;
     const int64_t n = static_cast<int64_t>(counters[kCountMisses]);
-    copy_rows<VecT, false>(ListRows<true>{miss.list}, n, miss.src, miss.src_stride_bytes, dst, dst_stride_bytes, miss.vecs, miss.log2_lpr, b, miss.blocks);
+    copy_rows<VecT, false>(ListRows{miss.list}, n, miss.src, miss.src_stride_bytes, dst, dst_stride_bytes, miss.vecs, miss.log2_lpr, b, miss.blocks);
     __syncthreads();                                       // every thread of the workgroup has read the number
     if (threadIdx.x == 0) {
         __threadfence();
@@ -817,9 +809,8 @@ int run_gather(mqg_ctx *ctx, const mqg_cache *c, int32_t idx_type, const void *i
     unsigned long long *counters = ctx->counters;
     int hit_vec, miss_vec;
     const RowSide hit = row_side(ctx->hit_list, c->cache_rows, c->cache_stride * elt, out, out_stride * elt, row_bytes, cap_ids, false, 0, &hit_vec);
-    RowSide miss = row_side(ctx->miss_list, c->feats, c->feat_stride * elt, out, out_stride * elt, row_bytes, cap_ids, true,
+    const RowSide miss = row_side(ctx->miss_list, c->feats, c->feat_stride * elt, out, out_stride * elt, row_bytes, cap_ids, true,
                                   ctx->miss_inflight_bytes, &miss_vec);
-    if (c->num_nodes == 0) miss.vecs = 0;                 // no row that a hole could read
     if (phases & kGatherCached) {
         const int cgrid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(cap_ids, cap_ids <= 4 * kClassifySmall ? kBlock : kBlock * 4)), 1024));
 #define MQG_CLASSIFY(IT)                                                                                               \

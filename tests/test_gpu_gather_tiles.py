@@ -128,3 +128,57 @@ def test_counts_with_ids_outside_the_graph(share):
         want.append([hits, int((~bad).sum()) - hits])
         assert torch.all(out[bad] == 3.0) and torch.all(out[~bad] == 1.0)
     assert stats.tolist() == want
+
+
+def test_more_ids_than_the_split_counts_in_one_word():
+    """2^25 ids and more: the tiles are counted apart from the hits and misses."""
+    from paper_2601_04707_amd import mqg
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    n, cap = 100_000, (1 << 25) + 5000
+    g = mqg.Graph(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(0, dtype=torch.int64, device="cuda"))
+    ctx = mqg.Context(g, cap, [1])
+    feats = torch.arange(n, device="cuda").remainder(2039).half().unsqueeze(1)
+    cache = mqg.Cache(g, feats, n // 2, cache_stride=1)
+    mqg.mqg_build_cache(ctx, g, cache)
+    ids = torch.randint(-100, n, (cap,), generator=gen, device="cuda", dtype=torch.int32)
+    out = torch.empty((cap, 1), dtype=torch.float16, device="cuda")
+    stats = torch.zeros(2, dtype=torch.int64, device="cuda")
+    for num in (cap, (1 << 25) - 1, 1 << 25, 1 << 25):
+        used = ids[:num]
+        valid = used >= 0
+        out.fill_(-1.0)
+        mqg.mqg_gather_features(ctx, cache, ids, torch.tensor([num], device="cuda"), out, stats)
+        assert torch.equal(out[:num, 0], torch.where(valid, used.remainder(2039).half(), torch.tensor(-1.0, device="cuda").half()))
+        assert torch.all(out[num:] == -1.0)
+        hits = int((cache.slot_of[used[valid].long()] >= 0).sum())
+        assert stats.tolist() == [hits, int(valid.sum()) - hits]
+
+
+def test_ids_outside_the_graph_cost_no_copy():
+    """700,001 ids, half of them -1: no longer than with cached ids in their place (3 times as long with places for them on the
+    list of missed rows, and far longer with reads of a row over the host link for each)."""
+    from paper_2601_04707_amd import mqg
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    n, num, dim = 100_000, 700_001, 64
+    g = mqg.Graph(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(0, dtype=torch.int64, device="cuda"))
+    ctx = mqg.Context(g, num, [1])
+    cache = mqg.Cache(g, torch.zeros((n, dim)).pin_memory(), n // 2, cache_stride=dim)
+    mqg.mqg_build_cache(ctx, g, cache)
+    cached = torch.nonzero(cache.slot_of >= 0).flatten()
+    hits = cached[torch.randint(0, len(cached), (num,), generator=gen, device="cuda")]
+    half = torch.where(torch.rand(num, generator=gen, device="cuda") < 0.5, -1, hits)
+    out = torch.empty((num, dim), device="cuda")
+    count = torch.tensor([num], device="cuda")
+    took = []
+    for ids in (hits, half):
+        best = float("inf")
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                mqg.mqg_gather_features(ctx, cache, ids, count, out, None)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        took.append(best)
+    assert took[1] < 1.4 * took[0], took

@@ -10,7 +10,7 @@
 //                     time by a wavefront; misses: feature matrix -> HBM output.  One launch for both, the few
 //                     workgroups that keep the host link busy first; in halves, and while profiling, a launch
 //                     each (<., 0> hits, <., 1> misses, so that profiles tell the HBM-bound from the link-bound)
-//   k_gather_slots    a cache that holds every node: slot lookup and copy in one launch
+//   k_gather_slots    a cache that holds every node: slot lookup and copy in one launch, but for many narrow rows
 //   k_gather_direct   no cache: every row straight from the feature matrix
 #include <hip/hip_ext.h>
 
@@ -694,7 +694,17 @@ int launch_direct(mqg_ctx *ctx, const IdxT *ids, const int64_t *num_ids, int64_t
     return MQG_OK;
 }
 
-// *done: false if the two sources' rows cannot be copied with the same vectors; nothing is launched then.
+// Up to how many ids a gather from a cache that holds every node goes without lists.  There every lane looks up the slot of its own
+// vector's row, and the counting workgroups once more: what that costs grows with the vectors, what the lists cost with the ids, and they take a
+// launch more.  Rows of 128 bytes and more in 16-byte vectors: always (with and without lists, 1 M rows of 128 bytes 64 and 63 us,
+// 2.5 M of 256 290 and 262); narrower ones up to 512 k ids (64 bytes: 500 k ids 30 and 28 us, 1 M 47 and 53, 2.5 M 110 and 132); rows that
+// take narrower vectors, or a single one, up to 128 k (300 bytes in 4-byte vectors: 130 k ids 25 and 23 us, 260 k 37 and 41, 2.5 M 414 and 584).
+int64_t most_ids_by_slots(const RowGeom &g) {
+    if (g.vb < 16 || g.vecs < 2) return int64_t(1) << 17;
+    return g.vecs >= 8 ? int64_t(1) << 62 : int64_t(1) << 19;
+}
+
+// *done: false if the two sources' rows cannot be copied with the same vectors, or the lists are faster; nothing is launched then.
 template <typename IdxT>
 int launch_slots(mqg_ctx *ctx, const mqg_cache *c, const IdxT *ids, const int64_t *num_ids, int64_t cap, void *out, int64_t out_stride_bytes,
                  int64_t row_bytes, int64_t elt, int64_t *stats, bool *done, hipStream_t s) {
@@ -704,7 +714,7 @@ int launch_slots(mqg_ctx *ctx, const mqg_cache *c, const IdxT *ids, const int64_
     int64_t bytes = copy_bytes(row_bytes, cs, out_stride_bytes, c->cache_rows, out, true);
     if (bytes > feat_bytes) bytes = copy_bytes(row_bytes, cs, out_stride_bytes, c->cache_rows, out, false);
     const RowGeom g = row_geom(bytes, cs, out_stride_bytes, c->cache_rows, out);
-    *done = bytes <= feat_bytes && pick_vec_bytes(bytes, fs, out_stride_bytes, c->feats, out) == g.vb;
+    *done = bytes <= feat_bytes && pick_vec_bytes(bytes, fs, out_stride_bytes, c->feats, out) == g.vb && cap <= most_ids_by_slots(g);
     if (!*done) return MQG_OK;
     const unsigned long long magic = flat_magic(cap, g);
     const int copy_blocks = magic ? flat_grid(cap, g) : hbm_grid(cap, g);

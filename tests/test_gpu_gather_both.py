@@ -95,3 +95,56 @@ def test_statistics_without_a_cache(rows, dim):
             torch.cuda.synchronize()
             assert torch.equal(out[: rows - fewer], want[: rows - fewer]) and torch.all(out[rows - fewer:] == 2.0)
             assert stats.tolist() == [0, int(valid[: rows - fewer].sum())]
+
+
+@pytest.mark.parametrize("dim,dtype,cap", [(16, torch.float32, 1 << 19), (16, torch.float32, (1 << 19) + 1), (32, torch.float32, (1 << 19) + 1),
+                                           (45, torch.float16, 1 << 17), (45, torch.float16, (1 << 17) + 1), (6, torch.float32, (1 << 17) + 1)])
+def test_every_node_cached_with_and_without_lists(dim, dtype, cap):
+    """On both sides of the numbers of ids from which narrow rows go through the lists again."""
+    from paper_2601_04707_amd import mqg
+    n = 40_000
+    gen = torch.Generator(device="cuda").manual_seed(dim)
+    g = mqg.Graph(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(0, dtype=torch.int64, device="cuda"))
+    feats = torch.randn((n, dim), generator=gen, device="cuda").to(dtype)
+    ctx = mqg.Context(g, cap, [1])
+    cache = mqg.Cache(g, feats.cpu().pin_memory(), n, cache_stride=dim)
+    mqg.mqg_build_cache(ctx, g, cache)
+    ids = torch.randint(-20, n + 20, (cap,), generator=gen, device="cuda")
+    for num in (cap, 5000):
+        valid = (ids >= 0) & (ids < n) & (torch.arange(cap, device="cuda") < num)
+        out = torch.full((cap, dim), 3.0, dtype=dtype, device="cuda")
+        stats = torch.zeros(2, dtype=torch.int64, device="cuda")
+        mqg.mqg_gather_features(ctx, cache, ids, torch.tensor([num], device="cuda"), out, stats)
+        want = torch.full_like(out, 3.0)
+        want[valid] = feats[ids[valid]]
+        assert torch.equal(out, want)
+        assert stats.tolist() == [int(valid.sum()), 0]
+
+
+def test_many_narrow_rows_with_every_node_cached():
+    """1 M rows of 300 bytes, 4-byte vectors: as fast from a cache that holds every node as from one that lacks a single one (1.35
+    times as long with a slot lookup per vector)."""
+    from paper_2601_04707_amd import mqg
+    n, num, dim = 2_000_000, 1_000_000, 150
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    g = mqg.Graph(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(0, dtype=torch.int64, device="cuda"))
+    feats = torch.zeros((n, dim), dtype=torch.float16, device="cuda")
+    ctx = mqg.Context(g, num, [1])
+    out = torch.empty((num, dim), dtype=torch.float16, device="cuda")
+    count = torch.tensor([num], device="cuda")
+    caches = [mqg.Cache(g, feats, k, cache_stride=dim) for k in (n, n - 1)]
+    for cache in caches:
+        mqg.mqg_build_cache(ctx, g, cache)
+    cached = torch.nonzero(caches[1].slot_of >= 0).flatten()
+    ids = cached[torch.randint(0, len(cached), (num,), generator=gen, device="cuda")]
+    best = [float("inf")] * 2
+    for _ in range(8):
+        for k, cache in enumerate(caches):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                mqg.mqg_gather_features(ctx, cache, ids, count, out, None)
+            b.record()
+            torch.cuda.synchronize()
+            best[k] = min(best[k], a.elapsed_time(b))
+    assert best[0] < 1.15 * best[1], best

@@ -173,6 +173,7 @@ k_lw_mass(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ col_idx, co
 // kBlock * WPT words (WPT = 1 up to 32 M nodes, ids staged through LDS and written coalesced;
 // otherwise 4, one 16-byte load per thread, ids written from the bit loop: those bitmaps are sparse).
 constexpr int kMassTileNodes = kBlock * 32;          // nodes behind one tile of kBlock words
+constexpr int kEmitFewTiles = 32, kEmitParts = 8;    // see k_lw_emit
 
 // The touched nodes from the masses themselves (bit i = mass[i] != 0), for graphs small enough that
 // reading every mass costs less than marking a bit per adjacency slot in k_lw_mass; the same launch
@@ -242,25 +243,69 @@ struct LwColumns {
     const unsigned long long *mass;
     int flat, debias;
     double *factor;                      // [sources]; null: a list of candidates, no factors
+    template <typename PtrT, int U>
+    __device__ __forceinline__ void values(const int32_t (&i)[U], double (&f)[U]) const {
+        const PtrT *rp = static_cast<const PtrT *>(row_ptr);
+        PtrT begin[U], end[U];
+        unsigned long long m[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            begin[u] = rp[i[u]];
+            end[u] = rp[int64_t(i[u]) + 1];
+            m[u] = mass[i[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double di = static_cast<double>(static_cast<int64_t>(end[u]) - static_cast<int64_t>(begin[u]) + 1);
+            const double mi = static_cast<double>(m[u]);
+            f[u] = debias ? 1.0 / sqrt(di) : flat ? 1.0 / (sqrt(mi / di) * sqrt(di)) : di / (mi * sqrt(di));
+        }
+    }
     template <typename PtrT>
     __device__ __forceinline__ double value(int64_t i) const {
-        const PtrT *rp = static_cast<const PtrT *>(row_ptr);
-        const double di = static_cast<double>(static_cast<int64_t>(rp[i + 1]) - static_cast<int64_t>(rp[i]) + 1);
-        const double m = static_cast<double>(mass[i]);
-        return debias ? 1.0 / sqrt(di) : flat ? 1.0 / (sqrt(m / di) * sqrt(di)) : di / (m * sqrt(di));
+        const int32_t node[1] = {static_cast<int32_t>(i)};
+        double f[1];
+        values<PtrT, 1>(node, f);
+        return f[0];
     }
 };
 
-// ids of the set bits, ascending, into out[0..total); the words are cleared; total to count_a/b.
+template <typename PtrT, int U, typename OutT>
+__device__ __forceinline__ void lw_emit_nodes(const int32_t *staged, int total, int part, int parts, int tile_base, OutT *__restrict__ out,
+                                              int32_t *__restrict__ local_of, int32_t pos_base, const LwColumns &columns) {
+    const int step = parts * kBlock;
+    for (int k0 = part * kBlock + threadIdx.x; k0 < total; k0 += U * step) {
+        int32_t v[U];
+        double f[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = staged[k0 + u * step < total ? k0 + u * step : k0];
+        if (columns.factor) columns.values<PtrT, U>(v, f);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + u * step;
+            if (k >= total) break;
+            out[tile_base + k] = static_cast<OutT>(v[u]);
+            if (local_of) local_of[v[u]] = pos_base + tile_base + k;
+            if (columns.factor) columns.factor[tile_base + k] = f[u];
+        }
+    }
+}
+
+// ids of the set bits, ascending, into out[0..total); the words are cleared (with several workgroups a tile: later, by
+// k_lw_count); total to count_a/b.
+// parts (WPT = 1): workgroups that share a tile's ids: on small graphs there are few tiles, and a node's factor is two loads and a
+// double division and square root (10 k of 20 k nodes in 3 workgroups 11 us).
 // scanned: tile_vals holds the exclusive scan of the tile counts, otherwise the counts themselves.
 template <typename PtrT, typename OutT, int WPT>
 __global__ void __launch_bounds__(kBlock)
 k_lw_emit(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_vals, int scanned, OutT *__restrict__ out,
-          int32_t *__restrict__ local_of, int32_t pos_base, LwColumns columns, int64_t *count_a, int64_t *count_b) {
+          int32_t *__restrict__ local_of, int32_t pos_base, LwColumns columns, int64_t *count_a, int64_t *count_b, int tiles, int parts) {
     __shared__ int lds[kWavesPerBlock];
     __shared__ int32_t staged[WPT == 1 ? kBlock * 32 : 1];   // every id of the tile, ascending
-    const int tile_base = scanned ? tile_vals[blockIdx.x] : tiles_before(tile_vals, lds);
-    const int64_t w0 = (int64_t(blockIdx.x) * kBlock + threadIdx.x) * WPT;
+    const int tile = WPT == 1 ? static_cast<int>(blockIdx.x) / parts : static_cast<int>(blockIdx.x);
+    const int part = static_cast<int>(blockIdx.x) - tile * parts;
+    const int tile_base = scanned ? tile_vals[tile] : tiles_before(tile_vals, lds, tile);
+    const int64_t w0 = (int64_t(tile) * kBlock + threadIdx.x) * WPT;
     uint32_t words[WPT];
     if constexpr (WPT == 4) {
         const uint4 w = *reinterpret_cast<const uint4 *>(bitmap + w0);
@@ -276,7 +321,7 @@ k_lw_emit(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_vals, 
     for (int q = 0; q < WPT; ++q) c += __popc(words[q]);
     int total;
     int ex = block_excl_scan<kWavesPerBlock>(c, &total, lds);
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    if (tile == tiles - 1 && part == 0 && threadIdx.x == 0) {
         const int64_t all = int64_t(tile_base) + total;
         if (count_a) *count_a = all;
         if (count_b) *count_b = all;
@@ -284,7 +329,7 @@ k_lw_emit(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_vals, 
     if (total == 0) return;                                // workgroup-uniform
     if constexpr (WPT == 1) {
         if (c) {
-            bitmap[w0] = 0;
+            if (parts == 1) bitmap[w0] = 0;
             const int32_t v0 = static_cast<int32_t>(w0 * 32);
             uint32_t bits = words[0];
             while (bits) {
@@ -294,12 +339,9 @@ k_lw_emit(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_vals, 
             }
         }
         __syncthreads();
-        for (int k = threadIdx.x; k < total; k += kBlock) {
-            const int32_t v = staged[k];
-            out[tile_base + k] = static_cast<OutT>(v);
-            if (local_of) local_of[v] = pos_base + tile_base + k;
-            if (columns.factor) columns.factor[tile_base + k] = columns.value<PtrT>(v);
-        }
+        // nodes whose loads are issued together, where the tile has as many
+        if (total > parts * kBlock) lw_emit_nodes<PtrT, 4>(staged, total, part, parts, tile_base, out, local_of, pos_base, columns);
+        else lw_emit_nodes<PtrT, 1>(staged, total, part, parts, tile_base, out, local_of, pos_base, columns);
     } else {
         if (c == 0) return;
         int32_t pos = tile_base + ex;
@@ -896,7 +938,7 @@ constexpr int64_t kSelfOffsetRows = 2048;
 
 // A wavefront per (row, chunk): the number of drawn nodes in the chunk's slots (chunk 0 also counts the self edge) and the
 // sum of their columns' factors; the rows' edges (row_count is zero before).  `cleared` workgroups more set
-// the masses of the candidates (of all nodes without a list of them) and the histogram back to zero; the
+// the masses of the candidates (of all nodes without a list of them), the histogram and (bitmap_words) the bitmap back to zero; the
 // block's flags word.  Bound by the lookups behind its caches: the two layers of a batch of 1,024 seeds on a graph of 233 k
 // nodes and mean degree 490 15.8 + 12.9 us, then 5.8 + 4.2
 // for a scan of the counts -> 13.6 + 9.1 (a workgroup per row 20 + 15: a hub's lookups take a 128-byte line each, and a compute
@@ -907,12 +949,13 @@ k_lw_count(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ col_idx, c
            int64_t *sizes, const int32_t *__restrict__ local_of, int32_t pos_base, const double *__restrict__ factor,
            int32_t *__restrict__ counts, double *__restrict__ psum, int32_t *__restrict__ row_count, int row_blocks, int cleared,
            const int32_t *__restrict__ cand, const int64_t *__restrict__ n_cand, int64_t all_nodes, unsigned long long *__restrict__ mass,
-           int32_t *__restrict__ sel_hist, int hist_len, int32_t *__restrict__ seed_flags) {
+           int32_t *__restrict__ sel_hist, int hist_len, uint32_t *__restrict__ bitmap, int64_t bitmap_words, int32_t *__restrict__ seed_flags) {
     const int lane = lane_id();
     if (static_cast<int>(blockIdx.x) >= row_blocks) {
         const int64_t first = int64_t(static_cast<int>(blockIdx.x) - row_blocks) * kBlock + threadIdx.x;
         const int64_t stride = int64_t(cleared) * kBlock;
         for (int64_t k = first; k < hist_len; k += stride) sel_hist[k] = 0;
+        for (int64_t k = first; k < bitmap_words; k += stride) bitmap[k] = 0;
         if (cand) {
             const int64_t nc = *n_cand;
             for (int64_t k = first; k < nc; k += stride) mass[cand[k]] = 0;
@@ -947,13 +990,13 @@ k_lw_count(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ col_idx, c
         chunk_range<kSlotUnroll * kWave>(d, c, &jb, &je);
         // a batch's ids are on their way while the positions of the batch before are looked up, and a batch's
         // factors while the next one's are
-        int64_t id[kSlotUnroll];
+        IdxT id[kSlotUnroll];
         double f[kSlotUnroll];
         auto load = [&](int64_t j0) __attribute__((always_inline)) {
 #pragma unroll
             for (int q = 0; q < kSlotUnroll; ++q) {
                 const int64_t j = j0 + q * kWave + lane;
-                id[q] = static_cast<int64_t>(col_idx[start + (j < je ? j : jb)]);
+                if (j0 + q * kWave < je) id[q] = col_idx[start + (j < je ? j : jb)];         // uniform
             }
         };
 #pragma unroll
@@ -962,10 +1005,13 @@ k_lw_count(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ col_idx, c
         for (int64_t j0 = jb; j0 < je; j0 += kSlotUnroll * kWave) {
             int32_t li[kSlotUnroll];
 #pragma unroll
-            for (int q = 0; q < kSlotUnroll; ++q) li[q] = local_of[id[q]] - pos_base;
+            for (int q = 0; q < kSlotUnroll; ++q)
+                if (j0 + q * kWave < je) li[q] = local_of[id[q]];
             if (j0 + kSlotUnroll * kWave < je) load(j0 + kSlotUnroll * kWave);
 #pragma unroll
             for (int q = 0; q < kSlotUnroll; ++q) {
+                if (j0 + q * kWave >= je) break;           // uniform
+                li[q] -= pos_base;
                 const bool in = li[q] >= 0 && j0 + q * kWave + lane < je;
                 cnt += popc64(ballot64(in));
                 acc += f[q];
@@ -1059,22 +1105,25 @@ k_lw_fill(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ col_idx, co
         }
         int64_t jb, je;
         chunk_range<kSlotUnroll * kWave>(d, c, &jb, &je);
-        int64_t id[kSlotUnroll];
+        IdxT id[kSlotUnroll];
         auto load = [&](int64_t j0) __attribute__((always_inline)) {
 #pragma unroll
             for (int q = 0; q < kSlotUnroll; ++q) {
                 const int64_t j = j0 + q * kWave + lane;
-                id[q] = static_cast<int64_t>(col_idx[start + (j < je ? j : jb)]);
+                if (j0 + q * kWave < je) id[q] = col_idx[start + (j < je ? j : jb)];         // uniform
             }
         };
         if (jb < je) load(jb);
         for (int64_t j0 = jb; j0 < je && pos < end; j0 += kSlotUnroll * kWave) {
             int32_t li[kSlotUnroll];
 #pragma unroll
-            for (int q = 0; q < kSlotUnroll; ++q) li[q] = local_of[id[q]] - pos_base;
+            for (int q = 0; q < kSlotUnroll; ++q)
+                if (j0 + q * kWave < je) li[q] = local_of[id[q]];
             if (j0 + kSlotUnroll * kWave < je) load(j0 + kSlotUnroll * kWave);
 #pragma unroll
             for (int q = 0; q < kSlotUnroll; ++q) {
+                if (j0 + q * kWave >= je) break;           // uniform
+                li[q] -= pos_base;
                 const bool in = li[q] >= 0 && j0 + q * kWave + lane < je;
                 const uint64_t m = ballot64(in);
                 if (in) {
@@ -1274,21 +1323,22 @@ static int sample_layerwise_impl(mqg_ctx *ctx, const mqg_graph *g, const void *s
     const int wpt = ctx->bitmap_words <= (int64_t(1) << 20) ? 1 : 4;
     const int tiles = static_cast<int>(ctx->bitmap_words / (int64_t(kBlock) * wpt));
     const int tiles_scanned = tiles > kSelfPrefixTiles ? 1 : 0;
+    const int emit_parts = tiles <= kEmitFewTiles ? kEmitParts : 1;
     auto count_tiles = [&]() -> int {
         if (wpt == 1) MQG_LAUNCH(ctx, "k_lw_tile_counts", s, (k_lw_tile_counts<1><<<tiles, kBlock, 0, s>>>(ctx->bitmap, w.word_offs)));
         else MQG_LAUNCH(ctx, "k_lw_tile_counts", s, (k_lw_tile_counts<4><<<tiles, kBlock, 0, s>>>(ctx->bitmap, w.word_offs)));
         return MQG_OK;
     };
-    auto emit_list = [&](auto *out, int32_t *local_of, int32_t pos_base, LwColumns columns, int64_t *count_a, int64_t *count_b) -> int {
+    auto emit_list = [&](auto *out, int32_t *local_of, int32_t pos_base, LwColumns columns, int64_t *count_a, int64_t *count_b, int parts) -> int {
         using OutT = std::remove_pointer_t<decltype(out)>;
         if (tiles_scanned) {
             int rc = device_scan(ctx, w.word_offs, tiles, w.scan_tiles, s);
             if (rc != MQG_OK) return rc;
         }
         if (wpt == 1)
-            MQG_LAUNCH(ctx, "k_lw_emit", s, (k_lw_emit<PtrT, OutT, 1><<<tiles, kBlock, 0, s>>>(ctx->bitmap, w.word_offs, tiles_scanned, out, local_of, pos_base, columns, count_a, count_b)));
+            MQG_LAUNCH(ctx, "k_lw_emit", s, (k_lw_emit<PtrT, OutT, 1><<<tiles * parts, kBlock, 0, s>>>(ctx->bitmap, w.word_offs, tiles_scanned, out, local_of, pos_base, columns, count_a, count_b, tiles, parts)));
         else
-            MQG_LAUNCH(ctx, "k_lw_emit", s, (k_lw_emit<PtrT, OutT, 4><<<tiles, kBlock, 0, s>>>(ctx->bitmap, w.word_offs, tiles_scanned, out, local_of, pos_base, columns, count_a, count_b)));
+            MQG_LAUNCH(ctx, "k_lw_emit", s, (k_lw_emit<PtrT, OutT, 4><<<tiles, kBlock, 0, s>>>(ctx->bitmap, w.word_offs, tiles_scanned, out, local_of, pos_base, columns, count_a, count_b, tiles, 1)));
         return MQG_OK;
     };
     const int cand_grid = static_cast<int>(std::max<int64_t>(1, ceil_div(n, kBlock)));
@@ -1352,7 +1402,7 @@ static int sample_layerwise_impl(mqg_ctx *ctx, const mqg_graph *g, const void *s
                     MQG_LAUNCH(ctx, "k_lw_mass_bits", s, (k_lw_mass_bits<<<tiles, kBlock, 0, s>>>(w.mass, n, ctx->bitmap, w.word_offs)));
                 else
                     rc = count_tiles();
-                if (rc == MQG_OK) rc = emit_list(w.cand, nullptr, 0, LwColumns{}, n_cand, nullptr);
+                if (rc == MQG_OK) rc = emit_list(w.cand, nullptr, 0, LwColumns{}, n_cand, nullptr, 1);
                 if (rc != MQG_OK) return rc;
             }
         }
@@ -1390,7 +1440,7 @@ static int sample_layerwise_impl(mqg_ctx *ctx, const mqg_graph *g, const void *s
                        (k_lw_finish<<<1, kBlock, 0, s>>>(cand, n_keys_dev, n, n_cand, layer_sizes[l], w.sel_state, w.bkey, w.bpos, bcount,
                                                          ctx->bitmap)));
             rc = count_tiles();
-            if (rc == MQG_OK) rc = emit_list(src_ids, ctx->local_of, pos_base, columns, &b.sizes[1], next_rows);
+            if (rc == MQG_OK) rc = emit_list(src_ids, ctx->local_of, pos_base, columns, &b.sizes[1], next_rows, emit_parts);
             if (rc != MQG_OK) return rc;
         }
         if (debias) {
@@ -1407,7 +1457,8 @@ static int sample_layerwise_impl(mqg_ctx *ctx, const mqg_graph *g, const void *s
         MQG_LAUNCH(ctx, "k_lw_count", s,
                    (k_lw_count<PtrT, IdxT><<<row_grid + clear_grid, kBlock, 0, s>>>(row_ptr, col_idx, dst, b.sizes, ctx->local_of, pos_base, w.factor,
                                                                                    w.chunk_counts, w.chunk_sum, w.row_count, row_grid, clear_grid, cand, n_cand,
-                                                                                   dense ? n : 0, w.mass, w.sel_hist, pick ? kFineBins : kSelHistLen,
+                                                                                   dense ? n : 0, w.mass, w.sel_hist, pick ? kFineBins : kSelHistLen, ctx->bitmap,
+                                                                                   !pick && emit_parts > 1 ? ctx->bitmap_words : 0,
                                                                                    l == L - 1 ? w.flags : nullptr)));
         const int scanned = rows_cap > kSelfOffsetRows ? 1 : 0;
         if (scanned) {

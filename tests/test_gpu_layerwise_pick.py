@@ -68,3 +68,33 @@ def test_many_rows(num_seeds, sizes):
     rp, ci = synth.chung_lu_graph(20000, 200_000, max_degree=900, seed=4)
     seeds = np.random.default_rng(3).permutation(20000)[:num_seeds].astype(np.int64)
     check(mqg, rp, ci, seeds, sizes, 5)
+
+
+@pytest.mark.parametrize("n", [262_144, 262_145])
+@pytest.mark.parametrize("candidates", [0, 2, 3])
+def test_large_layers_around_32_tiles(n, candidates):
+    """Up to 32 tiles of the node bitmap several workgroups share a tile's drawn nodes, and the bitmap is cleared by a later launch;
+    the node-wise sampler finds it clear."""
+    from paper_2601_04707_amd import mqg
+    rp, ci = synth.chung_lu_graph(n, 1_200_000, max_degree=2000, seed=6)
+    seeds = np.random.default_rng(4).permutation(n)[:1200].astype(np.int64)
+    sizes = [3000, 2500]
+    g = mqg.Graph(to_dev(rp), to_dev(ci))
+    dev_seeds = to_dev(torch.from_numpy(seeds).to(g.idx_dtype))
+    ctx, fresh = mqg.Context(g, len(seeds), [5, 5]), mqg.Context(g, len(seeds), [5, 5])
+    ctx.set_option(mqg.MQG_OPT_LAYERWISE_CANDIDATES, candidates)
+    out = mqg.LayerwiseBlocks(g, len(seeds), sizes)
+    want = oracle.ladies_blocks(rp.numpy(), ci.numpy(), seeds, sizes, 9, fastgcn=False, debias=False, flat=False)
+    got, ref = mqg.Blocks(g, len(seeds), [5, 5]), mqg.Blocks(g, len(seeds), [5, 5])
+    for _ in range(2):
+        mqg.mqg_sample_layerwise(ctx, g, dev_seeds, sizes, 9, out)
+        for l, (nd, ns, nnz, flags) in enumerate(out.host_sizes()):
+            assert (nd, ns, nnz, flags) == (want[l].num_dst, want[l].num_src, want[l].nnz, 0), l
+            assert np.array_equal(out.src_ids[l][:ns].cpu().numpy(), want[l].src_ids), l
+            assert np.array_equal(out.indices[l][:nnz].cpu().numpy(), want[l].indices), l
+            assert np.allclose(out.edge_w[l][:nnz].cpu().numpy(), want[l].edge_w, rtol=1e-6, atol=0), l
+        for c, b in ((ctx, got), (fresh, ref)):
+            mqg.mqg_sample_blocks(c, g, dev_seeds, [5, 5], 3, b)
+        assert got.host_sizes() == ref.host_sizes()
+        for l, (nd, ns, nnz, _) in enumerate(ref.host_sizes()):
+            assert torch.equal(got.src_ids[l][:ns], ref.src_ids[l][:ns]) and torch.equal(got.indices[l][:nnz], ref.indices[l][:nnz])

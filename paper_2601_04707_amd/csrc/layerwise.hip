@@ -1237,6 +1237,8 @@ k_lw_debias(const int32_t *__restrict__ order, const double *__restrict__ dq, co
         const bool in = r >= 0;
         const double alpha = in ? nd / (static_cast<double>(n - r) * static_cast<double>(r + 1)) : 0.0;
         const double x = 1.0 - alpha;
+        const int32_t at = in ? order[r] : 0;              // on its way during the scans
+        const double f = in ? factor[at] : 0.0, b = in ? b0[r] : 0.0;
         double gprod, hsum;
         const double g_incl = lw_block_scan_incl<true>(x, &gprod, lds);
         incl_of[threadIdx.x] = g_incl;                     // the exclusive product is the previous thread's inclusive one
@@ -1244,7 +1246,7 @@ k_lw_debias(const int32_t *__restrict__ order, const double *__restrict__ dq, co
         const double Gr = G * (threadIdx.x == 0 ? 1.0 : incl_of[threadIdx.x - 1]);
         const double term = alpha * Gr;
         const double h_incl = lw_block_scan_incl<false>(term, &hsum, lds);
-        if (in) factor[order[r]] *= b0[r] * Gr + (H + (h_incl - term));
+        if (in) factor[at] = f * (b * Gr + (H + (h_incl - term)));
         H += hsum;
         G *= gprod;
         __syncthreads();                                   // incl_of[] is rewritten by the next chunk

@@ -12,7 +12,7 @@ __device__ __forceinline__ int live_tiles(int64_t n, int tile) { return static_c
 // share cache lines, and the scatter finds in its L2 the keys that the histogram read (histograms of the seven
 // passes of a 4.3 M-edge backward 77 -> 71 us, of a degree sort of 1 M nodes 23 -> 19).  The live tiles are dealt, not the
 // capacity's: with half of it in use four of the XCDs went without work (a pass of 4.3 M keys in room for 8.1 M, scatter 52 -> 36 us).
-// A result of kNoTile: no tile for this workgroup.  The grid is the number of tiles rounded up to a multiple of eight.
+// (Where the host knows the count, all tiles are live, and no workgroup divides for them.)  A result of kNoTile: no tile for this workgroup.  The grid is the number of tiles rounded up to a multiple of eight.
 constexpr int kNoTile = 0x7FFFFFFF;
 __device__ __forceinline__ int xcd_tile(int live) {
     const int share = (live + 7) >> 3, k = static_cast<int>(blockIdx.x >> 3);

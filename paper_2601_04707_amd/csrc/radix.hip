@@ -35,7 +35,7 @@ k_radix_hist(const uint32_t *__restrict__ keys, int64_t n, const int64_t *__rest
     constexpr int D = 1 << DB, PER = D / kBlock;
     __shared__ int h[D];
     if (n_dev && *n_dev < n) n = *n_dev;
-    const int me = tile_major ? static_cast<int>(blockIdx.x) : xcd_tile(live_tiles(n, kBlock * items));
+    const int me = tile_major ? static_cast<int>(blockIdx.x) : xcd_tile(n_dev ? live_tiles(n, kBlock * items) : nblocks);
     if (me >= nblocks) return;
 #pragma unroll
     for (int q = 0; q < PER; ++q) h[q * kBlock + threadIdx.x] = 0;
@@ -71,7 +71,7 @@ constexpr int kScanRounds = 8;
 __global__ void __launch_bounds__(kBlock)
 k_radix_scan(int32_t *__restrict__ hist, int stride, int32_t *__restrict__ totals, int64_t n, const int64_t *__restrict__ n_dev, int tile) {
     if (n_dev && *n_dev < n) n = *n_dev;
-    const int nblocks = live_tiles(n, tile);
+    const int nblocks = n_dev ? live_tiles(n, tile) : stride;
     __shared__ int lds[2][kWavesPerBlock];
     int32_t *row = hist + int64_t(blockIdx.x) * stride;
     const int mine = (static_cast<int>(threadIdx.x) >> 6) * (kWave * kScanRounds) + lane_id();
@@ -179,7 +179,7 @@ k_radix_scatter(const uint32_t *__restrict__ keys_in, RadixPayload payload, int6
     const int lane = lane_id();
     const int wave = tid >> 6;
     if (n_dev && *n_dev < n) n = *n_dev;
-    const int me = SELF ? static_cast<int>(blockIdx.x) : xcd_tile(live_tiles(n, kBlock * items));
+    const int me = SELF ? static_cast<int>(blockIdx.x) : xcd_tile(n_dev ? live_tiles(n, kBlock * items) : nblocks);
     if (me >= nblocks) return;
     const int64_t base = int64_t(me) * kBlock * items;
     if (base >= n) return;

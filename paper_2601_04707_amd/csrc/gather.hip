@@ -12,6 +12,7 @@
 //                     each (<., 0> hits, <., 1> misses, so that profiles tell the HBM-bound from the link-bound)
 //   k_gather_slots    a cache that holds every node: slot lookup and copy in one launch, but for many narrow rows
 //   k_gather_direct   no cache: every row straight from the feature matrix
+// The last two count the rows for the statistics in a few workgroups beside the copy.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -26,27 +27,14 @@ namespace {
 
 // Words of a context's (or the static array's) counters; all but the last two are zero between gathers.
 constexpr int kCountSplit = 0;         // hits, misses and tiles so far, see classify_tiles
-constexpr int kCountBad = 1;           // ids outside the graph, or misses that k_gather_slots counts
+constexpr int kCountRare = 1;          // misses of a gather from a cache that holds every node, see count_ids
 constexpr int kCountTiles = 3;         // tiles of a split into more than its word can count
 constexpr int kCountMissed = 2;        // finished workgroups that copy misses
 constexpr int kCountHits = 4, kCountMisses = 5;    // entries of the lists of the last split; misses are zero again once they are copied
 
-// Stats of a gather without a cache: every valid id is a row served from feats.  counters[kCountBad] holds
-// the number of ids outside the graph that the copy skipped; it is left at zero for the next call.
-__global__ void k_direct_stats(int64_t *stats, const int64_t *num_ids, int64_t cap, unsigned long long *counters) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        int64_t n = *num_ids;
-        if (n > cap) n = cap;
-        if (n < 0) n = 0;
-        if (counters) {
-            n -= static_cast<int64_t>(counters[kCountBad]);
-            counters[kCountBad] = 0;
-        }
-        if (stats) {
-            stats[0] = 0;
-            stats[1] = n;
-        }
-    }
+// Stats of a gather of no ids.
+__global__ void k_direct_stats(int64_t *stats) {
+    if (blockIdx.x == 0 && threadIdx.x < 2) stats[threadIdx.x] = 0;
 }
 
 // Splits the ids into a hit list (output row, cache slot) and a miss list (output row, node id).
@@ -170,8 +158,7 @@ k_classify(const IdxT *__restrict__ ids, const int64_t *__restrict__ num_ids, in
 
 // Which rows to copy: entry r of a (output row, source row) list, or row ids[r] to output row r.
 // get() returns false for a row that must not be written (an id outside the feature matrix); the
-// source row is then 0, so that a load issued before the check stays inside the matrix.  skipped()
-// is called once per such row.
+// source row is then 0, so that a load issued before the check stays inside the matrix.
 struct ListRows {
     const int2 *list;
     __device__ __forceinline__ bool get(int64_t r, int64_t *src_row, int64_t *dst_row) const {
@@ -181,14 +168,11 @@ struct ListRows {
         return true;
     }
     __device__ __forceinline__ const char *at(int64_t row, const char *src, int64_t stride) const { return src + row * stride; }
-    __device__ __forceinline__ void skipped() const {}
 };
-template <typename IdxT, bool IN_LDS>
+template <typename IdxT>
 struct DirectRows {
     const IdxT *ids;
     int64_t num_rows;                    // rows of the source matrix
-    unsigned long long *bad;             // counter of skipped rows, may be null ...
-    int *bad_lds;                        // ... or the workgroup's own (IN_LDS)
     __device__ __forceinline__ bool get(int64_t r, int64_t *src_row, int64_t *dst_row) const {
         const int64_t id = static_cast<int64_t>(ids[r]);
         const bool ok = id >= 0 && id < num_rows;
@@ -197,10 +181,6 @@ struct DirectRows {
         return ok;
     }
     __device__ __forceinline__ const char *at(int64_t row, const char *src, int64_t stride) const { return src + row * stride; }
-    __device__ __forceinline__ void skipped() const {
-        if (IN_LDS) atomicAdd(bad_lds, 1);
-        else if (bad) atomicAdd(bad, 1ull);
-    }
 };
 
 // Row ids[r] to output row r, from the cache if it has a slot there and else from the feature matrix (row -1 - id).
@@ -222,7 +202,6 @@ struct SlotRows {
     __device__ __forceinline__ const char *at(int64_t row, const char *src, int64_t stride) const {
         return row >= 0 ? src + row * stride : feats + (-1 - row) * feat_stride_bytes;
     }
-    __device__ __forceinline__ void skipped() const {}
 };
 
 // A 16-byte load that is not kept in the caches on its way (STREAM: read-once data of a launch too
@@ -261,7 +240,6 @@ __device__ __forceinline__ void copy_rows_wide(const Rows &rows, int64_t n, cons
             const int64_t r = r0 + q;
             int64_t srow, drow;
             const bool valid = rows.get(r < n ? r : n - 1, &srow, &drow);          // a row past the end re-reads the last one
-            if (r < n && !valid && lane == 0) rows.skipped();
             rok[q] = r < n && valid;
             sp[q] = reinterpret_cast<const VecT *>(rows.at(srow, src, src_stride_bytes));
             dp[q] = reinterpret_cast<VecT *>(dst + drow * dst_stride_bytes);
@@ -325,7 +303,6 @@ __device__ __forceinline__ void copy_rows(const Rows &rows, int64_t n, const cha
             bool valid = false;
             if (r < n) {
                 valid = rows.get(r, &srow, &drow);
-                if (!valid && gl == 0) rows.skipped();
             }
             ok[u] = valid && gl < vecs;
             sp[u] = reinterpret_cast<const VecT *>(rows.at(srow, src, src_stride_bytes)) + gl;
@@ -372,7 +349,6 @@ __device__ __forceinline__ void copy_rows_flat(const Rows &rows, int64_t n, cons
             const int64_t col = static_cast<int64_t>(tc) - row * vecs;
             int64_t srow, drow;
             const bool valid = rows.get(row, &srow, &drow);
-            if (ok[u] && !valid && col == 0) rows.skipped();
             ok[u] = ok[u] && valid;
             sp[u] = reinterpret_cast<const VecT *>(rows.at(srow, src, src_stride_bytes)) + col;
             dp[u] = reinterpret_cast<VecT *>(dst + drow * dst_stride_bytes) + col;
@@ -431,37 +407,87 @@ k_gather_rows(RowSide hit, RowSide miss, char *__restrict__ dst, int64_t dst_str
     }
 }
 
-// STATS: the workgroup that ends last writes the statistics: each adds itself and its skipped ids to one word (counters
-// [kCountBad], workgroups in the upper half), left at zero.
-template <typename VecT, typename IdxT, bool STATS>
-__global__ void __launch_bounds__(kBlock)
-k_gather_direct(const IdxT *__restrict__ ids, const int64_t *__restrict__ num_ids, int64_t cap, int64_t src_rows,
-                unsigned long long *bad, const char *__restrict__ src, int64_t src_stride_bytes, char *__restrict__ dst,
-                int64_t dst_stride_bytes, int vecs, int log2_lpr, unsigned long long magic, int grid, int64_t *__restrict__ stats) {
-    __shared__ int bad_here;
-    int64_t n = *num_ids;
-    if (n > cap) n = cap;
-    if (STATS) {
-        if (threadIdx.x == 0) bad_here = 0;
-        __syncthreads();
+// The statistics of a gather without lists: count_blocks workgroups beside the copying ones count the hits and misses, and the one that
+// ends last writes them.  (Without a cache, in a recorded graph: 192 workgroups of 64 rows of 256 bytes 4.6 us with a launch for the
+// statistics, 5.5 where every copying workgroup counted its own rows, 13 ns for each one's atomic, 3.0 so; 400 k rows 28.3 -> 26.5.)
+struct CountLds {
+    int hits[kWavesPerBlock], misses[kWavesPerBlock];
+};
+inline int count_blocks_of(int64_t cap) { return static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(cap, kBlock * 8)), 256)); }
+// SLOTS: a hit has a slot; otherwise no id is a hit.
+template <bool SLOTS, typename IdxT>
+__device__ __forceinline__ void count_ids(const IdxT *__restrict__ ids, int64_t n, const int32_t *__restrict__ slot_of, int64_t num_nodes, int count_blocks,
+                                          unsigned long long *counters, int64_t *__restrict__ stats, CountLds &lds) {
+    constexpr int U = 4;
+    int h = 0, m = 0;
+    for (int64_t i0 = int64_t(blockIdx.x) * kBlock + threadIdx.x; i0 < n; i0 += int64_t(count_blocks) * kBlock * U) {
+        int64_t id[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = i0 + int64_t(u) * count_blocks * kBlock;
+            const int64_t raw = i < n ? static_cast<int64_t>(ids[i]) : -1;
+            id[u] = raw >= 0 && raw < num_nodes ? raw : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool hit = SLOTS && id[u] >= 0 && slot_of[id[u]] >= 0;
+            h += hit ? 1 : 0;
+            m += id[u] >= 0 && !hit ? 1 : 0;
+        }
     }
-    const DirectRows<IdxT, STATS> rows{ids, src_rows, STATS ? nullptr : bad, STATS ? &bad_here : nullptr};
-    if (magic) copy_rows_flat<VecT, false>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, magic, static_cast<int>(blockIdx.x), grid);
-    else copy_rows<VecT, false>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, log2_lpr, static_cast<int>(blockIdx.x), grid);
-    if (STATS) {
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const unsigned long long mine = 1ull << 32 | static_cast<unsigned>(bad_here);
-            const unsigned long long all = atomicAdd(bad, mine) + mine;
-            if (static_cast<int>(all >> 32) == grid) {
-                *bad = 0;
-                if (stats) {
-                    stats[0] = 0;
-                    stats[1] = (n < 0 ? 0 : n) - static_cast<int64_t>(all & 0xFFFFFFFFu);
-                }
+    h = wave_sum(h);
+    m = wave_sum(m);
+    const int wave = static_cast<int>(threadIdx.x) >> 6;
+    if (lane_id() == 0) {
+        lds.hits[wave] = h;
+        lds.misses[wave] = m;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long th = 0, tm = 0;
+#pragma unroll
+        for (int w = 0; w < kWavesPerBlock; ++w) {
+            th += static_cast<unsigned>(lds.hits[w]);
+            tm += static_cast<unsigned>(lds.misses[w]);
+        }
+        // the common ones and the workgroups in one word; the others, counted before their workgroup is, in another
+        const unsigned long long common = SLOTS ? th : tm, rare = SLOTS ? tm : 0;
+        if (rare) {
+            atomicAdd(&counters[kCountRare], rare);
+            __threadfence();
+        }
+        const unsigned long long mine = common | 1ull << 32, all = atomicAdd(&counters[kCountSplit], mine) + mine;
+        if (static_cast<int>(all >> 32) == count_blocks) {
+            const int64_t others = SLOTS ? static_cast<int64_t>(atomicExch(&counters[kCountRare], 0ull)) : 0;
+            counters[kCountSplit] = 0;
+            counters[kCountHits] = SLOTS ? all & 0xFFFFFFFFu : 0;
+            counters[kCountMisses] = 0;                    // they are copied
+            if (stats) {
+                stats[0] = SLOTS ? static_cast<int64_t>(all & 0xFFFFFFFFu) : 0;
+                stats[1] = SLOTS ? others : static_cast<int64_t>(all & 0xFFFFFFFFu);
             }
         }
     }
+}
+
+// No cache.  The first count_blocks workgroups count.
+template <typename VecT, typename IdxT>
+__global__ void __launch_bounds__(kBlock)
+k_gather_direct(const IdxT *__restrict__ ids, const int64_t *__restrict__ num_ids, int64_t cap, int64_t src_rows,
+                const char *__restrict__ src, int64_t src_stride_bytes, char *__restrict__ dst,
+                int64_t dst_stride_bytes, int vecs, int log2_lpr, unsigned long long magic, int count_blocks, int copy_blocks,
+                unsigned long long *counters, int64_t *__restrict__ stats) {
+    __shared__ CountLds lds;
+    int64_t n = *num_ids;
+    if (n > cap) n = cap;
+    const int vb = static_cast<int>(blockIdx.x) - count_blocks;
+    if (vb < 0) {
+        count_ids<false>(ids, n, nullptr, src_rows, count_blocks, counters, stats, lds);
+        return;
+    }
+    const DirectRows<IdxT> rows{ids, src_rows};
+    if (magic) copy_rows_flat<VecT, false>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, magic, vb, copy_blocks);
+    else copy_rows<VecT, false>(rows, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, log2_lpr, vb, copy_blocks);
 }
 
 // A cache that holds every node: no lists.  A row finds its slot while it is copied, in one launch; the first count_blocks
@@ -471,7 +497,7 @@ __global__ void __launch_bounds__(kBlock)
 k_gather_slots(SlotRows<IdxT> rows, const int64_t *__restrict__ num_ids, int64_t cap, const char *__restrict__ cache, int64_t cache_stride_bytes,
                char *__restrict__ dst, int64_t dst_stride_bytes, int vecs, int log2_lpr, unsigned long long magic, int count_blocks, int copy_blocks,
                unsigned long long *counters, int64_t *__restrict__ stats) {
-    __shared__ int lds[2][kWavesPerBlock];
+    __shared__ CountLds lds;
     const int b = static_cast<int>(blockIdx.x);
     int64_t n = *num_ids;
     if (n > cap) n = cap;
@@ -487,54 +513,7 @@ k_gather_slots(SlotRows<IdxT> rows, const int64_t *__restrict__ num_ids, int64_t
         }
         return;
     }
-    constexpr int U = 4;
-    int h = 0, m = 0;
-    for (int64_t i0 = int64_t(b) * kBlock + threadIdx.x; i0 < n; i0 += int64_t(count_blocks) * kBlock * U) {
-        int64_t id[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t i = i0 + int64_t(u) * count_blocks * kBlock;
-            const int64_t raw = i < n ? static_cast<int64_t>(rows.ids[i]) : -1;
-            id[u] = raw >= 0 && raw < rows.num_nodes ? raw : -1;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const bool hit = id[u] >= 0 && rows.slot_of[id[u]] >= 0;
-            h += hit ? 1 : 0;
-            m += id[u] >= 0 && !hit ? 1 : 0;
-        }
-    }
-    h = wave_sum(h);
-    m = wave_sum(m);
-    const int wave = static_cast<int>(threadIdx.x) >> 6;
-    if (lane_id() == 0) {
-        lds[0][wave] = h;
-        lds[1][wave] = m;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long th = 0, tm = 0;
-#pragma unroll
-        for (int w = 0; w < kWavesPerBlock; ++w) {
-            th += static_cast<unsigned>(lds[0][w]);
-            tm += static_cast<unsigned>(lds[1][w]);
-        }
-        if (tm) {                                          // counted before this workgroup is
-            atomicAdd(&counters[kCountBad], tm);
-            __threadfence();
-        }
-        const unsigned long long mine = th | 1ull << 32, all = atomicAdd(&counters[kCountSplit], mine) + mine;
-        if (static_cast<int>(all >> 32) == count_blocks) {
-            const unsigned long long missed = atomicExch(&counters[kCountBad], 0ull);
-            counters[kCountSplit] = 0;
-            counters[kCountHits] = all & 0xFFFFFFFFu;
-            counters[kCountMisses] = 0;                    // they are copied
-            if (stats) {
-                stats[0] = static_cast<int64_t>(all & 0xFFFFFFFFu);
-                stats[1] = static_cast<int64_t>(missed);
-            }
-        }
-    }
+    count_ids<true>(rows.ids, n, rows.slot_of, rows.num_nodes, count_blocks, counters, stats, lds);
 }
 
 // Widest power-of-two access (16, 8, 4 or 2 bytes) that keeps every row of both sides aligned.
@@ -662,15 +641,10 @@ int launch_rows(mqg_ctx *ctx, const char *name, int vec_bytes, const RowSide &hi
     return MQG_OK;
 }
 
-// Workgroups up to which the last one writes the statistics of a gather without a cache, in place of a launch for them
-// (both in a recorded graph: 60 workgroups 4.2 -> 3.9 us, 127 4.2 -> 4.2, 250 4.3 -> 4.9; and a launch less for the host, 2 to 3 us).
-constexpr int kDirectStatsGrid = 192;
-
 // from_host: the source is host memory, so the launch is sized for the link
 template <typename IdxT>
-int launch_direct(mqg_ctx *ctx, const IdxT *ids, const int64_t *num_ids, int64_t cap, int64_t src_rows,
-                  unsigned long long *bad, const void *src, int64_t src_stride_bytes, void *dst,
-                  int64_t dst_stride_bytes, int64_t row_bytes, bool from_host, int64_t *stats, bool *with_stats, hipStream_t s) {
+int launch_direct(mqg_ctx *ctx, const IdxT *ids, const int64_t *num_ids, int64_t cap, int64_t src_rows, const void *src,
+                  int64_t src_stride_bytes, void *dst, int64_t dst_stride_bytes, int64_t row_bytes, bool from_host, int64_t *stats, hipStream_t s) {
     row_bytes = copy_bytes(row_bytes, src_stride_bytes, dst_stride_bytes, src, dst, !from_host);
     const RowGeom g = row_geom(row_bytes, src_stride_bytes, dst_stride_bytes, src, dst);
     int grid = from_host ? link_grid(cap, g, ctx->miss_inflight_bytes) : hbm_grid(cap, g);
@@ -678,17 +652,16 @@ int launch_direct(mqg_ctx *ctx, const IdxT *ids, const int64_t *num_ids, int64_t
     if (magic) grid = flat_grid(cap, g);
     const char *sp = static_cast<const char *>(src);
     char *dp = static_cast<char *>(dst);
-    const bool last = bad && grid <= kDirectStatsGrid;
-    *with_stats = last;
-#define MQG_DIRECT(V, S)                                                                                                                    \
+    const int count_blocks = stats ? count_blocks_of(cap) : 0;
+#define MQG_DIRECT(V)                                                                                                                       \
     MQG_LAUNCH(ctx, "k_gather_direct", s,                                                                                                   \
-               (k_gather_direct<V, IdxT, S><<<grid, kBlock, 0, s>>>(ids, num_ids, cap, src_rows, bad, sp, src_stride_bytes, dp, dst_stride_bytes, \
-                                                                    g.vecs, g.log2_lpr, magic, grid, stats)))
+               (k_gather_direct<V, IdxT><<<count_blocks + grid, kBlock, 0, s>>>(ids, num_ids, cap, src_rows, sp, src_stride_bytes, dp, dst_stride_bytes, \
+                                                                                g.vecs, g.log2_lpr, magic, count_blocks, grid, ctx->counters, stats)))
     switch (g.vb) {
-        case 16: if (last) MQG_DIRECT(uint4, true); else MQG_DIRECT(uint4, false); break;
-        case 8: if (last) MQG_DIRECT(uint2, true); else MQG_DIRECT(uint2, false); break;
-        case 4: if (last) MQG_DIRECT(uint32_t, true); else MQG_DIRECT(uint32_t, false); break;
-        default: if (last) MQG_DIRECT(uint16_t, true); else MQG_DIRECT(uint16_t, false); break;
+        case 16: MQG_DIRECT(uint4); break;
+        case 8: MQG_DIRECT(uint2); break;
+        case 4: MQG_DIRECT(uint32_t); break;
+        default: MQG_DIRECT(uint16_t); break;
     }
 #undef MQG_DIRECT
     return MQG_OK;
@@ -718,7 +691,7 @@ int launch_slots(mqg_ctx *ctx, const mqg_cache *c, const IdxT *ids, const int64_
     if (!*done) return MQG_OK;
     const unsigned long long magic = flat_magic(cap, g);
     const int copy_blocks = magic ? flat_grid(cap, g) : hbm_grid(cap, g);
-    const int count_blocks = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(cap, kBlock * 8)), 256));
+    const int count_blocks = stats ? count_blocks_of(cap) : 0;
     const SlotRows<IdxT> rows{ids, c->slot_of, c->num_nodes, static_cast<const char *>(c->feats), fs};
 #define MQG_SLOTS(V)                                                                                                                        \
     MQG_LAUNCH(ctx, "k_gather_slots", s,                                                                                                    \
@@ -752,9 +725,7 @@ bool is_host_memory(const void *p) {
 int gather_direct_i32(mqg_ctx *ctx, const int32_t *ids, const int64_t *num_ids, int64_t cap, int64_t src_rows,
                       const void *src, int64_t src_stride_bytes, void *dst, int64_t dst_stride_bytes, int64_t row_bytes,
                       hipStream_t s) {
-    bool with_stats;
-    return launch_direct<int32_t>(ctx, ids, num_ids, cap, src_rows, nullptr, src, src_stride_bytes, dst, dst_stride_bytes,
-                                  row_bytes, is_host_memory(src), nullptr, &with_stats, s);
+    return launch_direct<int32_t>(ctx, ids, num_ids, cap, src_rows, src, src_stride_bytes, dst, dst_stride_bytes, row_bytes, is_host_memory(src), nullptr, s);
 }
 
 // Host-side argument checks shared by the gather entry points.  max_ids bounds cap_ids when the
@@ -789,25 +760,18 @@ int run_gather(mqg_ctx *ctx, const mqg_cache *c, int32_t idx_type, const void *i
     const int64_t elt = c->dtype == MQG_F16 ? 2 : 4;
     const int64_t row_bytes = int64_t(c->dim) * elt;
     if (cap_ids == 0) {
-        if (stats && (phases & kGatherMissed)) MQG_LAUNCH(ctx, "k_direct_stats", s, (k_direct_stats<<<1, 64, 0, s>>>(stats, num_ids, 0, nullptr)));
+        if (stats && (phases & kGatherMissed)) MQG_LAUNCH(ctx, "k_direct_stats", s, (k_direct_stats<<<1, 64, 0, s>>>(stats)));
         return MQG_OK;
     }
 
     if (!c->slot_of) {                                   // no cache: everything from feats
         if (!(phases & kGatherMissed)) return MQG_OK;
-        int rc;
-        bool with_stats = false;
         const bool from_host = is_host_memory(c->feats);
         if (idx_type == MQG_I64)
-            rc = launch_direct<int64_t>(ctx, static_cast<const int64_t *>(ids), num_ids, cap_ids, c->num_nodes, &ctx->counters[kCountBad],
-                                        c->feats, c->feat_stride * elt, out, out_stride * elt, row_bytes, from_host, stats, &with_stats, s);
-        else
-            rc = launch_direct<int32_t>(ctx, static_cast<const int32_t *>(ids), num_ids, cap_ids, c->num_nodes, &ctx->counters[kCountBad],
-                                        c->feats, c->feat_stride * elt, out, out_stride * elt, row_bytes, from_host, stats, &with_stats, s);
-        if (rc != MQG_OK) return rc;
-        // every valid id counts as served from feats; the launch also clears the count of skipped ids
-        if (!with_stats) MQG_LAUNCH(ctx, "k_direct_stats", s, (k_direct_stats<<<1, 64, 0, s>>>(stats, num_ids, cap_ids, ctx->counters)));
-        return MQG_OK;
+            return launch_direct<int64_t>(ctx, static_cast<const int64_t *>(ids), num_ids, cap_ids, c->num_nodes, c->feats, c->feat_stride * elt, out,
+                                          out_stride * elt, row_bytes, from_host, stats, s);
+        return launch_direct<int32_t>(ctx, static_cast<const int32_t *>(ids), num_ids, cap_ids, c->num_nodes, c->feats, c->feat_stride * elt, out,
+                                      out_stride * elt, row_bytes, from_host, stats, s);
     }
 
     if (phases == (kGatherCached | kGatherMissed) && c->num_cached == c->num_nodes && c->num_nodes > 0 && !ctx->profile) {

@@ -1,5 +1,5 @@
 """The gather's hits and misses in one launch: sides of different vector widths and strides, only hits, only misses, no rows; a
-second half on its own; and the statistics written by the last workgroup of a small gather without a cache, around that line."""
+second half on its own; and the statistics of a gather without a cache."""
 import pytest
 import torch
 
@@ -71,10 +71,10 @@ def test_every_node_cached(dim, dtype, feat_pad, cache_pad, idx):
             assert stats.tolist() == [hits, int(valid.sum()) - hits]
 
 
-@pytest.mark.parametrize("rows", [1, 2000, 12_287, 12_288, 12_289, 40_000])
+@pytest.mark.parametrize("rows", [1, 2000, 2047, 2048, 2049, 12_287, 12_288, 12_289, 40_000, 600_001])
 @pytest.mark.parametrize("dim", [64, 602])
 def test_statistics_without_a_cache(rows, dim):
-    """64 columns: 192 workgroups of 64 rows each are the most that write their own statistics."""
+    """A counting workgroup per 2,048 ids, 256 at most."""
     from paper_2601_04707_amd import mqg
     n = 5000
     gen = torch.Generator(device="cuda").manual_seed(rows)

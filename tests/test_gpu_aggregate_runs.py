@@ -92,9 +92,11 @@ def check_runs(num_dst, dim, dtype, stride):
 
 
 @pytest.mark.parametrize("scale", [1, 60, 80])
-def test_edges_find_their_rows(scale):
-    """The backward's order of edges where rows are empty in long stretches, hold one edge each, or thousands
-    (scale 80: enough edges for the weighted backward to write all rows down first)."""
+@pytest.mark.parametrize("cap_src", [3000, (1 << 22) + 1])
+def test_edges_find_their_rows(scale, cap_src):
+    """The backward's order of edges where rows are empty in long stretches, hold one edge each, or thousands: through buckets, and
+    with room for more than 2^22 sources through a radix sort (scale 80: enough edges for its weighted form to write all
+    rows down first)."""
     from paper_2601_04707_amd import mqg
     rng = np.random.default_rng(scale)
     lens = np.concatenate([np.zeros(70), [3], np.zeros(5000), np.ones(700), [9000, 0, 0, 64, 1], np.zeros(64), np.full(300, 2),
@@ -106,10 +108,11 @@ def test_edges_find_their_rows(scale):
     cols = rng.integers(0, ns, nnz)
     cols[cols == 17] = 18                                  # a source without edges
     ctx, blocks = bare_blocks(mqg, indptr, cols, nd, ns)
+    blocks.c[0].cap_src = cap_src
     rows = torch.from_numpy(np.repeat(np.arange(nd), lens))
     g = torch.randn((nd, 2), device="cuda")
     w = torch.rand(nnz, device="cuda")
-    gx = torch.full((ns, 2), 7.0, device="cuda")
+    gx = torch.full((cap_src, 2), 7.0, device="cuda")
     for weights in (None, w):
         coeff = w.double() if weights is not None else (1.0 / torch.from_numpy(np.maximum(lens, 1)).double())[rows].cuda()
         ref = spmm(torch.from_numpy(cols), rows, coeff, g.double(), ns)
@@ -119,12 +122,14 @@ def test_edges_find_their_rows(scale):
             mqg.mqg_sage_mean_aggregate_backward(ctx, blocks, 0, g, gx)
         else:
             mqg.mqg_weighted_aggregate_backward(ctx, blocks, 0, w, None, g, gx)
-        assert torch.all((gx.double() - ref).abs() <= (terms + 4)[:, None] * 2.0 ** -24 * mag)
+        assert torch.all((gx[:ns].double() - ref).abs() <= (terms + 4)[:, None] * 2.0 ** -24 * mag)
 
 
 @pytest.mark.parametrize("nd,per_row,extra", [(1, 3, 700), (64, 2, 5), (65, 1, 130), (1300, 2, 700), (20_001, 80, 3000)])
-def test_edges_past_the_last_offset(nd, per_row, extra):
-    """A block whose edge count is larger than its last offset: the edges past it are the last row's."""
+@pytest.mark.parametrize("cap_src", [500, (1 << 22) + 1])
+def test_edges_past_the_last_offset(nd, per_row, extra, cap_src):
+    """A block whose edge count is larger than its last offset: the edges past it are the last row's, in the order through
+    buckets and in the radix sort of blocks with room for more than 2^22 sources."""
     from paper_2601_04707_amd import mqg
     rng = np.random.default_rng(nd)
     lens = np.full(nd, per_row)
@@ -135,10 +140,11 @@ def test_edges_past_the_last_offset(nd, per_row, extra):
     offsets[-1] = nnz                                      # the buffers' size; the block's own last offset follows
     ctx, blocks = bare_blocks(mqg, offsets, cols, nd, ns)
     blocks._keep[0][nd] = int(indptr[-1])
+    blocks.c[0].cap_src = cap_src
     rows = torch.from_numpy(np.concatenate([np.repeat(np.arange(nd), lens), np.full(extra, nd - 1)]))
     g = torch.randn((nd, 2), device="cuda")
     w = torch.rand(nnz, device="cuda")
-    gx = torch.zeros((ns, 2), device="cuda")
+    gx = torch.zeros((cap_src, 2), device="cuda")
     for weights in (None, w):
         coeff = w.double() if weights is not None else torch.full((nnz,), 1.0 / per_row, dtype=torch.float64, device="cuda")
         ref = spmm(torch.from_numpy(cols), rows, coeff, g.double(), ns)
@@ -148,7 +154,7 @@ def test_edges_past_the_last_offset(nd, per_row, extra):
             mqg.mqg_sage_mean_aggregate_backward(ctx, blocks, 0, g, gx)
         else:
             mqg.mqg_weighted_aggregate_backward(ctx, blocks, 0, w, None, g, gx)
-        assert torch.all((gx.double() - ref).abs() <= (terms + 4)[:, None] * 2.0 ** -24 * mag)
+        assert torch.all((gx[:ns].double() - ref).abs() <= (terms + 4)[:, None] * 2.0 ** -24 * mag)
 
 
 def test_rows_wider_than_one_launch():

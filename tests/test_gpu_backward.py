@@ -89,10 +89,11 @@ def test_backward_parity_random_blocks(mqg, dim, dtype):
 @pytest.mark.parametrize("ns,nnz_target", [(200, 3000), (200_000, 50_000), (200_000, 400_000), (300_000, 200_000),
                                            (900_000, 60_000), (1_500_000, 60_000), (1_500_000, 300_000), (70_000, 65_536),
                                            (70_000, 65_537), (1 << 18, 100_000), ((1 << 18) + 1, 100_000)])
-def test_backward_through_every_shape_of_the_sort(mqg, ns, nnz_target):
-    """The by-source ordering takes digits of 8 to 11 bits by the number of source positions and cuts
-    its input into few or many tiles by the number of edges (up to 32 tiles: no scan launches); each
-    combination here is another pair of kernels.  Weighted too: there the sort makes the payload."""
+@pytest.mark.parametrize("cap_src", [0, (1 << 22) + 1])
+def test_backward_through_every_shape_of_the_sort(mqg, ns, nnz_target, cap_src):
+    """The by-source ordering goes through buckets in blocks with room for up to 2^22 sources and through a radix
+    sort in larger ones (cap_src; in place of the number of sources), and cuts its input into few or many tiles by the number of
+    edges (up to 32 tiles: no scan launches).  Weighted too: there the sort makes the payload."""
     rng = np.random.default_rng(ns + nnz_target)
     nd = max(1, nnz_target // 12)
     counts = rng.integers(0, 25, nd)
@@ -105,20 +106,21 @@ def test_backward_through_every_shape_of_the_sort(mqg, ns, nnz_target):
     dim = 4
     gout = rng.standard_normal((nd, dim)).astype(np.float32)
     ctx, blocks = bare_blocks(mqg, indptr, indices, nd, ns)
+    blocks.c[0].cap_src = max(ns, cap_src)
     gd = to_dev(torch.from_numpy(gout))
-    gx = torch.full((ns + 1, dim), 9.0, dtype=torch.float32, device="cuda")
+    gx = torch.full((max(ns, cap_src) + 1, dim), 9.0, dtype=torch.float32, device="cuda")
     mqg.mqg_sage_mean_aggregate_backward(ctx, blocks, 0, gd, gx)
     torch.cuda.synchronize()
     ref = oracle.mean_aggregate_backward(indptr, indices, ns, gout)
     check(gx[:ns].cpu().numpy(), ref, source_mass(indptr, indices, ns, gout), TOL[np.float32])
     assert torch.all(gx[ns:] == 9.0)
     ew = rng.standard_normal(nnz).astype(np.float32)
-    gxw = torch.zeros((ns, dim), dtype=torch.float32, device="cuda")
+    gxw = torch.zeros((max(ns, cap_src), dim), dtype=torch.float32, device="cuda")
     mqg.mqg_weighted_aggregate_backward(ctx, blocks, 0, to_dev(torch.from_numpy(ew)), None, gd, gxw)
     torch.cuda.synchronize()
     refw = oracle.weighted_aggregate_backward(indptr, indices, ns, ew, None, gout)
     massw = np.bincount(indices, weights=np.abs(ew.astype(np.float64)), minlength=ns) * float(np.abs(gout.astype(np.float64)).mean())
-    check(gxw.cpu().numpy(), refw, massw, TOL[np.float32])
+    check(gxw[:ns].cpu().numpy(), refw, massw, TOL[np.float32])
 
 
 def test_backward_empty_block_and_single_edges(mqg):
@@ -172,15 +174,15 @@ def test_backward_on_sampled_blocks_and_adjoint_identity(mqg, dtype):
             assert abs(lhs - rhs) < 1e-4 * max(1.0, abs(lhs))
 
 
-def test_backward_on_blocks_whose_sorts_take_different_digit_widths(mqg):
-    """One context, two blocks: the outer one has more than 2 M edge slots (its sort takes 8-bit
-    digits), the inner one a million with 21-bit source positions (two 11-bit passes, the widest
-    counter table there is).  The sort's scratch is sized once, for the larger block: it must also
-    hold the smaller block's wider table."""
+@pytest.mark.parametrize("cap_src,dim", [(0, 8), ((1 << 22) + 1, 2), ((1 << 27) + 1, 2)])
+def test_backward_on_blocks_whose_sorts_take_different_digit_widths(mqg, cap_src, dim):
+    """One context, two blocks of more than 2 M edge slots and of a million, whose order shares scratch that is sized once, for the
+    larger block.  Through buckets; and with more room for sources (cap_src) through radix sorts, of 8-bit digits
+    both or, with 28-bit source positions, of 8-bit digits in the outer block and 10-bit ones, a wider table of counts, in the inner one."""
     n = 1_200_000
     rp, ci = synth.chung_lu_graph(n, 6_000_000, max_degree=3000, seed=9)
     g = mqg.Graph(to_dev(rp), to_dev(ci))
-    fanouts, batch, dim = [2, 52], 20_000, 8
+    fanouts, batch = [2, 52], 20_000
     ctx = mqg.Context(g, batch, fanouts)
     blocks = mqg.Blocks(g, batch, fanouts)
     assert blocks.bounds[1][2] <= (2 << 20) < blocks.bounds[0][2] and blocks.bounds[1][1] > (1 << 20)
@@ -192,7 +194,8 @@ def test_backward_on_blocks_whose_sorts_take_different_digit_widths(mqg):
         nd, ns = b["num_dst"], b["num_src"]
         gout = rng.standard_normal((nd, dim)).astype(np.float32)
         ref = oracle.mean_aggregate_backward(b["indptr"], b["indices"], ns, gout)
-        gx = torch.zeros((blocks.bounds[l][1], dim), dtype=torch.float32, device="cuda")
+        cap = blocks.c[l].cap_src = max(blocks.bounds[l][1], cap_src)
+        gx = torch.zeros((cap, dim), dtype=torch.float32, device="cuda")
         mqg.mqg_sage_mean_aggregate_backward(ctx, blocks, l, to_dev(torch.from_numpy(gout)), gx)
         torch.cuda.synchronize()
         check(gx[:ns].cpu().numpy(), ref, source_mass(b["indptr"], b["indices"], ns, gout), TOL[np.float32])

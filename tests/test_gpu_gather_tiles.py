@@ -1,5 +1,5 @@
-"""The split of the ids into hits and misses at the edges of its tiles (1,024 ids, 4,096 for more than 512 k) and of its
-workgroups' loop (1,024 tiles at a time), with ids outside the graph among them.  Bytes and counts are exact."""
+"""The split of the ids into hits and misses at the edges of its tiles (256 ids for up to 32 k, 1,024 for up to 512 k, 4,096 above) and of
+its workgroups' loop (1,024 tiles at a time), with ids outside the graph among them.  Bytes and counts are exact."""
 import pytest
 import torch
 
@@ -7,7 +7,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("num_ids,cap,idx", [(1, 1, torch.int64), (1023, 1024, torch.int32), (1025, 1025, torch.int64), (5000, 524_288, torch.int32),
-                                             (524_288, 524_288, torch.int64), (4097, 524_289, torch.int64), (700_001, 700_001, torch.int32)])
+                                             (524_288, 524_288, torch.int64), (4097, 524_289, torch.int64), (700_001, 700_001, torch.int32),
+                                             (255, 131_072, torch.int32), (257, 131_073, torch.int64), (32_768, 131_072, torch.int64),
+                                             (32_769, 131_073, torch.int32), (33_793, 131_072, torch.int64), (131_073, 131_073, torch.int64),
+                                             (524_287, 524_289, torch.int32), (524_289, 524_289, torch.int64)])
 def test_tiles_of_ids(num_ids, cap, idx):
     from paper_2601_04707_amd import mqg
     gen = torch.Generator(device="cuda").manual_seed(num_ids)

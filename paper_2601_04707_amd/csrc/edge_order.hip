@@ -611,7 +611,6 @@ k_order_buckets(const uint16_t *__restrict__ keys, const int32_t *__restrict__ r
                     }
                     if (in) o += popc64(peers & lanes_below(lane));
                 }
-                wave_lds_sync();
                 if (mine && staged) {
                     stage[o] = row[u];
                     if (WEIGHTED) stage[kStage + o] = __float_as_int(weight[u]);

@@ -419,7 +419,8 @@ def run_workload(torch, np, mqg, synth, opts, name, *, cache_pct, in_flight, K, 
         roofline = roof("k_gather_direct", rows / K * (2 * row_bytes + ci.element_size()), HBM_PEAK_GBPS)
         host_link = None
     else:
-        # hit gather: row read from the HBM cache + row written + the 8-byte (row, slot) list entry
+        # hit gather: row read from the HBM cache + row written + the 8-byte (row, slot) list entry.  A profiling context copies the
+        # hits and the misses in a launch each, as the two halves of a gather do; a gather in one call copies both in one
         roofline = roof("k_gather_hit", hits / K * (2 * row_bytes + 8), HBM_PEAK_GBPS)
         host_link = roof("k_gather_miss", misses / K * row_bytes, HOST_LINK_PEAK_GBPS)
         if host_link:
@@ -436,7 +437,7 @@ def run_workload(torch, np, mqg, synth, opts, name, *, cache_pct, in_flight, K, 
 
     # the forward profile pass launches nothing else through the radix/scan kernels than the hash dedup
     # (k_relabel_rowinfo also carries the next block's row information, k_offsets_count and k_emit_offsets the row offsets)
-    dedup_kernels = ("k_bitmap_count", "k_bitmap_emit", "k_emit_offsets", "k_relabel", "k_relabel_rowinfo", "k_reset_local", "k_zero_u64",
+    dedup_kernels = ("k_bitmap_count", "k_bitmap_emit", "k_emit_offsets", "k_relabel", "k_relabel_rowinfo", "k_reset_local", "k_clear_hubs", "k_zero_u64",
                      "k_scan_tiles(radix)", "k_scan_tiles(bitmap)", "k_scan_reduce", "k_scan_apply")
     dedup_us = sum(v["us_per_step"] for k, v in kern.items()
                    if k in dedup_kernels or k.startswith("k_hash_") or k.startswith("k_radix_"))

@@ -182,7 +182,11 @@ typedef enum {
     MQG_OPT_FORCE_SLOW_SELECT = 1,       /* value != 0: every row with degree > fanout uses the
                                             repeated-minimum selection (test of the rare path) */
     MQG_OPT_PROFILE = 2,                 /* value != 0: bracket every kernel with HIP events
-                                            (adds a few microseconds per kernel)              */
+                                            (adds a few microseconds per kernel).  A gather
+                                            through a cache then launches k_classify,
+                                            k_gather_hit and k_gather_miss, as its two halves
+                                            do, also where a call without profiling copies
+                                            hits and misses in one launch                     */
     MQG_OPT_MISS_INFLIGHT_BYTES = 3,     /* bytes of host-memory reads the miss gather keeps
                                             outstanding (1 KiB..1 GiB, default 1 MiB): sizes
                                             its grid; enough to saturate the host link without

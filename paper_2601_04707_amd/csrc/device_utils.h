@@ -14,6 +14,12 @@ __device__ __forceinline__ uint64_t ballot64(bool p) { return __ballot(p); }
 
 __device__ __forceinline__ int popc64(uint64_t m) { return __popcll(m); }
 
+// base and how many lanes of m come before this one
+__device__ __forceinline__ int rank_below(uint64_t m, int base = 0) {
+    return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), static_cast<uint32_t>(base))));
+}
+
 // Value of v in lane `l`; l must be the same in every lane.
 __device__ __forceinline__ uint32_t readlane32(uint32_t v, int l) {
     return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), l));
@@ -109,6 +115,39 @@ __device__ __forceinline__ void wave_select_smallest(const uint64_t (&key)[NCH],
             --need;
         }
     }
+}
+
+// A bound that exactly k of the wavefront's words lie below, 0 if there is none to be found.  The words are uniform
+// 31-bit values, `gap` apart on average, or kNoWord, which never lies below.  The first bound is where k words are
+// expected, the next ones are moved by as many gaps as words were too many or too few, the gap a quarter smaller each
+// time: four bounds on average, of one comparison per chunk each, where a radix select took eight bits and twice the scalar
+// work per bit.  One search in twenty has not ended after ten; it goes on by halves.
+constexpr uint32_t kNoWord = 0x7FFFFFFFu;
+template <int NCH>
+__device__ __forceinline__ uint32_t word_bound(const uint32_t (&w)[NCH], int k, uint32_t gap) {
+    auto below = [&](uint32_t t) {
+        int n = 0;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) n += popc64(ballot64(w[c] < t));
+        return n;
+    };
+    uint32_t t = gap / 2 + static_cast<uint32_t>(k) * gap;
+    for (int tries = 0; tries < 10; ++tries) {
+        const int more = k - below(t);
+        if (more == 0) return t <= kNoWord ? t : 0;        // (past the end all lanes lie below)
+        t += static_cast<uint32_t>(more) * gap;
+        gap -= gap >> 2;
+    }
+    uint32_t lo = 0, hi = kNoWord;                         // fewer than k lie below lo
+    if (below(hi) < k) return 0;
+    while (hi - lo > 0) {
+        t = lo + (hi - lo) / 2;
+        const int n = below(t);
+        if (n == k) return t;
+        if (n < k) lo = t + 1;
+        else hi = t;
+    }
+    return below(hi) == k ? hi : 0;
 }
 
 // Inclusive prefix sum over the 64 lanes of a wavefront.

@@ -241,6 +241,41 @@ __device__ __forceinline__ void emit_neighbour(const IdxT *__restrict__ col_idx,
     a.nbr[out_pos] = u;
 }
 
+// The same for a wavefront that has one neighbour per lane after the other, in two steps that overlap with what it does in
+// between: the id is loaded when it is pushed, its position at the next push, and the one after that stores it.
+template <typename IdxT>
+struct NeighbourPipe {
+    const SampleArgs &a;
+    bool in1 = false, in2 = false;
+    int32_t out1 = 0, out2 = 0, u2 = 0, p2 = -1;
+    IdxT u1 = 0;
+    __device__ __forceinline__ explicit NeighbourPipe(const SampleArgs &args) : a(args) {}
+    __device__ __forceinline__ void advance() {
+        if (in2) {
+            int32_t u = u2;
+            if (p2 >= a.pos_base) u = ~(p2 - a.pos_base);
+            else if (a.local_of) (void)__hip_atomic_fetch_or(a.bitmap + (u >> 5), 1u << (u & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            a.nbr[out2] = u;
+        }
+        in2 = in1;
+        out2 = out1;
+        u2 = static_cast<int32_t>(u1);
+        p2 = -1;
+        if (a.local_of && in2) p2 = a.local_of[u2];
+    }
+    __device__ __forceinline__ void push(const IdxT *__restrict__ col_idx, bool in, int64_t pos, int32_t out) {
+        advance();
+        in1 = in;
+        out1 = out;
+        if (in) u1 = col_idx[pos];
+    }
+    __device__ __forceinline__ void drain() {
+        advance();
+        in1 = false;
+        advance();
+    }
+};
+
 // key(j) = mix64(hv ^ j) for the slots j of one row, with everything that depends only on the row
 // hoisted out: j < 2^31 touches only the low word of hv ^ j, so the high word after the first
 // xor-shift and its share of the first multiply are per-row constants.  Written on 32-bit halves
@@ -278,76 +313,110 @@ struct RowKeys {
 // six low bits, so the product splits into a part that depends on the row and base alone (scalar unit) and
 // a part that depends on the row and the lane alone (once per row): what is left of the first half of the
 // mixer per key is one 64-bit addition, and three multiplications per key remain of five.  One object
-// serves the slots of one range of 2^30 (the slot's two top bits reach the low bits).
+// serves the slots of one range of 2^30 (the slot's two top bits reach the low bits).  Where a wavefront takes
+// CHUNKS times 64 slots from a multiple of that on, those share the row's part.
+constexpr uint64_t kC1 = (uint64_t(RowKeys::kC1Hi) << 32) | RowKeys::kC1Lo;
+__device__ __forceinline__ uint32_t key_low(uint64_t hv, uint32_t range = 0) {           // low word after the first xor-shift, for slot 0 of the range
+    const uint32_t lo = static_cast<uint32_t>(hv);
+    return lo ^ static_cast<uint32_t>(((hv >> 32 << 32) | (lo ^ range)) >> 30);
+}
+__device__ __forceinline__ uint32_t key_hi_term(uint64_t hv) {                            // the high word's share of the first product
+    const uint32_t hi = static_cast<uint32_t>(hv >> 32);
+    return (hi ^ (hi >> 30)) * RowKeys::kC1Lo;
+}
+// The key's upper word, from the first product, before the final xor-shift, which would change its bit 0 only
+__device__ __forceinline__ uint32_t key_upper(uint64_t b) {
+    const uint32_t b_lo = static_cast<uint32_t>(b), b_hi = static_cast<uint32_t>(b >> 32);
+    const uint32_t c_lo = b_lo ^ __builtin_amdgcn_alignbit(b_hi, b_lo, 27);
+    const uint32_t c_hi = b_hi ^ (b_hi >> 27);
+    return __umulhi(c_lo, RowKeys::kC2Lo) + c_lo * RowKeys::kC2Hi + c_hi * RowKeys::kC2Lo;
+}
+template <int CHUNKS>
 struct WaveKeys {
-    uint32_t low;                 // low word after the first xor-shift, for slot 0 of the range
-    uint32_t hi_term;             // the high word's share of the first product
-    uint64_t lane_prod;           // (its low six bits, with the lane's) * C1
-    __device__ __forceinline__ WaveKeys(uint64_t hv, uint32_t range) {
-        const uint32_t hi = static_cast<uint32_t>(hv >> 32), lo = static_cast<uint32_t>(hv);
-        const uint64_t c1 = (uint64_t(RowKeys::kC1Hi) << 32) | RowKeys::kC1Lo;
-        hi_term = __builtin_amdgcn_readfirstlane((hi ^ (hi >> 30)) * RowKeys::kC1Lo);
-        low = __builtin_amdgcn_readfirstlane(lo ^ ((hi << 2) | ((lo ^ range) >> 30)));
-        lane_prod = static_cast<uint64_t>((low & 63u) ^ static_cast<uint32_t>(lane_id())) * c1;
+    static constexpr uint32_t kMask = CHUNKS * kWave - 1;
+    uint32_t low, hi_term;        // the same in all lanes
+    uint64_t lane_prod[CHUNKS];   // (its low bits, with the slot's) * C1
+    __device__ __forceinline__ WaveKeys(uint32_t low_word, uint32_t hi_share) : low(low_word), hi_term(hi_share) {
+#pragma unroll
+        for (int c = 0; c < CHUNKS; ++c) lane_prod[c] = static_cast<uint64_t>((low ^ static_cast<uint32_t>(c * kWave + lane_id())) & kMask) * kC1;
     }
-    // the word before the final xor-shift: its upper half differs from the key's in bit 0 only
-    __device__ __forceinline__ uint64_t raw(uint32_t base) const {
-        // (the empty asm keeps the row's part in scalar registers: the compiler would fold its product into
-        // the addition as a vector multiply-add)
-        const uint32_t rest = (low ^ base) & ~63u;
-        uint32_t p_lo = rest * RowKeys::kC1Lo;
-        uint32_t p_hi = static_cast<uint32_t>((uint64_t(rest) * RowKeys::kC1Lo) >> 32) + rest * RowKeys::kC1Hi + hi_term;
-        asm("" : "+s"(p_lo), "+s"(p_hi));
-        const uint64_t b = ((uint64_t(p_hi) << 32) | p_lo) + lane_prod;
-        const uint32_t b_lo = static_cast<uint32_t>(b), b_hi = static_cast<uint32_t>(b >> 32);
-        const uint32_t c_lo = b_lo ^ __builtin_amdgcn_alignbit(b_hi, b_lo, 27);
-        const uint32_t c_hi = b_hi ^ (b_hi >> 27);
-        const uint64_t q = static_cast<uint64_t>(c_lo) * RowKeys::kC2Lo;
-        const uint32_t d_hi = static_cast<uint32_t>(q >> 32) + c_lo * RowKeys::kC2Hi + c_hi * RowKeys::kC2Lo;
-        return (static_cast<uint64_t>(d_hi) << 32) | static_cast<uint32_t>(q);
+    // the row's part for the CHUNKS * 64 slots from base on
+    __device__ __forceinline__ uint64_t row_part(uint32_t base) const {
+        const uint32_t rest = (low ^ base) & ~kMask;
+        uint64_t p = uint64_t(rest) * RowKeys::kC1Lo + (uint64_t(rest * RowKeys::kC1Hi + hi_term) << 32);
+        // (this keeps it in scalar registers: the compiler would fold the product into the addition as a vector multiply-add)
+        asm("" : "+s"(p));
+        return p;
     }
-    static __device__ __forceinline__ uint64_t finish(uint64_t z) { return z ^ (z >> 31); }
+    __device__ __forceinline__ uint32_t upper(uint64_t part, int c = 0) const { return key_upper(part + lane_prod[c]); }
 };
 
-// Candidates are the slots whose key's upper word is at most thr (bit 0 set, so that it can be compared
-// with the upper word of raw()): about `expect` of the d slots.
-__device__ __forceinline__ uint32_t threshold_for(int expect, int d) {
-    if (d <= expect) return 0xFFFFFFFFu;
-    const float t = static_cast<float>(expect) / static_cast<float>(d) * 4294967296.0f;
-    return static_cast<uint32_t>(t < 4294967040.0f ? t : 4294967040.0f) | 1u;
+// A candidate: the upper 31 bits of its key and its slot.
+struct alignas(8) Candidate {
+    uint32_t word;
+    int32_t slot;
+};
+
+// The distance of a row's keys on average, in upper 31 bits.
+__device__ __forceinline__ uint32_t key_gap(int d) {
+    const float g = 2147483648.0f * __builtin_amdgcn_rcpf(static_cast<float>(d));
+    return g >= 1.0f ? static_cast<uint32_t>(g < 2147483520.0f ? g : 2147483520.0f) : 1u;
+}
+// About `expect` of the d slots have keys whose upper 31 bits lie below this.
+__device__ __forceinline__ uint32_t key_limit(int expect, int d, uint32_t gap) {
+    return d <= expect ? kNoWord : static_cast<uint32_t>(expect) * gap;
 }
 
-// The candidates among the slots base + lane, base = begin, begin + stride, ... (multiples of 64) of a row of
-// d, written by one wavefront to (ck, cs) in slot order, `cap` at most; returns their number.
-__device__ __forceinline__ int wave_candidates(uint64_t hv, int d, uint32_t thr, uint32_t begin, uint32_t stride, uint64_t *ck, int32_t *cs,
-                                               int cap) {
+// The slots of a row of d whose keys lie below limit, as candidates in `out` in slot order; returns their number (more than
+// the list's `cap`, a power of two: not all are there).  LONG: a wavefront's share of a long row, kHubChunks * 64 slots from
+// `begin` on, `stride` apart, most of which have few candidates or none in 64.  Otherwise a row of less than 2^30.
+constexpr int kHubChunks = 4;
+template <bool EMPTY>
+__device__ __forceinline__ void keep_candidates(uint32_t z, int slot, bool c, Candidate *out, int cap, int &cnt) {
+    const uint64_t m = ballot64(c);
+    if (EMPTY && !m) return;
+    if (c) out[rank_below(m, cnt) & (cap - 1)] = Candidate{z >> 1, slot};
+    cnt += popc64(m);
+}
+__device__ __forceinline__ int row_candidates(uint32_t low, uint32_t hi_term, int d, uint32_t limit, Candidate *out, int cap) {
+    const uint32_t above = limit << 1;                     // of the whole upper word, whose bit 0 is not known yet
+    const WaveKeys<1> keys(low, hi_term);
+    int cnt = 0, slot = lane_id(), base = 0;
+    for (; base + kWave <= d; base += kWave, slot += kWave) {
+        const uint32_t z = keys.upper(keys.row_part(base));
+        keep_candidates<false>(z, slot, z < above, out, cap, cnt);
+    }
+    if (base < d) {
+        const uint32_t z = keys.upper(keys.row_part(base));
+        keep_candidates<false>(z, slot, z < above && slot < d, out, cap, cnt);
+    }
+    return cnt;
+}
+__device__ __forceinline__ int hub_candidates(uint64_t hv, int d, uint32_t limit, uint32_t begin, uint32_t stride, Candidate *out, int cap) {
+    const uint32_t above = limit << 1;
     const int lane = lane_id();
     int cnt = 0;
-    auto keep = [&](uint64_t z, uint32_t base, bool c) {
-        const uint64_t m = ballot64(c);
-        if (m) {
-            const int p = cnt + popc64(m & lanes_below(lane));
-            if (c && p < cap) {
-                ck[p] = WaveKeys::finish(z);
-                cs[p] = static_cast<int32_t>(base) + lane;
-            }
-            cnt += popc64(m);
-        }
-    };
     for (uint32_t range = 0; range < static_cast<uint32_t>(d); range += 0x40000000u) {
-        const WaveKeys keys(hv, range);
+        const WaveKeys<kHubChunks> keys(__builtin_amdgcn_readfirstlane(key_low(hv, range)), __builtin_amdgcn_readfirstlane(key_hi_term(hv)));
         const uint32_t end = static_cast<uint32_t>(d) - range < 0x40000000u ? static_cast<uint32_t>(d) : range + 0x40000000u;
         uint32_t base = range + begin;
-        for (; base + 3 * stride + kWave <= end; base += 4 * stride) {
-            uint64_t z[4];
+        for (; base + kHubChunks * kWave <= end; base += stride) {
+            const uint64_t part = keys.row_part(base);
+            uint32_t z[kHubChunks];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) z[u] = keys.raw(base + u * stride);
+            for (int u = 0; u < kHubChunks; ++u) z[u] = keys.upper(part, u);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) keep(z[u], base + u * stride, static_cast<uint32_t>(z[u] >> 32) <= thr);
+            for (int u = 0; u < kHubChunks; ++u)
+                keep_candidates<true>(z[u], static_cast<int>(base + u * kWave) + lane, z[u] < above, out, cap, cnt);
         }
-        for (; base < end; base += stride) {
-            const uint64_t z = keys.raw(base);
-            keep(z, base, static_cast<uint32_t>(z >> 32) <= thr && base + lane < end);
+        if (base < end) {
+            const uint64_t part = keys.row_part(base);
+#pragma unroll
+            for (int u = 0; u < kHubChunks; ++u) {
+                if (base + u * kWave >= end) break;
+                const uint32_t z = keys.upper(part, u);
+                keep_candidates<true>(z, static_cast<int>(base + u * kWave) + lane, z < above && base + u * kWave + lane < end, out, cap, cnt);
+            }
         }
     }
     return cnt;
@@ -444,8 +513,9 @@ __device__ __forceinline__ void emit_selected_unordered(const uint64_t *ck, cons
     emit_by_slot<NCH>(slot, sel, k, sel_slot, col_idx, start, out_base, a);
 }
 
-// The per-row selection on caller-supplied candidates (mqg_select_row_candidates): one wavefront,
-// the same code path as k_sample / k_sample_prio after their threshold pass.
+// The per-row selection on caller-supplied candidates (mqg_select_row_candidates): one wavefront, the same code as in
+// k_sample_prio after its threshold pass, or, not prioritised, the bound on the keys' upper words that k_sample looks for
+// and, where there is none, the selection by whole keys.
 template <bool PRIO, bool ORDERED>
 __global__ void __launch_bounds__(kWave)
 k_select_candidates(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ slot_words, int cnt, int k,
@@ -453,7 +523,15 @@ k_select_candidates(const uint64_t *__restrict__ keys, const uint32_t *__restric
     constexpr int NCH = kCandidates / kWave;
     uint32_t slot[NCH];
     uint64_t sel[NCH];
-    select_candidates<NCH, PRIO, ORDERED>(keys, slot_words, cnt, k, slot, sel);
+    uint32_t word[NCH], bound = 0;
+    if (!PRIO) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) word[c] = c * kWave + lane_id() < cnt ? static_cast<uint32_t>(keys[c * kWave + lane_id()] >> 33) : kNoWord;
+        bound = word_bound(word, k, key_gap(cnt));
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) sel[c] = ballot64(word[c] < bound);
+    }
+    if (bound == 0) select_candidates<NCH, PRIO, ORDERED>(keys, slot_words, cnt, k, slot, sel);
     if (lane_id() == 0) {
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
@@ -510,13 +588,12 @@ __device__ void select_by_repeated_min(const IdxT *__restrict__ col_idx, int64_t
     if (lane < k) emit_neighbour(col_idx, start, my_slot, out_base + rank, a);
 }
 
-// What a wavefront keeps in LDS: the candidates of the row at hand, and the slots that its batch of rows
-// has selected (their position in the column array and where the neighbour goes).
+// What a wavefront keeps in LDS: the candidates of the row at hand, and the slots that its batch of rows has selected
+// (slot; row of the batch, and number among the row's slots from bit 8 on).
 struct SampleLds {
-    uint64_t key[kWavesPerBlock][kCandidates];
-    int32_t slot[kWavesPerBlock][kCandidates];
-    int64_t pos[kWavesPerBlock][kWave];
-    int32_t out[kWavesPerBlock][kWave];
+    Candidate cand[kWavesPerBlock][kCandidates];
+    uint2 pick[kWavesPerBlock][kWave];
+    int32_t slot[kWavesPerBlock][kWave];
 };
 
 // Hubs (degree > heavy_degree, listed with the row information): the four wavefronts of a workgroup walk
@@ -541,57 +618,65 @@ __device__ __forceinline__ void sample_hubs(const IdxT *__restrict__ col_idx, co
         const int64_t start = a.row_start[row];
         const int d = __builtin_amdgcn_readfirstlane(a.row_deg[row]);
         const uint64_t hv = readlane64(mix64(layer_hash ^ uint64_t(dst_ids[row])), 0);
-        uint64_t *ck = lds.key[turn & 1];
-        int32_t *cs = lds.slot[turn & 1];
-        const uint32_t thr = __builtin_amdgcn_readfirstlane(threshold_for(k + (k < 16 ? k + 32 : 48), d));
-        const int mine = wave_candidates(hv, d, thr, wave * kWave, kBlock, ck + wave * kWave, cs + wave * kWave, kWave);
+        Candidate *cand = lds.cand[turn & 1];
+        const uint32_t gap = __builtin_amdgcn_readfirstlane(key_gap(d));
+        const int mine = hub_candidates(hv, d, key_limit(k + (k < 16 ? k + 32 : 48), d, gap), wave * kHubChunks * kWave, kHubChunks * kBlock,
+                                        cand + wave * kWave, kWave);
         if (lane == 0) counts[turn & 1][wave] = mine;
         __syncthreads();
         if (wave != (turn & 3)) continue;
         const int32_t out_base = out_base_of(a, row);
-        uint64_t key[NCH], late[NCH], cand[NCH], sel[NCH];
-        uint32_t slot[NCH];
-        int total = 0, most = 0;
+        uint64_t sel[NCH];
+        uint32_t word[NCH], slot[NCH];
+        int most = 0;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
             const int n = __builtin_amdgcn_readfirstlane(counts[turn & 1][c]);
-            key[c] = lane < n ? ck[c * kWave + lane] : 0;
-            slot[c] = lane < n ? static_cast<uint32_t>(cs[c * kWave + lane]) : 0u;
-            late[c] = 0;
-            cand[c] = low_lanes(n);
-            total += n;
+            const Candidate v = cand[c * kWave + lane];
+            word[c] = lane < n ? v.word : kNoWord;
+            slot[c] = static_cast<uint32_t>(v.slot);
             most = n > most ? n : most;
         }
-        if (total < k || most > kWave) {                   // practically never
+        const uint32_t bound = most > kWave ? 0 : word_bound(word, k, gap);
+        if (bound == 0) {                                  // a list ran over, or equal words: practically never
             select_by_repeated_min(col_idx, start, d, k, hv, out_base, a);
             continue;
         }
-        wave_select_smallest<NCH, false, true>(key, late, slot, cand, k, sel, 31 - __builtin_clz(thr));
-        emit_by_slot<NCH>(slot, sel, k, lds.out[wave], col_idx, start, out_base, a);
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) sel[c] = ballot64(word[c] < bound);
+        emit_by_slot<NCH>(slot, sel, k, lds.slot[wave], col_idx, start, out_base, a);
     }
 }
 
 static_assert(kCandidates % kWave == 0, "candidates are selected in chunks of one per lane");
 
-// The chosen lanes of one chunk of candidates of a row, appended to the batch's list.
-__device__ __forceinline__ int push_selected(uint64_t sel, int slot, int64_t start, int32_t out_pos, int held, int64_t *pos, int32_t *out) {
-    const int lane = lane_id();
-    if ((sel >> lane) & 1) {
-        const int r = popc64(sel & lanes_below(lane));
-        pos[held + r] = start + slot;
-        out[held + r] = out_pos + r;
+// The slots of the lanes with `in`, of row r of the batch, appended to the batch's list.
+__device__ __forceinline__ int push_slots(bool in, int slot, int r, int held, int before, uint2 *pick) {
+    const uint64_t m = ballot64(in);
+    if (in) {
+        const int p = rank_below(m, before);
+        pick[held + p] = make_uint2(static_cast<uint32_t>(slot), static_cast<uint32_t>(r | p << 8));
     }
-    return popc64(sel);
+    return before + popc64(m);
 }
+// The k smallest of a row's candidates; false if that takes more than their words.
 template <int NCH>
-__device__ __forceinline__ void push_smallest(const uint64_t *ck, const int32_t *cs, int cnt, int k, int top, int64_t start, int32_t out_base,
-                                              int held, int64_t *pos, int32_t *out) {
-    uint32_t slot[NCH];
-    uint64_t sel[NCH];
-    select_candidates<NCH, false, true>(ck, cs, cnt, k, slot, sel, top);
+__device__ __forceinline__ bool push_smallest(const Candidate *cand, int cnt, int k, uint32_t gap, int r, int held, uint2 *pick) {
+    const int lane = lane_id();
+    uint32_t word[NCH];
+    int slot[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        const Candidate v = cand[c * kWave + lane];
+        word[c] = c * kWave + lane < cnt ? v.word : kNoWord;
+        slot[c] = v.slot;
+    }
+    const uint32_t bound = word_bound(word, k, gap);
+    if (bound == 0) return false;
     int n = 0;
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) n += push_selected(sel[c], static_cast<int>(slot[c]), start, out_base + n, held + n, pos, out);
+    for (int c = 0; c < NCH; ++c) n = push_slots(word[c] < bound, slot[c], r, held, n, pick);
+    return true;
 }
 
 // The first hub_blocks workgroups take the hubs (they are dispatched first and run the longest; 1,024 of them
@@ -599,12 +684,15 @@ __device__ __forceinline__ void push_smallest(const uint64_t *ck, const int32_t 
 // consecutive destinations, as many as leave a batch for every wavefront of the chip and select at most 64
 // slots: their row information is loaded by one instruction, and their neighbours' ids, positions and
 // marks - a chain of three dependent accesses - are fetched once for all.
-// Bound by instruction issue: 92 M keys of 43 k rows (graph of 111 M nodes) at 19 vector instructions per 64
-// keys, three of them quarter-rate multiplications, in 80 us (122 before: five multiplications, a hub's
-// four wavefronts meeting at three barriers per row); 23 M keys of 10 k rows 46 -> 32 us; 295 k rows of 223
-// slots 270 -> 147 us (the batches).
+// Bound by instruction issue, vector and scalar alike (stress: 35 M and 41 M instructions in 114 us): hence eight
+// wavefronts per SIMD, which takes a bound on the registers (without it 106 scalar registers leave room for seven: the three
+// sampling cases 2 to 7 % slower), candidates of half a word of the key, the k smallest of them by a bound (word_bound), and
+// divisions made once per batch, in its lanes.  92 M keys of 43 k rows (graph of 111 M nodes), ten vector instructions
+// per 64 keys, three of them quarter-rate multiplications: 80 -> 61 us; 23 M keys of 10 k rows 32 -> 24; 65 M keys
+// of 284 k rows 147 -> 114, of 44 k rows 45 -> 34.  While a batch is selected, the row information of the next one and the
+// neighbours of the last two are on their way (4 us of the 147).
 template <typename IdxT>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kBlock, 8)
 k_sample(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, SampleArgs a,
          const int32_t *__restrict__ heavy_rows, const int32_t *__restrict__ heavy_count, int hub_blocks) {
     __shared__ SampleLds lds;
@@ -623,67 +711,86 @@ k_sample(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, Sam
     const int64_t step = int64_t(static_cast<int>(gridDim.x) - hub_blocks) * kWavesPerBlock * batch;
     const int first_expect = k + 4 * static_cast<int>(__builtin_sqrtf(static_cast<float>(k))) + 8;     // candidates wanted of a long row
     const uint64_t layer_hash = layer_hash_of(a);
-    uint64_t *ck = lds.key[wave];
-    int32_t *cs = lds.slot[wave];
-    int64_t *pos = lds.pos[wave];
-    int32_t *out = lds.out[wave];
-    for (int64_t row0 = (int64_t(static_cast<int>(blockIdx.x) - hub_blocks) * kWavesPerBlock + wave) * batch; row0 < n; row0 += step) {
+    Candidate *cand = lds.cand[wave];
+    uint2 *pick = lds.pick[wave];
+    const int64_t first_row = (int64_t(static_cast<int>(blockIdx.x) - hub_blocks) * kWavesPerBlock + wave) * batch;
+    if (first_row >= n) return;
+    // row information of the batch at hand, one row per lane, loaded a batch ahead
+    auto row_of_lane = [&](int64_t row0) {
+        const int64_t last = n - 1;
+        const int64_t r = row0 + (lane < batch ? lane : 0);
+        return r < n ? r : last;
+    };
+    int64_t next_start;
+    int next_deg;
+    IdxT next_node;
+    {
+        const int64_t r = row_of_lane(first_row);
+        next_start = a.row_start[r];
+        next_deg = a.row_deg[r];
+        next_node = dst_ids[r];
+    }
+    // neighbours on their way: ids of the batch before, positions of the one before that
+    NeighbourPipe<IdxT> pipe(a);
+    for (int64_t row0 = first_row; row0 < n; row0 += step) {
         const int m = n - row0 < batch ? static_cast<int>(n - row0) : batch;
-        const int64_t my_row = row0 + (lane < m ? lane : 0);
-        const int64_t my_start = a.row_start[my_row];
-        const int my_deg = a.row_deg[my_row];
+        const int64_t my_row = row_of_lane(row0);
+        const int64_t my_start = next_start;
+        const int my_deg = next_deg;
         const int32_t my_out = out_base_of(a, my_row);
-        const uint64_t my_hv = mix64(layer_hash ^ uint64_t(dst_ids[my_row]));
+        const uint64_t my_hv = mix64(layer_hash ^ uint64_t(next_node));
+        {
+            const int64_t r = row_of_lane(row0 + step);
+            next_start = a.row_start[r];
+            next_deg = a.row_deg[r];
+            next_node = dst_ids[r];
+        }
+        const uint32_t my_gap = key_gap(my_deg), my_low = key_low(my_hv), my_hi_term = key_hi_term(my_hv);
         int held = 0;                                      // slots selected so far
         for (int r = 0; r < m; ++r) {
             const int d = static_cast<int>(readlane32(static_cast<uint32_t>(my_deg), r));
-            const int64_t start = static_cast<int64_t>(readlane64(static_cast<uint64_t>(my_start), r));
-            const int32_t out_base = static_cast<int32_t>(readlane32(static_cast<uint32_t>(my_out), r));
+            if (d > a.heavy_degree && d > k) continue;     // a hub: sampled by the first workgroups
             if (d <= k) {                                  // the whole row, no randomness
-                held += push_selected(low_lanes(d), lane, start, out_base, held, pos, out);
+                held += push_slots(lane < d, lane, r, held, 0, pick);
                 continue;
             }
-            if (d > a.heavy_degree) continue;              // a hub: sampled by the first workgroups
-            const uint64_t hv = readlane64(my_hv, r);
-            if (a.force_slow) {
-                select_by_repeated_min(col_idx, start, d, k, hv, out_base, a);
-                continue;
-            }
+            const uint32_t gap = readlane32(my_gap, r), low = readlane32(my_low, r), hi_term = readlane32(my_hi_term, r);
+            bool done = false;
             if (d <= kWave) {                              // one key per lane
-                const uint64_t key[1] = {WaveKeys::finish(WaveKeys(hv, 0).raw(0))};
-                const uint64_t late[1] = {0};
-                const uint32_t tie[1] = {0};
-                uint64_t cand[1] = {low_lanes(d)}, sel[1];
-                wave_select_smallest<1, false, false>(key, late, tie, cand, k, sel);
-                held += push_selected(sel[0], lane, start, out_base, held, pos, out);
-                continue;
+                const uint32_t x = low ^ static_cast<uint32_t>(lane);
+                const uint32_t z = key_upper(uint64_t(x) * RowKeys::kC1Lo + (uint64_t(x * RowKeys::kC1Hi + hi_term) << 32));
+                const uint32_t word[1] = {lane < d ? z >> 1 : kNoWord};
+                const uint32_t bound = a.force_slow ? 0 : word_bound(word, k, gap);
+                done = bound != 0;
+                if (done) (void)push_slots(word[0] < bound, lane, r, held, 0, pick);
+            } else if (!a.force_slow) {
+                // Longer rows: the slots whose keys lie under a limit are candidates, stored in ascending slot order; too
+                // few (3 rows in 100,000): again with a higher one.
+                int cnt = row_candidates(low, hi_term, d, key_limit(first_expect, d, gap), cand, kCandidates);
+                if (cnt < k) cnt = row_candidates(low, hi_term, d, key_limit(2 * first_expect + 32, d, gap), cand, kCandidates);
+                wave_lds_sync();
+                if (cnt < k || cnt > kCandidates) done = false;
+                else if (cnt <= kWave) done = push_smallest<1>(cand, cnt, k, gap, r, held, pick);
+                else if (cnt <= 2 * kWave) done = push_smallest<2>(cand, cnt, k, gap, r, held, pick);
+                else done = push_smallest<kCandidates / kWave>(cand, cnt, k, gap, r, held, pick);
+                wave_lds_sync();                           // the candidates' place is the next row's
             }
-            // Longer rows: the slots under a key threshold are candidates, stored in ascending slot order; too
-            // few (3 rows in 100,000): again with a higher one.
-            int expect = first_expect;
-            uint32_t thr;
-            int cnt;
-            do {
-                thr = __builtin_amdgcn_readfirstlane(threshold_for(expect, d));
-                cnt = wave_candidates(hv, d, thr, 0, kWave, ck, cs, kCandidates);
-                expect = 2 * expect + 32;
-            } while (cnt < k);
-            if (cnt > kCandidates) {
-                select_by_repeated_min(col_idx, start, d, k, hv, out_base, a);
-                continue;
+            if (done) {
+                held += k;
+            } else {
+                select_by_repeated_min(col_idx, static_cast<int64_t>(readlane64(static_cast<uint64_t>(my_start), r)), d, k, readlane64(my_hv, r),
+                                       static_cast<int32_t>(readlane32(static_cast<uint32_t>(my_out), r)), a);
             }
-            wave_lds_sync();
-            const int top = 31 - __builtin_clz(thr);
-            if (cnt <= kWave) push_smallest<1>(ck, cs, cnt, k, top, start, out_base, held, pos, out);
-            else if (cnt <= 2 * kWave) push_smallest<2>(ck, cs, cnt, k, top, start, out_base, held, pos, out);
-            else push_smallest<kCandidates / kWave>(ck, cs, cnt, k, top, start, out_base, held, pos, out);
-            held += k;
-            wave_lds_sync();                               // the candidates' place is the next row's
         }
         wave_lds_sync();
-        if (lane < held) emit_neighbour(col_idx, pos[lane], 0, out[lane], a);
-        wave_lds_sync();                                   // pos and out are the next batch's
+        const uint2 mine = pick[lane];
+        const int of = lane < held ? static_cast<int>(mine.y & 0xFF) : 0;
+        const int64_t slot_pos = __shfl(my_start, of, kWave) + static_cast<int32_t>(mine.x);
+        const int32_t out_pos = __shfl(my_out, of, kWave) + static_cast<int32_t>(mine.y >> 8);
+        pipe.push(col_idx, lane < held, slot_pos, out_pos);
+        wave_lds_sync();                                   // pick is the next batch's
     }
+    pipe.drain();
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1234,7 +1341,8 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
     const int bitmap_wpt = ctx->bitmap_words <= (int64_t(1) << 20) ? 1 : 4;     // words per thread, see k_bitmap_emit*
     const int bitmap_tiles = static_cast<int>(std::max<int64_t>(1, ctx->bitmap_words / (int64_t(kBlock) * bitmap_wpt)));
     const bool self_count = !use_hash && bitmap_wpt == 1 && bitmap_tiles <= kSelfCountTiles;    // see k_emit_offsets
-    const int heavy_degree = ctx->force_slow_select ? 0x7FFFFFFF : ctx->heavy_degree;
+    // (rows that are no hubs are walked in one range of 2^30 slots)
+    const int heavy_degree = ctx->force_slow_select ? 0x7FFFFFFF : std::min(ctx->heavy_degree, 1 << 30);
     auto row_info_args = [&](int l, int64_t dst_count) {
         RowInfoArgs<PtrT, IdxT> r;
         r.row_ptr = row_ptr;

@@ -74,6 +74,28 @@ def test_selection_of_unordered_candidates_with_ties(env, n, prioritised):
             assert np.array_equal(got, want), (name, n, k)
 
 
+@pytest.mark.parametrize("n", [2, 64, 65, 256])
+def test_selection_where_the_keys_are_not_spread_evenly(env, n):
+    """The bound on the keys' upper words is first looked for where evenly spread keys put it; here it lies far from there,
+    next to equal words, at the end of the range, or the words are all the same and the low bits decide."""
+    m, ctx = env
+    rng = np.random.default_rng(77 + n)
+    slots = np.sort(rng.choice(5000, n, replace=False)).astype(np.int64)
+    late = np.zeros(n, dtype=np.int64)
+    top = np.uint64(2**64 - 1)
+    sets = {
+        "few low words": rng.integers(0, 3 * n, n).astype(np.uint64) << np.uint64(33),
+        "the highest words": top - (rng.integers(0, 3 * n, n).astype(np.uint64) << np.uint64(33)),
+        "two far clusters": np.where(rng.random(n) < 0.5, rng.integers(0, 4 * n, n), 2**31 - 1 - rng.integers(0, 4 * n, n)).astype(np.uint64) << np.uint64(33),
+        "neighbouring words": np.arange(n, dtype=np.uint64) + np.uint64(2**30) << np.uint64(33),
+        "one word": (np.uint64(5) << np.uint64(40)) + rng.integers(0, 2**33, n).astype(np.uint64),
+    }
+    for name, keys in sets.items():
+        for k in sorted({1, n // 2, min(n, 25), min(n, 63), n}):
+            got = run(m, ctx, keys, slots, late, k, False, ordered=True)
+            assert np.array_equal(got, expected(keys, slots, late, k, False)), (name, n, k)
+
+
 def test_selection_argument_errors(env):
     m, ctx = env
     keys = torch.zeros(4, dtype=torch.int64, device="cuda")

@@ -162,19 +162,21 @@ int mqg_ctx_create(mqg_ctx **out, const mqg_graph *g, int32_t max_seeds, const i
 
     bool ok = true;
     ok = ok && dev_alloc(&c->local_of, c->num_nodes) == hipSuccess;
-    ok = ok && dev_alloc(&c->bitmap, c->bitmap_words) == hipSuccess;
+    ok = ok && dev_alloc(&c->bitmap, 2 * c->bitmap_words) == hipSuccess;
     ok = ok && dev_alloc(&c->tile_vals, c->max_tiles) == hipSuccess;
     ok = ok && dev_alloc(&c->bitmap_tile_vals, c->max_tiles) == hipSuccess;
     ok = ok && dev_alloc(&c->row_start, c->max_dst) == hipSuccess;
     ok = ok && dev_alloc(&c->row_deg, c->max_dst) == hipSuccess;
-    ok = ok && dev_alloc(reinterpret_cast<int32_t **>(&c->nbr), c->max_nnz) == hipSuccess;
+    int64_t all_nnz = 0;
+    for (int l = 0; l < L; ++l) all_nnz += c->bound_nnz[l];
+    ok = ok && dev_alloc(reinterpret_cast<int32_t **>(&c->nbr), all_nnz) == hipSuccess;
     ok = ok && dev_alloc(&c->heavy_rows, c->max_dst) == hipSuccess;
     ok = ok && dev_alloc(&c->heavy_count, MQG_MAX_LAYERS + 1) == hipSuccess;
     ok = ok && dev_alloc(&c->hit_list, c->max_src) == hipSuccess;
     ok = ok && dev_alloc(&c->miss_list, c->max_src) == hipSuccess;
     ok = ok && dev_alloc(&c->counters, 8) == hipSuccess;
     if (ok) ok = hipMemset(c->local_of, 0xFF, std::max<int64_t>(c->num_nodes, 1) * sizeof(int32_t)) == hipSuccess;
-    if (ok) ok = hipMemset(c->bitmap, 0, std::max<int64_t>(c->bitmap_words, 1) * sizeof(uint32_t)) == hipSuccess;
+    if (ok) ok = hipMemset(c->bitmap, 0, 2 * c->bitmap_words * sizeof(uint32_t)) == hipSuccess;
     if (ok) ok = hipMemset(c->counters, 0, 8 * sizeof(unsigned long long)) == hipSuccess;
     if (ok) ok = hipMemset(c->heavy_count, 0, (MQG_MAX_LAYERS + 1) * sizeof(int32_t)) == hipSuccess;
     if (ok) ok = hipDeviceSynchronize() == hipSuccess;

@@ -78,14 +78,14 @@ struct mqg_ctx {
     // scratch (device)
     int32_t *local_of = nullptr;         // [num_nodes] position of a node in the current source list plus the call's offset; less if absent
     int64_t pos_next = 0;                // offset of the next call's positions (take_positions)
-    uint32_t *bitmap = nullptr;          // [bitmap_words] nodes first seen in the current layer
+    uint32_t *bitmap = nullptr;          // [2 * bitmap_words] nodes first seen in the current layer; small graphs take the two halves in turn
     int64_t bitmap_words = 0;            // padded to a multiple of kBitmapTileWords
     int32_t *tile_vals = nullptr;        // [max_tiles] per-tile sums of the rows, then their exclusive scan
     int32_t *bitmap_tile_vals = nullptr; // [max_tiles] the same for the tiles of the bitmap
     int64_t max_tiles = 0;
     int64_t *row_start = nullptr;        // [max_dst] first adjacency slot of each destination
     int32_t *row_deg = nullptr;          // [max_dst] degree of each destination
-    void *nbr = nullptr;                 // [max_nnz] sampled neighbours, global ids, 32-bit
+    void *nbr = nullptr;                 // [sum of bound_nnz] sampled neighbours of every block, global ids, 32-bit
     int32_t *heavy_rows = nullptr;       // [max_dst] destinations whose degree exceeds heavy_degree
     int32_t *heavy_count = nullptr;      // [MQG_MAX_LAYERS] their number, per block; [MQG_MAX_LAYERS] seed-check flags
     int2 *hit_list = nullptr;            // [max_src] (output row, cache slot)

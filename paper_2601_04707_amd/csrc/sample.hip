@@ -1,8 +1,8 @@
 // L-hop fixed-fanout neighbour sampling into bipartite blocks (paper Sec. III-A, GraphSAGE
 // paragraph; block layout after Sec. IV "Mini-Batch Transfer To GPU" and Eq. 16).
 //
-// Per block, outward from the seeds (five launches; the first block's row information is a launch
-// of its own, every other block's rides with the block before it):
+// Per block, outward from the seeds (two or three launches, four on graphs of more than 3 M nodes; the first block's row
+// information is a launch of its own):
 //   row info       adjacency start/degree of every destination, copy of the destinations into the
 //                  block's source list, per-tile sums of min(fanout, degree), list of the hubs
 //   k_sample       a wavefront takes destinations one by one: smallest-k random keys, then for a few
@@ -10,19 +10,21 @@
 //                  row * fanout (no offsets needed yet), first-seen nodes marked in an N-bit bitmap
 //                  (destinations whose degree exceeds heavy_degree are taken by whole workgroups in the
 //                  same launch, so that a hub's key evaluation is spread over four wavefronts instead of
-//                  stretching the kernel's tail)
+//                  stretching the kernel's tail); workgroups of their own relabel the block before meanwhile, copy its
+//                  sources, which are this block's destinations, into this block's source list and add up the row tiles
 //   k_offsets_count  two independent jobs in one launch: indptr from the row tile sums (every
 //                  workgroup adds up the sums of the tiles before its own; only above 8,192 tiles
 //                  does one k_scan_tiles launch scan them first) and the popcount of every tile
 //                  of the bitmap
 //   k_bitmap_emit  popcount-rank the bitmap: new source nodes come out ascending by id, get their
-//                  position recorded in local_of[], the bitmap is cleared on the way
+//                  position recorded in local_of[], the bitmap is cleared on the way; the new sources' row information
+//                  for the next block outward, whose destinations they are, is recorded with them
 //   k_emit_offsets  graphs of up to half a million nodes: the two launches above in one - every
 //                  tile's workgroup counts the bits of the tiles before its own itself (the relabel
-//                  launch clears the bitmap then)
-//   k_relabel_rowinfo  indices[indptr[row] + j] = local_of[neighbour j of row], and in the same
-//                  launch the row information of the next block outward (whose destinations are
-//                  this block's sources); the outermost block ends with a plain k_relabel
+//                  clears the bitmap then, while the next block is marked in another)
+//   k_relabel      indices[indptr[row] + j] = local_of[neighbour j of row] of the outermost block
+//   k_relabel_rowinfo  graphs of more than 3 M nodes: that of every other block, and in the same
+//                  launch the row information of the next block outward
 // The hash-table dedup (an option) keeps the older order: offsets first, neighbours written compactly.
 // All sizes that depend on the data stay on the device; grids are sized by worst-case bounds.
 #include "common.h"
@@ -48,6 +50,29 @@ uint64_t host_mix64(uint64_t z) {
 
 // ------------------------------------------------------------------------------------------
 
+// Destinations of more than heavy_degree slots, hubs, are listed for the sampling kernels.
+struct HubList {
+    int32_t *rows;
+    int32_t *count;
+    int heavy_degree;
+    // places for what the threads of a workgroup have (all call it; lds as for block_excl_scan): one atomic per workgroup that has any
+    // (one per wavefront queued up at the counter: the row information of 295 k destinations 32 -> 21 us, of 43 k 10.2 -> 5.7 us)
+    __device__ __forceinline__ int take(int mine, int *lds) const {
+        int total;
+        const int ex = block_excl_scan<kWavesPerBlock>(mine, &total, lds);
+        if (total == 0) return 0;                          // workgroup-uniform
+        __syncthreads();
+        if (threadIdx.x == 0) lds[0] = atomicAdd(count, total);
+        __syncthreads();
+        return lds[0] + ex;
+    }
+};
+
+// the last launch of a call: counts and seed flags back to zero for the next one
+__device__ __forceinline__ void clear_hubs(int32_t *__restrict__ hub_count) {
+    if (threadIdx.x <= MQG_MAX_LAYERS) hub_count[threadIdx.x] = 0;
+}
+
 // Arguments of the row-information step of one block.
 template <typename PtrT, typename IdxT>
 struct RowInfoArgs {
@@ -60,9 +85,7 @@ struct RowInfoArgs {
     int32_t *row_deg;
     int32_t *tile_sums;
     int64_t *sizes_rw;
-    int heavy_degree;
-    int32_t *heavy_rows;
-    int32_t *heavy_count;
+    HubList hubs;
     int64_t n_seeds;             // >= 0: innermost block
     int32_t *local_of;
     int32_t pos_base;            // see take_positions
@@ -77,7 +100,7 @@ __device__ __forceinline__ void row_info_tile(const RowInfoArgs<PtrT, IdxT> &a, 
     const int64_t n = a.n_seeds >= 0 ? a.n_seeds : a.sizes[0];
     const int64_t i = int64_t(tile) * kBlock + threadIdx.x;
     int cnt = 0;
-    bool heavy = false;
+    int64_t d = 0;
     if (i < n) {
         IdxT v = a.dst[i];
         if (a.n_seeds >= 0) {
@@ -91,47 +114,41 @@ __device__ __forceinline__ void row_info_tile(const RowInfoArgs<PtrT, IdxT> &a, 
             if (a.local_of && atomicMax(&a.local_of[v], a.pos_base + static_cast<int32_t>(i)) >= a.pos_base) atomicOr(a.seed_flags, 2);
         }
         int64_t s = static_cast<int64_t>(a.row_ptr[v]);
-        int64_t d = static_cast<int64_t>(a.row_ptr[v + 1]) - s;
+        d = static_cast<int64_t>(a.row_ptr[v + 1]) - s;
         a.row_start[i] = s;
         a.row_deg[i] = static_cast<int32_t>(d);
         a.src_out[i] = v;
         cnt = d < a.fanout ? static_cast<int>(d) : a.fanout;
-        heavy = d > a.heavy_degree;
     }
-    // list the hubs: one atomic per workgroup that has any (one per wavefront queued up at the counter: the
-    // relabel and row information of a block of 295 k destinations 32 -> 21 us, of 43 k 10.2 -> 5.7 us)
-    const uint64_t hubs = ballot64(heavy);
     const int w = wave_sum(cnt);
-    const int wave = static_cast<int>(threadIdx.x) >> 6;
-    if (lane_id() == 0) {
-        lds[wave] = w;
-        lds[kWavesPerBlock + wave] = popc64(hubs);
-    }
+    if (lane_id() == 0) lds[threadIdx.x >> 6] = w;
     __syncthreads();
     if (threadIdx.x == 0) {
-        int t = 0, h = 0;
+        int t = 0;
 #pragma unroll
-        for (int k = 0; k < kWavesPerBlock; ++k) {
-            t += lds[k];
-            h += lds[kWavesPerBlock + k];
-        }
+        for (int k = 0; k < kWavesPerBlock; ++k) t += lds[k];
         a.tile_sums[tile] = t;
         if (tile == 0 && a.n_seeds >= 0) a.sizes_rw[0] = a.n_seeds;
-        if (h) lds[2 * kWavesPerBlock] = atomicAdd(a.heavy_count, h);
     }
-    __syncthreads();
-    if (heavy) {
-        int base = lds[2 * kWavesPerBlock];
-        for (int k = 0; k < wave; ++k) base += lds[kWavesPerBlock + k];
-        a.heavy_rows[base + popc64(hubs & lanes_below(lane_id()))] = static_cast<int32_t>(i);
-    }
+    const bool hub = i < n && d > a.hubs.heavy_degree;
+    const int place = a.hubs.take(hub ? 1 : 0, lds);
+    if (hub) a.hubs.rows[place] = static_cast<int32_t>(i);
 }
-constexpr int kRowInfoLds = 2 * kWavesPerBlock + 1;
+
+// What the sampling of the next block needs of its new destinations, recorded as they are listed: their adjacency, and
+// which of them are hubs.  row_ptr null: there is no next block.
+template <typename PtrT>
+struct NewRows {
+    const PtrT *row_ptr;
+    int64_t *row_start;
+    int32_t *row_deg;
+    HubList hubs;
+};
 
 template <typename PtrT, typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_row_info(RowInfoArgs<PtrT, IdxT> a) {
-    __shared__ int lds[kRowInfoLds];
+    __shared__ int lds[kWavesPerBlock];
     row_info_tile(a, static_cast<int>(blockIdx.x), lds);
 }
 
@@ -191,6 +208,83 @@ k_row_offsets(const int32_t *__restrict__ row_deg, int fanout, int64_t *sizes,
     __shared__ int lds[kWavesPerBlock];
     row_offsets_tile(row_deg, fanout, sizes, tile_vals, scanned, indptr, seed_flags, static_cast<int>(blockIdx.x),
                      static_cast<int>(gridDim.x), lds);
+}
+
+// ------------------------------------------------------------------------------------------
+
+// Neighbour j of row r sits at nbr[r * fanout + j]; its edge position is indptr[r] + j.  Workgroups
+// vb of nb walk the num_dst * fanout slots.
+__device__ __forceinline__ void relabel_slots(const int32_t *__restrict__ nbr, const int64_t *__restrict__ sizes,
+                                              const int32_t *__restrict__ indptr, int fanout,
+                                              const int32_t *__restrict__ local_of, int32_t pos_base, int32_t *__restrict__ indices, int vb, int nb) {
+    const uint32_t total = static_cast<uint32_t>(sizes[0] * fanout);
+    const uint32_t stride = static_cast<uint32_t>(nb) * kBlock;
+    for (uint64_t t64 = uint64_t(vb) * kBlock + threadIdx.x; t64 < total; t64 += stride) {
+        const uint32_t t = static_cast<uint32_t>(t64);
+        const uint32_t row = t / static_cast<uint32_t>(fanout);
+        const int j = static_cast<int>(t - row * static_cast<uint32_t>(fanout));
+        const int b = indptr[row];
+        if (j < indptr[row + 1] - b) {
+            const int32_t u = nbr[t];
+            indices[b + j] = u < 0 ? ~u : local_of[u] - pos_base;
+        }
+    }
+}
+
+// (clear: the frontier bitmap, when the emit launch left its words set; vb of nb workgroups)
+__device__ __forceinline__ void clear_words(uint32_t *__restrict__ clear, int64_t clear_words, int vb, int nb) {
+    if (!clear) return;
+    for (int64_t w = int64_t(vb) * kBlock + threadIdx.x; w < clear_words; w += int64_t(nb) * kBlock) clear[w] = 0;
+}
+
+// What the launch that samples a block does beside that, in workgroups of its own: the relabel of the block before, whose
+// sources are this block's destinations, their copy into this block's source list, and the sums of the rows' tiles.
+// (In a launch of its own before this one: 4 us of a batch of 1,024 seeds' 54, 25 of 8,192 seeds' 253.)
+template <typename IdxT>
+struct SideWork {
+    int relabel_blocks, row_tiles;                         // workgroups; both 0: nothing to do
+    const int32_t *nbr;                                    // of the block before
+    const int64_t *sizes;
+    const int32_t *indptr;
+    int fanout;
+    const int32_t *local_of;
+    int32_t pos_base;
+    int32_t *indices;
+    uint32_t *clear;
+    int64_t nclear;
+    const IdxT *dst;                                       // this block's destinations: the block before's sources
+    const int64_t *dst_count;
+    const int32_t *row_deg;
+    int row_fanout;                                        // this block's
+    IdxT *src_out;
+    int32_t *tile_sums;
+};
+
+template <typename IdxT>
+__device__ __forceinline__ void side_work(const SideWork<IdxT> &w, int b, int *lds) {
+    if (b < w.relabel_blocks) {
+        clear_words(w.clear, w.nclear, b, w.relabel_blocks);
+        relabel_slots(w.nbr, w.sizes, w.indptr, w.fanout, w.local_of, w.pos_base, w.indices, b, w.relabel_blocks);
+        return;
+    }
+    const int tile = b - w.relabel_blocks;
+    const int64_t n = *w.dst_count;
+    const int64_t i = int64_t(tile) * kBlock + threadIdx.x;
+    int cnt = 0;
+    if (i < n) {
+        const int d = w.row_deg[i];
+        w.src_out[i] = w.dst[i];
+        cnt = d < w.row_fanout ? d : w.row_fanout;
+    }
+    cnt = wave_sum(cnt);
+    if (lane_id() == 0) lds[threadIdx.x >> 6] = cnt;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int t = 0;
+#pragma unroll
+        for (int k = 0; k < kWavesPerBlock; ++k) t += lds[k];
+        w.tile_sums[tile] = t;
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -605,7 +699,8 @@ struct SampleLds {
 // turns at that, while the others go on with the next hub into the second set of lists: one barrier per hub.
 template <typename IdxT>
 __device__ __forceinline__ void sample_hubs(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, const SampleArgs &a,
-                            const int32_t *__restrict__ heavy_rows, int nheavy, int first, int step, SampleLds &lds, int (&counts)[2][kWavesPerBlock]) {
+                            const HubList &hubs, int first, int step, SampleLds &lds, int (&counts)[2][kWavesPerBlock]) {
+    const int nheavy = *hubs.count;
     static_assert(kWavesPerBlock * kWave == kCandidates, "one chunk of candidates per wavefront");
     constexpr int NCH = kWavesPerBlock;
     const int lane = lane_id();
@@ -614,7 +709,7 @@ __device__ __forceinline__ void sample_hubs(const IdxT *__restrict__ col_idx, co
     const uint64_t layer_hash = layer_hash_of(a);
     int turn = 0;
     for (int h = first; h < nheavy; h += step, ++turn) {   // the same for all four
-        const int row = __builtin_amdgcn_readfirstlane(heavy_rows[h]);
+        const int row = __builtin_amdgcn_readfirstlane(hubs.rows[h]);
         const int64_t start = a.row_start[row];
         const int d = __builtin_amdgcn_readfirstlane(a.row_deg[row]);
         const uint64_t hv = readlane64(mix64(layer_hash ^ uint64_t(dst_ids[row])), 0);
@@ -694,11 +789,16 @@ __device__ __forceinline__ bool push_smallest(const Candidate *cand, int cnt, in
 template <typename IdxT>
 __global__ void __launch_bounds__(kBlock, 8)
 k_sample(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, SampleArgs a,
-         const int32_t *__restrict__ heavy_rows, const int32_t *__restrict__ heavy_count, int hub_blocks) {
+         HubList hubs, int hub_blocks, int row_blocks, SideWork<IdxT> side) {
     __shared__ SampleLds lds;
     __shared__ int counts[2][kWavesPerBlock];
     if (static_cast<int>(blockIdx.x) < hub_blocks) {
-        sample_hubs(col_idx, dst_ids, a, heavy_rows, *heavy_count, static_cast<int>(blockIdx.x), hub_blocks, lds, counts);
+        sample_hubs(col_idx, dst_ids, a, hubs, static_cast<int>(blockIdx.x), hub_blocks, lds, counts);
+        return;
+    }
+    const int row_block = static_cast<int>(blockIdx.x) - hub_blocks - (side.relabel_blocks + side.row_tiles);
+    if (row_block < 0) {
+        side_work(side, static_cast<int>(blockIdx.x) - hub_blocks, counts[0]);
         return;
     }
     const int lane = lane_id();
@@ -708,12 +808,12 @@ k_sample(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, Sam
     const int64_t share = n / kBusyWaves;
     const int most = kWave / k < kBatchRows ? kWave / k : kBatchRows;
     const int batch = share < 1 ? 1 : share < most ? static_cast<int>(share) : most;
-    const int64_t step = int64_t(static_cast<int>(gridDim.x) - hub_blocks) * kWavesPerBlock * batch;
+    const int64_t step = int64_t(row_blocks) * kWavesPerBlock * batch;
     const int first_expect = k + 4 * static_cast<int>(__builtin_sqrtf(static_cast<float>(k))) + 8;     // candidates wanted of a long row
     const uint64_t layer_hash = layer_hash_of(a);
     Candidate *cand = lds.cand[wave];
     uint2 *pick = lds.pick[wave];
-    const int64_t first_row = (int64_t(static_cast<int>(blockIdx.x) - hub_blocks) * kWavesPerBlock + wave) * batch;
+    const int64_t first_row = (int64_t(row_block) * kWavesPerBlock + wave) * batch;
     if (first_row >= n) return;
     // row information of the batch at hand, one row per lane, loaded a batch ahead
     auto row_of_lane = [&](int64_t row0) {
@@ -885,14 +985,15 @@ constexpr int kPrioUnroll = 4;   // chunks of 64 slots whose loads are issued to
 template <typename IdxT>
 __device__ void sample_hubs_prio(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, const SampleArgs &a,
                                  const uint32_t *__restrict__ prio, const int32_t *__restrict__ prio_count,
-                                 const int32_t *__restrict__ heavy_rows, int nheavy, int first, int step,
+                                 const HubList &hubs, int first, int step,
                                  uint64_t *ck, uint32_t *cs, int32_t *sel_slot, int *cnt_s) {
     const int tid = threadIdx.x;
     const int lane = lane_id();
     const int wave = tid >> 6;
     const int k = a.fanout;
+    const int nheavy = *hubs.count;
     for (int h = first; h < nheavy; h += step) {
-        const int row = heavy_rows[h];
+        const int row = hubs.rows[h];
         const int64_t start = a.row_start[row];
         const int d = a.row_deg[row];
         const int32_t out_base = out_base_of(a, row);
@@ -951,20 +1052,25 @@ template <typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_sample_prio(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, SampleArgs a,
               const uint32_t *__restrict__ prio, const int32_t *__restrict__ prio_count,
-              const int32_t *__restrict__ heavy_rows, const int32_t *__restrict__ heavy_count, int hub_blocks) {
+              HubList hubs, int hub_blocks, SideWork<IdxT> side) {
     __shared__ uint64_t cand_key[kWavesPerBlock][kCandidates];
     __shared__ uint32_t cand_slot[kWavesPerBlock][kCandidates];   // bit 31: not cached
     __shared__ int32_t sel_slot[kWave];
     __shared__ int cnt_s;
     if (static_cast<int>(blockIdx.x) < hub_blocks) {
-        sample_hubs_prio(col_idx, dst_ids, a, prio, prio_count, heavy_rows, *heavy_count, static_cast<int>(blockIdx.x),
+        sample_hubs_prio(col_idx, dst_ids, a, prio, prio_count, hubs, static_cast<int>(blockIdx.x),
                          hub_blocks, cand_key[0], cand_slot[0], sel_slot, &cnt_s);
+        return;
+    }
+    const int row_block = static_cast<int>(blockIdx.x) - hub_blocks - (side.relabel_blocks + side.row_tiles);
+    if (row_block < 0) {
+        side_work(side, static_cast<int>(blockIdx.x) - hub_blocks, sel_slot);
         return;
     }
     const int lane = lane_id();
     const int wave = static_cast<int>(threadIdx.x) >> 6;
     const int64_t n = a.sizes[0];
-    const int64_t row = (int64_t(blockIdx.x) - hub_blocks) * kWavesPerBlock + wave;
+    const int64_t row = int64_t(row_block) * kWavesPerBlock + wave;
     if (row >= n) return;
 
     const int64_t start = a.row_start[row];
@@ -1128,6 +1234,47 @@ __device__ __forceinline__ void store_num_src(int64_t *sizes, int64_t *next_num_
     if (next_num_dst) *next_num_dst = num_src;
 }
 
+// The ids staged in LDS, ascending, to the source list from place `base` on.  Four a thread at a time: the two row offsets of
+// an id are a random access, on a graph of 111 M nodes one that misses the address translation too.
+template <typename PtrT, typename IdxT>
+__device__ __forceinline__ void store_staged(int32_t *staged, int total, int64_t base, IdxT *__restrict__ src_ids, int32_t *__restrict__ local_of,
+                                             int32_t pos_base, const NewRows<PtrT> &next, int *lds) {
+    constexpr int U = 4;
+    int hubs = 0;
+    for (int k0 = threadIdx.x; k0 < total; k0 += U * kBlock) {
+        int32_t v[U];
+        int64_t begin[U], degree[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = staged[k0 + u * kBlock < total ? k0 + u * kBlock : k0];
+        if (next.row_ptr) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                begin[u] = static_cast<int64_t>(next.row_ptr[v[u]]);
+                degree[u] = static_cast<int64_t>(next.row_ptr[int64_t(v[u]) + 1]) - begin[u];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + u * kBlock;
+            if (k >= total) break;
+            src_ids[base + k] = static_cast<IdxT>(v[u]);
+            local_of[v[u]] = pos_base + static_cast<int32_t>(base + k);
+            if (next.row_ptr) {
+                next.row_start[base + k] = begin[u];
+                next.row_deg[base + k] = static_cast<int32_t>(degree[u]);
+                const int hub = degree[u] > next.hubs.heavy_degree ? 1 : 0;
+                staged[k] = hub;                           // this thread's own entry
+                hubs += hub;
+            }
+        }
+    }
+    if (!next.row_ptr) return;
+    int place = next.hubs.take(hubs, lds);
+    if (hubs)
+        for (int k = threadIdx.x; k < total; k += kBlock)
+            if (staged[k]) next.hubs.rows[place++] = static_cast<int32_t>(base + k);
+}
+
 template <typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_bitmap_emit4(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_vals, int scanned,
@@ -1160,11 +1307,11 @@ k_bitmap_emit4(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_v
     *reinterpret_cast<uint4 *>(bitmap + w0) = make_uint4(0, 0, 0, 0);
 }
 
-template <typename IdxT>
+template <typename PtrT, typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_bitmap_emit1(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_vals, int scanned,
                int64_t *__restrict__ sizes, int64_t *__restrict__ next_num_dst, IdxT *__restrict__ src_ids,
-               int32_t *__restrict__ local_of, int32_t pos_base) {
+               int32_t *__restrict__ local_of, int32_t pos_base, NewRows<PtrT> next) {
     __shared__ int lds[kWavesPerBlock];
     __shared__ int32_t staged[kBlock * 32];                // every id of the tile, ascending
     const int tile_base = scanned ? tile_vals[blockIdx.x] : tiles_before(tile_vals, lds);
@@ -1186,12 +1333,7 @@ k_bitmap_emit1(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_v
         }
     }
     __syncthreads();
-    const int64_t base = num_dst + tile_base;
-    for (int k = threadIdx.x; k < total; k += kBlock) {
-        const int32_t v = staged[k];
-        src_ids[base + k] = static_cast<IdxT>(v);
-        local_of[v] = pos_base + static_cast<int32_t>(base + k);
-    }
+    store_staged(staged, total, num_dst + tile_base, src_ids, local_of, pos_base, next, lds);
 }
 
 // Small bitmaps (at most kSelfCountTiles tiles of 256 words, i.e. graphs of up to half a million
@@ -1200,12 +1342,13 @@ k_bitmap_emit1(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_v
 // the relabel launch that follows.  The same launch turns the row tile sums into indptr (the
 // workgroups past the bitmap's tiles), as k_offsets_count does on larger graphs.
 constexpr int kSelfCountTiles = 64;
-template <typename IdxT>
+constexpr int kRecordTiles = 384;
+template <typename PtrT, typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_emit_offsets(const uint32_t *__restrict__ bitmap, int bitmap_tiles, int64_t *sizes, int64_t *__restrict__ next_num_dst,
                IdxT *__restrict__ src_ids, int32_t *__restrict__ local_of, int32_t pos_base, const int32_t *__restrict__ row_deg, int fanout,
                const int32_t *__restrict__ row_tile_vals, int rows_scanned, int32_t *__restrict__ indptr,
-               const int32_t *__restrict__ seed_flags, int row_tiles) {
+               const int32_t *__restrict__ seed_flags, int row_tiles, NewRows<PtrT> next) {
     __shared__ int lds[kWavesPerBlock];
     __shared__ int32_t staged[kBlock * 32];                // every id of the tile, ascending
     const int tile = static_cast<int>(blockIdx.x);
@@ -1239,45 +1382,14 @@ k_emit_offsets(const uint32_t *__restrict__ bitmap, int bitmap_tiles, int64_t *s
         }
     }
     __syncthreads();
-    const int64_t base = num_dst + tile_base;
-    for (int k = threadIdx.x; k < total; k += kBlock) {
-        const int32_t v = staged[k];
-        src_ids[base + k] = static_cast<IdxT>(v);
-        local_of[v] = pos_base + static_cast<int32_t>(base + k);
-    }
-}
-
-// Neighbour j of row r sits at nbr[r * fanout + j]; its edge position is indptr[r] + j.  Workgroups
-// vb of nb walk the num_dst * fanout slots.
-__device__ __forceinline__ void relabel_slots(const int32_t *__restrict__ nbr, const int64_t *__restrict__ sizes,
-                                              const int32_t *__restrict__ indptr, int fanout,
-                                              const int32_t *__restrict__ local_of, int32_t pos_base, int32_t *__restrict__ indices, int vb, int nb) {
-    const uint32_t total = static_cast<uint32_t>(sizes[0] * fanout);
-    const uint32_t stride = static_cast<uint32_t>(nb) * kBlock;
-    for (uint64_t t64 = uint64_t(vb) * kBlock + threadIdx.x; t64 < total; t64 += stride) {
-        const uint32_t t = static_cast<uint32_t>(t64);
-        const uint32_t row = t / static_cast<uint32_t>(fanout);
-        const int j = static_cast<int>(t - row * static_cast<uint32_t>(fanout));
-        const int b = indptr[row];
-        if (j < indptr[row + 1] - b) {
-            const int32_t u = nbr[t];
-            indices[b + j] = u < 0 ? ~u : local_of[u] - pos_base;
-        }
-    }
-}
-
-// (clear: the frontier bitmap, when the emit launch left its words set; vb of nb workgroups)
-__device__ __forceinline__ void clear_words(uint32_t *__restrict__ clear, int64_t clear_words, int vb, int nb) {
-    if (!clear) return;
-    for (int64_t w = int64_t(vb) * kBlock + threadIdx.x; w < clear_words; w += int64_t(nb) * kBlock) clear[w] = 0;
+    store_staged(staged, total, num_dst + tile_base, src_ids, local_of, pos_base, next, lds);
 }
 
 __global__ void __launch_bounds__(kBlock)
 k_relabel(const int32_t *__restrict__ nbr, const int64_t *__restrict__ sizes, const int32_t *__restrict__ indptr, int fanout,
           const int32_t *__restrict__ local_of, int32_t pos_base, int32_t *__restrict__ indices, uint32_t *__restrict__ clear, int64_t nclear,
-          int32_t *__restrict__ heavy_count) {
-    // the last launch of a call: hub counts and seed flags back to zero for the next one
-    if (blockIdx.x == 0 && threadIdx.x <= MQG_MAX_LAYERS) heavy_count[threadIdx.x] = 0;
+          int32_t *__restrict__ hub_count) {
+    if (blockIdx.x == 0) clear_hubs(hub_count);
     clear_words(clear, nclear, static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
     relabel_slots(nbr, sizes, indptr, fanout, local_of, pos_base, indices, static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
 }
@@ -1288,11 +1400,10 @@ template <typename PtrT, typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_relabel_rowinfo(const int32_t *__restrict__ nbr, const int64_t *__restrict__ sizes, const int32_t *__restrict__ indptr,
                   int fanout, const int32_t *__restrict__ local_of, int32_t pos_base, int32_t *__restrict__ indices, int relabel_blocks,
-                  RowInfoArgs<PtrT, IdxT> next, uint32_t *__restrict__ clear, int64_t nclear) {
-    __shared__ int lds[kRowInfoLds];
+                  RowInfoArgs<PtrT, IdxT> next) {
+    __shared__ int lds[kWavesPerBlock];
     const int b = static_cast<int>(blockIdx.x);
     if (b < relabel_blocks) {
-        clear_words(clear, nclear, b, relabel_blocks);
         relabel_slots(nbr, sizes, indptr, fanout, local_of, pos_base, indices, b, relabel_blocks);
     } else {
         row_info_tile(next, b - relabel_blocks, lds);
@@ -1316,8 +1427,8 @@ k_reset_local(const IdxT *__restrict__ src_ids, const int64_t *__restrict__ size
 }
 
 __global__ void __launch_bounds__(kBlock)
-k_clear_hubs(int32_t *__restrict__ heavy_count) {
-    if (threadIdx.x <= MQG_MAX_LAYERS) heavy_count[threadIdx.x] = 0;
+k_clear_hubs(int32_t *__restrict__ hub_count) {
+    clear_hubs(hub_count);
 }
 
 template <typename PtrT, typename IdxT>
@@ -1343,6 +1454,14 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
     const bool self_count = !use_hash && bitmap_wpt == 1 && bitmap_tiles <= kSelfCountTiles;    // see k_emit_offsets
     // (rows that are no hubs are walked in one range of 2^30 slots)
     const int heavy_degree = ctx->force_slow_select ? 0x7FFFFFFF : std::min(ctx->heavy_degree, 1 << 30);
+    // Bitmaps of few tiles: the launch that lists new sources records their rows, and the sampling launch relabels (SideWork).
+    // Every tile with hubs adds to the list's count, one after the other, 13 ns each: from kRecordTiles on the row information goes
+    // with the relabel, in a launch of its own (recorded and not, batches of 1,024 and fanouts 15, 10, 5: 1 M nodes, 123 tiles, 88 and
+    // 94 us, 3 M 107.0 and 108.2, 4 M 105.6 and 103.7, 8 M 103 and 96, 111 M 179 and 151).
+    const bool one_list = !use_hash && bitmap_tiles <= kRecordTiles;       // of hubs for all blocks: they stay destinations
+    auto hub_list = [&](int l) {
+        return HubList{ctx->heavy_rows, ctx->heavy_count + (one_list ? 0 : l), heavy_degree};
+    };
     auto row_info_args = [&](int l, int64_t dst_count) {
         RowInfoArgs<PtrT, IdxT> r;
         r.row_ptr = row_ptr;
@@ -1354,9 +1473,7 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
         r.row_deg = ctx->row_deg;
         r.tile_sums = ctx->tile_vals;
         r.sizes_rw = blocks[l].sizes;
-        r.heavy_degree = heavy_degree;
-        r.heavy_rows = ctx->heavy_rows;
-        r.heavy_count = ctx->heavy_count + l;
+        r.hubs = hub_list(l);
         r.n_seeds = l == L - 1 ? dst_count : int64_t(-1);
         r.local_of = local_of;
         r.pos_base = pos_base;
@@ -1365,8 +1482,9 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
         return r;
     };
     auto tiles_of = [](int64_t rows) { return static_cast<int>(std::max<int64_t>(1, ceil_div(rows, kBlock))); };
-    // the innermost block's row information; every other block's is launched with the relabel before it
+    // the innermost block's row information; that of the others is recorded as their destinations are listed
     MQG_LAUNCH(ctx, "k_row_info", s, (k_row_info<PtrT, IdxT><<<tiles_of(need_dst), kBlock, 0, s>>>(row_info_args(L - 1, need_dst))));
+    SideWork<IdxT> side{};                                 // what the next sampling launch does for the block before
     for (int l = L - 1; l >= 0; --l) {
         mqg_block &b = blocks[l];
         const int k = fanouts[l];
@@ -1374,14 +1492,19 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
         const int64_t need_nnz = need_dst * k;
         const int row_tiles = tiles_of(need_dst);
         const int64_t next_dst = std::max(need_dst, std::min<int64_t>(g->num_nodes, need_dst + need_nnz));
+        // marks of this block, and the other half of the words, which the side work clears meanwhile, see k_emit_offsets
+        uint32_t *bitmap = ctx->bitmap + (self_count ? (l & 1) * ctx->bitmap_words : 0);
 
         // few tiles: every workgroup of the consumer adds up the tile sums before its own; many: one scan launch
         const int rows_scanned = row_tiles > kSelfPrefixTiles ? 1 : 0;
+        auto scan_rows = [&]() {
+            return rows_scanned ? launch_scan_tiles(ctx, ctx->tile_vals, row_tiles, nullptr, &b.sizes[2], nullptr, s, "k_scan_tiles(rows)") : int(MQG_OK);
+        };
         int rc = MQG_OK;
-        if (rows_scanned) rc = launch_scan_tiles(ctx, ctx->tile_vals, row_tiles, nullptr, &b.sizes[2], nullptr, s, "k_scan_tiles(rows)");
-        if (rc != MQG_OK) return rc;
         const int32_t *seed_flags = l == L - 1 ? ctx->heavy_count + MQG_MAX_LAYERS : nullptr;
         if (use_hash) {
+            rc = scan_rows();
+            if (rc != MQG_OK) return rc;
             if (l == L - 1) {                              // the seeds enter the table (and repeated ones are flagged) first
                 rc = hash_put_seeds(ctx, b.src_ids, g->idx_type, need_dst, b.sizes, s);   // ids as the row info checked them
                 if (rc != MQG_OK) return rc;
@@ -1398,25 +1521,36 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
         a.nbr = nbr;
         a.local_of = local_of;
         a.pos_base = pos_base;
-        a.bitmap = ctx->bitmap;
+        a.bitmap = bitmap;
         a.layer_hash = host_mix64(seed_hash ^ uint64_t(l));
         a.seed_dev = seed_dev;
         a.layer = l;
         a.fanout = k;
         a.force_slow = ctx->force_slow_select ? 1 : 0;
         a.heavy_degree = heavy_degree;
+        // (where the side work copies the destinations, this block's own source list is not complete yet)
+        const IdxT *dst_ids = !one_list || l == L - 1 ? src_ids : static_cast<const IdxT *>(blocks[l + 1].src_ids);
         const int hub_blocks = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, need_dst), 2048));
         // k_sample's wavefronts loop over their batches: no more workgroups than fill the chip four times
         // (the bound is often twice the number of destinations, and an idle workgroup costs a dispatch)
-        const int64_t row_blocks = std::min<int64_t>(std::max<int64_t>(1, ceil_div(need_dst, kWavesPerBlock)), ctx->prio_enabled ? int64_t(1) << 30 : 8192);
-        const int sample_grid = hub_blocks + static_cast<int>(row_blocks);
+        const int row_blocks = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(need_dst, kWavesPerBlock)), ctx->prio_enabled ? int64_t(1) << 30 : 8192));
+        if (side.relabel_blocks) {
+            side.row_tiles = row_tiles;
+            side.dst = dst_ids;
+            side.dst_count = b.sizes;
+            side.row_deg = ctx->row_deg;
+            side.row_fanout = k;
+            side.src_out = src_ids;
+            side.tile_sums = ctx->tile_vals;
+        }
+        const int sample_grid = hub_blocks + side.relabel_blocks + side.row_tiles + row_blocks;
         if (ctx->prio_enabled) {
             MQG_LAUNCH(ctx, "k_sample_prio", s,
-                       (k_sample_prio<IdxT><<<sample_grid, kBlock, 0, s>>>(col_idx, src_ids, a, ctx->prio_bitmap, ctx->prio_count,
-                                                                           ctx->heavy_rows, ctx->heavy_count + l, hub_blocks)));
+                       (k_sample_prio<IdxT><<<sample_grid, kBlock, 0, s>>>(col_idx, dst_ids, a, ctx->prio_bitmap, ctx->prio_count,
+                                                                           hub_list(l), hub_blocks, side)));
         } else {
             MQG_LAUNCH(ctx, "k_sample", s,
-                       (k_sample<IdxT><<<sample_grid, kBlock, 0, s>>>(col_idx, src_ids, a, ctx->heavy_rows, ctx->heavy_count + l, hub_blocks)));
+                       (k_sample<IdxT><<<sample_grid, kBlock, 0, s>>>(col_idx, dst_ids, a, hub_list(l), hub_blocks, row_blocks, side)));
         }
 
         if (use_hash) {
@@ -1427,47 +1561,62 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
             if (l > 0) MQG_LAUNCH(ctx, "k_row_info", s, (k_row_info<PtrT, IdxT><<<tiles_of(need_dst), kBlock, 0, s>>>(row_info_args(l - 1, need_dst))));
             continue;
         }
+        rc = scan_rows();
+        if (rc != MQG_OK) return rc;
         // num_src = num_dst + number of new nodes; it is also the next block's num_dst
         int64_t *next_num_dst = l > 0 ? &blocks[l - 1].sizes[0] : nullptr;
+        const NewRows<PtrT> next{l > 0 && one_list ? row_ptr : nullptr, ctx->row_start, ctx->row_deg, hub_list(l)};
         if (self_count) {
             // indptr from the row tile sums and the new sources from the bitmap, one launch
             MQG_LAUNCH(ctx, "k_emit_offsets", s,
-                       (k_emit_offsets<IdxT><<<bitmap_tiles + row_tiles, kBlock, 0, s>>>(ctx->bitmap, bitmap_tiles, b.sizes, next_num_dst, src_ids,
-                                                                                        ctx->local_of, pos_base, ctx->row_deg, k, ctx->tile_vals, rows_scanned,
-                                                                                        b.indptr, seed_flags, row_tiles)));
+                       (k_emit_offsets<PtrT, IdxT><<<bitmap_tiles + row_tiles, kBlock, 0, s>>>(bitmap, bitmap_tiles, b.sizes, next_num_dst, src_ids,
+                                                                                              ctx->local_of, pos_base, ctx->row_deg, k, ctx->tile_vals, rows_scanned,
+                                                                                              b.indptr, seed_flags, row_tiles, next)));
         } else {
             // indptr from the row tile sums, and the bitmap's tile popcounts
             if (bitmap_wpt == 1) {
                 MQG_LAUNCH(ctx, "k_offsets_count", s,
                            (k_offsets_count<1><<<row_tiles + bitmap_tiles, kBlock, 0, s>>>(ctx->row_deg, k, b.sizes, ctx->tile_vals, rows_scanned, b.indptr,
-                                                                                          seed_flags, row_tiles, ctx->bitmap, ctx->bitmap_tile_vals)));
+                                                                                          seed_flags, row_tiles, bitmap, ctx->bitmap_tile_vals)));
             } else {
                 MQG_LAUNCH(ctx, "k_offsets_count", s,
                            (k_offsets_count<4><<<row_tiles + bitmap_tiles, kBlock, 0, s>>>(ctx->row_deg, k, b.sizes, ctx->tile_vals, rows_scanned, b.indptr,
-                                                                                          seed_flags, row_tiles, ctx->bitmap, ctx->bitmap_tile_vals)));
+                                                                                          seed_flags, row_tiles, bitmap, ctx->bitmap_tile_vals)));
             }
             const int bits_scanned = bitmap_tiles > kSelfPrefixTiles ? 1 : 0;
             if (bits_scanned) rc = launch_scan_tiles(ctx, ctx->bitmap_tile_vals, bitmap_tiles, &b.sizes[0], &b.sizes[1], next_num_dst, s, "k_scan_tiles(bitmap)");
             if (rc != MQG_OK) return rc;
             if (bitmap_wpt == 1) {
                 MQG_LAUNCH(ctx, "k_bitmap_emit", s,
-                           (k_bitmap_emit1<IdxT><<<bitmap_tiles, kBlock, 0, s>>>(ctx->bitmap, ctx->bitmap_tile_vals, bits_scanned, b.sizes, next_num_dst, src_ids, ctx->local_of, pos_base)));
+                           (k_bitmap_emit1<PtrT, IdxT><<<bitmap_tiles, kBlock, 0, s>>>(bitmap, ctx->bitmap_tile_vals, bits_scanned, b.sizes, next_num_dst, src_ids, ctx->local_of, pos_base, next)));
             } else {
                 MQG_LAUNCH(ctx, "k_bitmap_emit", s,
-                           (k_bitmap_emit4<IdxT><<<bitmap_tiles, kBlock, 0, s>>>(ctx->bitmap, ctx->bitmap_tile_vals, bits_scanned, b.sizes, next_num_dst, src_ids, ctx->local_of, pos_base)));
+                           (k_bitmap_emit4<IdxT><<<bitmap_tiles, kBlock, 0, s>>>(bitmap, ctx->bitmap_tile_vals, bits_scanned, b.sizes, next_num_dst, src_ids, ctx->local_of, pos_base)));
             }
         }
         const int relabel_grid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(need_nnz, kBlock)), 4096));
-        need_dst = next_dst;
-        if (l > 0) {
+        uint32_t *clear = self_count ? bitmap : nullptr;
+        if (l > 0 && !one_list) {
             MQG_LAUNCH(ctx, "k_relabel_rowinfo", s,
-                       (k_relabel_rowinfo<PtrT, IdxT><<<relabel_grid + tiles_of(need_dst), kBlock, 0, s>>>(nbr, b.sizes, b.indptr, k, ctx->local_of, pos_base, b.indices,
-                                                                                                          relabel_grid, row_info_args(l - 1, need_dst),
-                                                                                                          self_count ? ctx->bitmap : nullptr, ctx->bitmap_words)));
+                       (k_relabel_rowinfo<PtrT, IdxT><<<relabel_grid + tiles_of(next_dst), kBlock, 0, s>>>(nbr, b.sizes, b.indptr, k, ctx->local_of, pos_base, b.indices,
+                                                                                                          relabel_grid, row_info_args(l - 1, next_dst))));
+        } else if (l > 0) {
+            side.relabel_blocks = relabel_grid;
+            side.nbr = nbr;
+            side.sizes = b.sizes;
+            side.indptr = b.indptr;
+            side.fanout = k;
+            side.local_of = ctx->local_of;
+            side.pos_base = pos_base;
+            side.indices = b.indices;
+            side.clear = clear;
+            side.nclear = ctx->bitmap_words;
         } else {
             MQG_LAUNCH(ctx, "k_relabel", s, (k_relabel<<<relabel_grid, kBlock, 0, s>>>(nbr, b.sizes, b.indptr, k, ctx->local_of, pos_base, b.indices,
-                                                                                       self_count ? ctx->bitmap : nullptr, ctx->bitmap_words, ctx->heavy_count)));
+                                                                                       clear, ctx->bitmap_words, ctx->heavy_count)));
         }
+        nbr += need_nnz;                                   // the next block is sampled while this one's are relabelled
+        need_dst = next_dst;
     }
     if (take_back) {
         int grid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(need_dst, kBlock)), 4096));

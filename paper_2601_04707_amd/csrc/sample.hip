@@ -462,9 +462,10 @@ __device__ __forceinline__ uint32_t key_limit(int expect, int d, uint32_t gap) {
 }
 
 // The slots of a row of d whose keys lie below limit, as candidates in `out` in slot order; returns their number (more than
-// the list's `cap`, a power of two: not all are there).  LONG: a wavefront's share of a long row, kHubChunks * 64 slots from
-// `begin` on, `stride` apart, most of which have few candidates or none in 64.  Otherwise a row of less than 2^30.
+// the list's `cap`, a power of two: not all are there).  row_candidates: of a row of up to 2^30.  hub_candidates: a wavefront's
+// share of a long row, every fourth part of CHUNKS * 64 slots, most of which have few candidates or none in 64.
 constexpr int kHubChunks = 4;
+constexpr int kHubChunksFrom = 16 * kHubChunks * kWave;    // slots, four parts per wavefront; of shorter rows one would hold too large a share (2,300 slots 99 -> 106 us)
 template <bool EMPTY>
 __device__ __forceinline__ void keep_candidates(uint32_t z, int slot, bool c, Candidate *out, int cap, int &cnt) {
     const uint64_t m = ballot64(c);
@@ -486,27 +487,29 @@ __device__ __forceinline__ int row_candidates(uint32_t low, uint32_t hi_term, in
     }
     return cnt;
 }
-__device__ __forceinline__ int hub_candidates(uint64_t hv, int d, uint32_t limit, uint32_t begin, uint32_t stride, Candidate *out, int cap) {
+template <int CHUNKS>
+__device__ __forceinline__ int hub_candidates(uint64_t hv, int d, uint32_t limit, int wave, Candidate *out, int cap) {
+    constexpr uint32_t kPart = CHUNKS * kWave, kStride = kPart * kWavesPerBlock;
     const uint32_t above = limit << 1;
     const int lane = lane_id();
     int cnt = 0;
     for (uint32_t range = 0; range < static_cast<uint32_t>(d); range += 0x40000000u) {
-        const WaveKeys<kHubChunks> keys(__builtin_amdgcn_readfirstlane(key_low(hv, range)), __builtin_amdgcn_readfirstlane(key_hi_term(hv)));
+        const WaveKeys<CHUNKS> keys(__builtin_amdgcn_readfirstlane(key_low(hv, range)), __builtin_amdgcn_readfirstlane(key_hi_term(hv)));
         const uint32_t end = static_cast<uint32_t>(d) - range < 0x40000000u ? static_cast<uint32_t>(d) : range + 0x40000000u;
-        uint32_t base = range + begin;
-        for (; base + kHubChunks * kWave <= end; base += stride) {
+        uint32_t base = range + wave * kPart;
+        for (; base + kPart <= end; base += kStride) {
             const uint64_t part = keys.row_part(base);
-            uint32_t z[kHubChunks];
+            uint32_t z[CHUNKS];
 #pragma unroll
-            for (int u = 0; u < kHubChunks; ++u) z[u] = keys.upper(part, u);
+            for (int u = 0; u < CHUNKS; ++u) z[u] = keys.upper(part, u);
 #pragma unroll
-            for (int u = 0; u < kHubChunks; ++u)
+            for (int u = 0; u < CHUNKS; ++u)
                 keep_candidates<true>(z[u], static_cast<int>(base + u * kWave) + lane, z[u] < above, out, cap, cnt);
         }
         if (base < end) {
             const uint64_t part = keys.row_part(base);
 #pragma unroll
-            for (int u = 0; u < kHubChunks; ++u) {
+            for (int u = 0; u < CHUNKS; ++u) {
                 if (base + u * kWave >= end) break;
                 const uint32_t z = keys.upper(part, u);
                 keep_candidates<true>(z, static_cast<int>(base + u * kWave) + lane, z < above && base + u * kWave + lane < end, out, cap, cnt);
@@ -715,8 +718,9 @@ __device__ __forceinline__ void sample_hubs(const IdxT *__restrict__ col_idx, co
         const uint64_t hv = readlane64(mix64(layer_hash ^ uint64_t(dst_ids[row])), 0);
         Candidate *cand = lds.cand[turn & 1];
         const uint32_t gap = __builtin_amdgcn_readfirstlane(key_gap(d));
-        const int mine = hub_candidates(hv, d, key_limit(k + (k < 16 ? k + 32 : 48), d, gap), wave * kHubChunks * kWave, kHubChunks * kBlock,
-                                        cand + wave * kWave, kWave);
+        const uint32_t limit = key_limit(k + (k < 16 ? k + 32 : 48), d, gap);
+        const int mine = d >= kHubChunksFrom ? hub_candidates<kHubChunks>(hv, d, limit, wave, cand + wave * kWave, kWave)
+                                             : hub_candidates<1>(hv, d, limit, wave, cand + wave * kWave, kWave);
         if (lane == 0) counts[turn & 1][wave] = mine;
         __syncthreads();
         if (wave != (turn & 3)) continue;

@@ -430,9 +430,11 @@ int mqg_select_smallest_keys(mqg_ctx *ctx, const uint64_t *keys_dev, int64_t n, 
  * Sec. III-A: s_node neighbours of a node drawn uniformly, here the k smallest
  * random keys): among `count` candidates, each a (key, slot word) pair, the k
  * first in the order (bit 31 of the slot word if `prioritised`, key, low 31
- * bits of the slot word) are chosen - the binary radix select on wavefront
- * ballots that the sampling kernels run after their threshold pass, exposed
- * so that a test can feed it keys with ties.
+ * bits of the slot word) are chosen.  Not prioritised, by the bound on the
+ * keys' upper 31 bits that the sampling kernels look for; where there is none
+ * (there they take the k smallest one after the other), and prioritised, by a
+ * binary radix select on wavefront ballots.  Exposed so that a test can feed it
+ * keys with ties.
  *   keys_dev, slot_words_dev  device [count], 1 <= k <= count <= 256
  *   ordered         non-zero: the candidates are stored in ascending slot
  *                   order (as the one-wavefront-per-row path stores them), so

@@ -134,7 +134,7 @@ __device__ __forceinline__ uint32_t word_bound(const uint32_t (&w)[NCH], int k, 
     uint32_t t = gap / 2 + static_cast<uint32_t>(k) * gap;
     for (int tries = 0; tries < 10; ++tries) {
         const int more = k - below(t);
-        if (more == 0) return t <= kNoWord ? t : 0;        // (past the end all lanes lie below)
+        if (more == 0) return t <= kNoWord ? t : below(kNoWord) == k ? kNoWord : 0;       // (past the end all lanes lie below)
         t += static_cast<uint32_t>(more) * gap;
         gap -= gap >> 2;
     }

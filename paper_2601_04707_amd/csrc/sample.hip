@@ -549,33 +549,6 @@ __device__ __forceinline__ void select_candidates(const uint64_t *ck, const Slot
     wave_select_smallest<NCH, PRIO, !ORDERED>(key, late, tie, cand, k, sel, top);
 }
 
-// The same for candidates in ascending slot order, emitted as the row's neighbours.
-template <int NCH, bool PRIO, typename IdxT, typename SlotT>
-__device__ __forceinline__ void emit_selected(const uint64_t *ck, const SlotT *cs, int cnt, int k,
-                                              const IdxT *__restrict__ col_idx, int64_t start, int32_t out_base,
-                                              const SampleArgs &a) {
-    const int lane = lane_id();
-    uint32_t slot[NCH];
-    uint64_t sel[NCH];
-    select_candidates<NCH, PRIO, true>(ck, cs, cnt, k, slot, sel);
-    int out_pos = out_base;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        if ((sel[c] >> lane) & 1)
-            emit_neighbour(col_idx, start, static_cast<int>(slot[c] & 0x7FFFFFFFu),
-                           out_pos + popc64(sel[c] & lanes_below(lane)), a);
-        out_pos += popc64(sel[c]);
-    }
-}
-template <bool PRIO, typename IdxT, typename SlotT>
-__device__ __forceinline__ void emit_selected_any(const uint64_t *ck, const SlotT *cs, int cnt, int k,
-                                                  const IdxT *__restrict__ col_idx, int64_t start, int32_t out_base,
-                                                  const SampleArgs &a) {
-    if (cnt <= kWave) emit_selected<1, PRIO>(ck, cs, cnt, k, col_idx, start, out_base, a);
-    else if (cnt <= 2 * kWave) emit_selected<2, PRIO>(ck, cs, cnt, k, col_idx, start, out_base, a);
-    else emit_selected<kCandidates / kWave, PRIO>(ck, cs, cnt, k, col_idx, start, out_base, a);
-}
-
 // The chosen of candidates that are in no particular order: their slots are listed in sel_slot (LDS, 64
 // entries) and emitted in ascending order.
 template <int NCH, typename IdxT>
@@ -598,21 +571,8 @@ __device__ __forceinline__ void emit_by_slot(const uint32_t (&slot)[NCH], const 
     if (lane < k) emit_neighbour(col_idx, start, my_slot, out_base + rank, a);
 }
 
-// Hub rows of the prioritised sampling: the candidates sit in LDS in arrival order.
-template <bool PRIO, typename IdxT, typename SlotT>
-__device__ __forceinline__ void emit_selected_unordered(const uint64_t *ck, const SlotT *cs, int cnt, int k,
-                                                        int32_t *sel_slot, const IdxT *__restrict__ col_idx,
-                                                        int64_t start, int32_t out_base, const SampleArgs &a) {
-    constexpr int NCH = kCandidates / kWave;
-    uint32_t slot[NCH];
-    uint64_t sel[NCH];
-    select_candidates<NCH, PRIO, false>(ck, cs, cnt, k, slot, sel);
-    emit_by_slot<NCH>(slot, sel, k, sel_slot, col_idx, start, out_base, a);
-}
-
-// The per-row selection on caller-supplied candidates (mqg_select_row_candidates): one wavefront, the same code as in
-// k_sample_prio after its threshold pass, or, not prioritised, the bound on the keys' upper words that k_sample looks for
-// and, where there is none, the selection by whole keys.
+// The per-row selection on caller-supplied candidates (mqg_select_row_candidates): one wavefront; the selection
+// by whole keys, or, not prioritised, first the bound on the keys' upper words that k_sample looks for.
 template <bool PRIO, bool ORDERED>
 __global__ void __launch_bounds__(kWave)
 k_select_candidates(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ slot_words, int cnt, int k,
@@ -685,224 +645,16 @@ __device__ void select_by_repeated_min(const IdxT *__restrict__ col_idx, int64_t
     if (lane < k) emit_neighbour(col_idx, start, my_slot, out_base + rank, a);
 }
 
-// What a wavefront keeps in LDS: the candidates of the row at hand, and the slots that its batch of rows has selected
-// (slot; row of the batch, and number among the row's slots from bit 8 on).
-struct SampleLds {
-    Candidate cand[kWavesPerBlock][kCandidates];
-    uint2 pick[kWavesPerBlock][kWave];
-    int32_t slot[kWavesPerBlock][kWave];
-};
-
-// Hubs (degree > heavy_degree, listed with the row information): the four wavefronts of a workgroup walk
-// one row together, 64 slots each in turn, each with a list of its own for 64 candidates.  About 2k + 32 are
-// expected in all, but no more than k + 48: a list that overflows, or too few candidates, costs k walks of the
-// row by one wavefront, milliseconds for a long one.  At k = 64 that is one row in 10^7 from 600 slots on, and
-// 2 in 10,000 of the short rows that only a low heavy_degree brings here; with 160 expected it was 6 in 10,000
-// (4,000 rows of 20,000 slots at k = 60: 2.3 ms instead of 0.08).  The k winners are selected by (key, slot) and then ordered by slot.  The wavefronts take
-// turns at that, while the others go on with the next hub into the second set of lists: one barrier per hub.
-template <typename IdxT>
-__device__ __forceinline__ void sample_hubs(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, const SampleArgs &a,
-                            const HubList &hubs, int first, int step, SampleLds &lds, int (&counts)[2][kWavesPerBlock]) {
-    const int nheavy = *hubs.count;
-    static_assert(kWavesPerBlock * kWave == kCandidates, "one chunk of candidates per wavefront");
-    constexpr int NCH = kWavesPerBlock;
-    const int lane = lane_id();
-    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
-    const int k = a.fanout;
-    const uint64_t layer_hash = layer_hash_of(a);
-    int turn = 0;
-    for (int h = first; h < nheavy; h += step, ++turn) {   // the same for all four
-        const int row = __builtin_amdgcn_readfirstlane(hubs.rows[h]);
-        const int64_t start = a.row_start[row];
-        const int d = __builtin_amdgcn_readfirstlane(a.row_deg[row]);
-        const uint64_t hv = readlane64(mix64(layer_hash ^ uint64_t(dst_ids[row])), 0);
-        Candidate *cand = lds.cand[turn & 1];
-        const uint32_t gap = __builtin_amdgcn_readfirstlane(key_gap(d));
-        const uint32_t limit = key_limit(k + (k < 16 ? k + 32 : 48), d, gap);
-        const int mine = d >= kHubChunksFrom ? hub_candidates<kHubChunks>(hv, d, limit, wave, cand + wave * kWave, kWave)
-                                             : hub_candidates<1>(hv, d, limit, wave, cand + wave * kWave, kWave);
-        if (lane == 0) counts[turn & 1][wave] = mine;
-        __syncthreads();
-        if (wave != (turn & 3)) continue;
-        const int32_t out_base = out_base_of(a, row);
-        uint64_t sel[NCH];
-        uint32_t word[NCH], slot[NCH];
-        int most = 0;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            const int n = __builtin_amdgcn_readfirstlane(counts[turn & 1][c]);
-            const Candidate v = cand[c * kWave + lane];
-            word[c] = lane < n ? v.word : kNoWord;
-            slot[c] = static_cast<uint32_t>(v.slot);
-            most = n > most ? n : most;
-        }
-        const uint32_t bound = most > kWave ? 0 : word_bound(word, k, gap);
-        if (bound == 0) {                                  // a list ran over, or equal words: practically never
-            select_by_repeated_min(col_idx, start, d, k, hv, out_base, a);
-            continue;
-        }
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) sel[c] = ballot64(word[c] < bound);
-        emit_by_slot<NCH>(slot, sel, k, lds.slot[wave], col_idx, start, out_base, a);
-    }
-}
-
-static_assert(kCandidates % kWave == 0, "candidates are selected in chunks of one per lane");
-
-// The slots of the lanes with `in`, of row r of the batch, appended to the batch's list.
-__device__ __forceinline__ int push_slots(bool in, int slot, int r, int held, int before, uint2 *pick) {
-    const uint64_t m = ballot64(in);
-    if (in) {
-        const int p = rank_below(m, before);
-        pick[held + p] = make_uint2(static_cast<uint32_t>(slot), static_cast<uint32_t>(r | p << 8));
-    }
-    return before + popc64(m);
-}
-// The k smallest of a row's candidates; false if that takes more than their words.
-template <int NCH>
-__device__ __forceinline__ bool push_smallest(const Candidate *cand, int cnt, int k, uint32_t gap, int r, int held, uint2 *pick) {
-    const int lane = lane_id();
-    uint32_t word[NCH];
-    int slot[NCH];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        const Candidate v = cand[c * kWave + lane];
-        word[c] = c * kWave + lane < cnt ? v.word : kNoWord;
-        slot[c] = v.slot;
-    }
-    const uint32_t bound = word_bound(word, k, gap);
-    if (bound == 0) return false;
-    int n = 0;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) n = push_slots(word[c] < bound, slot[c], r, held, n, pick);
-    return true;
-}
-
-// The first hub_blocks workgroups take the hubs (they are dispatched first and run the longest; 1,024 of them
-// instead of 2,048: 10 % slower where hubs hold most of the slots); the others' wavefronts take batches of
-// consecutive destinations, as many as leave a batch for every wavefront of the chip and select at most 64
-// slots: their row information is loaded by one instruction, and their neighbours' ids, positions and
-// marks - a chain of three dependent accesses - are fetched once for all.
-// Bound by instruction issue, vector and scalar alike (stress: 35 M and 41 M instructions in 114 us): hence eight
-// wavefronts per SIMD, which takes a bound on the registers (without it 106 scalar registers leave room for seven: the three
-// sampling cases 2 to 7 % slower), candidates of half a word of the key, the k smallest of them by a bound (word_bound), and
-// divisions made once per batch, in its lanes.  92 M keys of 43 k rows (graph of 111 M nodes), ten vector instructions
-// per 64 keys, three of them quarter-rate multiplications: 80 -> 61 us; 23 M keys of 10 k rows 32 -> 24; 65 M keys
-// of 284 k rows 147 -> 114, of 44 k rows 45 -> 34.  While a batch is selected, the row information of the next one and the
-// neighbours of the last two are on their way (4 us of the 147).
-template <typename IdxT>
-__global__ void __launch_bounds__(kBlock, 8)
-k_sample(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, SampleArgs a,
-         HubList hubs, int hub_blocks, int row_blocks, SideWork<IdxT> side) {
-    __shared__ SampleLds lds;
-    __shared__ int counts[2][kWavesPerBlock];
-    if (static_cast<int>(blockIdx.x) < hub_blocks) {
-        sample_hubs(col_idx, dst_ids, a, hubs, static_cast<int>(blockIdx.x), hub_blocks, lds, counts);
-        return;
-    }
-    const int row_block = static_cast<int>(blockIdx.x) - hub_blocks - (side.relabel_blocks + side.row_tiles);
-    if (row_block < 0) {
-        side_work(side, static_cast<int>(blockIdx.x) - hub_blocks, counts[0]);
-        return;
-    }
-    const int lane = lane_id();
-    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
-    const int64_t n = a.sizes[0];
-    const int k = a.fanout;
-    const int64_t share = n / kBusyWaves;
-    const int most = kWave / k < kBatchRows ? kWave / k : kBatchRows;
-    const int batch = share < 1 ? 1 : share < most ? static_cast<int>(share) : most;
-    const int64_t step = int64_t(row_blocks) * kWavesPerBlock * batch;
-    const int first_expect = k + 4 * static_cast<int>(__builtin_sqrtf(static_cast<float>(k))) + 8;     // candidates wanted of a long row
-    const uint64_t layer_hash = layer_hash_of(a);
-    Candidate *cand = lds.cand[wave];
-    uint2 *pick = lds.pick[wave];
-    const int64_t first_row = (int64_t(row_block) * kWavesPerBlock + wave) * batch;
-    if (first_row >= n) return;
-    // row information of the batch at hand, one row per lane, loaded a batch ahead
-    auto row_of_lane = [&](int64_t row0) {
-        const int64_t last = n - 1;
-        const int64_t r = row0 + (lane < batch ? lane : 0);
-        return r < n ? r : last;
-    };
-    int64_t next_start;
-    int next_deg;
-    IdxT next_node;
-    {
-        const int64_t r = row_of_lane(first_row);
-        next_start = a.row_start[r];
-        next_deg = a.row_deg[r];
-        next_node = dst_ids[r];
-    }
-    // neighbours on their way: ids of the batch before, positions of the one before that
-    NeighbourPipe<IdxT> pipe(a);
-    for (int64_t row0 = first_row; row0 < n; row0 += step) {
-        const int m = n - row0 < batch ? static_cast<int>(n - row0) : batch;
-        const int64_t my_row = row_of_lane(row0);
-        const int64_t my_start = next_start;
-        const int my_deg = next_deg;
-        const int32_t my_out = out_base_of(a, my_row);
-        const uint64_t my_hv = mix64(layer_hash ^ uint64_t(next_node));
-        {
-            const int64_t r = row_of_lane(row0 + step);
-            next_start = a.row_start[r];
-            next_deg = a.row_deg[r];
-            next_node = dst_ids[r];
-        }
-        const uint32_t my_gap = key_gap(my_deg), my_low = key_low(my_hv), my_hi_term = key_hi_term(my_hv);
-        int held = 0;                                      // slots selected so far
-        for (int r = 0; r < m; ++r) {
-            const int d = static_cast<int>(readlane32(static_cast<uint32_t>(my_deg), r));
-            if (d > a.heavy_degree && d > k) continue;     // a hub: sampled by the first workgroups
-            if (d <= k) {                                  // the whole row, no randomness
-                held += push_slots(lane < d, lane, r, held, 0, pick);
-                continue;
-            }
-            const uint32_t gap = readlane32(my_gap, r), low = readlane32(my_low, r), hi_term = readlane32(my_hi_term, r);
-            bool done = false;
-            if (d <= kWave) {                              // one key per lane
-                const uint32_t x = low ^ static_cast<uint32_t>(lane);
-                const uint32_t z = key_upper(uint64_t(x) * RowKeys::kC1Lo + (uint64_t(x * RowKeys::kC1Hi + hi_term) << 32));
-                const uint32_t word[1] = {lane < d ? z >> 1 : kNoWord};
-                const uint32_t bound = a.force_slow ? 0 : word_bound(word, k, gap);
-                done = bound != 0;
-                if (done) (void)push_slots(word[0] < bound, lane, r, held, 0, pick);
-            } else if (!a.force_slow) {
-                // Longer rows: the slots whose keys lie under a limit are candidates, stored in ascending slot order; too
-                // few (3 rows in 100,000): again with a higher one.
-                int cnt = row_candidates(low, hi_term, d, key_limit(first_expect, d, gap), cand, kCandidates);
-                if (cnt < k) cnt = row_candidates(low, hi_term, d, key_limit(2 * first_expect + 32, d, gap), cand, kCandidates);
-                wave_lds_sync();
-                if (cnt < k || cnt > kCandidates) done = false;
-                else if (cnt <= kWave) done = push_smallest<1>(cand, cnt, k, gap, r, held, pick);
-                else if (cnt <= 2 * kWave) done = push_smallest<2>(cand, cnt, k, gap, r, held, pick);
-                else done = push_smallest<kCandidates / kWave>(cand, cnt, k, gap, r, held, pick);
-                wave_lds_sync();                           // the candidates' place is the next row's
-            }
-            if (done) {
-                held += k;
-            } else {
-                select_by_repeated_min(col_idx, static_cast<int64_t>(readlane64(static_cast<uint64_t>(my_start), r)), d, k, readlane64(my_hv, r),
-                                       static_cast<int32_t>(readlane32(static_cast<uint32_t>(my_out), r)), a);
-            }
-        }
-        wave_lds_sync();
-        const uint2 mine = pick[lane];
-        const int of = lane < held ? static_cast<int>(mine.y & 0xFF) : 0;
-        const int64_t slot_pos = __shfl(my_start, of, kWave) + static_cast<int32_t>(mine.x);
-        const int32_t out_pos = __shfl(my_out, of, kWave) + static_cast<int32_t>(mine.y >> 8);
-        pipe.push(col_idx, lane < held, slot_pos, out_pos);
-        wave_lds_sync();                                   // pick is the next batch's
-    }
-    pipe.drain();
-}
-
 // ------------------------------------------------------------------------------------------
 // Cache-prioritised selection (the paper's Sec. I on global neighbour sampling: neighbours that are
 // in the feature cache are preferred, so that fewer distinct uncached rows enter a mini-batch).
 // The k slots of a row are the first k in the order (not cached, key, slot): with c cached
 // neighbours the row keeps min(k, c) of them, drawn uniformly, and fills up from the uncached ones,
-// drawn uniformly.  `prio` is a bitmap over the nodes, bit set = cached.
+// drawn uniformly.  `prio` is a bitmap over the nodes, bit set = cached; prio_count tabulates c.
+struct PrioArgs {
+    const uint32_t *prio;
+    const int32_t *prio_count;
+};
 
 __device__ __forceinline__ bool prio_less(bool ua, uint64_t ka, int sa, bool ub, uint64_t kb, int sb) {
     return ua != ub ? !ua : pair_less(ka, sa, kb, sb);
@@ -966,184 +718,327 @@ __device__ void select_by_repeated_min_prio(const IdxT *__restrict__ col_idx, in
     if (lane < k) emit_neighbour(col_idx, start, my_slot, out_base + rank, a);
 }
 
-// Candidate test shared by both shapes of the prioritised kernel: which pool competes and under
-// which key threshold (about 2k+32 candidates are expected to pass).
-struct PrioRule {
-    bool only_cached;        // at least k cached neighbours: only they compete
-    uint64_t thr;
-    __device__ __forceinline__ PrioRule(int d, int k, int cached) {
-        only_cached = cached >= k;
-        const int pool = only_cached ? cached : d - cached;
-        const int expect = 2 * (only_cached ? k : k - cached) + 32;
-        thr = kMaxKey;
-        if (pool > expect) thr = static_cast<uint64_t>((double(expect) / double(pool)) * 18446744073709551616.0);
-    }
-    __device__ __forceinline__ bool operator()(bool is_cached_slot, uint64_t key) const {
-        return only_cached ? (is_cached_slot && key <= thr) : (is_cached_slot || key <= thr);
+// Which of a row's d slots compete for how many of its k places: without priority all of them; with at least k cached
+// ones these, and only they are looked for; otherwise the uncached ones, for what the cached ones leave.
+struct Contest {
+    bool cached;                 // the competing slots are the cached ones
+    int want, pool;              // places and competitors
+    __device__ __forceinline__ Contest(bool prio, int d, int k, int c) {
+        cached = prio && c >= k;
+        want = prio && !cached ? k - c : k;
+        pool = !prio ? d : cached ? c : d - c;
     }
 };
 
+// (Every slot was looked up, by k_sample's rules before: a mini-batch of 8,192 seeds on 300 k nodes of 300 neighbours, one in five cached,
+// 536 -> 272 us, of 1,024 on 1 M nodes of 50 267 -> 133: the keys are cheap, a look-up is two dependent random accesses.)
+// Candidates of a row with cached neighbours, from the slots first + lane, first + stride + lane, ... on (multiples of 64), in slot
+// order; bit 31 of the slot says that it is not cached.  Only cached ones: a slot whose key is not below the limit is not looked
+// up.  Otherwise every slot is, and the cached ones are candidates whatever their keys.
 constexpr int kPrioUnroll = 4;   // chunks of 64 slots whose loads are issued together
-
-// Hubs: the four wavefronts of a workgroup share one row, as in sample_hubs.
 template <typename IdxT>
-__device__ void sample_hubs_prio(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, const SampleArgs &a,
-                                 const uint32_t *__restrict__ prio, const int32_t *__restrict__ prio_count,
-                                 const HubList &hubs, int first, int step,
-                                 uint64_t *ck, uint32_t *cs, int32_t *sel_slot, int *cnt_s) {
-    const int tid = threadIdx.x;
-    const int lane = lane_id();
-    const int wave = tid >> 6;
-    const int k = a.fanout;
+__device__ __forceinline__ int prio_candidates(uint64_t hv, const IdxT *__restrict__ row, int d, uint32_t limit, bool only_cached,
+                                               const uint32_t *__restrict__ prio, int first, int stride, Candidate *out, int cap) {
+    const uint32_t above = limit << 1;
+    const uint32_t lane = static_cast<uint32_t>(lane_id());
+    int cnt = 0;
+    for (uint32_t range = 0; range < static_cast<uint32_t>(d); range += 0x40000000u) {
+        const WaveKeys<1> keys(__builtin_amdgcn_readfirstlane(key_low(hv, range)), __builtin_amdgcn_readfirstlane(key_hi_term(hv)));
+        const uint32_t end = static_cast<uint32_t>(d) - range < 0x40000000u ? static_cast<uint32_t>(d) : range + 0x40000000u;
+        for (uint32_t base = range + first; base < end; base += kPrioUnroll * stride) {
+            uint32_t z[kPrioUnroll], u[kPrioUnroll], bits[kPrioUnroll];
+            bool look[kPrioUnroll];
+#pragma unroll
+            for (int q = 0; q < kPrioUnroll; ++q) {
+                z[q] = keys.upper(keys.row_part(base + q * stride));
+                look[q] = base + q * stride + lane < end && (!only_cached || z[q] < above);
+                u[q] = bits[q] = 0;
+            }
+#pragma unroll
+            for (int q = 0; q < kPrioUnroll; ++q)
+                if (look[q]) u[q] = static_cast<uint32_t>(row[base + q * stride + lane]);
+#pragma unroll
+            for (int q = 0; q < kPrioUnroll; ++q)
+                if (look[q]) bits[q] = prio[u[q] >> 5];
+#pragma unroll
+            for (int q = 0; q < kPrioUnroll; ++q) {
+                const bool hit = (bits[q] >> (u[q] & 31)) & 1u;                // (not looked up: no bits)
+                const uint32_t slot = base + q * stride + lane;
+                keep_candidates<true>(z[q], static_cast<int>(slot | (hit ? 0u : 0x80000000u)), only_cached ? hit : hit || (look[q] && z[q] < above),
+                                      out, cap, cnt);
+            }
+        }
+    }
+    return cnt;
+}
+
+// What a wavefront keeps in LDS: the candidates of the row at hand, and the slots that its batch of rows has selected
+// (slot; row of the batch, and number among the row's slots from bit 8 on).
+struct SampleLds {
+    Candidate cand[kWavesPerBlock][kCandidates];
+    uint2 pick[kWavesPerBlock][kWave];
+    int32_t slot[kWavesPerBlock][kWave];
+};
+
+// Hubs (degree > heavy_degree, listed with the row information): the four wavefronts of a workgroup walk
+// one row together, 64 slots each in turn, each with a list of its own for 64 candidates.  About 2k + 32 are
+// expected in all, but no more than k + 48: a list that overflows, or too few candidates, costs k walks of the
+// row by one wavefront, milliseconds for a long one.  At k = 64 that is one row in 10^7 from 600 slots on, and
+// 2 in 10,000 of the short rows that only a low heavy_degree brings here; with 160 expected it was 6 in 10,000
+// (4,000 rows of 20,000 slots at k = 60: 2.3 ms instead of 0.08).  The k winners are selected by (key, slot) and then ordered by slot.  The wavefronts take
+// turns at that, while the others go on with the next hub into the second set of lists: one barrier per hub.
+// With priority the cached slots, which may lie close together, are candidates without a limit: lists for 256 each, one set of them.
+template <typename IdxT, bool PRIO>
+__device__ __forceinline__ void sample_hubs(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, const SampleArgs &a,
+                            const PrioArgs &pa, const HubList &hubs, int first, int step, SampleLds &lds, int (&counts)[2][kWavesPerBlock]) {
     const int nheavy = *hubs.count;
-    for (int h = first; h < nheavy; h += step) {
-        const int row = hubs.rows[h];
+    static_assert(kWavesPerBlock * kWave == kCandidates, "one chunk of candidates per wavefront");
+    constexpr int NCH = kWavesPerBlock;
+    constexpr int kList = PRIO ? kCandidates : kWave;
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    const int k = a.fanout;
+    const uint64_t layer_hash = layer_hash_of(a);
+    int turn = 0;
+    for (int h = first; h < nheavy; h += step, ++turn) {   // the same for all four
+        const int row = __builtin_amdgcn_readfirstlane(hubs.rows[h]);
         const int64_t start = a.row_start[row];
-        const int d = a.row_deg[row];
-        const int32_t out_base = out_base_of(a, row);
+        const int d = __builtin_amdgcn_readfirstlane(a.row_deg[row]);
         const IdxT node = dst_ids[row];
-        const uint64_t hv = mix64(layer_hash_of(a) ^ uint64_t(node));
-        const RowKeys key_of(hv);
-        const IdxT *nbrs = col_idx + start;
-        const PrioRule rule(d, k, prio_count[node]);
-        if (tid == 0) *cnt_s = 0;
+        const uint64_t hv = readlane64(mix64(layer_hash ^ uint64_t(node)), 0);
+        const int c_row = PRIO ? __builtin_amdgcn_readfirstlane(pa.prio_count[node]) : 0;
+        const Contest contest(PRIO, d, k, c_row);
+        Candidate *cand = &lds.cand[0][0] + (PRIO ? 0 : (turn & 1) * kCandidates);
+        const uint32_t gap = __builtin_amdgcn_readfirstlane(key_gap(contest.pool));
+        const uint32_t limit = key_limit(contest.want + (contest.want < 16 ? contest.want + 32 : 48), contest.pool, gap);
+        Candidate *list = cand + wave * kList;
+        const int mine = PRIO && c_row > 0 ? prio_candidates(hv, col_idx + start, d, limit, contest.cached, pa.prio, wave * kWave, kBlock, list, kList)
+                         : d >= kHubChunksFrom ? hub_candidates<kHubChunks>(hv, d, limit, wave, list, kList)
+                                               : hub_candidates<1>(hv, d, limit, wave, list, kList);
+        if (lane == 0) counts[turn & 1][wave] = mine;
         __syncthreads();
-        for (int base = 0; base < d; base += kPrioUnroll * kBlock) {
-            uint32_t u[kPrioUnroll], wbits[kPrioUnroll];
+        if (wave == (turn & 3)) {
+            const int32_t out_base = out_base_of(a, row);
+            uint64_t sel[NCH];
+            uint32_t word[NCH], slot[NCH], bound = 0;
+            int n[NCH], most = 0;
 #pragma unroll
-            for (int q = 0; q < kPrioUnroll; ++q) {
-                const int j = base + q * kBlock + tid;
-                u[q] = j < d ? static_cast<uint32_t>(nbrs[j]) : 0u;
+            for (int c = 0; c < NCH; ++c) {
+                n[c] = __builtin_amdgcn_readfirstlane(counts[turn & 1][c]);
+                most = n[c] > most ? n[c] : most;
             }
+            if constexpr (PRIO) {                          // the four lists end to end
+                int end[NCH];
+                end[0] = n[0];
 #pragma unroll
-            for (int q = 0; q < kPrioUnroll; ++q) wbits[q] = prio[u[q] >> 5];
+                for (int c = 1; c < NCH; ++c) end[c] = end[c - 1] + n[c];
+                bool sure[NCH];
+                const bool fits = most <= kList && end[NCH - 1] <= kCandidates;
 #pragma unroll
-            for (int q = 0; q < kPrioUnroll; ++q) {
-                const int j = base + q * kBlock + tid;
-                const bool cj = j < d && ((wbits[q] >> (u[q] & 31)) & 1u);
-                const uint64_t key = key_of(j);
-                const bool c = j < d && rule(cj, key);
-                const uint64_t m = ballot64(c);
-                if (m) {
-                    int p0 = 0;
-                    if (lane == 0) p0 = atomicAdd(cnt_s, popc64(m));
-                    p0 = __shfl(p0, 0, 64);
-                    if (c) {
-                        const int p = p0 + popc64(m & lanes_below(lane));
-                        if (p < kCandidates) {
-                            ck[p] = key;
-                            cs[p] = static_cast<uint32_t>(j) | (cj ? 0u : 0x80000000u);
-                        }
-                    }
+                for (int c = 0; c < NCH; ++c) {
+                    const int i = c * kWave + lane;
+                    const int w = (i >= end[0] ? 1 : 0) + (i >= end[1] ? 1 : 0) + (i >= end[2] ? 1 : 0);
+                    const int before = w == 0 ? 0 : w == 1 ? end[0] : w == 2 ? end[1] : end[2];
+                    const bool live = fits && i < end[NCH - 1];
+                    const Candidate v = live ? cand[w * kList + i - before] : Candidate{kNoWord, 0};
+                    const bool hit = c_row > 0 && v.slot >= 0;
+                    word[c] = live && hit == contest.cached ? v.word : kNoWord;
+                    slot[c] = static_cast<uint32_t>(v.slot);
+                    sure[c] = live && hit && !contest.cached;
                 }
+                if (fits) bound = word_bound(word, contest.want, gap);
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) sel[c] = ballot64(word[c] < bound || sure[c]);
+            } else {
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) {
+                    const Candidate v = cand[c * kWave + lane];
+                    word[c] = lane < n[c] ? v.word : kNoWord;
+                    slot[c] = static_cast<uint32_t>(v.slot);
+                }
+                if (most <= kWave) bound = word_bound(word, k, gap);
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) sel[c] = ballot64(word[c] < bound);
             }
+            if (bound != 0) emit_by_slot<NCH>(slot, sel, k, lds.slot[wave], col_idx, start, out_base, a);
+            // a list ran over, or equal words: practically never
+            else if constexpr (PRIO) select_by_repeated_min_prio(col_idx, start, d, k, hv, out_base, a, pa.prio);
+            else select_by_repeated_min(col_idx, start, d, k, hv, out_base, a);
         }
-        __syncthreads();
-        const int cnt = *cnt_s;
-        if (cnt < k || cnt > kCandidates) {                // workgroup-uniform; practically never
-            if (wave == 0) select_by_repeated_min_prio(col_idx, start, d, k, hv, out_base, a, prio);
-            __syncthreads();
-            continue;
-        }
-        if (wave == 0) emit_selected_unordered<true>(ck, cs, cnt, k, sel_slot, col_idx, start, out_base, a);
-        __syncthreads();
+        if (PRIO) __syncthreads();                         // the lists are the next hub's
     }
 }
 
-// Same launch shape as k_sample: the first hub_blocks workgroups take the hubs, every other
-// workgroup gives each of its four wavefronts one destination.
-template <typename IdxT>
-__global__ void __launch_bounds__(kBlock)
-k_sample_prio(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, SampleArgs a,
-              const uint32_t *__restrict__ prio, const int32_t *__restrict__ prio_count,
-              HubList hubs, int hub_blocks, SideWork<IdxT> side) {
-    __shared__ uint64_t cand_key[kWavesPerBlock][kCandidates];
-    __shared__ uint32_t cand_slot[kWavesPerBlock][kCandidates];   // bit 31: not cached
-    __shared__ int32_t sel_slot[kWave];
-    __shared__ int cnt_s;
+static_assert(kCandidates % kWave == 0, "candidates are selected in chunks of one per lane");
+
+// The slots of the lanes with `in`, of row r of the batch, appended to the batch's list.
+__device__ __forceinline__ int push_slots(bool in, int slot, int r, int held, int before, uint2 *pick) {
+    const uint64_t m = ballot64(in);
+    if (in) {
+        const int p = rank_below(m, before);
+        pick[held + p] = make_uint2(static_cast<uint32_t>(slot), static_cast<uint32_t>(r | p << 8));
+    }
+    return before + popc64(m);
+}
+// The `want` smallest of a row's competing candidates, and with priority those that need not compete (flagged: the candidates say
+// whether they are cached); false if that takes more than their words.
+template <int NCH, bool PRIO>
+__device__ __forceinline__ bool push_smallest(const Candidate *cand, int cnt, int want, uint32_t gap, int r, int held, uint2 *pick, bool flagged, bool cached) {
+    const int lane = lane_id();
+    uint32_t word[NCH];
+    int slot[NCH];
+    bool sure[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        const Candidate v = cand[c * kWave + lane];
+        const bool live = c * kWave + lane < cnt;
+        const bool hit = PRIO && flagged && v.slot >= 0;
+        word[c] = live && (!PRIO || hit == cached) ? v.word : kNoWord;
+        sure[c] = PRIO && live && hit && !cached;
+        slot[c] = PRIO ? v.slot & 0x7FFFFFFF : v.slot;
+    }
+    const uint32_t bound = word_bound(word, want, gap);
+    if (bound == 0) return false;
+    int n = 0;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) n = push_slots(word[c] < bound || sure[c], slot[c], r, held, n, pick);
+    return true;
+}
+
+// The first hub_blocks workgroups take the hubs (they are dispatched first and run the longest; 1,024 of them
+// instead of 2,048: 10 % slower where hubs hold most of the slots); the others' wavefronts take batches of
+// consecutive destinations, as many as leave a batch for every wavefront of the chip and select at most 64
+// slots: their row information is loaded by one instruction, and their neighbours' ids, positions and
+// marks - a chain of three dependent accesses - are fetched once for all.
+// Bound by instruction issue, vector and scalar alike (stress: 35 M and 41 M instructions in 114 us): hence eight
+// wavefronts per SIMD, which takes a bound on the registers (without it 106 scalar registers leave room for seven: the three
+// sampling cases 2 to 7 % slower), candidates of half a word of the key, the k smallest of them by a bound (word_bound), and
+// divisions made once per batch, in its lanes.  92 M keys of 43 k rows (graph of 111 M nodes), ten vector instructions
+// per 64 keys, three of them quarter-rate multiplications: 80 -> 61 us; 23 M keys of 10 k rows 32 -> 24; 65 M keys
+// of 284 k rows 147 -> 114, of 44 k rows 45 -> 34.  While a batch is selected, the row information of the next one and the
+// neighbours of the last two are on their way (4 us of the 147).
+template <typename IdxT, bool PRIO>
+__global__ void __launch_bounds__(kBlock, 8)
+k_sample(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, SampleArgs a, PrioArgs pa,
+         HubList hubs, int hub_blocks, int row_blocks, SideWork<IdxT> side) {
+    __shared__ SampleLds lds;
+    __shared__ int counts[2][kWavesPerBlock];
     if (static_cast<int>(blockIdx.x) < hub_blocks) {
-        sample_hubs_prio(col_idx, dst_ids, a, prio, prio_count, hubs, static_cast<int>(blockIdx.x),
-                         hub_blocks, cand_key[0], cand_slot[0], sel_slot, &cnt_s);
+        sample_hubs<IdxT, PRIO>(col_idx, dst_ids, a, pa, hubs, static_cast<int>(blockIdx.x), hub_blocks, lds, counts);
         return;
     }
     const int row_block = static_cast<int>(blockIdx.x) - hub_blocks - (side.relabel_blocks + side.row_tiles);
     if (row_block < 0) {
-        side_work(side, static_cast<int>(blockIdx.x) - hub_blocks, sel_slot);
+        side_work(side, static_cast<int>(blockIdx.x) - hub_blocks, counts[0]);
         return;
     }
     const int lane = lane_id();
-    const int wave = static_cast<int>(threadIdx.x) >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
     const int64_t n = a.sizes[0];
-    const int64_t row = int64_t(row_block) * kWavesPerBlock + wave;
-    if (row >= n) return;
-
-    const int64_t start = a.row_start[row];
-    const int d = a.row_deg[row];
     const int k = a.fanout;
-    const int32_t out_base = out_base_of(a, row);
-    if (d <= k) {
-        if (lane < d) emit_neighbour(col_idx, start, lane, out_base + lane, a);
-        return;
+    const int64_t share = n / kBusyWaves;
+    const int most = kWave / k < kBatchRows ? kWave / k : kBatchRows;
+    const int batch = share < 1 ? 1 : share < most ? static_cast<int>(share) : most;
+    const int64_t step = int64_t(row_blocks) * kWavesPerBlock * batch;
+    auto expected = [](int want) { return want + 4 * static_cast<int>(__builtin_sqrtf(static_cast<float>(want))) + 8; };   // candidates of a long row
+    const int first_expect = expected(k);
+    const uint64_t layer_hash = layer_hash_of(a);
+    Candidate *cand = lds.cand[wave];
+    uint2 *pick = lds.pick[wave];
+    const int64_t first_row = (int64_t(row_block) * kWavesPerBlock + wave) * batch;
+    if (first_row >= n) return;
+    // row information of the batch at hand, one row per lane, loaded a batch ahead
+    auto row_of_lane = [&](int64_t row0) {
+        const int64_t last = n - 1;
+        const int64_t r = row0 + (lane < batch ? lane : 0);
+        return r < n ? r : last;
+    };
+    int64_t next_start;
+    int next_deg;
+    IdxT next_node;
+    {
+        const int64_t r = row_of_lane(first_row);
+        next_start = a.row_start[r];
+        next_deg = a.row_deg[r];
+        next_node = dst_ids[r];
     }
-    if (d > a.heavy_degree) return;                        // a hub: sampled by the first workgroups
-    const IdxT node = dst_ids[row];
-    const uint64_t hv = mix64(layer_hash_of(a) ^ uint64_t(node));
-    if (a.force_slow) {
-        select_by_repeated_min_prio(col_idx, start, d, k, hv, out_base, a, prio);
-        return;
-    }
-    const IdxT *nbrs = col_idx + start;
-    if (d <= kWave) {
-        const bool unc = lane < d ? !is_cached(nbrs, lane, prio) : true;
-        const uint64_t key[1] = {RowKeys(hv)(lane)};
-        const uint64_t late[1] = {ballot64(unc)};
-        const uint32_t tie[1] = {0};
-        uint64_t cand[1] = {low_lanes(d)}, sel[1];
-        wave_select_smallest<1, true, false>(key, late, tie, cand, k, sel);
-        if ((sel[0] >> lane) & 1) emit_neighbour(col_idx, start, lane, out_base + popc64(sel[0] & lanes_below(lane)), a);
-        return;
-    }
-
-    // d > 64.  The number of cached neighbours of the row (tabulated when the priority was set)
-    // decides the pool the threshold applies to: with at least k of them only cached slots compete;
-    // otherwise all of them are taken and the uncached slots compete for the rest.
-    const PrioRule rule(d, k, prio_count[node]);
-    uint64_t *ck = cand_key[wave];
-    uint32_t *cs = cand_slot[wave];
-    int cnt = 0;
-    const RowKeys key_of(hv);
-    for (int base = 0; base < d; base += kPrioUnroll * kWave) {
-        uint32_t u[kPrioUnroll], wbits[kPrioUnroll];
-#pragma unroll
-        for (int q = 0; q < kPrioUnroll; ++q) {
-            const int j = base + q * kWave + lane;
-            u[q] = j < d ? static_cast<uint32_t>(nbrs[j]) : 0u;
+    // neighbours on their way: ids of the batch before, positions of the one before that
+    NeighbourPipe<IdxT> pipe(a);
+    for (int64_t row0 = first_row; row0 < n; row0 += step) {
+        const int m = n - row0 < batch ? static_cast<int>(n - row0) : batch;
+        const int64_t my_row = row_of_lane(row0);
+        const int64_t my_start = next_start;
+        const int my_deg = next_deg;
+        const int32_t my_out = out_base_of(a, my_row);
+        const uint64_t my_hv = mix64(layer_hash ^ uint64_t(next_node));
+        const int my_cached = PRIO ? pa.prio_count[next_node] : 0;
+        {
+            const int64_t r = row_of_lane(row0 + step);
+            next_start = a.row_start[r];
+            next_deg = a.row_deg[r];
+            next_node = dst_ids[r];
         }
-#pragma unroll
-        for (int q = 0; q < kPrioUnroll; ++q) wbits[q] = prio[u[q] >> 5];
-#pragma unroll
-        for (int q = 0; q < kPrioUnroll; ++q) {
-            const int j = base + q * kWave + lane;
-            const bool cj = j < d && ((wbits[q] >> (u[q] & 31)) & 1u);
-            const uint64_t key = key_of(j);
-            const bool c = j < d && rule(cj, key);
-            const uint64_t m = ballot64(c);
-            if (c) {
-                const int p = cnt + popc64(m & lanes_below(lane));
-                if (p < kCandidates) {
-                    ck[p] = key;
-                    cs[p] = static_cast<uint32_t>(j) | (cj ? 0u : 0x80000000u);
-                }
+        const Contest my_contest(PRIO, my_deg, k, my_cached);
+        const int my_expect = PRIO ? expected(my_contest.want) : 0;
+        const uint32_t my_gap = key_gap(my_contest.pool > 0 ? my_contest.pool : 1), my_low = key_low(my_hv), my_hi_term = key_hi_term(my_hv);
+        int held = 0;                                      // slots selected so far
+        for (int r = 0; r < m; ++r) {
+            const int d = static_cast<int>(readlane32(static_cast<uint32_t>(my_deg), r));
+            if (d > a.heavy_degree && d > k) continue;     // a hub: sampled by the first workgroups
+            if (d <= k) {                                  // the whole row, no randomness
+                held += push_slots(lane < d, lane, r, held, 0, pick);
+                continue;
             }
-            cnt += popc64(m);
+            const uint32_t gap = readlane32(my_gap, r), low = readlane32(my_low, r), hi_term = readlane32(my_hi_term, r);
+            const Contest contest(PRIO, d, k, PRIO ? static_cast<int>(readlane32(static_cast<uint32_t>(my_cached), r)) : 0);
+            const bool flagged = PRIO && (contest.cached || contest.want < k);             // the row has cached neighbours
+            const IdxT *nbrs = PRIO ? col_idx + static_cast<int64_t>(readlane64(static_cast<uint64_t>(my_start), r)) : nullptr;
+            bool done = false;
+            if (d <= kWave) {                              // one key per lane
+                const uint32_t x = low ^ static_cast<uint32_t>(lane);
+                const uint32_t z = key_upper(uint64_t(x) * RowKeys::kC1Lo + (uint64_t(x * RowKeys::kC1Hi + hi_term) << 32));
+                bool hit = false;
+                if (flagged && lane < d) hit = is_cached(nbrs, lane, pa.prio);
+                const uint32_t word[1] = {lane < d && (!PRIO || hit == contest.cached) ? z >> 1 : kNoWord};
+                const uint32_t bound = a.force_slow ? 0 : word_bound(word, contest.want, gap);
+                done = bound != 0;
+                if (done) (void)push_slots(word[0] < bound || (PRIO && hit && !contest.cached), lane, r, held, 0, pick);
+            } else if (!a.force_slow) {
+                // Longer rows: the slots whose keys lie under a limit are candidates, stored in ascending slot order; too
+                // few (3 rows in 100,000): again with a higher one.
+                const int expect = PRIO ? static_cast<int>(readlane32(static_cast<uint32_t>(my_expect), r)) : first_expect;
+                auto candidates = [&](int e) {
+                    const uint32_t limit = key_limit(e, contest.pool, gap);
+                    if (flagged) return prio_candidates(readlane64(my_hv, r), nbrs, d, limit, contest.cached, pa.prio, 0, kWave, cand, kCandidates);
+                    return row_candidates(low, hi_term, d, limit, cand, kCandidates);
+                };
+                int cnt = candidates(expect);
+                if (cnt < k) cnt = candidates(2 * expect + 32);
+                wave_lds_sync();
+                if (cnt < k || cnt > kCandidates) done = false;
+                else if (cnt <= kWave) done = push_smallest<1, PRIO>(cand, cnt, contest.want, gap, r, held, pick, flagged, contest.cached);
+                else if (cnt <= 2 * kWave) done = push_smallest<2, PRIO>(cand, cnt, contest.want, gap, r, held, pick, flagged, contest.cached);
+                else done = push_smallest<kCandidates / kWave, PRIO>(cand, cnt, contest.want, gap, r, held, pick, flagged, contest.cached);
+                wave_lds_sync();                           // the candidates' place is the next row's
+            }
+            if (done) {
+                held += k;
+            } else {
+                const int64_t start = static_cast<int64_t>(readlane64(static_cast<uint64_t>(my_start), r));
+                const int32_t out_base = static_cast<int32_t>(readlane32(static_cast<uint32_t>(my_out), r));
+                if constexpr (PRIO) select_by_repeated_min_prio(col_idx, start, d, k, readlane64(my_hv, r), out_base, a, pa.prio);
+                else select_by_repeated_min(col_idx, start, d, k, readlane64(my_hv, r), out_base, a);
+            }
         }
+        wave_lds_sync();
+        const uint2 mine = pick[lane];
+        const int of = lane < held ? static_cast<int>(mine.y & 0xFF) : 0;
+        const int64_t slot_pos = __shfl(my_start, of, kWave) + static_cast<int32_t>(mine.x);
+        const int32_t out_pos = __shfl(my_out, of, kWave) + static_cast<int32_t>(mine.y >> 8);
+        pipe.push(col_idx, lane < held, slot_pos, out_pos);
+        wave_lds_sync();                                   // pick is the next batch's
     }
-    if (cnt < k || cnt > kCandidates) {
-        select_by_repeated_min_prio(col_idx, start, d, k, hv, out_base, a, prio);
-        return;
-    }
-    wave_lds_sync();
-    emit_selected_any<true>(ck, cs, cnt, k, col_idx, start, out_base, a);
+    pipe.drain();
 }
 
 // prio_count[v] = number of cached neighbours of node v.  A lane owns a node; rows of up to 32 slots
@@ -1537,7 +1432,7 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
         const int hub_blocks = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, need_dst), 2048));
         // k_sample's wavefronts loop over their batches: no more workgroups than fill the chip four times
         // (the bound is often twice the number of destinations, and an idle workgroup costs a dispatch)
-        const int row_blocks = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(need_dst, kWavesPerBlock)), ctx->prio_enabled ? int64_t(1) << 30 : 8192));
+        const int row_blocks = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(need_dst, kWavesPerBlock)), 8192));
         if (side.relabel_blocks) {
             side.row_tiles = row_tiles;
             side.dst = dst_ids;
@@ -1550,11 +1445,11 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
         const int sample_grid = hub_blocks + side.relabel_blocks + side.row_tiles + row_blocks;
         if (ctx->prio_enabled) {
             MQG_LAUNCH(ctx, "k_sample_prio", s,
-                       (k_sample_prio<IdxT><<<sample_grid, kBlock, 0, s>>>(col_idx, dst_ids, a, ctx->prio_bitmap, ctx->prio_count,
-                                                                           hub_list(l), hub_blocks, side)));
+                       (k_sample<IdxT, true><<<sample_grid, kBlock, 0, s>>>(col_idx, dst_ids, a, PrioArgs{ctx->prio_bitmap, ctx->prio_count}, hub_list(l),
+                                                                            hub_blocks, row_blocks, side)));
         } else {
             MQG_LAUNCH(ctx, "k_sample", s,
-                       (k_sample<IdxT><<<sample_grid, kBlock, 0, s>>>(col_idx, dst_ids, a, hub_list(l), hub_blocks, row_blocks, side)));
+                       (k_sample<IdxT, false><<<sample_grid, kBlock, 0, s>>>(col_idx, dst_ids, a, PrioArgs{}, hub_list(l), hub_blocks, row_blocks, side)));
         }
 
         if (use_hash) {

@@ -361,6 +361,15 @@ __device__ __forceinline__ void copy_rows_flat(const Rows &rows, int64_t n, cons
     }
 }
 
+// Rows by a list of (output row, source row) whose length the host knows.
+template <typename VecT>
+__global__ void __launch_bounds__(kBlock)
+k_gather_listed(const int2 *__restrict__ list, int64_t n, const char *__restrict__ src, int64_t src_stride_bytes, char *__restrict__ dst,
+                int64_t dst_stride_bytes, int vecs, int log2_lpr, unsigned long long magic, int grid) {
+    if (magic) copy_rows_flat<VecT, false>(ListRows{list}, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, magic, static_cast<int>(blockIdx.x), grid);
+    else copy_rows<VecT, false>(ListRows{list}, n, src, src_stride_bytes, dst, dst_stride_bytes, vecs, log2_lpr, static_cast<int>(blockIdx.x), grid);
+}
+
 // One side of a gather: entries of a list, copied from src.
 struct RowSide {
     const int2 *list;
@@ -721,11 +730,27 @@ bool is_host_memory(const void *p) {
 
 }  // namespace
 
-// Rows listed by 32-bit ids straight from `src` (used by the cache build to fill the cache).
-int gather_direct_i32(mqg_ctx *ctx, const int32_t *ids, const int64_t *num_ids, int64_t cap, int64_t src_rows,
-                      const void *src, int64_t src_stride_bytes, void *dst, int64_t dst_stride_bytes, int64_t row_bytes,
-                      hipStream_t s) {
-    return launch_direct<int32_t>(ctx, ids, num_ids, cap, src_rows, src, src_stride_bytes, dst, dst_stride_bytes, row_bytes, is_host_memory(src), nullptr, s);
+// The rows of a list of (output row, source row), every one of them valid, from `src` (used by the cache build to fill the cache).
+int gather_listed(mqg_ctx *ctx, const int2 *list, int64_t n, const void *src, int64_t src_stride_bytes, void *dst, int64_t dst_stride_bytes,
+                  int64_t row_bytes, hipStream_t s) {
+    const bool from_host = is_host_memory(src);
+    row_bytes = copy_bytes(row_bytes, src_stride_bytes, dst_stride_bytes, src, dst, !from_host);
+    const RowGeom g = row_geom(row_bytes, src_stride_bytes, dst_stride_bytes, src, dst);
+    const unsigned long long magic = from_host ? 0 : flat_magic(n, g);
+    const int grid = from_host ? link_grid(n, g, ctx->miss_inflight_bytes) : magic ? flat_grid(n, g) : hbm_grid(n, g);
+    const char *sp = static_cast<const char *>(src);
+    char *dp = static_cast<char *>(dst);
+#define MQG_LISTED(V)                                                                                                                       \
+    MQG_LAUNCH(ctx, "k_gather_listed", s,                                                                                                   \
+               (k_gather_listed<V><<<grid, kBlock, 0, s>>>(list, n, sp, src_stride_bytes, dp, dst_stride_bytes, g.vecs, g.log2_lpr, magic, grid)))
+    switch (g.vb) {
+        case 16: MQG_LISTED(uint4); break;
+        case 8: MQG_LISTED(uint2); break;
+        case 4: MQG_LISTED(uint32_t); break;
+        default: MQG_LISTED(uint16_t); break;
+    }
+#undef MQG_LISTED
+    return MQG_OK;
 }
 
 // Host-side argument checks shared by the gather entry points.  max_ids bounds cap_ids when the

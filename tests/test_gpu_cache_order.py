@@ -1,0 +1,36 @@
+"""The cache's rows are copied in the order of the ids, by a list made in tiles of 4,096 ids: node counts around one and
+several tiles, from one cached node to all of them, rows of every vector width, features on the host and on the GPU; the table, the
+ids and the rows are the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2601_04707_amd import synth
+from gpu_util import to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,dim,dtype,host", [(1, 3, torch.float32, True), (63, 5, torch.float16, True), (4095, 4, torch.float32, True),
+                                              (4096, 33, torch.float16, False), (4097, 25, torch.float32, True),
+                                              (12_289, 6, torch.float16, True), (12_289, 300, torch.float32, False)])
+def test_rows_of_the_cache(n, dim, dtype, host):
+    from paper_2601_04707_amd import mqg
+    rng = np.random.default_rng(n + dim)
+    deg = rng.integers(0, 6, n)
+    deg[rng.integers(0, n, 3)] = 40
+    rp = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(deg, out=rp[1:])
+    ci = rng.integers(0, n, rp[-1])
+    g = mqg.Graph(to_dev(torch.from_numpy(rp)), to_dev(torch.from_numpy(ci)))
+    ctx = mqg.Context(g, 1, [1])
+    feats = synth.node_features(n, dim, seed=2).to(dtype)
+    src = feats.pin_memory() if host else feats.cuda()
+    for m in sorted({1, n // 3 + 1, n - n // 4, n}):
+        cache = mqg.Cache(g, src, m)
+        mqg.mqg_build_cache(ctx, g, cache)
+        torch.cuda.synchronize()
+        assert np.array_equal(cache.slot_of.cpu().numpy(), oracle.build_cache(rp, m).slot_of)
+        ids = cache.cached_ids.cpu()
+        assert torch.equal(cache.cache_rows[:, :dim].cpu(), feats[ids.long()])

@@ -88,10 +88,10 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
 
 // key64[v] = min over the adjacency slots j of node v of mix(mix(tag_hash ^ v) ^ j); all ones for
 // a node without neighbours.  A lane owns a node; rows of up to 32 slots are walked by their
-// lane, longer rows by the whole wavefront, one after the other.
+// lane, longer rows by the whole wavefront, one after the other.  lead: see k_assign_ranked.
 template <typename PtrT>
 __global__ void __launch_bounds__(kBlock)
-k_ticket_keys(const PtrT *__restrict__ row_ptr, int64_t n, uint64_t tag_hash, uint64_t *__restrict__ key64) {
+k_ticket_keys(const PtrT *__restrict__ row_ptr, int64_t n, uint64_t tag_hash, uint64_t *__restrict__ key64, uint32_t *__restrict__ lead, int bits) {
     const int lane = lane_id();
     const int64_t v = int64_t(blockIdx.x) * kBlock + threadIdx.x;
     int d = 0;
@@ -117,7 +117,11 @@ k_ticket_keys(const PtrT *__restrict__ row_ptr, int64_t n, uint64_t tag_hash, ui
         m = wave_min_u64(m);
         if (lane == l) best = m;
     }
-    if (v < n) key64[v] = best;
+    if (v < n) {
+        const uint32_t none = ~uint32_t(0) >> (32 - bits), k = static_cast<uint32_t>(best >> (64 - bits));
+        key64[v] = best;
+        lead[v] = d == 0 ? none : k < none ? k : none - 1;
+    }
 }
 
 template <typename IdxT>
@@ -316,6 +320,38 @@ k_assign_slots(const int32_t *__restrict__ ranked, int64_t num_cached, int32_t *
     }
 }
 
+// Slots from the nodes ranked by the leading bits of their ticket keys alone (stably, so by id where they are equal): a node counts
+// how many of those that share its bits come before it by whole key and id.  The keys of nodes without neighbours, which
+// are all the same, are alone in the last value.  A value of the leading bits holds the keys of at most E / 2^bits of E slots on
+// average, at any degrees, and lead_bits makes that two at most, so that the counting is short (2.4 M nodes, 124 M slots: 27 bits in three
+// passes and 16 us here; all 64 took eight passes and a gather of the upper words in between, 255 us, now 106).  Nodes past the last slot count only if they share the last one's bits.
+template <typename IdxT>
+__global__ void __launch_bounds__(kBlock)
+k_assign_ranked(const uint32_t *__restrict__ lead, const int32_t *__restrict__ ranked, const uint64_t *__restrict__ key64, int64_t n, int bits,
+                int64_t num_cached, int32_t *__restrict__ slot_of, IdxT *__restrict__ cached_ids, int32_t *__restrict__ listed) {
+    const int64_t p = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+    if (p == 0) *listed = 0;
+    if (p >= n) return;
+    const uint32_t k = lead[p];
+    if (p >= num_cached && k != lead[num_cached - 1]) return;
+    const int32_t v = ranked[p];
+    int64_t slot = p;
+    if (k != ~uint32_t(0) >> (32 - bits)) {
+        const uint64_t key = (p > 0 && lead[p - 1] == k) || (p + 1 < n && lead[p + 1] == k) ? key64[v] : 0;
+        for (int64_t q = p - 1; q >= 0 && lead[q] == k; --q) slot -= key64[ranked[q]] > key ? 1 : 0;           // smaller ids
+        for (int64_t q = p + 1; q < n && lead[q] == k; ++q) slot += key64[ranked[q]] < key ? 1 : 0;            // larger ids
+    }
+    if (slot < num_cached) {
+        slot_of[v] = static_cast<int32_t>(slot);
+        if (cached_ids) cached_ids[slot] = static_cast<IdxT>(v);
+    }
+}
+// As many leading bits as the passes hold that it takes to have at most two slots to a value.
+int lead_bits(int64_t num_edges, int64_t n) {
+    const int want = std::max(8, radix_key_bits(static_cast<uint64_t>(std::max<int64_t>(num_edges, 1))) - 1);
+    return std::min(32, radix_passes(want, n) * radix_digit_bits(want, n));
+}
+
 // The cached nodes as (slot, id), by tiles of consecutive ids, ascending inside a tile: rows that lie side by side in the
 // feature matrix are then copied side by side, and the line of 128 bytes that two of them share comes over the link once.
 // (490 k rows of 400 bytes, one node in five: 4,477 us in the order of the slots, 4,258 so; one in two 9.16 and 8.15 us per
@@ -422,6 +458,9 @@ int run_build_cache(mqg_ctx *ctx, const mqg_graph *g, mqg_cache *c, const mqg_ca
     Temp tmp(ctx);
     const int ngrid = static_cast<int>(ceil_div(n, kBlock));
     const int32_t *ranked = nullptr;
+    const uint32_t *lead = nullptr;                  // not null: ranked by the leading `bits` bits of key64 only
+    uint64_t *key64 = nullptr;
+    int bits = 0;
     uint32_t *walk_flags = nullptr;                  // bit 0: a training id outside the graph
 
     if (policy == MQG_CACHE_TOP_DEGREE) {
@@ -449,19 +488,25 @@ int run_build_cache(mqg_ctx *ctx, const mqg_graph *g, mqg_cache *c, const mqg_ca
         if (rc0 != MQG_OK) return rc0;
         ranked = which < 0 ? vals_a : rb.vals[which];
     } else if (policy == MQG_CACHE_DEGREE_SAMPLED) {
-        uint64_t *key64;
-        if (!tmp.alloc(&key64, n)) return fail(ctx, MQG_ERR_HIP, "mqg_build_cache: temporary allocation failed");
+        RadixBufs rb;
+        uint32_t *lead_in;
+        if (!(tmp.alloc(&key64, n) && tmp.alloc(&lead_in, n) && tmp.alloc(&rb.keys[0], n) && tmp.alloc(&rb.keys[1], n) && tmp.alloc(&rb.vals[0], n) &&
+              tmp.alloc(&rb.vals[1], n) && tmp.alloc(&rb.hist, radix_hist_len_max(n)) && tmp.alloc(&rb.totals, kRadixTotals)))
+            return fail(ctx, MQG_ERR_HIP, "mqg_build_cache: temporary allocation failed");
+        bits = lead_bits(g->num_edges, n);
         // the tag keeps this draw apart from every block's neighbour draw (block index -1)
         const uint64_t tag_hash = host_mix64(host_mix64(plan->seed + kGolden) ^ ~uint64_t(0));
         if (g->ptr_type == MQG_I64)
-            MQG_LAUNCH(ctx, "k_ticket_keys", s, (k_ticket_keys<int64_t><<<ngrid, kBlock, 0, s>>>(static_cast<const int64_t *>(g->row_ptr), n, tag_hash, key64)));
+            MQG_LAUNCH(ctx, "k_ticket_keys", s, (k_ticket_keys<int64_t><<<ngrid, kBlock, 0, s>>>(static_cast<const int64_t *>(g->row_ptr), n, tag_hash, key64, lead_in, bits)));
         else
-            MQG_LAUNCH(ctx, "k_ticket_keys", s, (k_ticket_keys<int32_t><<<ngrid, kBlock, 0, s>>>(static_cast<const int32_t *>(g->row_ptr), n, tag_hash, key64)));
-        int rc0 = rank_by_key64(ctx, tmp, key64, n, &ranked, s);
+            MQG_LAUNCH(ctx, "k_ticket_keys", s, (k_ticket_keys<int32_t><<<ngrid, kBlock, 0, s>>>(static_cast<const int32_t *>(g->row_ptr), n, tag_hash, key64, lead_in, bits)));
+        int which = -1;
+        int rc0 = radix_sort_pairs(ctx, lead_in, nullptr, rb, n, nullptr, bits, s, &which);
         if (rc0 != MQG_OK) return rc0;
+        ranked = rb.vals[which];
+        lead = rb.keys[which];
     } else {  // MQG_CACHE_RANDOM_WALK, MQG_CACHE_RANDOM_WALK_SAMPLED
         double *pa, *pb, *pass;
-        uint64_t *key64;
         if (!(tmp.alloc(&pa, n) && tmp.alloc(&pb, n) && tmp.alloc(&pass, n) && tmp.alloc(&key64, n) && tmp.alloc(&walk_flags, 1)))
             return fail(ctx, MQG_ERR_HIP, "mqg_build_cache: temporary allocation failed");
         e = hipMemsetAsync(pa, 0, static_cast<size_t>(n) * sizeof(double), s);
@@ -550,7 +595,11 @@ int run_build_cache(mqg_ctx *ctx, const mqg_graph *g, mqg_cache *c, const mqg_ca
         int32_t *listed;
         if (!(tmp.alloc(&list, c->num_cached) && tmp.alloc(&listed, 1))) return fail(ctx, MQG_ERR_HIP, "mqg_build_cache: temporary allocation failed");
         const int cgrid = static_cast<int>(ceil_div(c->num_cached, kBlock));
-        if (g->idx_type == MQG_I64)
+        if (lead && g->idx_type == MQG_I64)
+            MQG_LAUNCH(ctx, "k_assign_ranked", s, (k_assign_ranked<int64_t><<<ngrid, kBlock, 0, s>>>(lead, ranked, key64, n, bits, c->num_cached, c->slot_of, static_cast<int64_t *>(c->cached_ids), listed)));
+        else if (lead)
+            MQG_LAUNCH(ctx, "k_assign_ranked", s, (k_assign_ranked<int32_t><<<ngrid, kBlock, 0, s>>>(lead, ranked, key64, n, bits, c->num_cached, c->slot_of, static_cast<int32_t *>(c->cached_ids), listed)));
+        else if (g->idx_type == MQG_I64)
             MQG_LAUNCH(ctx, "k_assign_slots", s, (k_assign_slots<int64_t><<<cgrid, kBlock, 0, s>>>(ranked, c->num_cached, c->slot_of, static_cast<int64_t *>(c->cached_ids), listed)));
         else
             MQG_LAUNCH(ctx, "k_assign_slots", s, (k_assign_slots<int32_t><<<cgrid, kBlock, 0, s>>>(ranked, c->num_cached, c->slot_of, static_cast<int32_t *>(c->cached_ids), listed)));

@@ -34,3 +34,26 @@ def test_rows_of_the_cache(n, dim, dtype, host):
         assert np.array_equal(cache.slot_of.cpu().numpy(), oracle.build_cache(rp, m).slot_of)
         ids = cache.cached_ids.cpu()
         assert torch.equal(cache.cache_rows[:, :dim].cpu(), feats[ids.long()])
+
+
+@pytest.mark.parametrize("n,degree", [(5, 1), (300, 0), (4000, 1), (2000, 300), (70_000, 3), (2_097_153, 2)])
+def test_drawn_nodes_that_share_their_leading_bits(n, degree):
+    """The draw ranks nodes by as many leading bits of their keys as give two slots to a value: with few bits many nodes share
+    theirs, also at the last slot; nodes without neighbours come last, by id."""
+    from paper_2601_04707_amd import mqg
+    rng = np.random.default_rng(n)
+    deg = np.where(rng.random(n) < 0.3, 0, degree)
+    rp = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(deg, out=rp[1:])
+    ci = rng.integers(0, n, max(int(rp[-1]), 1))[: rp[-1]]
+    g = mqg.Graph(to_dev(torch.from_numpy(rp)), to_dev(torch.from_numpy(ci)))
+    ctx = mqg.Context(g, 1, [1])
+    src = synth.node_features(n, 4, seed=2).pin_memory()
+    with_slots = int((deg > 0).sum())
+    for m in sorted({1, n // 3, with_slots, min(n, with_slots + 2), n} - {0}):
+        cache = mqg.Cache(g, src, m)
+        mqg.mqg_build_cache_ex(ctx, g, cache, mqg.MQG_CACHE_DEGREE_SAMPLED, seed=5)
+        torch.cuda.synchronize()
+        want = oracle.build_cache_sampled(rp, m, 5)
+        assert np.array_equal(cache.slot_of.cpu().numpy(), want.slot_of)
+        assert np.array_equal(cache.cached_ids.cpu().numpy()[:m], want.cached_ids)

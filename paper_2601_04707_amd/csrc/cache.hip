@@ -77,18 +77,13 @@ uint64_t host_mix64(uint64_t z) {
     return z;
 }
 
-__device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        uint64_t o = __shfl_xor(v, off, 64);
-        v = o < v ? o : v;
-    }
-    return v;
-}
-
 // key64[v] = min over the adjacency slots j of node v of mix(mix(tag_hash ^ v) ^ j); all ones for
-// a node without neighbours.  A lane owns a node; rows of up to 32 slots are walked by their
+// a node without neighbours.  A lane owns a node; rows of up to kLaneSlots slots are walked by their
 // lane, longer rows by the whole wavefront, one after the other.  lead: see k_assign_ranked.
+// Bound by the multiplications of the keys and by what a long row costs beside them.  2.4 M nodes, 124 M slots: six
+// multiplications of 64-bit words a key, and twelve exchanges through LDS a row, 184 us; five of 32 bits, three where a wavefront walks,
+// and the smallest upper word by six instructions, 142.  The line: 20 slots 162, 48 145.
+constexpr int kLaneSlots = 32;
 template <typename PtrT>
 __global__ void __launch_bounds__(kBlock)
 k_ticket_keys(const PtrT *__restrict__ row_ptr, int64_t n, uint64_t tag_hash, uint64_t *__restrict__ key64, uint32_t *__restrict__ lead, int bits) {
@@ -98,24 +93,42 @@ k_ticket_keys(const PtrT *__restrict__ row_ptr, int64_t n, uint64_t tag_hash, ui
     if (v < n) d = static_cast<int>(row_ptr[v + 1] - row_ptr[v]);
     const uint64_t hv = mix64(tag_hash ^ static_cast<uint64_t>(v));
     uint64_t best = ~uint64_t(0);
-    if (d <= 32)
+    if (d <= kLaneSlots) {
+        const RowKeys key_of(hv);
         for (int j = 0; j < d; ++j) {
-            uint64_t k = mix64(hv ^ static_cast<uint64_t>(j));
+            const uint64_t k = key_of(j);
             best = k < best ? k : best;
         }
-    uint64_t big = ballot64(d > 32);
+    }
+    uint64_t big = ballot64(d > kLaneSlots);
     while (big) {
         const int l = __ffsll(static_cast<long long>(big)) - 1;
         big &= big - 1;
         const int dl = static_cast<int>(readlane32(static_cast<uint32_t>(d), l));
         const uint64_t hl = readlane64(hv, l);
         uint64_t m = ~uint64_t(0);
-        for (int j = lane; j < dl; j += kWave) {
-            uint64_t k = mix64(hl ^ static_cast<uint64_t>(j));
-            m = k < m ? k : m;
+        for (uint32_t range = 0; range < static_cast<uint32_t>(dl); range += 0x40000000u) {
+            const WaveKeys<1> keys(key_low(hl, range), key_hi_term(hl));
+            const uint32_t end = static_cast<uint32_t>(dl) - range < 0x40000000u ? static_cast<uint32_t>(dl) : range + 0x40000000u;
+            uint32_t base = range;
+            for (; base + kWave <= end; base += kWave) {
+                const uint64_t k = keys.whole(keys.row_part(base));
+                m = k < m ? k : m;
+            }
+            if (base < end) {
+                const uint64_t k = keys.whole(keys.row_part(base));
+                m = k < m && base + lane < end ? k : m;
+            }
         }
-        m = wave_min_u64(m);
-        if (lane == l) best = m;
+        // the smallest upper word, almost always of one lane; equal ones one after the other
+        const uint32_t top = wave_min_u32(static_cast<uint32_t>(m >> 32));
+        uint64_t same = ballot64(static_cast<uint32_t>(m >> 32) == top), least = ~uint64_t(0);
+        while (same) {
+            const uint64_t k = readlane64(m, __ffsll(static_cast<long long>(same)) - 1);
+            least = k < least ? k : least;
+            same &= same - 1;
+        }
+        if (lane == l) best = least;
     }
     if (v < n) {
         const uint32_t none = ~uint32_t(0) >> (32 - bits), k = static_cast<uint32_t>(best >> (64 - bits));

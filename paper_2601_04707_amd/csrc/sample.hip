@@ -370,81 +370,6 @@ struct NeighbourPipe {
     }
 };
 
-// key(j) = mix64(hv ^ j) for the slots j of one row, with everything that depends only on the row
-// hoisted out: j < 2^31 touches only the low word of hv ^ j, so the high word after the first
-// xor-shift and its share of the first multiply are per-row constants.  Written on 32-bit halves
-// (funnel shifts are one v_alignbit each): 5 multiplies per key instead of 6.
-struct RowKeys {
-    static constexpr uint32_t kC1Lo = 0x1CE4E5B9u, kC1Hi = 0xBF58476Du;
-    static constexpr uint32_t kC2Lo = 0x133111EBu, kC2Hi = 0x94D049BBu;
-    uint32_t lo, hi_shl2, a_hi, c1_term;
-    __device__ __forceinline__ explicit RowKeys(uint64_t hv) {
-        const uint32_t hi = static_cast<uint32_t>(hv >> 32);
-        lo = static_cast<uint32_t>(hv);
-        hi_shl2 = hi << 2;
-        a_hi = hi ^ (hi >> 30);
-        c1_term = a_hi * kC1Lo;
-    }
-    __device__ __forceinline__ uint64_t operator()(int j) const {
-        const uint32_t lo0 = lo ^ static_cast<uint32_t>(j);
-        const uint32_t a_lo = lo0 ^ (hi_shl2 | (lo0 >> 30));                       // z ^= z >> 30
-        const uint64_t p = static_cast<uint64_t>(a_lo) * kC1Lo;                      // z *= C1
-        const uint32_t b_lo = static_cast<uint32_t>(p);
-        const uint32_t b_hi = static_cast<uint32_t>(p >> 32) + a_lo * kC1Hi + c1_term;
-        const uint32_t c_lo = b_lo ^ __builtin_amdgcn_alignbit(b_hi, b_lo, 27);      // z ^= z >> 27
-        const uint32_t c_hi = b_hi ^ (b_hi >> 27);
-        const uint64_t q = static_cast<uint64_t>(c_lo) * kC2Lo;                      // z *= C2
-        const uint32_t d_lo = static_cast<uint32_t>(q);
-        const uint32_t d_hi = static_cast<uint32_t>(q >> 32) + c_lo * kC2Hi + c_hi * kC2Lo;
-        const uint32_t e_lo = d_lo ^ __builtin_amdgcn_alignbit(d_hi, d_lo, 31);      // z ^= z >> 31
-        const uint32_t e_hi = d_hi ^ (d_hi >> 31);
-        return (static_cast<uint64_t>(e_hi) << 32) | e_lo;
-    }
-};
-
-// The same keys for a wavefront that walks a row 64 slots at a time, slot = base + lane with base a
-// multiple of 64.  Up to the first multiplication a lane's word differs from the wavefront's only in its
-// six low bits, so the product splits into a part that depends on the row and base alone (scalar unit) and
-// a part that depends on the row and the lane alone (once per row): what is left of the first half of the
-// mixer per key is one 64-bit addition, and three multiplications per key remain of five.  One object
-// serves the slots of one range of 2^30 (the slot's two top bits reach the low bits).  Where a wavefront takes
-// CHUNKS times 64 slots from a multiple of that on, those share the row's part.
-constexpr uint64_t kC1 = (uint64_t(RowKeys::kC1Hi) << 32) | RowKeys::kC1Lo;
-__device__ __forceinline__ uint32_t key_low(uint64_t hv, uint32_t range = 0) {           // low word after the first xor-shift, for slot 0 of the range
-    const uint32_t lo = static_cast<uint32_t>(hv);
-    return lo ^ static_cast<uint32_t>(((hv >> 32 << 32) | (lo ^ range)) >> 30);
-}
-__device__ __forceinline__ uint32_t key_hi_term(uint64_t hv) {                            // the high word's share of the first product
-    const uint32_t hi = static_cast<uint32_t>(hv >> 32);
-    return (hi ^ (hi >> 30)) * RowKeys::kC1Lo;
-}
-// The key's upper word, from the first product, before the final xor-shift, which would change its bit 0 only
-__device__ __forceinline__ uint32_t key_upper(uint64_t b) {
-    const uint32_t b_lo = static_cast<uint32_t>(b), b_hi = static_cast<uint32_t>(b >> 32);
-    const uint32_t c_lo = b_lo ^ __builtin_amdgcn_alignbit(b_hi, b_lo, 27);
-    const uint32_t c_hi = b_hi ^ (b_hi >> 27);
-    return __umulhi(c_lo, RowKeys::kC2Lo) + c_lo * RowKeys::kC2Hi + c_hi * RowKeys::kC2Lo;
-}
-template <int CHUNKS>
-struct WaveKeys {
-    static constexpr uint32_t kMask = CHUNKS * kWave - 1;
-    uint32_t low, hi_term;        // the same in all lanes
-    uint64_t lane_prod[CHUNKS];   // (its low bits, with the slot's) * C1
-    __device__ __forceinline__ WaveKeys(uint32_t low_word, uint32_t hi_share) : low(low_word), hi_term(hi_share) {
-#pragma unroll
-        for (int c = 0; c < CHUNKS; ++c) lane_prod[c] = static_cast<uint64_t>((low ^ static_cast<uint32_t>(c * kWave + lane_id())) & kMask) * kC1;
-    }
-    // the row's part for the CHUNKS * 64 slots from base on
-    __device__ __forceinline__ uint64_t row_part(uint32_t base) const {
-        const uint32_t rest = (low ^ base) & ~kMask;
-        uint64_t p = uint64_t(rest) * RowKeys::kC1Lo + (uint64_t(rest * RowKeys::kC1Hi + hi_term) << 32);
-        // (this keeps it in scalar registers: the compiler would fold the product into the addition as a vector multiply-add)
-        asm("" : "+s"(p));
-        return p;
-    }
-    __device__ __forceinline__ uint32_t upper(uint64_t part, int c = 0) const { return key_upper(part + lane_prod[c]); }
-};
-
 // A candidate: the upper 31 bits of its key and its slot.
 struct alignas(8) Candidate {
     uint32_t word;

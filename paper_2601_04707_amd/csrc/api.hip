@@ -162,7 +162,7 @@ int mqg_ctx_create(mqg_ctx **out, const mqg_graph *g, int32_t max_seeds, const i
 
     bool ok = true;
     ok = ok && dev_alloc(&c->local_of, c->num_nodes) == hipSuccess;
-    ok = ok && dev_alloc(&c->bitmap, 2 * c->bitmap_words) == hipSuccess;
+    ok = ok && dev_alloc(&c->bitmap, 3 * c->bitmap_words) == hipSuccess;
     ok = ok && dev_alloc(&c->tile_vals, c->max_tiles) == hipSuccess;
     ok = ok && dev_alloc(&c->bitmap_tile_vals, c->max_tiles) == hipSuccess;
     ok = ok && dev_alloc(&c->row_start, c->max_dst) == hipSuccess;
@@ -176,7 +176,7 @@ int mqg_ctx_create(mqg_ctx **out, const mqg_graph *g, int32_t max_seeds, const i
     ok = ok && dev_alloc(&c->miss_list, c->max_src) == hipSuccess;
     ok = ok && dev_alloc(&c->counters, 8) == hipSuccess;
     if (ok) ok = hipMemset(c->local_of, 0xFF, std::max<int64_t>(c->num_nodes, 1) * sizeof(int32_t)) == hipSuccess;
-    if (ok) ok = hipMemset(c->bitmap, 0, 2 * c->bitmap_words * sizeof(uint32_t)) == hipSuccess;
+    if (ok) ok = hipMemset(c->bitmap, 0, 3 * c->bitmap_words * sizeof(uint32_t)) == hipSuccess;
     if (ok) ok = hipMemset(c->counters, 0, 8 * sizeof(unsigned long long)) == hipSuccess;
     if (ok) ok = hipMemset(c->heavy_count, 0, (MQG_MAX_LAYERS + 1) * sizeof(int32_t)) == hipSuccess;
     if (ok) ok = hipDeviceSynchronize() == hipSuccess;

@@ -78,7 +78,7 @@ struct mqg_ctx {
     // scratch (device)
     int32_t *local_of = nullptr;         // [num_nodes] position of a node in the current source list plus the call's offset; less if absent
     int64_t pos_next = 0;                // offset of the next call's positions (take_positions)
-    uint32_t *bitmap = nullptr;          // [2 * bitmap_words] nodes first seen in the current layer; small graphs take the two halves in turn
+    uint32_t *bitmap = nullptr;          // [3 * bitmap_words] nodes first seen in the current layer; small graphs take two thirds in turn, the last one is the seeds'
     int64_t bitmap_words = 0;            // padded to a multiple of kBitmapTileWords
     int32_t *tile_vals = nullptr;        // [max_tiles] per-tile sums of the rows, then their exclusive scan
     int32_t *bitmap_tile_vals = nullptr; // [max_tiles] the same for the tiles of the bitmap

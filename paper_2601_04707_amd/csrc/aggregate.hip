@@ -589,47 +589,70 @@ k_permute_edges(const int32_t *__restrict__ perm, const int32_t *__restrict__ in
     }
 }
 
-// Weights of the sampled estimator of P H, P = D^-1/2 (A + I) D^-1/2 (paper Eq. 1-3): one wavefront
-// per destination row; edge p = (v_i, v_j) gets deg(v_i)/n_i / sqrt((deg(v_i)+1)(deg(v_j)+1)), the
+// Weights of the sampled estimator of P H, P = D^-1/2 (A + I) D^-1/2 (paper Eq. 1-3): LANES lanes per
+// destination row; edge p = (v_i, v_j) gets deg(v_i)/n_i / sqrt((deg(v_i)+1)(deg(v_j)+1)), the
 // row's diagonal term is 1/(deg(v_i)+1).  Computed in double, rounded once to float.
-template <typename PtrT, typename IdxT>
+// Bound by the double division and square root, which a wavefront pays for whole, and by the chain of four loads: the row's and
+// its first edges' are under way together.  (A wavefront per row, one load after the other: 10 k rows of 25 edges 10.3 us, 7.0 so; whole
+// calls with their aggregations 1 to 4 % faster, the most at fanouts of 3 to 10.)
+template <typename PtrT, typename IdxT, int LANES>
 __global__ void __launch_bounds__(kBlock)
 k_gcn_edge_weights(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ src_ids, const int32_t *__restrict__ indptr,
                    const int32_t *__restrict__ indices, const int64_t *__restrict__ sizes, float *__restrict__ edge_w,
-                   float *__restrict__ self_w) {
-    const int lane = lane_id();
+                   float *__restrict__ self_w, int grid) {
+    const int lane = static_cast<int>(threadIdx.x) % LANES;
     const int64_t n = sizes[0];
-    const int64_t wave0 = int64_t(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
-    const int64_t nwaves = int64_t(gridDim.x) * kWavesPerBlock;
-    for (int64_t i = wave0; i < n; i += nwaves) {
+    const int64_t step = int64_t(grid) * (kBlock / LANES);
+    for (int64_t i = int64_t(blockIdx.x) * (kBlock / LANES) + threadIdx.x / LANES; i < n; i += step) {
         const int64_t v = static_cast<int64_t>(src_ids[i]);
-        const double deg_i = static_cast<double>(static_cast<int64_t>(row_ptr[v + 1]) - static_cast<int64_t>(row_ptr[v]));
         const int b = indptr[i], e = indptr[i + 1];
+        int p = b + lane;
+        int64_t u = p < e ? static_cast<int64_t>(src_ids[indices[p]]) : v;
+        const int64_t v0 = static_cast<int64_t>(row_ptr[v]), v1 = static_cast<int64_t>(row_ptr[v + 1]);
+        int64_t u0 = static_cast<int64_t>(row_ptr[u]), u1 = static_cast<int64_t>(row_ptr[u + 1]);
+        const double deg_i = static_cast<double>(v1 - v0);
         const double scale = deg_i / static_cast<double>(e - b);
         if (lane == 0) self_w[i] = static_cast<float>(1.0 / (deg_i + 1.0));
-        for (int p = b + lane; p < e; p += kWave) {
-            const int64_t u = static_cast<int64_t>(src_ids[indices[p]]);
-            const double deg_j = static_cast<double>(static_cast<int64_t>(row_ptr[u + 1]) - static_cast<int64_t>(row_ptr[u]));
+        while (p < e) {
+            const double deg_j = static_cast<double>(u1 - u0);
             edge_w[p] = static_cast<float>(scale * (1.0 / sqrt((deg_i + 1.0) * (deg_j + 1.0))));
+            p += LANES;
+            if (p < e) {
+                u = static_cast<int64_t>(src_ids[indices[p]]);
+                u0 = static_cast<int64_t>(row_ptr[u]);
+                u1 = static_cast<int64_t>(row_ptr[u + 1]);
+            }
         }
     }
 }
 
 }  // namespace
 
-int run_gcn_edge_weights(mqg_ctx *ctx, const mqg_graph *g, const mqg_block *b, float *edge_w, float *self_w, hipStream_t s) {
-    const int grid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(b->cap_dst, kWavesPerBlock)), 256 * 32));
-#define MQG_GCNW(PT, IT)                                                                                              \
-    MQG_LAUNCH(ctx, "k_gcn_edge_weights", s,                                                                          \
-               (k_gcn_edge_weights<PT, IT><<<grid, kBlock, 0, s>>>(static_cast<const PT *>(g->row_ptr),                \
-                                                                   static_cast<const IT *>(b->src_ids), b->indptr,    \
-                                                                   b->indices, b->sizes, edge_w, self_w)))
-    if (g->ptr_type == MQG_I64 && g->idx_type == MQG_I64) MQG_GCNW(int64_t, int64_t);
-    else if (g->ptr_type == MQG_I64) MQG_GCNW(int64_t, int32_t);
-    else if (g->idx_type == MQG_I64) MQG_GCNW(int32_t, int64_t);
-    else MQG_GCNW(int32_t, int32_t);
+template <typename PtrT, typename IdxT>
+static int launch_gcn_edge_weights(mqg_ctx *ctx, const mqg_graph *g, const mqg_block *b, float *edge_w, float *self_w, hipStream_t s) {
+    // As many lanes as a row has edges at most, by the block's capacities (longer rows take several rounds).
+    const int64_t most = b->cap_nnz / std::max<int64_t>(b->cap_dst, 1);
+#define MQG_GCNW(LANES)                                                                                                                \
+    do {                                                                                                                               \
+        const int grid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(b->cap_dst, kBlock / LANES)), 256 * 32));     \
+        MQG_LAUNCH(ctx, "k_gcn_edge_weights", s,                                                                                       \
+                   (k_gcn_edge_weights<PtrT, IdxT, LANES><<<grid, kBlock, 0, s>>>(                                                     \
+                       static_cast<const PtrT *>(g->row_ptr), static_cast<const IdxT *>(b->src_ids), b->indptr, b->indices, b->sizes,  \
+                       edge_w, self_w, grid)));                                                                                        \
+    } while (0)
+    if (most <= 8) MQG_GCNW(8);
+    else if (most <= 16) MQG_GCNW(16);
+    else if (most <= 32) MQG_GCNW(32);
+    else MQG_GCNW(64);
 #undef MQG_GCNW
     return MQG_OK;
+}
+
+int run_gcn_edge_weights(mqg_ctx *ctx, const mqg_graph *g, const mqg_block *b, float *edge_w, float *self_w, hipStream_t s) {
+    if (g->ptr_type == MQG_I64 && g->idx_type == MQG_I64) return launch_gcn_edge_weights<int64_t, int64_t>(ctx, g, b, edge_w, self_w, s);
+    if (g->ptr_type == MQG_I64) return launch_gcn_edge_weights<int64_t, int32_t>(ctx, g, b, edge_w, self_w, s);
+    if (g->idx_type == MQG_I64) return launch_gcn_edge_weights<int32_t, int64_t>(ctx, g, b, edge_w, self_w, s);
+    return launch_gcn_edge_weights<int32_t, int32_t>(ctx, g, b, edge_w, self_w, s);
 }
 
 int run_weighted_aggregate(mqg_ctx *ctx, const mqg_block *b, const float *edge_w, const float *self_w, const void *x,

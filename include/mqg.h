@@ -116,7 +116,10 @@ typedef struct mqg_cache {
  *                         and a flags word (0 = ok; in the innermost block bit 0
  *                         = some seed id was outside [0, num_nodes) and has been
  *                         replaced by node 0, bit 1 = a seed id occurs more
- *                         than once; the batch is then not a valid sample).
+ *                         than once; the batch is then not a valid sample:
+ *                         repeated ids keep their rows, the bounds below count
+ *                         distinct ones, and the last of the sources that do
+ *                         not fit are left out, edges to them point at 0).
  * Capacity bounds checked by mqg_sample_blocks (MQG_ERR_CAPACITY otherwise), with
  * need_dst(L-1) = num_seeds and need_dst(l) = need_src(l+1):
  *   cap_dst >= need_dst,  cap_nnz >= need_nnz = need_dst * fanouts[l],

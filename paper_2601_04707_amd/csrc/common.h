@@ -194,15 +194,15 @@ int ensure_hash_scratch(mqg_ctx *ctx);
 void free_hash_scratch(mqg_ctx *ctx);
 int hash_put_seeds(mqg_ctx *ctx, const void *seeds, int idx_type, int64_t need_dst, const int64_t *sizes, hipStream_t s);
 int hash_dedup_block(mqg_ctx *ctx, const int32_t *nbr, int64_t need_nnz, int64_t num_nodes, int idx_type, void *src_ids,
-                     int64_t *sizes, int64_t *sizes_next, int32_t *indices, hipStream_t s);
+                     int64_t *sizes, int64_t *sizes_next, int64_t most_src, int32_t *indices, hipStream_t s);
 int hash_clear(mqg_ctx *ctx, hipStream_t s);
 
 // A range of `count` offset positions for local_of; take_back: the call's last launch has to set its entries to -1.
 int take_positions(mqg_ctx *ctx, int64_t count, hipStream_t s, int32_t *base, bool *take_back);
 
-// Exclusive scan of vals[0..n) in place by one workgroup; the total (plus *addend if given) is
+// Exclusive scan of vals[0..n) in place by one workgroup; the total (plus *addend if given), `most` at most, is
 // stored to *total_a and *total_b where non-null.
-int launch_scan_tiles(mqg_ctx *ctx, int32_t *vals, int64_t n, const int64_t *addend,
-                      int64_t *total_a, int64_t *total_b, hipStream_t s, const char *name = "k_scan_tiles");
+int launch_scan_tiles(mqg_ctx *ctx, int32_t *vals, int64_t n, const int64_t *addend, int64_t *total_a, int64_t *total_b,
+                      hipStream_t s, const char *name = "k_scan_tiles", int64_t most = INT64_MAX);
 
 }  // namespace mqg

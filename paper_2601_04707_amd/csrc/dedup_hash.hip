@@ -96,10 +96,11 @@ k_hash_put_nbr(const int32_t *__restrict__ nbr, const int64_t *__restrict__ size
 template <typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_hash_assign(const uint32_t *__restrict__ sorted_keys, const unsigned long long *__restrict__ new_count,
-              int64_t *sizes, int64_t *sizes_next, IdxT *__restrict__ src_ids,
+              int64_t *sizes, int64_t *sizes_next, int64_t most_src, IdxT *__restrict__ src_ids,
               unsigned long long *__restrict__ table, uint32_t mask) {
-    const int64_t cnt = static_cast<int64_t>(*new_count);
     const int64_t nd = sizes[0];
+    int64_t cnt = static_cast<int64_t>(*new_count);
+    if (nd + cnt > most_src) cnt = most_src - nd;          // repeated seeds: the last of the new sources are left out (nd <= most_src)
     const int64_t stride = int64_t(gridDim.x) * kBlock;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         sizes[1] = nd + cnt;
@@ -137,7 +138,7 @@ k_hash_relabel(const int32_t *__restrict__ nbr, const int64_t *__restrict__ size
             if (cur == kEmpty) break;                      // cannot happen: every neighbour was inserted
             slot = (slot + 1) & mask;
         }
-        indices[e] = pos;
+        indices[e] = pos < 0 ? 0 : pos;                    // below 0 (kNewMark): left out of the sources, see k_hash_assign
     }
 }
 
@@ -207,7 +208,7 @@ int hash_put_seeds(mqg_ctx *ctx, const void *seeds, int idx_type, int64_t need_d
 
 // One block's dedup + relabel: nbr[0..nnz) -> new source ids (ascending) appended to src_ids, indices.
 int hash_dedup_block(mqg_ctx *ctx, const int32_t *nbr, int64_t need_nnz, int64_t num_nodes, int idx_type, void *src_ids,
-                     int64_t *sizes, int64_t *sizes_next, int32_t *indices, hipStream_t s) {
+                     int64_t *sizes, int64_t *sizes_next, int64_t most_src, int32_t *indices, hipStream_t s) {
     const uint32_t mask = static_cast<uint32_t>(ctx->hash_capacity - 1);
     const int egrid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(need_nnz, kBlock)), 4096));
     MQG_LAUNCH(ctx, "k_zero_u64", s, (k_zero_u64<<<1, 64, 0, s>>>(ctx->hash_new_count)));
@@ -221,11 +222,11 @@ int hash_dedup_block(mqg_ctx *ctx, const int32_t *nbr, int64_t need_nnz, int64_t
     const uint32_t *sorted = which < 0 ? ctx->hash_new_keys : ctx->hash_sort.keys[which];
     if (idx_type == MQG_I64)
         MQG_LAUNCH(ctx, "k_hash_assign", s,
-                   (k_hash_assign<int64_t><<<egrid, kBlock, 0, s>>>(sorted, ctx->hash_new_count, sizes, sizes_next,
+                   (k_hash_assign<int64_t><<<egrid, kBlock, 0, s>>>(sorted, ctx->hash_new_count, sizes, sizes_next, most_src,
                                                                     static_cast<int64_t *>(src_ids), ctx->hash_table, mask)));
     else
         MQG_LAUNCH(ctx, "k_hash_assign", s,
-                   (k_hash_assign<int32_t><<<egrid, kBlock, 0, s>>>(sorted, ctx->hash_new_count, sizes, sizes_next,
+                   (k_hash_assign<int32_t><<<egrid, kBlock, 0, s>>>(sorted, ctx->hash_new_count, sizes, sizes_next, most_src,
                                                                     static_cast<int32_t *>(src_ids), ctx->hash_table, mask)));
     MQG_LAUNCH(ctx, "k_hash_relabel", s, (k_hash_relabel<<<egrid, kBlock, 0, s>>>(nbr, sizes, ctx->hash_table, mask, indices)));
     return MQG_OK;

@@ -161,10 +161,10 @@ k_row_info(RowInfoArgs<PtrT, IdxT> a) {
     row_info_tile<true>(a, static_cast<int>(blockIdx.x), lds);
 }
 
-// One workgroup of 1024 threads: vals[0..n) -> exclusive scan in place; totals stored.
+// One workgroup of 1024 threads: vals[0..n) -> exclusive scan in place; totals, `most` at most, stored.
 __global__ void __launch_bounds__(1024)
 k_scan_tiles(int32_t *__restrict__ vals, int64_t n, const int64_t *__restrict__ addend,
-             int64_t *__restrict__ total_a, int64_t *__restrict__ total_b) {
+             int64_t *__restrict__ total_a, int64_t *__restrict__ total_b, int64_t most) {
     __shared__ int lds[16];
     int64_t carry = 0;
     for (int64_t base = 0; base < n; base += 1024) {
@@ -177,6 +177,7 @@ k_scan_tiles(int32_t *__restrict__ vals, int64_t n, const int64_t *__restrict__ 
     }
     if (threadIdx.x == 0) {
         int64_t t = carry + (addend ? *addend : 0);
+        t = t < most ? t : most;
         if (total_a) *total_a = t;
         if (total_b) *total_b = t;
     }
@@ -235,7 +236,8 @@ __device__ __forceinline__ void relabel_slots(const int32_t *__restrict__ nbr, c
         const int b = indptr[row];
         if (j < indptr[row + 1] - b) {
             const int32_t u = nbr[t];
-            indices[b + j] = u < 0 ? ~u : local_of[u] - pos_base;
+            const int32_t p = u < 0 ? ~u : local_of[u] - pos_base;
+            indices[b + j] = p < 0 ? 0 : p;                // below 0: left out of the sources, see store_num_src
         }
     }
 }
@@ -1110,18 +1112,21 @@ k_offsets_count(const int32_t *__restrict__ row_deg, int fanout, int64_t *sizes,
     else bitmap_count_tile<WPT>(bitmap, except, bitmap_tile_sums, b - row_tiles, lds);
 }
 
-// num_src of a block is also num_dst of the next block outward
-__device__ __forceinline__ void store_num_src(int64_t *sizes, int64_t *next_num_dst, int64_t num_src) {
+// num_src of a block is also num_dst of the next block outward.  A call's bounds count distinct seeds; repeated ones, which are
+// flagged but keep their rows, can leave more new sources than that.  The last of those, beyond `most`, are not listed.
+__device__ __forceinline__ void store_num_src(int64_t *sizes, int64_t *next_num_dst, int64_t num_src, int64_t most) {
+    num_src = num_src < most ? num_src : most;
     sizes[1] = num_src;
     if (next_num_dst) *next_num_dst = num_src;
 }
 
-// The ids staged in LDS, ascending, to the source list from place `base` on.  Four a thread at a time: the two row offsets of
+// The ids staged in LDS, ascending, to the source list from place `base` on, up to place `most`.  Four a thread at a time: the two row offsets of
 // an id are a random access, on a graph of 111 M nodes one that misses the address translation too.
 template <typename PtrT, typename IdxT>
-__device__ __forceinline__ void store_staged(int32_t *staged, int total, int64_t base, IdxT *__restrict__ src_ids, int32_t *__restrict__ local_of,
-                                             int32_t pos_base, const NewRows<PtrT> &next, int *lds) {
+__device__ __forceinline__ void store_staged(int32_t *staged, int total, int64_t base, int64_t most, IdxT *__restrict__ src_ids,
+                                             int32_t *__restrict__ local_of, int32_t pos_base, const NewRows<PtrT> &next, int *lds) {
     constexpr int U = 4;
+    if (base + total > most) total = base < most ? static_cast<int>(most - base) : 0;      // workgroup-uniform
     int hubs = 0;
     for (int k0 = threadIdx.x; k0 < total; k0 += U * kBlock) {
         int32_t v[U];
@@ -1160,7 +1165,7 @@ __device__ __forceinline__ void store_staged(int32_t *staged, int total, int64_t
 template <typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_bitmap_emit4(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_vals, int scanned,
-               int64_t *__restrict__ sizes, int64_t *__restrict__ next_num_dst, IdxT *__restrict__ src_ids,
+               int64_t *__restrict__ sizes, int64_t *__restrict__ next_num_dst, int64_t most, IdxT *__restrict__ src_ids,
                int32_t *__restrict__ local_of, int32_t pos_base) {
     __shared__ int lds[kWavesPerBlock];
     const int tile_base = scanned ? tile_vals[blockIdx.x] : tiles_before(tile_vals, lds);
@@ -1170,7 +1175,7 @@ k_bitmap_emit4(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_v
     int total;
     int ex = block_excl_scan<kWavesPerBlock>(c, &total, lds);
     const int64_t num_dst = sizes[0];
-    if (!scanned && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) store_num_src(sizes, next_num_dst, num_dst + tile_base + total);
+    if (!scanned && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) store_num_src(sizes, next_num_dst, num_dst + tile_base + total, most);
     if (c == 0) return;
     int64_t pos = num_dst + tile_base + ex;
     uint32_t words[4] = {w.x, w.y, w.z, w.w};
@@ -1181,8 +1186,10 @@ k_bitmap_emit4(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_v
             int b = __ffs(bits) - 1;
             bits &= bits - 1;
             int32_t v = static_cast<int32_t>((w0 + q) * 32 + b);
-            src_ids[pos] = static_cast<IdxT>(v);
-            local_of[v] = pos_base + static_cast<int32_t>(pos);
+            if (pos < most) {
+                src_ids[pos] = static_cast<IdxT>(v);
+                local_of[v] = pos_base + static_cast<int32_t>(pos);
+            }
             ++pos;
         }
     }
@@ -1192,7 +1199,7 @@ k_bitmap_emit4(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_v
 template <typename PtrT, typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_bitmap_emit1(uint32_t *__restrict__ bitmap, const uint32_t *__restrict__ except, const int32_t *__restrict__ tile_vals, int scanned,
-               int64_t *__restrict__ sizes, int64_t *__restrict__ next_num_dst, IdxT *__restrict__ src_ids,
+               int64_t *__restrict__ sizes, int64_t *__restrict__ next_num_dst, int64_t most, IdxT *__restrict__ src_ids,
                int32_t *__restrict__ local_of, int32_t pos_base, NewRows<PtrT> next) {
     __shared__ int lds[kWavesPerBlock];
     __shared__ int32_t staged[kBlock * 32];                // every id of the tile, ascending
@@ -1203,7 +1210,7 @@ k_bitmap_emit1(uint32_t *__restrict__ bitmap, const uint32_t *__restrict__ excep
     int total;
     int ex = block_excl_scan<kWavesPerBlock>(c, &total, lds);
     const int64_t num_dst = sizes[0];
-    if (!scanned && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) store_num_src(sizes, next_num_dst, num_dst + tile_base + total);
+    if (!scanned && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) store_num_src(sizes, next_num_dst, num_dst + tile_base + total, most);
     if (c || except) bitmap[w0] = 0;                       // (seeds are marked too)
     if (total == 0) return;                                // workgroup-uniform
     if (c) {
@@ -1215,7 +1222,7 @@ k_bitmap_emit1(uint32_t *__restrict__ bitmap, const uint32_t *__restrict__ excep
         }
     }
     __syncthreads();
-    store_staged(staged, total, num_dst + tile_base, src_ids, local_of, pos_base, next, lds);
+    store_staged(staged, total, num_dst + tile_base, most, src_ids, local_of, pos_base, next, lds);
 }
 
 // Small bitmaps (at most kSelfCountTiles tiles of 256 words, i.e. graphs of up to half a million
@@ -1228,7 +1235,7 @@ constexpr int kRecordTiles = 384;
 template <typename PtrT, typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_emit_offsets(const uint32_t *__restrict__ bitmap, const uint32_t *__restrict__ except, int bitmap_tiles, int64_t *sizes, int64_t *__restrict__ next_num_dst,
-               IdxT *__restrict__ src_ids, int32_t *__restrict__ local_of, int32_t pos_base, const int32_t *__restrict__ row_deg, int fanout,
+               int64_t most, IdxT *__restrict__ src_ids, int32_t *__restrict__ local_of, int32_t pos_base, const int32_t *__restrict__ row_deg, int fanout,
                const int32_t *__restrict__ row_tile_vals, int rows_scanned, int32_t *__restrict__ indptr,
                const int32_t *__restrict__ seed_flags, int row_tiles, NewRows<PtrT> next) {
     __shared__ int lds[kWavesPerBlock];
@@ -1273,7 +1280,7 @@ k_emit_offsets(const uint32_t *__restrict__ bitmap, const uint32_t *__restrict__
     int total;
     int ex = block_excl_scan<kWavesPerBlock>(c, &total, lds);
     const int64_t num_dst = sizes[0];
-    if (tile == bitmap_tiles - 1 && threadIdx.x == 0) store_num_src(sizes, next_num_dst, num_dst + tile_base + total);
+    if (tile == bitmap_tiles - 1 && threadIdx.x == 0) store_num_src(sizes, next_num_dst, num_dst + tile_base + total, most);
     if (total == 0) return;                                // workgroup-uniform
     if (c) {
         const int32_t v0 = static_cast<int32_t>(w0 * 32);
@@ -1284,7 +1291,7 @@ k_emit_offsets(const uint32_t *__restrict__ bitmap, const uint32_t *__restrict__
         }
     }
     __syncthreads();
-    store_staged(staged, total, num_dst + tile_base, src_ids, local_of, pos_base, next, lds);
+    store_staged(staged, total, num_dst + tile_base, most, src_ids, local_of, pos_base, next, lds);
 }
 
 __global__ void __launch_bounds__(kBlock)
@@ -1399,6 +1406,9 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
         const int64_t need_nnz = need_dst * k;
         const int row_tiles = tiles_of(need_dst);
         const int64_t next_dst = std::max(need_dst, std::min<int64_t>(g->num_nodes, need_dst + need_nnz));
+        // Where repeated seeds leave more sources than the bound, an inner block's end there, the next block's scratch being sized by
+        // it, the outermost one's with the room that there is.
+        const int64_t most_src = l > 0 ? next_dst : std::min(b.cap_src, ctx->max_src);
         // marks of this block, and the other half of the words, which the side work clears meanwhile, see k_emit_offsets
         uint32_t *bitmap = ctx->bitmap + (self_count ? (l & 1) * ctx->bitmap_words : 0);
 
@@ -1469,7 +1479,7 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
 
         if (use_hash) {
             rc = hash_dedup_block(ctx, nbr, need_nnz, g->num_nodes, g->idx_type, b.src_ids, b.sizes,
-                                  l > 0 ? blocks[l - 1].sizes : nullptr, b.indices, s);
+                                  l > 0 ? blocks[l - 1].sizes : nullptr, most_src, b.indices, s);
             if (rc != MQG_OK) return rc;
             need_dst = next_dst;
             if (l > 0) MQG_LAUNCH(ctx, "k_row_info", s, (k_row_info<PtrT, IdxT><<<tiles_of(need_dst), kBlock, 0, s>>>(row_info_args(l - 1, need_dst))));
@@ -1483,7 +1493,7 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
         if (self_count) {
             // indptr from the row tile sums and the new sources from the bitmap, one launch
             MQG_LAUNCH(ctx, "k_emit_offsets", s,
-                       (k_emit_offsets<PtrT, IdxT><<<bitmap_tiles + row_tiles, kBlock, 0, s>>>(bitmap, except, bitmap_tiles, b.sizes, next_num_dst, src_ids,
+                       (k_emit_offsets<PtrT, IdxT><<<bitmap_tiles + row_tiles, kBlock, 0, s>>>(bitmap, except, bitmap_tiles, b.sizes, next_num_dst, most_src, src_ids,
                                                                                               ctx->local_of, pos_base, ctx->row_deg, k, ctx->tile_vals, rows_scanned,
                                                                                               b.indptr, seed_flags, row_tiles, next)));
         } else {
@@ -1498,14 +1508,14 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
                                                                                           seed_flags, row_tiles, bitmap, except, ctx->bitmap_tile_vals)));
             }
             const int bits_scanned = bitmap_tiles > kSelfPrefixTiles ? 1 : 0;
-            if (bits_scanned) rc = launch_scan_tiles(ctx, ctx->bitmap_tile_vals, bitmap_tiles, &b.sizes[0], &b.sizes[1], next_num_dst, s, "k_scan_tiles(bitmap)");
+            if (bits_scanned) rc = launch_scan_tiles(ctx, ctx->bitmap_tile_vals, bitmap_tiles, &b.sizes[0], &b.sizes[1], next_num_dst, s, "k_scan_tiles(bitmap)", most_src);
             if (rc != MQG_OK) return rc;
             if (bitmap_wpt == 1) {
                 MQG_LAUNCH(ctx, "k_bitmap_emit", s,
-                           (k_bitmap_emit1<PtrT, IdxT><<<bitmap_tiles, kBlock, 0, s>>>(bitmap, except, ctx->bitmap_tile_vals, bits_scanned, b.sizes, next_num_dst, src_ids, ctx->local_of, pos_base, next)));
+                           (k_bitmap_emit1<PtrT, IdxT><<<bitmap_tiles, kBlock, 0, s>>>(bitmap, except, ctx->bitmap_tile_vals, bits_scanned, b.sizes, next_num_dst, most_src, src_ids, ctx->local_of, pos_base, next)));
             } else {
                 MQG_LAUNCH(ctx, "k_bitmap_emit", s,
-                           (k_bitmap_emit4<IdxT><<<bitmap_tiles, kBlock, 0, s>>>(bitmap, ctx->bitmap_tile_vals, bits_scanned, b.sizes, next_num_dst, src_ids, ctx->local_of, pos_base)));
+                           (k_bitmap_emit4<IdxT><<<bitmap_tiles, kBlock, 0, s>>>(bitmap, ctx->bitmap_tile_vals, bits_scanned, b.sizes, next_num_dst, most_src, src_ids, ctx->local_of, pos_base)));
             }
         }
         const int relabel_grid = static_cast<int>(std::min<int64_t>(std::max<int64_t>(1, ceil_div(need_nnz, kBlock)), 4096));
@@ -1575,8 +1585,8 @@ int take_positions(mqg_ctx *ctx, int64_t count, hipStream_t s, int32_t *base, bo
 }
 
 int launch_scan_tiles(mqg_ctx *ctx, int32_t *vals, int64_t n, const int64_t *addend, int64_t *total_a,
-                      int64_t *total_b, hipStream_t s, const char *name) {
-    MQG_LAUNCH(ctx, name, s, (k_scan_tiles<<<1, 1024, 0, s>>>(vals, n, addend, total_a, total_b)));
+                      int64_t *total_b, hipStream_t s, const char *name, int64_t most) {
+    MQG_LAUNCH(ctx, name, s, (k_scan_tiles<<<1, 1024, 0, s>>>(vals, n, addend, total_a, total_b, most)));
     return MQG_OK;
 }
 

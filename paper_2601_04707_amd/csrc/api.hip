@@ -158,25 +158,28 @@ int mqg_ctx_create(mqg_ctx **out, const mqg_graph *g, int32_t max_seeds, const i
         return fail(nullptr, MQG_ERR_UNSUPPORTED, "mqg_ctx_create: more than 2^31 sampled edges per block");
     }
     c->bitmap_words = std::max<int64_t>(1, mqg::ceil_div(mqg::ceil_div(g->num_nodes, 32), mqg::kBitmapTileWords)) * mqg::kBitmapTileWords;
+    c->records_rows = c->bitmap_words <= mqg::kRecordTiles * mqg::kBlock;
     c->max_tiles = std::max<int64_t>(mqg::ceil_div(c->max_dst, mqg::kBlock), c->bitmap_words / mqg::kBlock) + 1;
 
     bool ok = true;
     ok = ok && dev_alloc(&c->local_of, c->num_nodes) == hipSuccess;
-    ok = ok && dev_alloc(&c->bitmap, 3 * c->bitmap_words) == hipSuccess;
+    const int64_t bitmaps = c->records_rows ? 3 : 1;
+    ok = ok && dev_alloc(&c->bitmap, bitmaps * c->bitmap_words) == hipSuccess;
     ok = ok && dev_alloc(&c->tile_vals, c->max_tiles) == hipSuccess;
     ok = ok && dev_alloc(&c->bitmap_tile_vals, c->max_tiles) == hipSuccess;
     ok = ok && dev_alloc(&c->row_start, c->max_dst) == hipSuccess;
     ok = ok && dev_alloc(&c->row_deg, c->max_dst) == hipSuccess;
-    int64_t all_nnz = 0;
-    for (int l = 0; l < L; ++l) all_nnz += c->bound_nnz[l];
-    ok = ok && dev_alloc(reinterpret_cast<int32_t **>(&c->nbr), all_nnz) == hipSuccess;
+    c->nbr_room = c->max_nnz;
+    if (c->records_rows)
+        for (int l = 1; l < L; ++l) c->nbr_room = std::max(c->nbr_room, c->bound_nnz[l - 1] + c->bound_nnz[l] + 32);
+    ok = ok && dev_alloc(&c->nbr, c->nbr_room) == hipSuccess;
     ok = ok && dev_alloc(&c->heavy_rows, c->max_dst) == hipSuccess;
     ok = ok && dev_alloc(&c->heavy_count, MQG_MAX_LAYERS + 1) == hipSuccess;
     ok = ok && dev_alloc(&c->hit_list, c->max_src) == hipSuccess;
     ok = ok && dev_alloc(&c->miss_list, c->max_src) == hipSuccess;
     ok = ok && dev_alloc(&c->counters, 8) == hipSuccess;
     if (ok) ok = hipMemset(c->local_of, 0xFF, std::max<int64_t>(c->num_nodes, 1) * sizeof(int32_t)) == hipSuccess;
-    if (ok) ok = hipMemset(c->bitmap, 0, 3 * c->bitmap_words * sizeof(uint32_t)) == hipSuccess;
+    if (ok) ok = hipMemset(c->bitmap, 0, bitmaps * c->bitmap_words * sizeof(uint32_t)) == hipSuccess;
     if (ok) ok = hipMemset(c->counters, 0, 8 * sizeof(unsigned long long)) == hipSuccess;
     if (ok) ok = hipMemset(c->heavy_count, 0, (MQG_MAX_LAYERS + 1) * sizeof(int32_t)) == hipSuccess;
     if (ok) ok = hipDeviceSynchronize() == hipSuccess;

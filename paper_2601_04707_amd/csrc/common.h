@@ -17,6 +17,13 @@ constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kBitmapTileWords = 1024;   // the frontier bitmap is padded to a multiple of this many words
 constexpr int kCandidates = 256;         // per-wavefront candidate slots of the threshold selection
 
+// Graphs of up to this many bitmap tiles of kBlock words (3 M nodes): in sampling, the launch that lists new sources records
+// their rows, and the launch that samples the next block relabels the one before, which takes three bitmaps and places for two
+// blocks' neighbours.  Every tile with hubs adds to the list's count, one after the other, 13 ns each: above, the row information
+// goes with the relabel, in a launch of its own, and one of each is enough (recorded and not, batches of 1,024 and fanouts 15, 10, 5: 1 M
+// nodes, 123 tiles, 88 and 94 us, 3 M 107.0 and 108.2, 4 M 105.6 and 103.7, 8 M 103 and 96, 111 M 179 and 151).
+constexpr int kRecordTiles = 384;
+
 // Ping-pong buffers of the radix sort (see radix.h)
 struct RadixBufs {
     uint32_t *keys[2] = {nullptr, nullptr};     // [n_cap] each
@@ -78,16 +85,18 @@ struct mqg_ctx {
     // scratch (device)
     int32_t *local_of = nullptr;         // [num_nodes] position of a node in the current source list plus the call's offset; less if absent
     int64_t pos_next = 0;                // offset of the next call's positions (take_positions)
-    uint32_t *bitmap = nullptr;          // [3 * bitmap_words] nodes first seen in the current layer; small graphs take two thirds in turn, the last one is the seeds'
+    uint32_t *bitmap = nullptr;          // [bitmap_words] nodes first seen in the current layer; with records_rows three of them: two in turn, and the seeds'
     int64_t bitmap_words = 0;            // padded to a multiple of kBitmapTileWords
+    bool records_rows = false;           // see kRecordTiles
     int32_t *tile_vals = nullptr;        // [max_tiles] per-tile sums of the rows, then their exclusive scan
     int32_t *bitmap_tile_vals = nullptr; // [max_tiles] the same for the tiles of the bitmap
     int64_t max_tiles = 0;
     int64_t *row_start = nullptr;        // [max_dst] first adjacency slot of each destination
     int32_t *row_deg = nullptr;          // [max_dst] degree of each destination
-    void *nbr = nullptr;                 // [sum of bound_nnz] sampled neighbours of every block, global ids, 32-bit
+    int32_t *nbr = nullptr;              // [nbr_room] sampled neighbours of the current block, with records_rows of the one before it, too
+    int64_t nbr_room = 0;
     int32_t *heavy_rows = nullptr;       // [max_dst] destinations whose degree exceeds heavy_degree
-    int32_t *heavy_count = nullptr;      // [MQG_MAX_LAYERS] their number, per block; [MQG_MAX_LAYERS] seed-check flags
+    int32_t *heavy_count = nullptr;      // [MQG_MAX_LAYERS] their number, per block (records_rows: the first is that of all blocks); [MQG_MAX_LAYERS] seed-check flags
     int2 *hit_list = nullptr;            // [max_src] (output row, cache slot)
     int2 *miss_list = nullptr;           // [max_src] (output row, node id)
     unsigned long long *counters = nullptr;  // [8] kCount* in gather.hip

@@ -1231,7 +1231,6 @@ k_bitmap_emit1(uint32_t *__restrict__ bitmap, const uint32_t *__restrict__ excep
 // the relabel launch that follows.  The same launch turns the row tile sums into indptr (the
 // workgroups past the bitmap's tiles), as k_offsets_count does on larger graphs.
 constexpr int kSelfCountTiles = 64;
-constexpr int kRecordTiles = 384;
 template <typename PtrT, typename IdxT>
 __global__ void __launch_bounds__(kBlock)
 k_emit_offsets(const uint32_t *__restrict__ bitmap, const uint32_t *__restrict__ except, int bitmap_tiles, int64_t *sizes, int64_t *__restrict__ next_num_dst,
@@ -1346,7 +1345,6 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
     const PtrT *row_ptr = static_cast<const PtrT *>(g->row_ptr);
     const IdxT *col_idx = static_cast<const IdxT *>(g->col_idx);
     const IdxT *seeds = static_cast<const IdxT *>(seeds_v);
-    int32_t *nbr = static_cast<int32_t *>(ctx->nbr);
     const uint64_t seed_hash = host_mix64(rng_seed + kGolden);
 
     const bool use_hash = ctx->dedup_hash;
@@ -1363,11 +1361,7 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
     const bool self_count = !use_hash && bitmap_wpt == 1 && bitmap_tiles <= kSelfCountTiles;    // see k_emit_offsets
     // (rows that are no hubs are walked in one range of 2^30 slots)
     const int heavy_degree = ctx->force_slow_select ? 0x7FFFFFFF : std::min(ctx->heavy_degree, 1 << 30);
-    // Bitmaps of few tiles: the launch that lists new sources records their rows, and the sampling launch relabels (SideWork).
-    // Every tile with hubs adds to the list's count, one after the other, 13 ns each: from kRecordTiles on the row information goes
-    // with the relabel, in a launch of its own (recorded and not, batches of 1,024 and fanouts 15, 10, 5: 1 M nodes, 123 tiles, 88 and
-    // 94 us, 3 M 107.0 and 108.2, 4 M 105.6 and 103.7, 8 M 103 and 96, 111 M 179 and 151).
-    const bool one_list = !use_hash && bitmap_tiles <= kRecordTiles;       // of hubs for all blocks: they stay destinations
+    const bool one_list = !use_hash && ctx->records_rows;                  // of hubs for all blocks: they stay destinations
     auto hub_list = [&](int l) {
         return HubList{ctx->heavy_rows, ctx->heavy_count + (one_list ? 0 : l), heavy_degree};
     };
@@ -1405,6 +1399,9 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
         IdxT *src_ids = static_cast<IdxT *>(b.src_ids);
         const int64_t need_nnz = need_dst * k;
         const int row_tiles = tiles_of(need_dst);
+        // where a block is relabelled while the next one is sampled, they take the two ends of the room in turn (two neighbouring blocks
+        // fit it side by side), at whole lines
+        int32_t *nbr = ctx->nbr + (one_list && (l & 1) ? (ctx->nbr_room - need_nnz) & ~int64_t(31) : 0);
         const int64_t next_dst = std::max(need_dst, std::min<int64_t>(g->num_nodes, need_dst + need_nnz));
         // Where repeated seeds leave more sources than the bound, an inner block's end there, the next block's scratch being sized by
         // it, the outermost one's with the room that there is.
@@ -1540,7 +1537,6 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
             MQG_LAUNCH(ctx, "k_relabel", s, (k_relabel<<<relabel_grid, kBlock, 0, s>>>(nbr, b.sizes, b.indptr, k, ctx->local_of, pos_base, b.indices,
                                                                                        clear, ctx->bitmap_words, ctx->heavy_count)));
         }
-        nbr += need_nnz;                                   // the next block is sampled while this one's are relabelled
         need_dst = next_dst;
     }
     if (take_back) {

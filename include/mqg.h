@@ -433,16 +433,16 @@ int mqg_select_smallest_keys(mqg_ctx *ctx, const uint64_t *keys_dev, int64_t n, 
  * Sec. III-A: s_node neighbours of a node drawn uniformly, here the k smallest
  * random keys): among `count` candidates, each a (key, slot word) pair, the k
  * first in the order (bit 31 of the slot word if `prioritised`, key, low 31
- * bits of the slot word) are chosen.  Not prioritised, by the bound on the
- * keys' upper 31 bits that the sampling kernels look for; where there is none
- * (there they take the k smallest one after the other), and prioritised, by a
- * binary radix select on wavefront ballots.  Exposed so that a test can feed it
- * keys with ties.
+ * bits of the slot word) are chosen.  As the sampling kernels do it: by a bound
+ * on the keys' upper 31 bits that exactly k lie below (prioritised: of the
+ * candidates that compete, if those without bit 31 are fewer than k the others,
+ * for the places that these leave), and where equal upper bits leave none, one
+ * after the other by whole keys.  Exposed so that a test can feed it keys with
+ * ties.
  *   keys_dev, slot_words_dev  device [count], 1 <= k <= count <= 256
  *   ordered         non-zero: the candidates are stored in ascending slot
- *                   order (as the one-wavefront-per-row path stores them), so
- *                   equal keys are resolved by position; zero: by slot value
- *                   (the hub path, whose candidates arrive in any order)
+ *                   order, so equal keys are resolved by position; zero: by
+ *                   slot value
  *   out_mask_dev    device [8] words: bit c of the 256-bit mask = candidate c chosen
  */
 int mqg_select_row_candidates(mqg_ctx *ctx, const uint64_t *keys_dev, const uint32_t *slot_words_dev,

@@ -480,36 +480,6 @@ __device__ __forceinline__ int hub_candidates(uint64_t hv, int d, uint32_t limit
     return cnt;
 }
 
-// lexicographic (key, slot) order
-__device__ __forceinline__ bool pair_less(uint64_t ka, int sa, uint64_t kb, int sb) {
-    return ka < kb || (ka == kb && sa < sb);
-}
-
-// Candidates 0..cnt of a row in LDS (key, slot; bit 31 of the slot word = comes after every
-// unmarked candidate, PRIO only).  Picks the k first in the sampling order and returns, per chunk
-// of 64 candidates, the chosen lanes; slot[] gets each lane's slot words.  ORDERED: the candidates
-// are stored in ascending slot order, so equal keys need no second key.
-template <int NCH, bool PRIO, bool ORDERED, typename SlotT>
-__device__ __forceinline__ void select_candidates(const uint64_t *ck, const SlotT *cs, int cnt, int k,
-                                                  uint32_t (&slot)[NCH], uint64_t (&sel)[NCH], int top = 31) {
-    const int lane = lane_id();
-    uint64_t key[NCH], late[NCH], cand[NCH];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        const int ci = c * kWave + lane;
-        const bool valid = ci < cnt;
-        key[c] = valid ? ck[ci] : 0;
-        slot[c] = valid ? static_cast<uint32_t>(cs[ci]) : 0u;
-        const int left = cnt - c * kWave;
-        cand[c] = left <= 0 ? 0 : low_lanes(left);
-        late[c] = PRIO ? ballot64((slot[c] >> 31) != 0) : 0;
-    }
-    uint32_t tie[NCH];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) tie[c] = slot[c] & 0x7FFFFFFFu;
-    wave_select_smallest<NCH, PRIO, !ORDERED>(key, late, tie, cand, k, sel, top);
-}
-
 // The chosen of candidates that are in no particular order: their slots are listed in sel_slot (LDS, 64
 // entries) and emitted in ascending order.
 template <int NCH, typename IdxT>
@@ -532,80 +502,6 @@ __device__ __forceinline__ void emit_by_slot(const uint32_t (&slot)[NCH], const 
     if (lane < k) emit_neighbour(col_idx, start, my_slot, out_base + rank, a);
 }
 
-// The per-row selection on caller-supplied candidates (mqg_select_row_candidates): one wavefront; the selection
-// by whole keys, or, not prioritised, first the bound on the keys' upper words that k_sample looks for.
-template <bool PRIO, bool ORDERED>
-__global__ void __launch_bounds__(kWave)
-k_select_candidates(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ slot_words, int cnt, int k,
-                    uint32_t *__restrict__ out_mask) {
-    constexpr int NCH = kCandidates / kWave;
-    uint32_t slot[NCH];
-    uint64_t sel[NCH];
-    uint32_t word[NCH], bound = 0;
-    if (!PRIO) {
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) word[c] = c * kWave + lane_id() < cnt ? static_cast<uint32_t>(keys[c * kWave + lane_id()] >> 33) : kNoWord;
-        bound = word_bound(word, k, key_gap(cnt));
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) sel[c] = ballot64(word[c] < bound);
-    }
-    if (bound == 0) select_candidates<NCH, PRIO, ORDERED>(keys, slot_words, cnt, k, slot, sel);
-    if (lane_id() == 0) {
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            out_mask[2 * c] = static_cast<uint32_t>(sel[c]);
-            out_mask[2 * c + 1] = static_cast<uint32_t>(sel[c] >> 32);
-        }
-    }
-}
-
-// Unconditional selection: k rounds, each finding the smallest (key, slot) pair above the
-// previous round's.  O(k*d/64) key evaluations; used when the threshold pass cannot be
-// trusted (fewer than k or more than kCandidates keys under the threshold) and in tests.
-template <typename IdxT>
-__device__ void select_by_repeated_min(const IdxT *__restrict__ col_idx, int64_t start, int d, int k,
-                                       uint64_t hv, int32_t out_base, const SampleArgs &a) {
-    const int lane = lane_id();
-    const RowKeys key_of(hv);
-    uint64_t prev_key = 0;
-    int prev_slot = -1;
-    int my_slot = -1;                                // lane r keeps the r-th selected slot
-    for (int r = 0; r < k; ++r) {
-        uint64_t best_key = kMaxKey;
-        int best_slot = 0x7FFFFFFF;
-        for (int base = 0; base < d; base += kWave) {
-            int j = base + lane;
-            if (j < d) {
-                uint64_t key = key_of(j);
-                bool above = (r == 0) || pair_less(prev_key, prev_slot, key, j);
-                if (above && pair_less(key, j, best_key, best_slot)) {
-                    best_key = key;
-                    best_slot = j;
-                }
-            }
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            uint64_t ok = __shfl_xor(best_key, off, 64);
-            int os = __shfl_xor(best_slot, off, 64);
-            if (pair_less(ok, os, best_key, best_slot)) {
-                best_key = ok;
-                best_slot = os;
-            }
-        }
-        prev_key = best_key;
-        prev_slot = best_slot;
-        if (lane == r) my_slot = best_slot;
-    }
-    // order the k chosen slots ascending
-    int rank = 0;
-    for (int t = 0; t < k; ++t) {
-        int other = static_cast<int>(readlane32(static_cast<uint32_t>(my_slot), t));
-        rank += (other < my_slot) ? 1 : 0;
-    }
-    if (lane < k) emit_neighbour(col_idx, start, my_slot, out_base + rank, a);
-}
-
 // ------------------------------------------------------------------------------------------
 // Cache-prioritised selection (the paper's Sec. I on global neighbour sampling: neighbours that are
 // in the feature cache are preferred, so that fewer distinct uncached rows enter a mini-batch).
@@ -617,60 +513,63 @@ struct PrioArgs {
     const int32_t *prio_count;
 };
 
-__device__ __forceinline__ bool prio_less(bool ua, uint64_t ka, int sa, bool ub, uint64_t kb, int sb) {
-    return ua != ub ? !ua : pair_less(ka, sa, kb, sb);
-}
-
 template <typename IdxT>
 __device__ __forceinline__ bool is_cached(const IdxT *__restrict__ row, int j, const uint32_t *__restrict__ prio) {
     const uint32_t u = static_cast<uint32_t>(row[j]);
     return (prio[u >> 5] >> (u & 31)) & 1u;
 }
 
-// k rounds of wave-wide minimum extraction in the (not cached, key, slot) order; unconditional.
-template <typename IdxT>
-__device__ void select_by_repeated_min_prio(const IdxT *__restrict__ col_idx, int64_t start, int d, int k, uint64_t hv,
-                                            int32_t out_base, const SampleArgs &a, const uint32_t *__restrict__ prio) {
-    const int lane = lane_id();
-    const RowKeys key_of(hv);
-    const IdxT *row = col_idx + start;
-    bool prev_unc = false;
-    uint64_t prev_key = 0;
-    int prev_slot = -1;
-    int my_slot = -1;
+// One of those that a selection chooses from: first those that are not late (PRIO only), then by key, equal keys by tie.
+template <typename TieT>
+struct Ranked {
+    bool late;
+    uint64_t key;
+    TieT tie;
+    template <bool PRIO>
+    __device__ __forceinline__ bool before(const Ranked &o) const {
+        const bool less = key < o.key || (key == o.key && tie < o.tie);
+        return PRIO && late != o.late ? !late : less;
+    }
+};
+
+// Unconditional selection of the first k of d: k rounds, each of which finds the first one, at(j), after the previous round's,
+// and takes it, take(round, it).  O(k*d/64) evaluations of at.  (last: not before any.)
+template <bool PRIO, typename TieT, typename At, typename Take>
+__device__ __forceinline__ void take_one_by_one(int d, int k, const Ranked<TieT> &last, const At &at, const Take &take) {
+    Ranked<TieT> prev{};
     for (int r = 0; r < k; ++r) {
-        bool best_unc = true;
-        uint64_t best_key = kMaxKey;
-        int best_slot = 0x7FFFFFFF;
-        for (int base = 0; base < d; base += kWave) {
-            int j = base + lane;
-            if (j < d) {
-                const uint64_t key = key_of(j);
-                const bool unc = !is_cached(row, j, prio);
-                const bool above = (r == 0) || prio_less(prev_unc, prev_key, prev_slot, unc, key, j);
-                if (above && prio_less(unc, key, j, best_unc, best_key, best_slot)) {
-                    best_unc = unc;
-                    best_key = key;
-                    best_slot = j;
-                }
+        Ranked<TieT> best = last;
+        uint32_t j = lane_id();
+        for (int left = d; left > 0; left -= kWave, j += kWave) {
+            if (lane_id() < left) {
+                const Ranked<TieT> v = at(static_cast<int>(j));
+                if ((r == 0 || prev.template before<PRIO>(v)) && v.template before<PRIO>(best)) best = v;
             }
         }
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) {
-            const uint64_t ok = __shfl_xor(best_key, off, 64);
-            const int os = __shfl_xor(best_slot, off, 64);
-            const bool ou = __shfl_xor(static_cast<int>(best_unc), off, 64) != 0;
-            if (prio_less(ou, ok, os, best_unc, best_key, best_slot)) {
-                best_unc = ou;
-                best_key = ok;
-                best_slot = os;
-            }
+            Ranked<TieT> o;
+            o.late = PRIO && __shfl_xor(static_cast<int>(best.late), off, 64) != 0;
+            o.key = __shfl_xor(best.key, off, 64);
+            o.tie = __shfl_xor(best.tie, off, 64);
+            if (o.template before<PRIO>(best)) best = o;
         }
-        prev_unc = best_unc;
-        prev_key = best_key;
-        prev_slot = best_slot;
-        if (lane == r) my_slot = best_slot;
+        prev = best;
+        take(r, best);
     }
+}
+
+// A row's k slots one by one, where the faster selections found no bound or too many or too few candidates, and in tests.
+template <bool PRIO, typename IdxT>
+__device__ void select_by_repeated_min(const IdxT *__restrict__ col_idx, int64_t start, int d, int k, uint64_t hv,
+                                       int32_t out_base, const SampleArgs &a, const uint32_t *__restrict__ prio) {
+    const int lane = lane_id();
+    const RowKeys key_of(hv);
+    int my_slot = -1;                                // lane r keeps the r-th selected slot
+    take_one_by_one<PRIO>(d, k, Ranked<int>{PRIO, kMaxKey, 0x7FFFFFFF},
+                          [&](int j) { return Ranked<int>{PRIO && !is_cached(col_idx + start, j, prio), key_of(j), j}; },
+                          [&](int r, const Ranked<int> &v) { if (lane == r) my_slot = v.tie; });
+    // order the k chosen slots ascending
     int rank = 0;
     for (int t = 0; t < k; ++t) {
         int other = static_cast<int>(readlane32(static_cast<uint32_t>(my_slot), t));
@@ -844,8 +743,7 @@ __device__ __forceinline__ void sample_hubs(const IdxT *__restrict__ col_idx, co
             }
             if (bound != 0) emit_by_slot<NCH>(slot, sel, k, lds.slot[wave], col_idx, start, out_base, a);
             // a list ran over, or equal words: practically never
-            else if constexpr (PRIO) select_by_repeated_min_prio(col_idx, start, d, k, hv, out_base, a, pa.prio);
-            else select_by_repeated_min(col_idx, start, d, k, hv, out_base, a);
+            else select_by_repeated_min<PRIO>(col_idx, start, d, k, hv, out_base, a, pa.prio);
         }
         if (SEEDS && threadIdx.x == 0) hubs.rows[atomicAdd(hubs.count, 1)] = row;     // the next blocks' too
         if (PRIO) __syncthreads();                         // the lists are the next hub's
@@ -886,6 +784,53 @@ __device__ __forceinline__ bool push_smallest(const Candidate *cand, int cnt, in
 #pragma unroll
     for (int c = 0; c < NCH; ++c) n = push_slots(word[c] < bound || sure[c], slot[c], r, held, n, pick);
     return true;
+}
+
+// The same for any number of candidates.
+template <bool PRIO>
+__device__ __forceinline__ bool push_candidates(const Candidate *cand, int cnt, int want, uint32_t gap, int r, int held, uint2 *pick, bool flagged, bool cached) {
+    if (cnt <= kWave) return push_smallest<1, PRIO>(cand, cnt, want, gap, r, held, pick, flagged, cached);
+    if (cnt <= 2 * kWave) return push_smallest<2, PRIO>(cand, cnt, want, gap, r, held, pick, flagged, cached);
+    return push_smallest<kCandidates / kWave, PRIO>(cand, cnt, want, gap, r, held, pick, flagged, cached);
+}
+
+// The selection that k_sample makes from a row's candidates, on candidates of the caller's (mqg_select_row_candidates), one wavefront: the
+// bound on the keys' upper words, and one by one where there is none.  A candidate's slot is its index here; late ones are those that are not cached.
+// The slot words tell equal keys apart (ordered: the indexes alone).
+template <bool PRIO>
+__global__ void __launch_bounds__(kWave)
+k_select_candidates(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ slot_words, int cnt, int k, int ordered,
+                    uint32_t *__restrict__ out_mask) {
+    __shared__ Candidate cand[kCandidates];
+    __shared__ uint2 pick[kCandidates];
+    __shared__ uint32_t mask[kCandidates / 32];
+    const int lane = lane_id();
+    if (lane < kCandidates / 32) mask[lane] = 0;
+    auto late = [&](int i) { return PRIO && (slot_words[i] >> 31) != 0; };
+    int hits = 0;
+    for (int base = 0; base < cnt; base += kWave) {
+        const int i = base + lane;
+        const bool live = i < cnt;
+        const bool hit = PRIO && live && !late(i);
+        if (live) cand[i] = Candidate{static_cast<uint32_t>(keys[i] >> 33), PRIO && !hit ? static_cast<int32_t>(static_cast<uint32_t>(i) | 0x80000000u) : i};
+        hits += popc64(ballot64(hit));
+    }
+    wave_lds_sync();
+    const Contest contest(PRIO, cnt, k, hits);
+    auto take = [&](uint32_t i) { (void)atomicOr(&mask[i >> 5], 1u << (i & 31)); };
+    if (push_candidates<PRIO>(cand, cnt, contest.want, key_gap(contest.pool), 0, 0, pick, hits > 0, contest.cached)) {
+        wave_lds_sync();
+        for (int i = lane; i < k; i += kWave) take(pick[i].x);
+    } else {
+        auto at = [&](int i) {
+            const uint64_t slot = ordered ? 0 : slot_words[i] & 0x7FFFFFFFu;
+            return Ranked<uint64_t>{late(i), keys[i], slot << 8 | static_cast<uint64_t>(i)};
+        };
+        take_one_by_one<PRIO>(cnt, k, Ranked<uint64_t>{PRIO, kMaxKey, ~uint64_t(0)}, at,
+                              [&](int, const Ranked<uint64_t> &v) { if (lane == 0) take(static_cast<uint32_t>(v.tie) & 0xFF); });
+    }
+    wave_lds_sync();
+    if (lane < kCandidates / 32) out_mask[lane] = mask[lane];
 }
 
 // The first hub_blocks workgroups take the hubs (they are dispatched first and run the longest; 1,024 of them
@@ -996,10 +941,7 @@ k_sample(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, Sam
                 int cnt = candidates(expect);
                 if (cnt < k) cnt = candidates(2 * expect + 32);
                 wave_lds_sync();
-                if (cnt < k || cnt > kCandidates) done = false;
-                else if (cnt <= kWave) done = push_smallest<1, PRIO>(cand, cnt, contest.want, gap, r, held, pick, flagged, contest.cached);
-                else if (cnt <= 2 * kWave) done = push_smallest<2, PRIO>(cand, cnt, contest.want, gap, r, held, pick, flagged, contest.cached);
-                else done = push_smallest<kCandidates / kWave, PRIO>(cand, cnt, contest.want, gap, r, held, pick, flagged, contest.cached);
+                done = cnt >= k && cnt <= kCandidates && push_candidates<PRIO>(cand, cnt, contest.want, gap, r, held, pick, flagged, contest.cached);
                 wave_lds_sync();                           // the candidates' place is the next row's
             }
             if (done) {
@@ -1007,8 +949,7 @@ k_sample(const IdxT *__restrict__ col_idx, const IdxT *__restrict__ dst_ids, Sam
             } else {
                 const int64_t start = static_cast<int64_t>(readlane64(static_cast<uint64_t>(my_start), r));
                 const int32_t out_base = static_cast<int32_t>(readlane32(static_cast<uint32_t>(my_out), r));
-                if constexpr (PRIO) select_by_repeated_min_prio(col_idx, start, d, k, readlane64(my_hv, r), out_base, a, pa.prio);
-                else select_by_repeated_min(col_idx, start, d, k, readlane64(my_hv, r), out_base, a);
+                select_by_repeated_min<PRIO>(col_idx, start, d, k, readlane64(my_hv, r), out_base, a, pa.prio);
             }
         }
         wave_lds_sync();
@@ -1597,10 +1538,8 @@ int run_sample_blocks(mqg_ctx *ctx, const mqg_graph *g, const void *seeds, int32
 
 int run_select_row_candidates(mqg_ctx *ctx, const uint64_t *keys, const uint32_t *slot_words, int32_t cnt, int32_t k,
                               int32_t prioritised, int32_t ordered, uint32_t *out_mask, hipStream_t s) {
-    if (prioritised && ordered) MQG_LAUNCH(ctx, "k_select_candidates", s, (k_select_candidates<true, true><<<1, kWave, 0, s>>>(keys, slot_words, cnt, k, out_mask)));
-    else if (prioritised) MQG_LAUNCH(ctx, "k_select_candidates", s, (k_select_candidates<true, false><<<1, kWave, 0, s>>>(keys, slot_words, cnt, k, out_mask)));
-    else if (ordered) MQG_LAUNCH(ctx, "k_select_candidates", s, (k_select_candidates<false, true><<<1, kWave, 0, s>>>(keys, slot_words, cnt, k, out_mask)));
-    else MQG_LAUNCH(ctx, "k_select_candidates", s, (k_select_candidates<false, false><<<1, kWave, 0, s>>>(keys, slot_words, cnt, k, out_mask)));
+    if (prioritised) MQG_LAUNCH(ctx, "k_select_candidates", s, (k_select_candidates<true><<<1, kWave, 0, s>>>(keys, slot_words, cnt, k, ordered, out_mask)));
+    else MQG_LAUNCH(ctx, "k_select_candidates", s, (k_select_candidates<false><<<1, kWave, 0, s>>>(keys, slot_words, cnt, k, ordered, out_mask)));
     return MQG_OK;
 }
 

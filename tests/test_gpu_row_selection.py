@@ -1,6 +1,6 @@
-"""The per-row selection of the sampling kernels (binary radix select on wavefront ballots) fed with
-crafted candidates through the C ABI: the chosen set must be the first k of a plain sort by
-(late flag, key, slot), also when many keys are exactly equal - a case that real 64-bit sampling
+"""The sampling kernels' selection from a row's candidates (a bound on the keys' upper words, in three forms by the number of
+candidates, and one by one where equal words leave no bound) fed with crafted candidates through the C ABI: the chosen set must be
+the first k of a plain sort by (late flag, key, slot), also when many keys are exactly equal - a case that real 64-bit sampling
 keys never produce, so the block parity tests cannot reach it."""
 import numpy as np
 import pytest
@@ -47,7 +47,7 @@ def key_sets(rng, n):
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 128, 129, 200, 256])
 @pytest.mark.parametrize("prioritised", [False, True])
 def test_selection_in_slot_order_with_ties(env, n, prioritised):
-    """Candidates stored in ascending slot order (the one-wavefront-per-row path)."""
+    """Candidates stored in ascending slot order."""
     m, ctx = env
     rng = np.random.default_rng(n * 2 + int(prioritised))
     slots = np.sort(rng.choice(5000, n, replace=False)).astype(np.int64)
@@ -62,7 +62,7 @@ def test_selection_in_slot_order_with_ties(env, n, prioritised):
 @pytest.mark.parametrize("n", [1, 64, 65, 130, 256])
 @pytest.mark.parametrize("prioritised", [False, True])
 def test_selection_of_unordered_candidates_with_ties(env, n, prioritised):
-    """Candidates in arrival order (the hub path): equal keys are resolved by slot value."""
+    """Candidates in any order: equal keys are resolved by slot value."""
     m, ctx = env
     rng = np.random.default_rng(1000 + n * 2 + int(prioritised))
     slots = rng.permutation(40000)[:n].astype(np.int64)
@@ -72,6 +72,31 @@ def test_selection_of_unordered_candidates_with_ties(env, n, prioritised):
             got = run(m, ctx, keys, slots, late, k, prioritised, ordered=False)
             want = expected(keys, slots, late, k, prioritised)
             assert np.array_equal(got, want), (name, n, k)
+
+
+@pytest.mark.parametrize("n", [2, 64, 65, 128, 256])
+@pytest.mark.parametrize("cached", [0, 1, 0.3, 0.9, None])
+def test_prioritised_selection_where_the_keys_are_not_spread_evenly(env, n, cached):
+    """Fewer, exactly as many and more cached candidates than places (None: all), whose words lie close together, far from the others',
+    or are all the same: the bound is looked for among those that compete only."""
+    m, ctx = env
+    rng = np.random.default_rng(7 * n + int(10 * (cached or 0)))
+    slots = rng.permutation(40000)[:n].astype(np.int64)
+    hits = n if cached is None else min(n, int(np.ceil(cached * n)) if cached < 1 else cached)
+    late = rng.permutation(np.arange(n) >= hits).astype(np.int64)
+    sets = {
+        "cached low": np.where(late, 2**31 - 1 - rng.integers(0, 4 * n, n), rng.integers(0, 3 * n, n)).astype(np.uint64) << np.uint64(33),
+        "cached high": np.where(late, rng.integers(0, 4 * n, n), 2**31 - 1 - rng.integers(0, 3 * n, n)).astype(np.uint64) << np.uint64(33),
+        "neighbouring words": rng.permutation(n).astype(np.uint64) + np.uint64(2**30) << np.uint64(33),
+        "one word": (np.uint64(5) << np.uint64(40)) + rng.integers(0, 2**33, n).astype(np.uint64),
+        "one key": np.full(n, 2**64 - 1, dtype=np.uint64),
+    }
+    for name, keys in sets.items():
+        for k in sorted({1, n // 2, min(n, 25), max(1, hits - 1), max(1, hits), min(n, hits + 1), n}):
+            for ordered in (False, True):
+                slot = np.sort(slots) if ordered else slots
+                got = run(m, ctx, keys, slot, late, k, True, ordered)
+                assert np.array_equal(got, expected(keys, slot, late, k, True)), (name, n, k, ordered)
 
 
 @pytest.mark.parametrize("n", [2, 64, 65, 256])

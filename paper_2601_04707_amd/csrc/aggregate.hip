@@ -593,8 +593,8 @@ k_permute_edges(const int32_t *__restrict__ perm, const int32_t *__restrict__ in
 // destination row; edge p = (v_i, v_j) gets deg(v_i)/n_i / sqrt((deg(v_i)+1)(deg(v_j)+1)), the
 // row's diagonal term is 1/(deg(v_i)+1).  Computed in double, rounded once to float.
 // Bound by the double division and square root, which a wavefront pays for whole, and by the chain of four loads: the row's and
-// its first edges' are under way together.  (A wavefront per row, one load after the other: 10 k rows of 25 edges 10.3 us, 7.0 so; whole
-// calls with their aggregations 1 to 4 % faster, the most at fanouts of 3 to 10.)
+// its first edges' are under way together.  (A wavefront per row, one load after the other: 10 k rows of 25 edges 10.3 us, 7.0 so.  Beside
+// the weighted sums and their backwards, 306 us, that is within the spread of the runs.)
 template <typename PtrT, typename IdxT, int LANES>
 __global__ void __launch_bounds__(kBlock)
 k_gcn_edge_weights(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ src_ids, const int32_t *__restrict__ indptr,
@@ -630,7 +630,9 @@ k_gcn_edge_weights(const PtrT *__restrict__ row_ptr, const IdxT *__restrict__ sr
 
 template <typename PtrT, typename IdxT>
 static int launch_gcn_edge_weights(mqg_ctx *ctx, const mqg_graph *g, const mqg_block *b, float *edge_w, float *self_w, hipStream_t s) {
-    // As many lanes as a row has edges at most, by the block's capacities (longer rows take several rounds).
+    // As many lanes as a row has edges at most, by the block's capacities: what the rows hold is known on the device only.  A block with
+    // room for more rows than its edges fill takes several rounds (64 edges a row: 10 k rows 7.7 us in eight, 6.6 in one; 300 rows 5.4 and
+    // 4.7), one with room for more edges leaves lanes idle, as a wavefront per row did (10 k rows of 25: 4.9 and 4.6).
     const int64_t most = b->cap_nnz / std::max<int64_t>(b->cap_dst, 1);
 #define MQG_GCNW(LANES)                                                                                                                \
     do {                                                                                                                               \

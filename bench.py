@@ -460,7 +460,9 @@ def run_workload(torch, np, mqg, synth, opts, name, *, cache_pct, in_flight, K, 
         "stage_kernel_sum_us_per_step": {"sample": round(sample_us, 1), "gather": round(gather_us, 1), "aggregate": round(agg_us, 1),
                                          "dedup_relabel_part_of_sample": round(dedup_us, 1),
                                          "note": "sums of the kernels' own times, each kernel between two events of its own "
-                                                 "(which add a few microseconds per launch)"},
+                                                 "(which add a few microseconds per launch).  On graphs of up to 3 M nodes the "
+                                                 "relabels of all blocks but the outermost run inside k_sample: they are in sample, "
+                                                 "not in dedup_relabel_part_of_sample"},
         "roofline": roofline, "roofline_host_link": host_link,
     }
 
@@ -496,10 +498,10 @@ def run_workload(torch, np, mqg, synth, opts, name, *, cache_pct, in_flight, K, 
 
     # ================================================================ the headline workload only
     # ---------------------------------------------------------------- sampling against its own bounds
-    # Integer ALU: one key costs 3 32-bit multiplies (quarter rate) and about 16 full-rate integer
-    # operations = 28 lane-cycles; the chip has 256 CUs x 4 SIMDs x 16 lanes at 2.4 GHz.
+    # Integer ALU: k_sample spends ten vector instructions on 64 keys of a long row, three of them 32-bit multiplies at a
+    # quarter of the rate = 19 lane-cycles a key; the chip has 256 CUs x 4 SIMDs x 16 lanes at 2.4 GHz.
     keys_per_step = keys_eval / max(keys_batches, 1)
-    alu_peak_keys = 256 * 4 * 16 * 2.4e9 / 28.0
+    alu_peak_keys = 256 * 4 * 16 * 2.4e9 / 19.0
     k_sample_us = kern.get("k_sample_prio" if opts.prioritise_cache else "k_sample", {}).get("us_per_step", 0.0)
     sampling = {
         "edges_per_s_sampling_alone": round(edges / K / max(chain[0], 1e-9) * 1e6, 1),

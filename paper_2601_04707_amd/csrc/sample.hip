@@ -1061,24 +1061,39 @@ __device__ __forceinline__ void store_num_src(int64_t *sizes, int64_t *next_num_
     if (next_num_dst) *next_num_dst = num_src;
 }
 
-// The ids staged in LDS, ascending, to the source list from place `base` on, up to place `most`.  (Four a thread at a time, for the random
-// reads of their row offsets: the listings of 2.4 M nodes and 290 k, 1 M and 1.3 M sources 8.5, 11.4 and 12.0 us, one at a time 8.2, 11.2 and 12.2.)
+// The ids staged in LDS, ascending, to the source list from place `base` on, up to place `most`.  Four a thread at a time: the two row offsets of
+// an id are a random access, on a graph of 111 M nodes one that misses the address translation too.
 template <typename PtrT, typename IdxT>
 __device__ __forceinline__ void store_staged(int32_t *staged, int total, int64_t base, int64_t most, IdxT *__restrict__ src_ids,
                                              int32_t *__restrict__ local_of, int32_t pos_base, const NewRows<PtrT> &next, int *lds) {
+    constexpr int U = 4;
     if (base + total > most) total = base < most ? static_cast<int>(most - base) : 0;      // workgroup-uniform
     int hubs = 0;
-    for (int k = threadIdx.x; k < total; k += kBlock) {
-        const int32_t v = staged[k];
-        src_ids[base + k] = static_cast<IdxT>(v);
-        local_of[v] = pos_base + static_cast<int32_t>(base + k);
+    for (int k0 = threadIdx.x; k0 < total; k0 += U * kBlock) {
+        int32_t v[U];
+        int64_t begin[U], degree[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = staged[k0 + u * kBlock < total ? k0 + u * kBlock : k0];
         if (next.row_ptr) {
-            const int64_t begin = static_cast<int64_t>(next.row_ptr[v]), degree = static_cast<int64_t>(next.row_ptr[int64_t(v) + 1]) - begin;
-            next.row_start[base + k] = begin;
-            next.row_deg[base + k] = static_cast<int32_t>(degree);
-            const int hub = degree > next.hubs.heavy_degree ? 1 : 0;
-            staged[k] = hub;                               // this thread's own entry
-            hubs += hub;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                begin[u] = static_cast<int64_t>(next.row_ptr[v[u]]);
+                degree[u] = static_cast<int64_t>(next.row_ptr[int64_t(v[u]) + 1]) - begin[u];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + u * kBlock;
+            if (k >= total) break;
+            src_ids[base + k] = static_cast<IdxT>(v[u]);
+            local_of[v[u]] = pos_base + static_cast<int32_t>(base + k);
+            if (next.row_ptr) {
+                next.row_start[base + k] = begin[u];
+                next.row_deg[base + k] = static_cast<int32_t>(degree[u]);
+                const int hub = degree[u] > next.hubs.heavy_degree ? 1 : 0;
+                staged[k] = hub;                           // this thread's own entry
+                hubs += hub;
+            }
         }
     }
     if (!next.row_ptr) return;

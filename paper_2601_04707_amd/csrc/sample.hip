@@ -1107,8 +1107,8 @@ __device__ __forceinline__ void store_staged(int32_t *staged, int total, int64_t
 // then bounds the sources however often seeds repeat.  (The test costs 0.3 us in each of the three listings of a graph of 111 M nodes, 9.7 us on average.)
 template <typename IdxT, bool BOUNDED>
 __global__ void __launch_bounds__(kBlock)
-k_bitmap_emit4(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_vals, int scanned,
-               int64_t *__restrict__ sizes, int64_t *__restrict__ next_num_dst, int64_t most, IdxT *__restrict__ src_ids,
+k_bitmap_emit4(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_vals, int scanned, int32_t most,
+               int64_t *__restrict__ sizes, int64_t *__restrict__ next_num_dst, IdxT *__restrict__ src_ids,
                int32_t *__restrict__ local_of, int32_t pos_base) {
     __shared__ int lds[kWavesPerBlock];
     const int tile_base = scanned ? tile_vals[blockIdx.x] : tiles_before(tile_vals, lds);
@@ -1141,8 +1141,8 @@ k_bitmap_emit4(uint32_t *__restrict__ bitmap, const int32_t *__restrict__ tile_v
 
 template <typename PtrT, typename IdxT>
 __global__ void __launch_bounds__(kBlock)
-k_bitmap_emit1(uint32_t *__restrict__ bitmap, const uint32_t *__restrict__ except, const int32_t *__restrict__ tile_vals, int scanned,
-               int64_t *__restrict__ sizes, int64_t *__restrict__ next_num_dst, int64_t most, IdxT *__restrict__ src_ids,
+k_bitmap_emit1(uint32_t *__restrict__ bitmap, const uint32_t *__restrict__ except, const int32_t *__restrict__ tile_vals, int scanned, int32_t most,
+               int64_t *__restrict__ sizes, int64_t *__restrict__ next_num_dst, IdxT *__restrict__ src_ids,
                int32_t *__restrict__ local_of, int32_t pos_base, NewRows<PtrT> next) {
     __shared__ int lds[kWavesPerBlock];
     __shared__ int32_t staged[kBlock * 32];                // every id of the tile, ascending
@@ -1176,8 +1176,8 @@ k_bitmap_emit1(uint32_t *__restrict__ bitmap, const uint32_t *__restrict__ excep
 constexpr int kSelfCountTiles = 64;
 template <typename PtrT, typename IdxT>
 __global__ void __launch_bounds__(kBlock)
-k_emit_offsets(const uint32_t *__restrict__ bitmap, const uint32_t *__restrict__ except, int bitmap_tiles, int64_t *sizes, int64_t *__restrict__ next_num_dst,
-               int64_t most, IdxT *__restrict__ src_ids, int32_t *__restrict__ local_of, int32_t pos_base, const int32_t *__restrict__ row_deg, int fanout,
+k_emit_offsets(const uint32_t *__restrict__ bitmap, const uint32_t *__restrict__ except, int bitmap_tiles, int32_t most, int64_t *sizes, int64_t *__restrict__ next_num_dst,
+               IdxT *__restrict__ src_ids, int32_t *__restrict__ local_of, int32_t pos_base, const int32_t *__restrict__ row_deg, int fanout,
                const int32_t *__restrict__ row_tile_vals, int rows_scanned, int32_t *__restrict__ indptr,
                const int32_t *__restrict__ seed_flags, int row_tiles, NewRows<PtrT> next) {
     __shared__ int lds[kWavesPerBlock];
@@ -1347,8 +1347,9 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
         int32_t *nbr = ctx->nbr + (one_list && (l & 1) ? (ctx->nbr_room - need_nnz) & ~int64_t(31) : 0);
         const int64_t next_dst = std::max(need_dst, std::min<int64_t>(g->num_nodes, need_dst + need_nnz));
         // Where repeated seeds leave more sources than the bound, an inner block's end there, the next block's scratch being sized by
-        // it, the outermost one's with the room that there is.
-        const int64_t most_src = l > 0 ? next_dst : std::min(b.cap_src, ctx->max_src);
+        // it, the outermost one's with the room that there is.  (32 bits, where the listings' arguments had a gap: as a 64-bit argument more
+        // it made each 0.25 us longer, 4.2 -> 4.5 us on 22 k nodes.)
+        const int32_t most_src = static_cast<int32_t>(l > 0 ? next_dst : std::min(b.cap_src, ctx->max_src));
         // marks of this block, and the other half of the words, which the side work clears meanwhile, see k_emit_offsets
         uint32_t *bitmap = ctx->bitmap + (self_count ? (l & 1) * ctx->bitmap_words : 0);
 
@@ -1433,7 +1434,7 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
         if (self_count) {
             // indptr from the row tile sums and the new sources from the bitmap, one launch
             MQG_LAUNCH(ctx, "k_emit_offsets", s,
-                       (k_emit_offsets<PtrT, IdxT><<<bitmap_tiles + row_tiles, kBlock, 0, s>>>(bitmap, except, bitmap_tiles, b.sizes, next_num_dst, most_src, src_ids,
+                       (k_emit_offsets<PtrT, IdxT><<<bitmap_tiles + row_tiles, kBlock, 0, s>>>(bitmap, except, bitmap_tiles, most_src, b.sizes, next_num_dst, src_ids,
                                                                                               ctx->local_of, pos_base, ctx->row_deg, k, ctx->tile_vals, rows_scanned,
                                                                                               b.indptr, seed_flags, row_tiles, next)));
         } else {
@@ -1452,12 +1453,12 @@ int sample_blocks_impl(mqg_ctx *ctx, const mqg_graph *g, const void *seeds_v, in
             if (rc != MQG_OK) return rc;
             if (bitmap_wpt == 1) {
                 MQG_LAUNCH(ctx, "k_bitmap_emit", s,
-                           (k_bitmap_emit1<PtrT, IdxT><<<bitmap_tiles, kBlock, 0, s>>>(bitmap, except, ctx->bitmap_tile_vals, bits_scanned, b.sizes, next_num_dst, most_src, src_ids, ctx->local_of, pos_base, next)));
+                           (k_bitmap_emit1<PtrT, IdxT><<<bitmap_tiles, kBlock, 0, s>>>(bitmap, except, ctx->bitmap_tile_vals, bits_scanned, most_src, b.sizes, next_num_dst, src_ids, ctx->local_of, pos_base, next)));
             } else {
                 const bool bounded = need_dst + need_nnz > g->num_nodes;
 #define MQG_EMIT4(BOUNDED)                                                                                                                   \
                 MQG_LAUNCH(ctx, "k_bitmap_emit", s,                                                                                          \
-                           (k_bitmap_emit4<IdxT, BOUNDED><<<bitmap_tiles, kBlock, 0, s>>>(bitmap, ctx->bitmap_tile_vals, bits_scanned, b.sizes, next_num_dst, most_src, src_ids, ctx->local_of, pos_base)))
+                           (k_bitmap_emit4<IdxT, BOUNDED><<<bitmap_tiles, kBlock, 0, s>>>(bitmap, ctx->bitmap_tile_vals, bits_scanned, most_src, b.sizes, next_num_dst, src_ids, ctx->local_of, pos_base)))
                 if (bounded) MQG_EMIT4(true);
                 else MQG_EMIT4(false);
 #undef MQG_EMIT4

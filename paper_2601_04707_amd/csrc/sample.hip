@@ -519,43 +519,90 @@ __device__ __forceinline__ bool is_cached(const IdxT *__restrict__ row, int j, c
     return (prio[u >> 5] >> (u & 31)) & 1u;
 }
 
-// One of those that a selection chooses from: first those that are not late (PRIO only), then by key, equal keys by tie.
-template <typename TieT>
-struct Ranked {
-    bool late;
-    uint64_t key;
-    TieT tie;
-    template <bool PRIO>
-    __device__ __forceinline__ bool before(const Ranked &o) const {
-        const bool less = key < o.key || (key == o.key && tie < o.tie);
-        return PRIO && late != o.late ? !late : less;
-    }
-};
+// lexicographic (key, slot) order
+__device__ __forceinline__ bool pair_less(uint64_t ka, int sa, uint64_t kb, int sb) {
+    return ka < kb || (ka == kb && sa < sb);
+}
 
-// Unconditional selection of the first k of d: k rounds, each of which finds the first one, at(j), after the previous round's,
-// and takes it, take(round, it).  O(k*d/64) evaluations of at.  (last: not before any.)
-template <bool PRIO, typename TieT, typename At, typename Take>
-__device__ __forceinline__ void take_one_by_one(int d, int k, const Ranked<TieT> &last, const At &at, const Take &take) {
-    Ranked<TieT> prev{};
+// Unconditional selection among d: k rounds, each finding the smallest (key, index) pair above the previous round's,
+// whose index it takes: take(round, index).  O(k*d/64) key evaluations.
+template <typename KeyAt, typename Take>
+__device__ __forceinline__ void take_one_by_one(int d, int k, const KeyAt &key_at, const Take &take) {
+    uint64_t prev_key = 0;
+    int prev_slot = -1;
     for (int r = 0; r < k; ++r) {
-        Ranked<TieT> best = last;
-        uint32_t j = lane_id();
-        for (int left = d; left > 0; left -= kWave, j += kWave) {
+        uint64_t best_key = kMaxKey;
+        int best_slot = 0x7FFFFFFF;
+        uint32_t next = lane_id();
+        for (int left = d; left > 0; left -= kWave, next += kWave) {
             if (lane_id() < left) {
-                const Ranked<TieT> v = at(static_cast<int>(j));
-                if ((r == 0 || prev.template before<PRIO>(v)) && v.template before<PRIO>(best)) best = v;
+                const int j = static_cast<int>(next);
+                const uint64_t key = key_at(j);
+                const bool above = (r == 0) || pair_less(prev_key, prev_slot, key, j);
+                if (above && pair_less(key, j, best_key, best_slot)) {
+                    best_key = key;
+                    best_slot = j;
+                }
             }
         }
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) {
-            Ranked<TieT> o;
-            o.late = PRIO && __shfl_xor(static_cast<int>(best.late), off, 64) != 0;
-            o.key = __shfl_xor(best.key, off, 64);
-            o.tie = __shfl_xor(best.tie, off, 64);
-            if (o.template before<PRIO>(best)) best = o;
+            const uint64_t ok = __shfl_xor(best_key, off, 64);
+            const int os = __shfl_xor(best_slot, off, 64);
+            if (pair_less(ok, os, best_key, best_slot)) {
+                best_key = ok;
+                best_slot = os;
+            }
         }
-        prev = best;
-        take(r, best);
+        prev_key = best_key;
+        prev_slot = best_slot;
+        take(r, best_slot);
+    }
+}
+
+__device__ __forceinline__ bool prio_less(bool ua, uint64_t ka, int sa, bool ub, uint64_t kb, int sb) {
+    return ua != ub ? !ua : pair_less(ka, sa, kb, sb);
+}
+
+// The same in the (late, key, index) order.
+template <typename KeyAt, typename LateAt, typename Take>
+__device__ __forceinline__ void take_one_by_one_prio(int d, int k, const KeyAt &key_at, const LateAt &late_at, const Take &take) {
+    bool prev_late = false;
+    uint64_t prev_key = 0;
+    int prev_slot = -1;
+    for (int r = 0; r < k; ++r) {
+        bool best_late = true;
+        uint64_t best_key = kMaxKey;
+        int best_slot = 0x7FFFFFFF;
+        uint32_t next = lane_id();
+        for (int left = d; left > 0; left -= kWave, next += kWave) {
+            if (lane_id() < left) {
+                const int j = static_cast<int>(next);
+                const uint64_t key = key_at(j);
+                const bool late = late_at(j);
+                const bool above = (r == 0) || prio_less(prev_late, prev_key, prev_slot, late, key, j);
+                if (above && prio_less(late, key, j, best_late, best_key, best_slot)) {
+                    best_late = late;
+                    best_key = key;
+                    best_slot = j;
+                }
+            }
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const uint64_t ok = __shfl_xor(best_key, off, 64);
+            const int os = __shfl_xor(best_slot, off, 64);
+            const bool ol = __shfl_xor(static_cast<int>(best_late), off, 64) != 0;
+            if (prio_less(ol, ok, os, best_late, best_key, best_slot)) {
+                best_late = ol;
+                best_key = ok;
+                best_slot = os;
+            }
+        }
+        prev_late = best_late;
+        prev_key = best_key;
+        prev_slot = best_slot;
+        take(r, best_slot);
     }
 }
 
@@ -565,10 +612,11 @@ __device__ void select_by_repeated_min(const IdxT *__restrict__ col_idx, int64_t
                                        int32_t out_base, const SampleArgs &a, const uint32_t *__restrict__ prio) {
     const int lane = lane_id();
     const RowKeys key_of(hv);
+    const IdxT *row = col_idx + start;
     int my_slot = -1;                                // lane r keeps the r-th selected slot
-    take_one_by_one<PRIO>(d, k, Ranked<int>{PRIO, kMaxKey, 0x7FFFFFFF},
-                          [&](int j) { return Ranked<int>{PRIO && !is_cached(col_idx + start, j, prio), key_of(j), j}; },
-                          [&](int r, const Ranked<int> &v) { if (lane == r) my_slot = v.tie; });
+    auto take = [&](int r, int slot) { if (lane == r) my_slot = slot; };
+    if constexpr (PRIO) take_one_by_one_prio(d, k, key_of, [&](int j) { return !is_cached(row, j, prio); }, take);
+    else take_one_by_one(d, k, key_of, take);
     // order the k chosen slots ascending
     int rank = 0;
     for (int t = 0; t < k; ++t) {
@@ -795,39 +843,48 @@ __device__ __forceinline__ bool push_candidates(const Candidate *cand, int cnt, 
 }
 
 // The selection that k_sample makes from a row's candidates, on candidates of the caller's (mqg_select_row_candidates), one wavefront: the
-// bound on the keys' upper words, and one by one where there is none.  A candidate's slot is its index here; late ones are those that are not cached.
-// The slot words tell equal keys apart (ordered: the indexes alone).
+// bound on the keys' upper words, and one by one where there is none.  Late candidates are those that are not cached.  The candidates are first
+// put in the order of their slot words' low 31 bits (ordered: they are), which tell equal keys apart, as a row's slots do.
 template <bool PRIO>
 __global__ void __launch_bounds__(kWave)
 k_select_candidates(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ slot_words, int cnt, int k, int ordered,
                     uint32_t *__restrict__ out_mask) {
+    __shared__ int from[kCandidates];                      // the caller's index of a candidate
     __shared__ Candidate cand[kCandidates];
     __shared__ uint2 pick[kCandidates];
     __shared__ uint32_t mask[kCandidates / 32];
     const int lane = lane_id();
     if (lane < kCandidates / 32) mask[lane] = 0;
-    auto late = [&](int i) { return PRIO && (slot_words[i] >> 31) != 0; };
+    for (int i = lane; i < cnt; i += kWave) {
+        const uint32_t slot = slot_words[i] & 0x7FFFFFFFu;
+        int rank = ordered ? i : 0;
+        for (int o = 0; o < cnt && !ordered; ++o) {
+            const uint32_t other = slot_words[o] & 0x7FFFFFFFu;
+            rank += other < slot || (other == slot && o < i) ? 1 : 0;
+        }
+        from[rank] = i;
+    }
+    wave_lds_sync();
+    auto key_at = [&](int j) { return keys[from[j]]; };
+    auto late_at = [&](int j) { return (slot_words[from[j]] >> 31) != 0; };
     int hits = 0;
     for (int base = 0; base < cnt; base += kWave) {
-        const int i = base + lane;
-        const bool live = i < cnt;
-        const bool hit = PRIO && live && !late(i);
-        if (live) cand[i] = Candidate{static_cast<uint32_t>(keys[i] >> 33), PRIO && !hit ? static_cast<int32_t>(static_cast<uint32_t>(i) | 0x80000000u) : i};
+        const int j = base + lane;
+        const bool hit = PRIO && j < cnt && !late_at(j);
+        if (j < cnt) cand[j] = Candidate{static_cast<uint32_t>(key_at(j) >> 33), PRIO && !hit ? static_cast<int32_t>(static_cast<uint32_t>(j) | 0x80000000u) : j};
         hits += popc64(ballot64(hit));
     }
     wave_lds_sync();
     const Contest contest(PRIO, cnt, k, hits);
-    auto take = [&](uint32_t i) { (void)atomicOr(&mask[i >> 5], 1u << (i & 31)); };
+    auto choose = [&](int j) { (void)atomicOr(&mask[from[j] >> 5], 1u << (from[j] & 31)); };
+    auto take = [&](int, int j) { if (lane == 0) choose(j); };
     if (push_candidates<PRIO>(cand, cnt, contest.want, key_gap(contest.pool), 0, 0, pick, hits > 0, contest.cached)) {
         wave_lds_sync();
-        for (int i = lane; i < k; i += kWave) take(pick[i].x);
+        for (int i = lane; i < k; i += kWave) choose(static_cast<int>(pick[i].x));
+    } else if constexpr (PRIO) {
+        take_one_by_one_prio(cnt, k, key_at, late_at, take);
     } else {
-        auto at = [&](int i) {
-            const uint64_t slot = ordered ? 0 : slot_words[i] & 0x7FFFFFFFu;
-            return Ranked<uint64_t>{late(i), keys[i], slot << 8 | static_cast<uint64_t>(i)};
-        };
-        take_one_by_one<PRIO>(cnt, k, Ranked<uint64_t>{PRIO, kMaxKey, ~uint64_t(0)}, at,
-                              [&](int, const Ranked<uint64_t> &v) { if (lane == 0) take(static_cast<uint32_t>(v.tie) & 0xFF); });
+        take_one_by_one(cnt, k, key_at, take);
     }
     wave_lds_sync();
     if (lane < kCandidates / 32) out_mask[lane] = mask[lane];

@@ -897,8 +897,8 @@ k_select_candidates(const uint64_t *__restrict__ keys, const uint32_t *__restric
 // marks - a chain of three dependent accesses - are fetched once for all.
 // Bound by instruction issue, vector and scalar alike (stress: 35 M and 41 M instructions in 114 us): hence eight
 // wavefronts per SIMD, which takes a bound on the registers (without it 106 scalar registers leave room for seven: the three
-// sampling cases 2 to 7 % slower), candidates of half a word of the key, the k smallest of them by a bound (word_bound), and
-// divisions made once per batch, in its lanes.  92 M keys of 43 k rows (graph of 111 M nodes), ten vector instructions
+// sampling cases 2 to 7 % slower; with it 18 to 29 scalar registers, prioritised 99 to 107, are kept in lanes of vector ones),
+// candidates of half a word of the key, the k smallest of them by a bound (word_bound), and divisions made once per batch, in its lanes.  92 M keys of 43 k rows (graph of 111 M nodes), ten vector instructions
 // per 64 keys, three of them quarter-rate multiplications: 80 -> 61 us; 23 M keys of 10 k rows 32 -> 24; 65 M keys
 // of 284 k rows 147 -> 114, of 44 k rows 45 -> 34.  While a batch is selected, the row information of the next one and the
 // neighbours of the last two are on their way (4 us of the 147).
@@ -1118,8 +1118,9 @@ __device__ __forceinline__ void store_num_src(int64_t *sizes, int64_t *next_num_
     if (next_num_dst) *next_num_dst = num_src;
 }
 
-// The ids staged in LDS, ascending, to the source list from place `base` on, up to place `most`.  Four a thread at a time: the two row offsets of
-// an id are a random access, on a graph of 111 M nodes one that misses the address translation too.
+// The ids staged in LDS, ascending, to the source list from place `base` on, up to place `most`.  Four a thread at a time, the two row
+// offsets of an id being a random access: a listing of 9 tiles of 22 k nodes 4.6 us, 5.3 one at a time, a call for 179 seeds there 39.7 and 40.5; the
+// listings of 2.4 M nodes, whose 300 tiles hide each other's, 8.5 to 12 us both ways.
 template <typename PtrT, typename IdxT>
 __device__ __forceinline__ void store_staged(int32_t *staged, int total, int64_t base, int64_t most, IdxT *__restrict__ src_ids,
                                              int32_t *__restrict__ local_of, int32_t pos_base, const NewRows<PtrT> &next, int *lds) {
@@ -1227,8 +1228,9 @@ k_bitmap_emit1(uint32_t *__restrict__ bitmap, const uint32_t *__restrict__ excep
 
 // Small bitmaps (at most kSelfCountTiles tiles of 256 words, i.e. graphs of up to half a million
 // nodes): no counting launch.  Every tile's workgroup counts the set bits of the tiles before its own
-// itself, so the words must stay as they are until every workgroup has read them: they are cleared by
-// the relabel launch that follows.  The same launch turns the row tile sums into indptr (the
+// itself, so the words must stay as they are until every workgroup has read them: the relabel clears
+// them, which, of all blocks but the outermost, runs beside the sampling of the next block; so that marks
+// its nodes in another bitmap.  The same launch turns the row tile sums into indptr (the
 // workgroups past the bitmap's tiles), as k_offsets_count does on larger graphs.
 constexpr int kSelfCountTiles = 64;
 template <typename PtrT, typename IdxT>

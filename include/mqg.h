@@ -228,7 +228,7 @@ int mqg_ctx_kernel_names(mqg_ctx *ctx, char *buf, int64_t buf_len);
  * s < cache->num_cached, fills slot_of (-1 elsewhere), cached_ids (if not
  * NULL) and copies the cached rows from cache->feats into cache->cache_rows.
  * In: every field of *cache (buffers allocated by the caller).  Temporary
- * device memory (24 bytes per node) is allocated and freed inside the call,
+ * device memory (24 bytes per node, 8 per cached one) is allocated and freed inside the call,
  * which is therefore synchronous with respect to the host - unless
  * mqg_ctx_reserve(MQG_RESERVE_CACHE_BUILD) has set it aside beforehand.
  */
